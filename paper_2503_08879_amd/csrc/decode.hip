@@ -35,6 +35,46 @@ __device__ __forceinline__ StepGeom step_geom(const DecodeParams& p) {
   return s;
 }
 
+// Source addresses of the 16-byte loads of a bf16 decode wave.  The wave's it-th block holds the tokens
+// t_begin + (wave + it * NW) * BT ..+ BT of the row; load i covers TPL consecutive ones of them, which lie in one
+// 16-token group and so in one page.  PAGED: the page ids of the next 64 groups sit in one register, a group
+// per lane, filled once per 64 groups; a load takes its id by readlane.  (Looking the page up per load puts a
+// table load in front of every block's K and V loads, and loads complete in order: waiting for the table
+// means waiting for every K and V load already in flight.  448 rows x 8192 tokens x 7 heads in pages of 16:
+// 724 us, 2.6 TB/s; with the ids in a register 294 us, 6.4 TB/s, which is what the strided layout takes.)
+template <bool PAGED, int ROWB, int BT, int NW, int TPL>
+struct BlockSource {
+  static constexpr int GPB = BT / 16;  // 16-token groups per block
+  CacheRow K, V;
+  int t_begin, t_end, slot, wave, my_page;
+
+  // page ids of the 64 groups from block it0 on (it0 * GPB a multiple of 64); every lane takes part
+  __device__ __forceinline__ void fill_pages(int it0) {
+    if (!PAGED) return;
+    const int lane = threadIdx.x & 63;
+    int tok = t_begin + (wave + (it0 + lane / GPB) * NW) * BT + (lane % GPB) * 16;
+    tok = tok < t_end ? tok : t_begin;  // past the slice: its loads are clamped to t_begin as well
+    const int pid = K.tab[tok >> K.shift];
+    my_page = pid < 0 ? 0 : (pid >= K.n_pages ? K.n_pages - 1 : pid);
+  }
+  __device__ __forceinline__ bool refill_before(int it) const { return PAGED && ((it * GPB) & 63) == 0; }
+  // this lane's token of load i of block it; tokens past the slice become one that is inside it
+  __device__ __forceinline__ const char* at(const CacheRow& r, const char* fresh, int it, int i, int tq) const {
+    const int b0 = t_begin + (wave + it * NW) * BT;
+    int tok = b0 + i * TPL + tq;
+    if (!PAGED) {
+      tok = tok < t_end ? tok : t_begin;
+      return tok == slot ? fresh : r.base + (int64_t)tok * ROWB;
+    }
+    const int g = (i * TPL) / 16;
+    const int g0 = b0 + g * 16 < t_end ? b0 + g * 16 : t_begin;  // first token of the group my_page was filled for
+    tok = tok < t_end ? tok : g0;
+    const int pid = __builtin_amdgcn_readlane(my_page, (it * GPB + g) & 63);
+    const char* page = r.base + (int64_t)pid * r.page_bytes;
+    return tok == slot ? fresh : page + (int64_t)(tok & ((1 << r.shift) - 1)) * ROWB;
+  }
+};
+
 // Called once per row of a launch whose workgroups own whole rows: the last row to finish advances
 // the device-side count (for sliced rows the merge launch does).  Every workgroup has read ring[0] before it gets here (the
 // value went into its addresses), so the store cannot overtake a reader; the next launch on the
@@ -294,12 +334,12 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
 
   const int row = blockIdx.y, split = blockIdx.x;
   const int prob = row / p.Hkv, c = row % p.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tq = lane / CH, cl = lane % CH;  // load / PV role: token sub-index, 16-byte chunk
   const int n = lane & 15, j = lane >> 4;    // MFMA role: column (token), row block
 
-  const CacheRowT<PG, ROWB> Kr = {cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, 2)};
-  const CacheRowT<PG, ROWB> Vr = {cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2)};
+  const CacheRow Kr = cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, 2);
+  const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2);
   const char* kn = p.k_new ? (const char*)p.k_new + (int64_t)row * ROWB : nullptr;
   const char* vn = p.v_new ? (const char*)p.v_new + (int64_t)row * ROWB : nullptr;
   const StepGeom sg = step_geom(p);
@@ -329,18 +369,18 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
   uint4* buf = kbuf[wave];
   const int nblk = (t_end - t_begin + BT - 1) / BT;
   uint4 kv[NLOAD], vv[NLOAD];
-  auto load_block = [&](int b, uint4* dst, const CacheRowT<PG, ROWB>& base, const char* fresh) {
+  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, slot, wave, 0};
+  auto load_block = [&](int it, uint4* dst, const CacheRow& base, const char* fresh) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
-      const int tok = t_begin + b * BT + i * TPL + tq;
-      const int tc = tok < t_end ? tok : t_begin;
-      const char* src = (tc == slot) ? fresh : base.at(tc);
-      dst[i] = STREAM ? ld16_stream(src + cl * 16) : ld16(src + cl * 16);
+      const char* a = src.at(base, fresh, it, i, tq) + cl * 16;
+      dst[i] = STREAM ? ld16_stream(a) : ld16(a);
     }
   };
   if (wave < nblk) {  // first blocks in flight before anything else is waited for
-    load_block(wave, kv, Kr, kn);
-    load_block(wave, vv, Vr, vn);
+    src.fill_pages(0);
+    load_block(0, kv, Kr, kn);
+    load_block(0, vv, Vr, vn);
   }
   // A operand of tile slot ts, k-step kc, kept in LDS (registers are short here): lane (row m = n,
   // k-group j) reads q[head m % GPAD][8*(4*kc + j) ..+8] if m / GPAD == ts, zeros otherwise
@@ -357,7 +397,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
     qbuf[set][ts][kc][l] = v;
   }
   __syncthreads();
-  for (int b = wave; b < nblk; b += NW) {
+  for (int b = wave, it = 0; b < nblk; b += NW, ++it) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // last block's LDS reads are done
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
@@ -366,7 +406,10 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const bool more = b + NW < nblk;
-    if (more) load_block(b + NW, kv, Kr, kn);
+    if (more) {
+      if (src.refill_before(it + 1)) src.fill_pages(it + 1);
+      load_block(it + 1, kv, Kr, kn);
+    }
 
     // logits of the block
     f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f}, ds = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -432,10 +475,8 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
       float vf[EPL];
       unpack16<DT_BF16>(vv[i], vf);
       if (more) {  // the register is free: V of the next block, as early as possible
-        const int tokn = t_begin + (b + NW) * BT + i * TPL + tq;
-        const int tcn = tokn < t_end ? tokn : t_begin;
-        const char* src = (tcn == slot) ? vn : Vr.at(tcn);
-        vv[i] = STREAM ? ld16_stream(src + cl * 16) : ld16(src + cl * 16);
+        const char* a = src.at(Vr, vn, it + 1, i, tq) + cl * 16;
+        vv[i] = STREAM ? ld16_stream(a) : ld16(a);
       }
 #pragma unroll
       for (int g4 = 0; g4 < GPAD / 4; ++g4) {
@@ -531,12 +572,12 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
 
   const int row = blockIdx.y, split = blockIdx.x;
   const int prob = row / p.Hkv, c = row % p.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tq = lane / CH, cl = lane % CH;  // load role: token sub-index, 16-byte chunk
   const int n = lane & 15, j = lane >> 4;    // MFMA role: column, row block / k-group
 
-  const CacheRowT<PG, ROWB> Kr = {cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, 2)};
-  const CacheRowT<PG, ROWB> Vr = {cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2)};
+  const CacheRow Kr = cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, 2);
+  const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2);
   const char* kn = p.k_new ? (const char*)p.k_new + (int64_t)row * ROWB : nullptr;
   const char* vn = p.v_new ? (const char*)p.v_new + (int64_t)row * ROWB : nullptr;
   const StepGeom sg = step_geom(p);
@@ -564,18 +605,18 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   reinterpret_cast<uint4*>(&pT[wave][0][0])[lane] = make_uint4(0u, 0u, 0u, 0u);  // rows of absent heads stay 0
   const int nblk = (t_end - t_begin + BT - 1) / BT;
   uint4 kv[NLOAD], vv[NLOAD];
-  auto load_block = [&](int b, uint4* dst, const CacheRowT<PG, ROWB>& base, const char* fresh) {
+  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, slot, wave, 0};
+  auto load_block = [&](int it, uint4* dst, const CacheRow& base, const char* fresh) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
-      const int tok = t_begin + b * BT + i * TPL + tq;
-      const int tc = tok < t_end ? tok : t_begin;
-      const char* src = (tc == slot) ? fresh : base.at(tc);
-      dst[i] = STREAM ? ld16_stream(src + cl * 16) : ld16(src + cl * 16);
+      const char* a = src.at(base, fresh, it, i, tq) + cl * 16;
+      dst[i] = STREAM ? ld16_stream(a) : ld16(a);
     }
   };
   if (wave < nblk) {
-    load_block(wave, kv, Kr, kn);
-    load_block(wave, vv, Vr, vn);
+    src.fill_pages(0);
+    load_block(0, kv, Kr, kn);
+    load_block(0, vv, Vr, vn);
   }
   for (int it = tid; it < (p.q_sink ? 2 : 1) * NT * KSTEPS * 64; it += kThreads) {
     const int l = it & 63, kc = (it >> 6) % KSTEPS, ts = (it / (64 * KSTEPS)) % NT, set = it / (64 * KSTEPS * NT);
@@ -593,7 +634,7 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   // land in different banks
   auto vswz = [](int t) { return CH == 16 ? (((t & 3) << 1) | (((t >> 3) & 1) << 3)) : ((t & 3) << 1); };
 
-  for (int b = wave; b < nblk; b += NW) {
+  for (int b = wave, it = 0; b < nblk; b += NW, ++it) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // last block's reads of the buffer are done
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
@@ -602,7 +643,10 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const bool more = b + NW < nblk;
-    if (more) load_block(b + NW, kv, Kr, kn);
+    if (more) {
+      if (src.refill_before(it + 1)) src.fill_pages(it + 1);
+      load_block(it + 1, kv, Kr, kn);
+    }
 
     f32x4_t d[NACC], ds[NACC];
 #pragma unroll
@@ -665,7 +709,7 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
       buf[t * CH + (cl ^ vswz(t))] = vv[i];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (more) load_block(b + NW, vv, Vr, vn);
+    if (more) load_block(it + 1, vv, Vr, vn);
 
     // out += P.V: A = weights [head n][tokens 8j..8j+7], B = values [tokens 8j..8j+7][dim 16 nd + n]
     const uint4 pa = *reinterpret_cast<const uint4*>(&pT[wave][n][8 * j]);

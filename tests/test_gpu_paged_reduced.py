@@ -200,3 +200,34 @@ def test_paged_reduced_cache_arguments_are_checked():
     assert code_of(good, -1) == 1  # negative count without a device-side one
     torch.cuda.synchronize()
     assert float(out.max()) == -7.0
+
+
+@pytest.mark.parametrize(
+    "P,Hq,Hkv,d,cap,page_size",
+    [
+        (65, 28, 4, 64, 4096 + 53, 16),   # 4-wave workgroups own rows, 5-8 heads: the ids of 4096 tokens, then one refill
+        (48, 8, 4, 64, 8192 + 37, 16),    # 8-wave workgroups, up to 4 heads: refill after 8192 tokens
+        (48, 28, 4, 64, 8192, 64),        # exactly one filling
+        (65, 36, 4, 128, 4096 + 16, 32),  # more than 8 heads, the refill's one 16-token group
+    ],
+)
+def test_paged_rows_longer_than_one_filling_of_page_ids(ref, P, Hq, Hkv, d, cap, page_size):
+    """A decode wave keeps the page ids of its next 64 groups of 16 tokens in a register: rows around that length."""
+    import torch
+
+    import paper_2503_08879_amd as sk
+
+    rng = np.random.default_rng(cap + Hq)
+    Kc, Vc = (synth.round_to_dtype(rng.standard_normal((P, Hkv, cap, d), dtype=np.float32), BF16) for _ in range(2))
+    q = synth.round_to_dtype(rng.standard_normal((P, Hq, d), dtype=np.float32), BF16)
+    table, Kpool, Vpool, _ = fresh_pools(P, Hkv, d, cap, page_size, BF16, seed=cap)
+    for j in range(table.shape[1]):
+        t0, t1 = j * page_size, min((j + 1) * page_size, cap)
+        Kpool[table[:, j], :, : t1 - t0] = Kc[:, :, t0:t1]
+        Vpool[table[:, j], :, : t1 - t0] = Vc[:, :, t0:t1]
+    Kp, Vp = synth.host_to_torch(Kpool, BF16), synth.host_to_torch(Vpool, BF16)
+    tab = torch.from_numpy(table).cuda()
+    desc, ws, out = gu.gpu_decode_setup(BF16, P, Hq, Hkv, d, 4, cap - 68, 64, cap)
+    sk.sagekv_decode_attn_paged(desc, sk.compact_pages(tab, Kp, Vp), synth.host_to_torch(q, BF16), Kp, Vp, cap, out, ws)
+    want = ref.decode_attn(BF16, 0, q, Kc, Vc, cap)
+    assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[BF16]
