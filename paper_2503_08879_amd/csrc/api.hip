@@ -23,6 +23,8 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // of magnitude of margin while the band still holds only a handful of candidates per row.
 constexpr float kBand = 1.0f / 4096.0f;
 
+constexpr int64_t kFillWorkgroups = 512;  // see score_chunk
+
 // Sizes of the fast (pre-filtered) eviction path for one descriptor; ok = the path applies.
 struct FastPlan {
   bool ok;
@@ -31,6 +33,16 @@ struct FastPlan {
   int64_t stepB;
   float wA, wB, wC;
 };
+
+// Tokens one workgroup of the first pass over K covers: 1024, less where the call is too small for that to fill the
+// chip (two workgroups per CU, a few rounds of them).  At most 1024 chunks per row (the candidate selection gives each a
+// thread).
+int score_chunk(const sagekv_select_desc* d) {
+  const int64_t rows = (int64_t)d->n_problems * d->n_kv_heads;
+  int chunk = d->dtype == SAGEKV_BF16 ? kScoreChunk : 512;
+  while (chunk > 256 && rows * ((d->L + chunk - 1) / chunk) < kFillWorkgroups && (d->L + chunk / 2 - 1) / (chunk / 2) <= 1024) chunk /= 2;
+  return chunk;
+}
 
 FastPlan fast_plan(const sagekv_select_desc* d) {
   FastPlan f = {};
@@ -81,10 +93,11 @@ FastPlan fast_plan(const sagekv_select_desc* d) {
   // A chunk's own slots: twice the candidates an average chunk is expected to keep (rank * wB tokens
   // per list over the row's chunks), so that only chunks where the candidates crowd (a needle
   // cluster, the tokens next to the recent window of a trained model) reach into the overflow pool.
-  const int64_t n_chunks = (d->L + kScoreChunk - 1) / kScoreChunk;
+  const int chunk = score_chunk(d);
+  const int64_t n_chunks = (d->L + chunk - 1) / chunk;
   const double per_chunk = (double)f.rank * (double)f.wB * lists / (double)n_chunks;
   int cap_c = 32;
-  while (cap_c < 2.0 * per_chunk + 16.0 && cap_c < kScoreChunk) cap_c *= 2;
+  while (cap_c < 2.0 * per_chunk + 16.0 && cap_c < chunk) cap_c *= 2;
   f.cap_c = cap_c;
   return f;
 }
@@ -100,7 +113,7 @@ struct SelectLayout {
   int64_t slots_per_row, cs_pitch;
   FastPlan fast;
   int64_t Lp;
-  int n_chunks, rows, G, n_lists;
+  int n_chunks, chunk, rows, G, n_lists;
 };
 
 bool check_select(const sagekv_select_desc* d, sagekv_status* st) {
@@ -142,7 +155,8 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
   l.G = d->n_q_heads / d->n_kv_heads;
   l.n_lists = d->head_mode == SAGEKV_HEADS_PER_QUERY ? l.G : 1;
   l.Lp = (d->L + 3) / 4 * 4;
-  l.n_chunks = (int)((d->L + kScoreChunk - 1) / kScoreChunk);
+  l.chunk = score_chunk(d);
+  l.n_chunks = (int)((d->L + l.chunk - 1) / l.chunk);
   l.fast = fast_plan(d);
   l.small = l.fast.ok;
   size_t off = 0;
@@ -152,7 +166,7 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
     return at;
   };
   const size_t rows = (size_t)l.rows;
-  l.logits = take(l.small ? 0 : rows * l.n_chunks * l.G * kScoreChunk * sizeof(float));
+  l.logits = take(l.small ? 0 : rows * l.n_chunks * l.G * l.chunk * sizeof(float));
   l.partials = take(rows * l.G * l.n_chunks * sizeof(float2));
   l.stats = take(rows * l.G * sizeof(RowStat));
   l.ghist = take(rows * l.n_lists * kHistBins * sizeof(int));
@@ -180,6 +194,8 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
     }
   }
   // last, so that no other offset depends on whether the caller brought its own score rows
+  // (one-sweep rows whose selection holds its scores in registers need none)
+  own_scores = own_scores && (l.small || d->L > kRowSelectMax);
   l.scores = take(own_scores ? rows * l.n_lists * l.Lp * sizeof(float) : 0);
   if (cs_in_scores) {  // the first half of a list's score row: exact scores, the second: token indices
     l.cand_score = l.scores;
@@ -462,6 +478,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
   sp.logits = (float*)(ws + l.logits);
   sp.partials = partials;
   sp.n_chunks = l.n_chunks;
+  sp.chunk = l.chunk;
   sp.g0 = 0;
   sp.scale = scale;
   sp.stats = stats;
@@ -648,28 +665,41 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     e = launch_score(sp, SCORE_LOGITS, s);
     t.end(SAGEKV_STAGE_SCORE);
     if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
-    ExactStatsParams xp = {};
-    xp.geo = geo;
-    xp.partials = partials;
-    xp.logits = sp.logits;
-    xp.n_chunks = l.n_chunks;
-    xp.stats = stats;
-    xp.ghist = ghist;
-    xp.n_lists = l.n_lists;
-    xp.q_last = q_last;
-    xp.K = K;
-    xp.ks_problem = d->k_stride_problem;
-    xp.ks_head = d->k_stride_head;
-    xp.ks_token = d->k_stride_token;
-    xp.pm = pm;
+    if (d->L <= kRowSelectMax) {
+      RowSelectParams rp = {};
+      rp.geo = geo;
+      rp.logits = sp.logits;
+      rp.partials = partials;
+      rp.n_chunks = l.n_chunks;
+      rp.chunk = l.chunk;
+      rp.scores = scores_out;
+      rp.pitch = pitch;
+      rp.q_last = q_last;
+      rp.K = K;
+      rp.ks_problem = d->k_stride_problem;
+      rp.ks_head = d->k_stride_head;
+      rp.ks_token = d->k_stride_token;
+      rp.pm = pm;
+      rp.kept_idx = kept_idx;
+      rp.S = d->n_sink;
+      rp.W = d->n_recent;
+      rp.k = d->k;
+      rp.n_lists = l.n_lists;
+      rp.band = kBand;
+      t.begin(SAGEKV_STAGE_TOPK);
+      e = launch_row_select(rp, s);
+      t.end(SAGEKV_STAGE_TOPK);
+      if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+    } else {
     t.begin(SAGEKV_STAGE_STATS);
-    e = launch_stats_exact(xp, s);
+    e = launch_stats(tp, l.rows, s);
     t.end(SAGEKV_STAGE_STATS);
     if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
     CombineParams cp = {};
     cp.geo = geo;
     cp.logits = sp.logits;
     cp.n_chunks = l.n_chunks;
+    cp.chunk = l.chunk;
     cp.stats = stats;
     cp.scores = scores;
     cp.pitch = pitch;
@@ -685,6 +715,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     e = launch_topk(kp, s);
     t.end(SAGEKV_STAGE_TOPK);
     if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+    }
   }
 
   GatherParams gp = {};

@@ -100,11 +100,35 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-__device__ __forceinline__ int wave_sum_i(int v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+// DPP moves within a wave, for scans and reductions of ints: a step costs a few cycles, a shuffle through LDS about
+// fifty nanoseconds, and the single-workgroup kernels are chains of such steps.  Lanes the move has no source for get `fill`.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_i32(int fill, int v) {
+  return __builtin_amdgcn_update_dpp(fill, v, CTRL, ROW_MASK, 0xF, false);
+}
+// inclusive prefix sum over the wave
+__device__ __forceinline__ int wave_scan_incl(int v) {
+  v += dpp_i32<0x111, 0xF>(0, v);  // row_shr:1
+  v += dpp_i32<0x112, 0xF>(0, v);  // row_shr:2
+  v += dpp_i32<0x114, 0xF>(0, v);  // row_shr:4
+  v += dpp_i32<0x118, 0xF>(0, v);  // row_shr:8
+  v += dpp_i32<0x142, 0xA>(0, v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_i32<0x143, 0xC>(0, v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
+// minimum / maximum over the wave, in every lane (wave-uniform)
+__device__ __forceinline__ int wave_max_i(int v) {
+  constexpr int lo = -0x7FFFFFFF - 1;
+  auto mx = [](int a, int b) { return a > b ? a : b; };
+  v = mx(v, dpp_i32<0x111, 0xF>(lo, v));
+  v = mx(v, dpp_i32<0x112, 0xF>(lo, v));
+  v = mx(v, dpp_i32<0x114, 0xF>(lo, v));
+  v = mx(v, dpp_i32<0x118, 0xF>(lo, v));
+  v = mx(v, dpp_i32<0x142, 0xA>(lo, v));
+  v = mx(v, dpp_i32<0x143, 0xC>(lo, v));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ int wave_min_i(int v) { return ~wave_max_i(~v); }
 
 // exp(x) * inv for x <= 0-ish and a normal `inv` in [2^-62, 1] (a softmax weight: inv = 1/Z), via the
 // hardware exp2 with the rounding error of x*log2(e) folded back in (relative error a few 1e-7 where
@@ -152,12 +176,7 @@ __host__ __device__ inline float heavy_logit_threshold(float M, float Z) {
 template <int NT>
 __device__ __forceinline__ int block_scan_incl(int v, int* wave_tot, int* total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
-  }
+  const int x = wave_scan_incl(v);
   __syncthreads();  // protects wave_tot against the previous use
   if (lane == 63) wave_tot[w] = x;
   __syncthreads();

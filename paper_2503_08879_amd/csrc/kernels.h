@@ -15,7 +15,7 @@ struct RowStat {
 };
 
 constexpr int kHistBins = 2048;      // first radix digit: key bits 30..20
-constexpr int kScoreChunk = 1024;    // tokens one score workgroup covers
+constexpr int kScoreChunk = 1024;    // most tokens one score workgroup covers (256, 512 or 1024, see score_chunk)
 constexpr int kCombineChunk = 4096;  // tokens one combine workgroup covers
 
 struct RowGeom {
@@ -149,9 +149,10 @@ struct ScoreParams {
   // error of its exponential, and a head whose mass sits on a few such tokens would get a normaliser that
   // is off by as much; two heads' errors differ, and that can reorder group-sum scores a few 1e-6 apart.
   const float* heavy_thr;
-  float* logits;                          // SCORE_LOGITS: [rows][n_chunks][G][kScoreChunk]
+  float* logits;                          // SCORE_LOGITS: [rows][n_chunks][G][chunk]
   float2* partials;                       // [rows][G][n_chunks]  (max, sum exp(x - max))
   int n_chunks;
+  int chunk;  // tokens a workgroup covers (SCORE_SCORES: always kScoreChunk)
   int g0;  // first head of the group handled by this launch
   float scale;
   // SCORE_SCORES: score[i] = sum_g exp(l[g][i] - M_g) / Z_g (or one row per head), histogram of the
@@ -171,26 +172,30 @@ struct StatsParams {
   int n_lists;     // selection lists per row: 1 (group-sum) or G (per-query)
 };
 
-// One-sweep dense path: exact statistics from the logit scratch (see stats_exact_kernel).
-struct ExactStatsParams {
+// One-sweep dense path, rows of up to kRowSelectMax tokens: statistics, scores and selection in one launch.
+constexpr int kRowSelectMax = 32768;
+struct RowSelectParams {
   RowGeom geo;
-  const float2* partials;  // [rows][G][n_chunks]: the chunks' maxima are used
   const float* logits;     // the score pass's scratch
-  int n_chunks;
-  RowStat* stats;          // out [rows][G]
-  int* ghist;              // [rows * n_lists][kHistBins], zeroed here
-  int n_lists;
+  const float2* partials;  // [rows][G][n_chunks]
+  int n_chunks, chunk;
+  float* scores;           // nullable [rows * n_lists][pitch]: every token's score
+  int64_t pitch;
   const void* q_last;
   const void* K;
   int64_t ks_problem, ks_head, ks_token;
   PageMap pm;
+  int32_t* kept_idx;       // [rows][S + n_lists * k + W]
+  int S, W, k;
+  int n_lists;             // 1 or G
+  float band;
 };
 
 struct CombineParams {
   RowGeom geo;
   RowGate gate;
   const float* logits;
-  int n_chunks;  // score chunks per row (logit scratch layout)
+  int n_chunks, chunk;  // score chunks per row and their size (logit scratch layout)
   const RowStat* stats;
   float* scores;  // [rows * n_lists][pitch]
   int64_t pitch;
@@ -336,7 +341,7 @@ hipError_t launch_score_filter(const ScoreParams& p, hipStream_t s);
 hipError_t launch_topk_cand(const TopkCandParams& p, hipStream_t s);
 hipError_t launch_score(const ScoreParams& p, ScoreMode mode, hipStream_t s);  // any mode but SCORE_FILTER
 hipError_t launch_stats(const StatsParams& p, int rows, hipStream_t s);
-hipError_t launch_stats_exact(const ExactStatsParams& p, hipStream_t s);
+hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 hipError_t launch_topk(const TopkParams& p, hipStream_t s);
 hipError_t launch_gather(const GatherParams& p, hipStream_t s);

@@ -26,7 +26,6 @@ namespace sagekv {
 
 namespace {
 
-constexpr int kMaxBand = 1024;  // candidates re-scored in fp64 per row on the fast path
 constexpr int kFastMaxG = 16;
 constexpr float kHeavyShare = 0.01f;  // see sample_stats_kernel (0.3 % and 0.1 % measured worse)
 

@@ -13,9 +13,17 @@ constexpr int kTopkWaves = kTopkThreads / kWave;
 struct TopkShared {
   int hist[kHistBins];
   int wave_tot[kTopkWaves];
-  int pick_bin;
-  int pick_rem;
+  int pick[2];  // bin, rank left inside it
 };
+
+// Logit scratch layout: [row][chunk][head][chunk tokens], so a score workgroup writes one
+// contiguous block and the readers still take 16 bytes per head per thread.
+__device__ __forceinline__ int64_t logit_index(const RowGeom& geo, int n_chunks, int chunk_tokens, int row, int g,
+                                               int64_t tok) {
+  const int shift = __builtin_ctz((unsigned)chunk_tokens);
+  const int64_t chunk = tok >> shift;
+  return ((((int64_t)row * n_chunks + chunk) * geo.G + g) << shift) + (tok - (chunk << shift));
+}
 
 // Exact softmax statistics of one head of a row from its per-chunk partials (max, sum exp(x - max)):
 // M = overall maximum of the fp32 logits, Z = sum_i exp(l_i - M) combined in fp64.  Called by all 64
@@ -40,29 +48,33 @@ __device__ inline RowStat merge_partials_wave(const float2* pr, int n_chunks) {
 }
 
 // Largest digit b such that count(digits >= b) >= k_rem; returns b and the rank left inside it.
-__device__ inline void pick_digit(TopkShared& sh, int nb, int k_rem, int* bin, int* rem) {
+__device__ inline void pick_digit(const int* hist, int* wave_tot, int* pick /* [2] */, int nb, int k_rem, int* bin,
+                                  int* rem) {
   const int t = threadIdx.x;
   if (t == 0) {
-    sh.pick_bin = 0;
-    sh.pick_rem = 1;
+    pick[0] = 0;
+    pick[1] = 1;
   }
   const int i0 = nb - 1 - 2 * t, i1 = nb - 2 - 2 * t;  // descending digits
-  const int c0 = i0 >= 0 ? sh.hist[i0] : 0;
-  const int c1 = i1 >= 0 ? sh.hist[i1] : 0;
+  const int c0 = i0 >= 0 ? hist[i0] : 0;
+  const int c1 = i1 >= 0 ? hist[i1] : 0;
   int tot;
-  const int incl = block_scan_incl<kTopkThreads>(c0 + c1, sh.wave_tot, &tot);
+  const int incl = block_scan_incl<kTopkThreads>(c0 + c1, wave_tot, &tot);
   const int before = incl - c0 - c1;
   if (before < k_rem && k_rem <= before + c0) {
-    sh.pick_bin = i0;
-    sh.pick_rem = k_rem - before;
+    pick[0] = i0;
+    pick[1] = k_rem - before;
   } else if (before + c0 < k_rem && k_rem <= incl) {
-    sh.pick_bin = i1;
-    sh.pick_rem = k_rem - before - c0;
+    pick[0] = i1;
+    pick[1] = k_rem - before - c0;
   }
   __syncthreads();
-  *bin = sh.pick_bin;
-  *rem = sh.pick_rem;
+  *bin = pick[0];
+  *rem = pick[1];
   __syncthreads();
+}
+__device__ inline void pick_digit(TopkShared& sh, int nb, int k_rem, int* bin, int* rem) {
+  pick_digit(sh.hist, sh.wave_tot, sh.pick, nb, k_rem, bin, rem);
 }
 
 __device__ inline void hist_pass(TopkShared& sh, const float* cand, int64_t E, uint32_t prefix, uint32_t mask, int shift,
@@ -168,26 +180,126 @@ __device__ inline float refined_score(const RowGeom& geo, const void* q_last, co
   return (float)tot;
 }
 
-// The same value computed by one whole wave: lanes split head_dim, fp64 tree reduction (the fp64
+// One head's share of that value computed by one whole wave: lanes split head_dim, fp64 tree reduction (the fp64
 // sum order differs from the sequential one by ~1e-16 relative, far below fp32 rounding).
+template <int DT>
+__device__ inline double refined_term_wave(const RowGeom& geo, const void* q_last, const void* K, const PageMap& pm,
+                                           int64_t ks_problem, int64_t ks_head, int64_t ks_token, const RowStat& st,
+                                           int prob, int c, int64_t tok, int g) {
+  const int D = geo.D, lane = threadIdx.x & 63;
+  const int64_t k_off = kv_offset(pm, pm.ks_page, ks_problem, ks_head, ks_token, prob, c, tok);
+  const int64_t q_off = ((int64_t)prob * geo.Hq + c * geo.G + g) * D;
+  double acc = 0.0;
+  for (int j = lane; j < D; j += 64) acc += elem_f64<DT>(q_last, q_off + j) * elem_f64<DT>(K, k_off + j);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
+  return exp(acc * (1.0 / sqrt((double)D)) - (double)st.M) / st.Z;
+}
 template <int DT>
 __device__ inline float refined_score_wave(const RowGeom& geo, const void* q_last, const void* K, const PageMap& pm,
                                         int64_t ks_problem, int64_t ks_head, int64_t ks_token, const RowStat* row_stats,
                                         int prob, int c, int64_t tok, int g_lo, int g_hi) {
-  const int D = geo.D, G = geo.G, lane = threadIdx.x & 63;
-  const int64_t k_off = kv_offset(pm, pm.ks_page, ks_problem, ks_head, ks_token, prob, c, tok);
-  const double inv = 1.0 / sqrt((double)D);
   double tot = 0.0;
-  for (int g = g_lo; g < g_hi; ++g) {
-    const int64_t q_off = ((int64_t)prob * geo.Hq + c * G + g) * D;
-    double acc = 0.0;
-    for (int j = lane; j < D; j += 64) acc += elem_f64<DT>(q_last, q_off + j) * elem_f64<DT>(K, k_off + j);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
-    const RowStat st = row_stats[g];
-    tot += exp(acc * inv - (double)st.M) / st.Z;
-  }
+  for (int g = g_lo; g < g_hi; ++g)
+    tot += refined_term_wave<DT>(geo, q_last, K, pm, ks_problem, ks_head, ks_token, row_stats[g], prob, c, tok, g);
   return (float)tot;
+}
+
+// ---- selection among scores held in registers ---------------------------------------------------
+// N scores per thread of a 1024-thread workgroup, -1: no element.  All functions are called by every thread.
+constexpr int kMaxBand = 1024;  // elements around the k-th that are ranked exactly among themselves
+
+struct RegSelect {
+  union {
+    int hist[2][kHistBins];
+    double term[kMaxBand];  // refine_band: fp64 terms of a batch of (member, head)
+  };
+  int wave_tot[kTopkWaves], pick[2];
+  int red_min[kTopkWaves], red_max[kTopkWaves];
+  int band_tok[kMaxBand];
+  float band_v[kMaxBand];
+  int n_band, n_above;
+};
+
+// Bracket of the k-th largest score: its bit pattern lies in [*tlo, *thi], at most 2^9 apart (2^-14 relative).
+// Two histograms over the keys' own range: 2048 bins from the smallest to the largest key, then 2048 bins
+// inside the bin that holds the k-th.  (Digits of the bit pattern would put most of a row into a few bins: the
+// LDS atomics of a wave then serialise on one address.)  Also clears n_band and n_above.
+template <int N>
+__device__ __forceinline__ void bracket_kth(RegSelect& sh, const float (&v)[N], int k, uint32_t* tlo, uint32_t* thi) {
+  const int tid = threadIdx.x, wave = tid >> 6;
+  int4* h4 = reinterpret_cast<int4*>(&sh.hist[0][0]);
+  for (int b = tid; b < 2 * kHistBins / 4; b += kTopkThreads) h4[b] = make_int4(0, 0, 0, 0);
+  int mn = 0x7FFFFFFF, mx = -1;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int key = __float_as_int(v[i]);
+    if (key >= 0) mn = key < mn ? key : mn;
+    mx = key > mx ? key : mx;
+  }
+  mn = wave_min_i(mn);
+  mx = wave_max_i(mx);
+  if ((tid & 63) == 0) {
+    sh.red_min[wave] = mn;
+    sh.red_max[wave] = mx;
+  }
+  if (tid == 0) sh.n_band = sh.n_above = 0;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kTopkWaves; ++w) {
+    mn = sh.red_min[w] < mn ? sh.red_min[w] : mn;
+    mx = sh.red_max[w] > mx ? sh.red_max[w] : mx;
+  }
+  const uint32_t range = mx >= mn ? (uint32_t)(mx - mn) : 0u;
+  const int s1 = range < (uint32_t)kHistBins ? 0 : 21 - __clz((int)range);  // range >> s1 < 2048
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int key = __float_as_int(v[i]);
+    if (key >= 0) atomicAdd(&sh.hist[0][(uint32_t)(key - mn) >> s1], 1);
+  }
+  __syncthreads();
+  int bin, rem;
+  pick_digit(sh.hist[0], sh.wave_tot, sh.pick, kHistBins, k, &bin, &rem);
+  const int base = mn + (int)((uint32_t)bin << s1);
+  const int s2 = s1 > 11 ? s1 - 11 : 0;
+  if (s1 == 0) {
+    *tlo = *thi = (uint32_t)base;
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int key = __float_as_int(v[i]);
+    if (key >= 0 && (int)((uint32_t)(key - mn) >> s1) == bin) atomicAdd(&sh.hist[1][(uint32_t)(key - base) >> s2], 1);
+  }
+  __syncthreads();
+  pick_digit(sh.hist[1], sh.wave_tot, sh.pick, kHistBins, rem, &bin, &rem);
+  *tlo = (uint32_t)base + ((uint32_t)bin << s2);
+  *thi = *tlo + ((1u << s2) - 1u);
+}
+
+// fp64 scores of the band's members (band_tok) into band_v: the (member, head) terms spread over the waves, added
+// in head order.  Ends with a barrier.
+template <int DT>
+__device__ __forceinline__ void refine_band(RegSelect& sh, int nb, const RowGeom& geo, const void* q_last, const void* K,
+                                            const PageMap& pm, int64_t ks_problem, int64_t ks_head, int64_t ks_token,
+                                            const RowStat* stats, int prob, int c, int g_lo, int g_hi) {
+  const int tid = threadIdx.x, heads = g_hi - g_lo, per = kMaxBand / heads;
+  for (int m0 = 0; m0 < nb; m0 += per) {
+    const int cnt = nb - m0 < per ? nb - m0 : per;
+    for (int t = tid >> 6; t < cnt * heads; t += kTopkWaves) {
+      const int g = g_lo + t % heads;
+      const double x = refined_term_wave<DT>(geo, q_last, K, pm, ks_problem, ks_head, ks_token, stats[g], prob, c,
+                                             sh.band_tok[m0 + t / heads], g);
+      if ((tid & 63) == 0) sh.term[t] = x;
+    }
+    __syncthreads();
+    for (int t = tid; t < cnt; t += kTopkThreads) {
+      double tot = 0.0;
+      for (int g = 0; g < heads; ++g) tot += sh.term[t * heads + g];
+      sh.band_v[m0 + t] = (float)tot;
+    }
+    __syncthreads();
+  }
 }
 
 }  // namespace sagekv

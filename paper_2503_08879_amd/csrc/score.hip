@@ -9,7 +9,8 @@
 //                   every token's score from known (M, Z) (two-sweep dense path: rows the pre-filter
 //                   could not certify, without a logit scratch).
 //   sample_logits_kernel  logits of the sampled blocks of the pre-filtered path.
-//   stats_kernel    merges the partials of a row into (M, Z) per head, in fp64.
+//   stats_kernel    merges the partials of a row into (M, Z) per head, in fp64 (one-sweep rows that row_select_kernel
+//                   cannot hold, two-sweep path).
 //   combine_kernel  score[i] = sum_g exp(logit[g][i] - M_g) / Z_g  (fp32) and the first radix
 //                   histogram of the candidates' scores, merged across workgroups with atomics.
 #include "device_utils.h"
@@ -23,26 +24,60 @@ namespace {
 constexpr int kScoreThreads = 256;
 constexpr int kScoreWaves = kScoreThreads / kWave;
 constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine launch
-constexpr int kBlocksPerWave = kScoreChunk / (kScoreWaves * 64);  // 64-token blocks per wave
+// A score workgroup takes a chunk of BPW blocks of 64 tokens per wave (BPW = 1, 2, 4: 256, 512, 1024 tokens).
 
-// Logit scratch layout: [row][chunk][head][kScoreChunk], so a score workgroup writes one
-// contiguous block and the combine stage still reads 16 bytes per head per thread.
-__device__ __forceinline__ int64_t logit_index(const RowGeom& geo, int n_chunks, int row, int g, int64_t tok) {
-  const int64_t chunk = tok / kScoreChunk;
-  return (((int64_t)row * n_chunks + chunk) * geo.G + g) * kScoreChunk + (tok - chunk * kScoreChunk);
+// Softmax terms that a wave takes with an fp64 exponent, up to kHeavyBatch at a time: exp(l - m), l = the logit of query
+// row q + q_off and key row K + k_off (D elements each) in fp64.  Sixteen lanes share a term, so the loads of a
+// batch are in flight together (one term after the other costs a memory round trip each: 16 terms of a chunk that
+// holds the sink tokens took 35 us, a batch takes about 2).  Called by all 64 lanes of a wave; rare: out of line.
+constexpr int kHeavyBatch = 32;
+struct HeavyTerms {
+  int64_t k_off[kHeavyBatch], q_off[kHeavyBatch];
+  double val[kHeavyBatch];
+  float m[kHeavyBatch];
+  int code[kHeavyBatch];  // whose sum the term belongs to
+};
+template <int DT, int D>
+__device__ __noinline__ void exact_terms(HeavyTerms* h, int cnt, const void* K, const void* q) {
+  constexpr int EPT = D / 16;  // elements per lane
+  const int lane = threadIdx.x & 63, grp = lane >> 4, sub = lane & 15;
+  for (int e0 = 0; e0 < cnt; e0 += 8) {
+    double acc[2] = {0.0, 0.0};
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int e = e0 + 4 * u + grp < cnt ? e0 + 4 * u + grp : cnt - 1;
+      const int64_t ko = h->k_off[e] + sub * EPT, qo = h->q_off[e] + sub * EPT;
+#pragma unroll
+      for (int i = 0; i < EPT; ++i) acc[u] += elem_f64<DT>(q, qo + i) * elem_f64<DT>(K, ko + i);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+      for (int o = 8; o >= 1; o >>= 1) acc[u] += __shfl_xor(acc[u], o);
+      const int e = e0 + 4 * u + grp;
+      if (sub == 0 && e < cnt) h->val[e] = exp(acc[u] / sqrt((double)D) - (double)h->m[e]);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
-// One wave handles 64 tokens per block: LPT lanes share a token (16 bytes each), so one
+// fp32 caches.  One wave handles 64 tokens per block: LPT lanes share a token (16 bytes each), so one
 // 16-byte load instruction covers TPL = 64/LPT whole tokens, fully coalesced; LPT such loads
 // make a block.  After load i the lane with (lane % LPT) == i keeps the reduced dot product,
 // so each lane ends a block owning exactly one token's logits for all heads.
-template <int DT, int D, int GB>
-__global__ __launch_bounds__(kScoreThreads) void score_kernel(ScoreParams p) {
+//
+// The softmax partial (M, Z) of the chunk is taken after the last block, from the logits in registers.  Terms
+// heavy enough for their logit's fp32 error to show in Z (heavy_logit_threshold, with the CHUNK's own M and
+// Z: a term's share of its chunk is at least its share of the row, and a chunk whose Z is good to 1e-7 is
+// all the row's Z needs) enter with a logit recomputed in fp64.
+template <int DT, int D, int GB, int BPW>
+__global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) {
   constexpr int EPL = Elem<DT>::per_lane;
   constexpr int EB = Elem<DT>::bytes;
   constexpr int LPT = D / EPL;
   constexpr int TPL = 64 / LPT;
-  constexpr int SB = LPT < 8 ? LPT : 8;  // loads in flight per batch
+  constexpr int SB = GB > 4 ? 8 : 16;  // loads per batch
+  constexpr int kChunk = 64 * BPW * kScoreWaves;
 
   const int row = blockIdx.y;
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
@@ -50,106 +85,150 @@ __global__ __launch_bounds__(kScoreThreads) void score_kernel(ScoreParams p) {
   const int tq = lane / LPT, cl = lane % LPT;
   const int64_t L = p.geo.L;
 
+  // batches of SB loads, the next one in flight while the current one is used
+  constexpr int NB = LPT / SB;  // batches per block
+  const int64_t wave_base = (int64_t)blockIdx.x * kChunk + (int64_t)wave * BPW * 64;
+  uint4 kv[2][SB];
+  auto load_batch = [&](int n, uint4* dst) {
+    const int64_t tok_base = wave_base + (n / NB) * 64;
+    if (tok_base < L) {  // wave-uniform
+#pragma unroll
+      for (int i = 0; i < SB; ++i) {
+        int64_t tok = tok_base + ((n % NB) * SB + i) * TPL + tq;
+        tok = tok < L ? tok : L - 1;  // tail: re-read the last token, masked below
+        const int64_t off = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
+        dst[i] = ld16((const char*)p.K + off * EB + cl * 16);
+      }
+    }
+  };
+  load_batch(0, kv[0]);
   uint4 q[GB];
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
     int h = c * p.geo.G + p.g0 + g;
     q[g] = ld16((const char*)p.q_last + (((int64_t)prob * p.geo.Hq + h) * D + cl * EPL) * EB);
   }
-
-  float m[GB], sum[GB];
+  float xs[BPW][GB];  // -INFINITY: no token
 #pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    m[g] = -INFINITY;
-    sum[g] = 0.f;
-  }
-
-  const int64_t chunk_base = (int64_t)blockIdx.x * kScoreChunk;
-  for (int blk = 0; blk < kBlocksPerWave; ++blk) {
-    const int64_t tok_base = chunk_base + (int64_t)(wave * kBlocksPerWave + blk) * 64;
-    if (tok_base >= L) break;  // wave-uniform
-    float keep[GB];
+  for (int n = 0; n < BPW * NB; ++n) {
+    const int blk = n / NB, i0 = (n % NB) * SB;
+    const int64_t tok_base = wave_base + blk * 64;
+    if (n + 1 < BPW * NB) load_batch(n + 1, kv[(n + 1) & 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (i0 == 0) {
 #pragma unroll
-    for (int g = 0; g < GB; ++g) keep[g] = 0.f;
-#pragma unroll
-    for (int i0 = 0; i0 < LPT; i0 += SB) {
-      uint4 kv[SB];
-#pragma unroll
-      for (int i = 0; i < SB; ++i) {
-        int64_t tok = tok_base + (i0 + i) * TPL + tq;
-        tok = tok < L ? tok : L - 1;  // tail: re-read the last token, masked below
-        const int64_t off = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
-        kv[i] = ld16((const char*)p.K + off * EB + cl * 16);
-      }
+      for (int g = 0; g < GB; ++g) xs[blk][g] = 0.f;
+    }
+    if (tok_base < L) {
 #pragma unroll
       for (int i = 0; i < SB; ++i) {
 #pragma unroll
         for (int g = 0; g < GB; ++g) {
-          float v = group_sum<LPT>(dot16<DT>(kv[i], q[g], 0.f));
-          keep[g] = (cl == i0 + i) ? v : keep[g];
+          const float v = group_sum<LPT>(dot16<DT>(kv[n & 1][i], q[g], 0.f));
+          xs[blk][g] = (cl == i0 + i) ? v : xs[blk][g];
         }
       }
     }
-    const int64_t tok = tok_base + cl * TPL + tq;
-    if (tok < L) {
+    if (i0 + SB == LPT) {
+      const int64_t tok = tok_base + cl * TPL + tq;
 #pragma unroll
       for (int g = 0; g < GB; ++g) {
-        float x = keep[g] * p.scale;
-        p.logits[logit_index(p.geo, p.n_chunks, row, p.g0 + g, tok)] = x;
-        float mn = fmaxf(m[g], x);
-        sum[g] = sum[g] * exp_fast(m[g] - mn) + exp_fast(x - mn);
-        m[g] = mn;
+        xs[blk][g] = tok < L ? xs[blk][g] * p.scale : -INFINITY;
+        if (tok < L) p.logits[logit_index(p.geo, p.n_chunks, p.chunk, row, p.g0 + g, tok)] = xs[blk][g];
       }
     }
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // (max, sum) of the chunk: lanes -> wave -> workgroup
-  __shared__ float2 part[kScoreWaves][GB];
+  __shared__ float part_m[kScoreWaves][GB], part_s[kScoreWaves][GB];
+  float M[GB];
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
-    float M = wave_max(m[g]);
-    float s = (m[g] == -INFINITY) ? 0.f : sum[g] * exp_fast(m[g] - M);
+    float m = xs[0][g];
+#pragma unroll
+    for (int blk = 1; blk < BPW; ++blk) m = fmaxf(m, xs[blk][g]);
+    m = wave_max(m);
+    if (lane == 0) part_m[wave][g] = m;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int g = 0; g < GB; ++g) {
+    M[g] = part_m[0][g];
+#pragma unroll
+    for (int w = 1; w < kScoreWaves; ++w) M[g] = fmaxf(M[g], part_m[w][g]);
+    float s = 0.f;
+#pragma unroll
+    for (int blk = 0; blk < BPW; ++blk) s += exp_fast(xs[blk][g] - M[g]);
     s = group_sum<64>(s);
-    if (lane == 0) part[wave][g] = make_float2(M, s);
+    if (lane == 0) part_s[wave][g] = s;
+  }
+  __syncthreads();
+  float thr[GB];
+  bool any_heavy = false;
+#pragma unroll
+  for (int g = 0; g < GB; ++g) {
+    float z = 0.f;
+#pragma unroll
+    for (int w = 0; w < kScoreWaves; ++w) z += part_s[w][g];
+    thr[g] = heavy_logit_threshold(M[g], z);
+#pragma unroll
+    for (int blk = 0; blk < BPW; ++blk) any_heavy |= xs[blk][g] >= thr[g];
+  }
+  __syncthreads();       // part_s has been read
+  __shared__ HeavyTerms heavy[kScoreWaves];
+  if (__any(any_heavy)) {  // wave-uniform: this wave's sums again, the heavy terms with fp64 exponents
+    HeavyTerms* hv = &heavy[wave];
+    for (int done = 0, total = 1; done < total; done += kHeavyBatch) {  // usually one batch
+      total = 0;
+#pragma unroll
+      for (int g = 0; g < GB; ++g)
+#pragma unroll
+        for (int blk = 0; blk < BPW; ++blk) {
+          const unsigned long long b = __ballot(xs[blk][g] >= thr[g]);
+          const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
+          if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
+            const int64_t tok = wave_base + blk * 64 + cl * TPL + tq;
+            hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
+            hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + g) * D;
+            hv->m[e] = M[g];
+            hv->code[e] = g;
+          }
+          total += __popcll(b);
+        }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int cnt = total - done < kHeavyBatch ? total - done : kHeavyBatch;
+      exact_terms<DT, D>(hv, cnt, p.K, p.q_last);
+#pragma unroll
+      for (int g = 0; g < GB; ++g) {
+        double z = 0.0;
+        if (done == 0) {
+          float s = 0.f;
+#pragma unroll
+          for (int blk = 0; blk < BPW; ++blk) s += xs[blk][g] >= thr[g] ? 0.f : exp_fast(xs[blk][g] - M[g]);
+          z = (double)group_sum<64>(s);
+        } else {
+          z = (double)part_s[wave][g];
+        }
+        for (int e = 0; e < cnt; ++e) z += hv->code[e] == g ? hv->val[e] : 0.0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane == 0) part_s[wave][g] = (float)z;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
   }
   __syncthreads();
   if (threadIdx.x < GB) {
     const int g = threadIdx.x;
-    float M = part[0][g].x;
-#pragma unroll
-    for (int w = 1; w < kScoreWaves; ++w) M = fmaxf(M, part[w][g].x);
-    float s = 0.f;
+    float m = part_m[0][g], s = 0.f;
 #pragma unroll
     for (int w = 0; w < kScoreWaves; ++w) {
-      float2 pw = part[w][g];
-      s += (pw.x == -INFINITY) ? 0.f : pw.y * exp_fast(pw.x - M);
+      m = fmaxf(m, part_m[w][g]);
+      s += part_s[w][g];
     }
-    p.partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + blockIdx.x] = make_float2(M, s);
+    p.partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + blockIdx.x] = make_float2(m, s);
   }
 }
-
-// exp(l - m) for a term the softmax sum takes with an fp64 exponent (ScoreParams::heavy_thr): the logit of
-// the head whose query row is qrow (bf16, D elements) and of token t of the wave's staged block
-// (16-byte chunks, XOR-swizzled as the staging loop wrote them) is recomputed in fp64.  Called by all 64
-// lanes of the wave with the same arguments (two elements per lane); every lane gets the result.
-// Rare: out of line.
-template <int D>
-__device__ __noinline__ float heavy_term(const uint4* buf, int t, const uint32_t* qrow, float m) {
-  constexpr int CH = D / 8;
-  const int lane = threadIdx.x & 63;
-  double acc = 0.0;
-  if (lane < D / 2) {
-    const int kk = lane >> 2;  // 16-byte chunk of elements 2 * lane, 2 * lane + 1
-    const uint32_t kw = reinterpret_cast<const uint32_t*>(&buf[t * CH + (kk ^ (t & (CH - 1)))])[lane & 3];
-    const uint32_t qw = qrow[lane];
-    acc = (double)__uint_as_float(kw << 16) * (double)__uint_as_float(qw << 16) +
-          (double)__uint_as_float(kw & 0xFFFF0000u) * (double)__uint_as_float(qw & 0xFFFF0000u);
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
-  return (float)exp(acc / sqrt((double)D) - (double)m);
-}
-
 
 // bf16 scoring on the matrix cores.  The dot products of a 16-token tile against the group's
 // query heads are one 16x16x(head_dim) product: A = queries (heads in rows, zero padded),
@@ -172,8 +251,8 @@ __device__ __noinline__ float heavy_term(const uint4* buf, int t, const uint32_t
 //
 // PAGED: the chunk's pages (at most 64: pages hold 16 tokens or more) are looked up once, one per
 // lane, and every load takes its page from the lane that holds it.
-// One score chunk (kScoreChunk tokens of row `row`) by one workgroup of kScoreThreads threads.
-template <int D, int GPAD, int MODE, bool PAGED>
+// One score chunk (64 * BPW * kScoreWaves tokens of row `row`) by one workgroup of kScoreThreads threads.
+template <int D, int GPAD, int MODE, bool PAGED, int BPW>
 __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, int row, int chunk) {
   constexpr int CH = D / 8;         // 16-byte chunks per token
   constexpr int TPL = 64 / CH;      // tokens per coalesced wave load
@@ -183,14 +262,18 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   constexpr int NACC = 4 / TILES;   // accumulators per block
   constexpr bool FILTER = MODE == SCORE_FILTER;
   constexpr bool KEEP = MODE == SCORE_LOGITS || MODE == SCORE_SCORES;  // per-token values held to the end
-  constexpr bool PARTIALS = MODE != SCORE_SCORES;
+  constexpr bool PARTIALS = MODE == SCORE_FILTER || MODE == SCORE_PARTIALS;  // running sums (SCORE_LOGITS: at the end)
+  constexpr bool HEAVY = PARTIALS;
+  constexpr int kChunk = 64 * BPW * kScoreWaves;
 
   __shared__ uint4 lds[kScoreWaves][64 * CH];
   __shared__ float2 part[kScoreWaves][4][4];
+  // HEAVY: the lanes whose logit (block, accumulator, register) is a heavy term of the softmax sum
+  __shared__ unsigned long long heavy_mask[HEAVY ? kScoreWaves : 1][BPW][NACC][4];
   __shared__ int n_kept_wg;  // FILTER: candidates this workgroup has kept so far
 
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tq = lane / CH, cl = lane % CH;  // load role: token sub-index, chunk
   const int n = lane & 15, j = lane >> 4;    // MFMA role: column (token), k-group / row block
   const int64_t L = p.geo.L;
@@ -201,33 +284,48 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   int my_page = 0, first_page = 0;
   if (PAGED) {
     Krow = (const char*)p.K + (int64_t)c * p.ks_head * 2;
-    first_page = (int)(((int64_t)chunk * kScoreChunk) >> p.pm.shift);
+    first_page = (int)(((int64_t)chunk * kChunk) >> p.pm.shift);
     const int last_page = (int)((L - 1) >> p.pm.shift);
     const int pg = first_page + lane < last_page ? first_page + lane : last_page;
     my_page = page_of(p.pm, prob, (int64_t)pg << p.pm.shift);
   }
-  // address of this lane's 16 bytes of token tok (every lane of the wave calls it together)
-  auto k_addr = [&](int64_t tok) -> const char* {
-    if (PAGED) {
-      const int pid = __shfl(my_page, (int)(tok >> p.pm.shift) - first_page);
-      return Krow + ((int64_t)pid * p.pm.ks_page * 2 + (tok & ((1 << p.pm.shift) - 1)) * tok_bytes) + cl * 16;
-    }
-    return Krow + tok * tok_bytes + cl * 16;
-  };
-
   // The waves of a workgroup take the chunk's 64-token blocks round robin, so the workgroup reads
   // one contiguous 64 KiB run at a time; the first block's loads go out before anything else.
-  const int64_t wave_base = (int64_t)chunk * kScoreChunk + (int64_t)wave * 64;
+  const int64_t wave_base = (int64_t)chunk * kChunk + (int64_t)wave * 64;
   constexpr int64_t kBlockStride = 64 * kScoreWaves;
+  const int64_t lane_off = (int64_t)tq * tok_bytes + cl * 16;
   uint4 kv[NLOAD];
-  if (wave_base < L) {
+  // the block of 64 tokens from tb on (tb wave-uniform, < L).  Load i covers the TPL tokens from tb + i * TPL on, which
+  // share a page: its address is a wave-uniform base plus the lane's offset, but for the row's last, partial block.
+  auto load_block = [&](int64_t tb) {
+    if (tb + 64 <= L) {
 #pragma unroll
-    for (int i = 0; i < NLOAD; ++i) {
-      int64_t tok = wave_base + i * TPL + tq;
-      tok = tok < L ? tok : L - 1;  // tail: re-read the last token, masked below
-      kv[i] = ld16_stream(k_addr(tok));
+      for (int i = 0; i < NLOAD; ++i) {
+        const char* base;
+        if (PAGED) {
+          const int64_t tok = tb + i * TPL;
+          const int pid = __builtin_amdgcn_readlane(my_page, (int)(tok >> p.pm.shift) - first_page);
+          base = Krow + ((int64_t)pid * p.pm.ks_page * 2 + (tok & ((1 << p.pm.shift) - 1)) * tok_bytes);
+        } else {
+          base = Krow + (tb + i * TPL) * tok_bytes;
+        }
+        kv[i] = ld16_stream(base + lane_off);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NLOAD; ++i) {
+        int64_t tok = tb + i * TPL + tq;
+        tok = tok < L ? tok : L - 1;  // re-read the last token, masked below
+        if (PAGED) {
+          const int pid = __shfl(my_page, (int)(tok >> p.pm.shift) - first_page);
+          kv[i] = ld16_stream(Krow + ((int64_t)pid * p.pm.ks_page * 2 + (tok & ((1 << p.pm.shift) - 1)) * tok_bytes) + cl * 16);
+        } else {
+          kv[i] = ld16_stream(Krow + tok * tok_bytes + cl * 16);
+        }
+      }
     }
-  }
+  };
+  if (wave_base < L) load_block(wave_base);
   // A operand: lane (row m = n, k-group j) holds q[head m % GPAD][8*(4*kc + j) ..+8]
   const int my_head = n % GPAD, my_slot = n / GPAD;
   uint4 qa[KSTEPS];
@@ -252,17 +350,14 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   // softmax weights of this lane's 4 heads: the sample's (M^, 1/Z^) for the filter, the exact (M, 1/Z)
   // for the scores; the row's filter threshold(s)
   float fM[4] = {0.f, 0.f, 0.f, 0.f}, fInv[4] = {0.f, 0.f, 0.f, 0.f}, ftau = 0.f;
-  // terms with an fp64 exponent (ScoreParams::heavy_thr): the passes that follow a sample stage; the
-  // one-sweep dense pass (SCORE_LOGITS) leaves them to stats_exact_kernel
-  constexpr bool HEAVY = MODE == SCORE_FILTER || MODE == SCORE_PARTIALS;
+  // terms with an fp64 exponent (ScoreParams::heavy_thr): the passes that follow a sample stage; the one-sweep
+  // dense pass (SCORE_LOGITS) takes the thresholds from the chunk's own statistics, after its last block
   float hthr[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
   if (HEAVY && p.heavy_thr) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (hbase + r < gb) hthr[r] = p.heavy_thr[(int64_t)row * p.geo.G + p.g0 + hbase + r];
   }
-  const uint32_t* q_group = reinterpret_cast<const uint32_t*>(
-      (const char*)p.q_last + (((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0) * D) * 2);  // query rows of this launch's heads
   float ftau_h[4] = {INFINITY, INFINITY, INFINITY, INFINITY};  // per-query lists: a threshold per head
   const bool per_head = FILTER && p.filt.n_lists > 1;
   if (FILTER) {
@@ -296,9 +391,11 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   // their latency overlaps block b's MFMA phase.  Per-token results stay in registers until the wave
   // has loaded its last block: loads and stores share one in-order completion counter, so a
   // store inside the loop would put its write-ack latency on the critical path of every block.
-  float xs[KEEP ? kBlocksPerWave : 1][NACC][4];
+  bool seen_heavy = false;
+  if (HEAVY && lane < BPW * NACC * 4) (&heavy_mask[wave][0][0][0])[lane] = 0ull;
+  float xs[KEEP ? BPW : 1][NACC][4];
 #pragma unroll
-  for (int blk = 0; blk < kBlocksPerWave; ++blk) {
+  for (int blk = 0; blk < BPW; ++blk) {
     const int64_t tok_base = wave_base + (int64_t)blk * kBlockStride;
     if (tok_base < L) {  // wave-uniform
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // previous block's LDS reads are done
@@ -308,13 +405,10 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         buf[t * CH + (cl ^ (t & (CH - 1)))] = kv[i];
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      if (blk + 1 < kBlocksPerWave && tok_base + kBlockStride < L) {
-#pragma unroll
-        for (int i = 0; i < NLOAD; ++i) {
-          int64_t tok = tok_base + kBlockStride + i * TPL + tq;
-          tok = tok < L ? tok : L - 1;
-          kv[i] = ld16_stream(k_addr(tok));
-        }
+      if (blk + 1 < BPW && tok_base + kBlockStride < L) {
+        int64_t next = tok_base + kBlockStride;
+        asm volatile("" : "+s"(next));  // the addresses of later blocks are not computed (and held) up front
+        load_block(next);
       }
       f32x4_t acc[NACC];
 #pragma unroll
@@ -343,7 +437,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         for (int r = 0; r < 4; ++r) {
           const float x = acc[a][r] * p.scale;
           xs[KEEP ? blk : 0][a][r] = x;
-          if (tok < L && hbase + r < gb) {
+          if (MODE != SCORE_LOGITS && tok < L && hbase + r < gb) {
             if (PARTIALS) {
               const float mn = fmaxf(m[r], x);
               const bool hv = HEAVY && x >= hthr[r];  // rare: its term is added below, with an fp64 exponent
@@ -397,39 +491,153 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
           }
         }
       }
-      if (HEAVY && __any(any_heavy)) {  // wave-uniform, rare: the wave takes its heavy terms one at a time
+      if (HEAVY && __any(any_heavy)) {  // wave-uniform, rare: noted here, added after the last block
+        seen_heavy = true;
 #pragma unroll
         for (int a = 0; a < NACC; ++a) {
           const int t_local = (a * TILES + (4 * j) / GPAD) * 16 + n;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            unsigned long long todo = __ballot(tok_base + t_local < L && hbase + r < gb && xs[0][a][r] >= hthr[r]);
-            while (todo) {
-              const int src = __ffsll((long long)todo) - 1;  // the lane that holds this (token, head)
-              todo &= todo - 1;
-              const int js = src >> 4, ns = src & 15;
-              const int t_src = (a * TILES + (4 * js) / GPAD) * 16 + ns;
-              const int h_src = (4 * js) % GPAD + r;
-              const float term = heavy_term<D>(buf, t_src, q_group + (int64_t)h_src * (D / 2), __shfl(m[r], src));
-              if (lane == src) sum[r] += term;
-            }
+            const unsigned long long b = __ballot(tok_base + t_local < L && hbase + r < gb && xs[0][a][r] >= hthr[r]);
+            if (lane == 0) heavy_mask[wave][blk][a][r] = b;
           }
         }
       }
+      // one block ahead is enough, and all that the registers of two workgroups per CU hold: without this the passes
+      // that have no branch here load two blocks ahead (300-400 registers, one workgroup per CU)
+      __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  // The wave's heavy terms into z[r], r = its lanes' four heads.  mask(blk, a, r): the lanes whose logit is one; mx[r]: the
+  // maximum the lane's exponentials are relative to; shared: a row block's 16 lanes all take its terms, else each
+  // lane its own.
+  auto add_heavy = [&](double (&z)[4], const float (&mx)[4], auto mask, bool shared) {
+    HeavyTerms* hv = reinterpret_cast<HeavyTerms*>(buf);  // the wave's staging buffer is free after its last block
+    static_assert(sizeof(HeavyTerms) <= sizeof(lds[0]), "heavy terms fit the staging buffer");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int done = 0, total = 1; done < total; done += kHeavyBatch) {  // usually one batch
+      total = 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int blk = 0; blk < BPW; ++blk)
+#pragma unroll
+          for (int a = 0; a < NACC; ++a) {
+            const unsigned long long b = mask(blk, a, r);
+            const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
+            if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
+              const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
+              hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
+              hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + hbase + r) * D;
+              hv->m[e] = mx[r];
+              hv->code[e] = 4 * (shared ? j : lane) + r;
+            }
+            total += __popcll(b);
+          }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int cnt = total - done < kHeavyBatch ? total - done : kHeavyBatch;
+      exact_terms<DT_BF16, D>(hv, cnt, p.K, p.q_last);
+      for (int e = 0; e < cnt; ++e)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[r] += hv->code[e] == 4 * (shared ? j : lane) + r ? hv->val[e] : 0.0;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+  };
+  if (HEAVY && seen_heavy) {
+    double z[4] = {0.0, 0.0, 0.0, 0.0};
+    add_heavy(z, m, [&](int blk, int a, int r) { return heavy_mask[wave][blk][a][r]; }, false);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sum[r] += (float)z[r];
   }
   if (MODE == SCORE_LOGITS) {
 #pragma unroll
-    for (int blk = 0; blk < kBlocksPerWave; ++blk) {
+    for (int blk = 0; blk < BPW; ++blk) {
+      const bool in = wave_base + (int64_t)blk * kBlockStride < L;  // wave-uniform: the block exists
 #pragma unroll
       for (int a = 0; a < NACC; ++a) {
         const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (tok < L && hbase + r < gb)
-            p.logits[logit_index(p.geo, p.n_chunks, row, p.g0 + hbase + r, tok)] = xs[KEEP ? blk : 0][a][r];
+        for (int r = 0; r < 4; ++r) {
+          float& x = xs[KEEP ? blk : 0][a][r];
+          if (in && tok < L && hbase + r < gb)
+            p.logits[logit_index(p.geo, p.n_chunks, p.chunk, row, p.g0 + hbase + r, tok)] = x;
+          else
+            x = -INFINITY;
+        }
       }
     }
+    // softmax partial of the chunk, heavy terms as in score_kernel
+    __shared__ float s_M[16], s_thr[16];
+    auto merge = [&](int g, bool use_max) -> float {  // the chunk's value of head g from part[wave][row block][r]
+      float v = use_max ? -INFINITY : 0.f;
+      for (int w = 0; w < kScoreWaves; ++w)
+        for (int jj = 0; jj < 4; ++jj)
+          if ((4 * jj) % GPAD == (g / 4) * 4) v = use_max ? fmaxf(v, part[w][jj][g % 4].x) : v + part[w][jj][g % 4].y;
+      return v;
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float M = -INFINITY;
+#pragma unroll
+      for (int blk = 0; blk < BPW; ++blk)
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) M = fmaxf(M, xs[KEEP ? blk : 0][a][r]);
+#pragma unroll
+      for (int o = 8; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+      if (n == 0) part[wave][j][r].x = M;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < gb) s_M[threadIdx.x] = merge(threadIdx.x, true);
+    __syncthreads();
+    float M4[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      M4[r] = hbase + r < gb ? s_M[hbase + r] : 0.f;
+      float sm = 0.f;
+#pragma unroll
+      for (int blk = 0; blk < BPW; ++blk)
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) sm += exp_fast(xs[KEEP ? blk : 0][a][r] - M4[r]);
+      sm = group_sum<16>(sm);
+      if (n == 0) part[wave][j][r].y = sm;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < gb) s_thr[threadIdx.x] = heavy_logit_threshold(s_M[threadIdx.x], merge(threadIdx.x, false));
+    __syncthreads();
+    bool any_heavy = false;
+    float thr[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      thr[r] = hbase + r < gb ? s_thr[hbase + r] : INFINITY;
+#pragma unroll
+      for (int blk = 0; blk < BPW; ++blk)
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) any_heavy |= xs[KEEP ? blk : 0][a][r] >= thr[r];
+    }
+    if (__any(any_heavy)) {  // wave-uniform: this wave's sums again, the heavy terms with fp64 exponents
+      double z[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float sm = 0.f;
+#pragma unroll
+        for (int blk = 0; blk < BPW; ++blk)
+#pragma unroll
+          for (int a = 0; a < NACC; ++a) {
+            const float x = xs[KEEP ? blk : 0][a][r];
+            sm += x >= thr[r] ? 0.f : exp_fast(x - M4[r]);
+          }
+        z[r] = (double)group_sum<16>(sm);
+      }
+      add_heavy(z, M4, [&](int blk, int a, int r) { return __ballot(xs[KEEP ? blk : 0][a][r] >= thr[r]); }, true);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (n == 0) part[wave][j][r].y = (float)z[r];
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < gb)
+      p.partials[((int64_t)row * p.geo.G + p.g0 + threadIdx.x) * p.n_chunks + chunk] =
+          make_float2(s_M[threadIdx.x], merge(threadIdx.x, false));
+    return;
   }
   if (MODE == SCORE_SCORES) {
     // xs holds exp(l - M) / Z of this lane's heads.  One list per row: the group's sum (the lanes that
@@ -440,7 +648,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
     const int64_t cand_lo = p.S, cand_hi = L - p.W;
     if (!per_q) {
 #pragma unroll
-      for (int blk = 0; blk < kBlocksPerWave; ++blk)
+      for (int blk = 0; blk < BPW; ++blk)
 #pragma unroll
         for (int a = 0; a < NACC; ++a) {
           float v = (xs[KEEP ? blk : 0][a][0] + xs[KEEP ? blk : 0][a][1]) + (xs[KEEP ? blk : 0][a][2] + xs[KEEP ? blk : 0][a][3]);
@@ -459,7 +667,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
       const bool mine = per_q ? (hbase <= li && li < hbase + 4) : rep;
       const int r_sel = per_q ? (li - hbase) & 3 : 0;
 #pragma unroll
-      for (int blk = 0; blk < kBlocksPerWave; ++blk)
+      for (int blk = 0; blk < BPW; ++blk)
 #pragma unroll
         for (int a = 0; a < NACC; ++a) {
           const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
@@ -517,19 +725,23 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
 // grid (chunks, rows).  A gated launch (rows the pre-filter could not certify, usually none) has a
 // few y-blocks only, each walking over all rows and working on the flagged ones: an empty launch
 // then costs a handful of workgroups instead of one per (chunk, row).
-template <int D, int GPAD, int MODE, bool PAGED>
-__global__ __launch_bounds__(kScoreThreads) void score_mfma_kernel(ScoreParams p, int gb) {
+template <int D, int GPAD, int MODE, bool PAGED, int BPW>
+__global__ __launch_bounds__(kScoreThreads, GPAD == 16 && MODE != SCORE_FILTER ? 1 : 2) void score_mfma_kernel(ScoreParams p, int gb) {
   if (MODE != SCORE_FILTER && p.gate.row_flag) {
     if (*p.gate.n_flagged == 0) return;  // the usual case: nothing to redo
     const int rows = p.geo.n_problems * p.geo.Hkv;
     for (int row = blockIdx.y; row < rows; row += gridDim.y) {
       if (p.gate.row_flag[row] == 0) continue;  // workgroup-uniform
-      score_mfma_chunk<D, GPAD, MODE, PAGED>(p, gb, row, (int)blockIdx.x);
+      score_mfma_chunk<D, GPAD, MODE, PAGED, BPW>(p, gb, row, (int)blockIdx.x);
       __syncthreads();  // the chunk's last LDS reads, before the next row's writes
     }
     return;
   }
-  score_mfma_chunk<D, GPAD, MODE, PAGED>(p, gb, (int)blockIdx.y, (int)blockIdx.x);
+  // Workgroups go to the eight XCDs in turn.  Where a row has a multiple of eight chunks, its first one (the sink
+  // tokens: heavy terms, a longer tail) would always meet the same XCD: the first eight chunks are rotated by the row.
+  // (All chunks rotated: 1.41 instead of 1.28 ms at 256 rows x 128 chunks, the stream over K loses its order.)
+  const unsigned chunk = blockIdx.x < 8 && gridDim.x >= 8 ? (blockIdx.x + blockIdx.y) & 7u : blockIdx.x;
+  score_mfma_chunk<D, GPAD, MODE, PAGED, BPW>(p, gb, (int)blockIdx.y, (int)chunk);
 }
 
 // Logits of the sampled blocks (fast path), same MFMA scheme as score_mfma_kernel: one wave per
@@ -607,91 +819,6 @@ __global__ __launch_bounds__(64) void stats_kernel(StatsParams p) {
   }
 }
 
-// One-sweep dense path: every token's fp32 logit is in scratch, so a head's normaliser is summed from
-// there once its maximum is known: Z = sum_i exp(l_i - M) in fp64, the terms heavy enough for their
-// logit's fp32 error to show in Z (heavy_logit_threshold) with the logit recomputed in fp64 from K.
-// (The pre-filtered and two-sweep paths do the same inside the score kernel, with a threshold from
-// the sample; here nothing is known about the row before the sweep.)  One workgroup per row.
-constexpr int kMaxHeavy = 4096;  // heavy terms per (row, head) taken exactly; beyond: as fp32 terms
-
-template <int DT>
-__global__ __launch_bounds__(kTopkThreads) void stats_exact_kernel(ExactStatsParams p) {
-  __shared__ double red_d[kTopkWaves];
-  __shared__ RowStat s_stat[64];  // up to 64 heads per KV head
-  __shared__ float s_thr[64];
-  __shared__ int heavy_tok[kMaxHeavy];
-  __shared__ int n_heavy;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = blockIdx.x;
-  const int G = p.geo.G, D = p.geo.D;
-  const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
-  const int64_t L = p.geo.L;
-  for (int b = tid; b < kHistBins * p.n_lists; b += kTopkThreads) p.ghist[(int64_t)row * p.n_lists * kHistBins + b] = 0;
-  // the chunks' maxima and fp32 sums, one wave per head: M, and a Z that stands unless the head has heavy terms
-  for (int g = wave; g < G; g += kTopkWaves) {
-    const RowStat st = merge_partials_wave(p.partials + ((int64_t)row * G + g) * p.n_chunks, p.n_chunks);
-    if (lane == 0) {
-      s_stat[g] = st;
-      s_thr[g] = heavy_logit_threshold(st.M, (float)st.Z);
-    }
-  }
-  __syncthreads();
-  auto block_sum = [&](double v) -> double {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-    __syncthreads();  // red_d free
-    if (lane == 0) red_d[wave] = v;
-    __syncthreads();
-    double t = 0.0;
-    for (int w = 0; w < kTopkWaves; ++w) t += red_d[w];
-    return t;
-  };
-  for (int g = 0; g < G; ++g) {
-    const float M = s_stat[g].M, thr = s_thr[g];
-    if (!(thr <= M)) continue;  // no term of this head is heavy enough (workgroup-uniform)
-    __syncthreads();            // the previous head's list has been read
-    if (tid == 0) n_heavy = 0;
-    __syncthreads();
-    // the row's logits of this head, four at a time (a chunk's kScoreChunk logits of a head are contiguous)
-    double z = 0.0;
-    for (int64_t t4 = (int64_t)tid * 4; t4 < L; t4 += 4 * kTopkThreads) {
-      const float4 v = *reinterpret_cast<const float4*>(p.logits + logit_index(p.geo, p.n_chunks, row, g, t4));
-      const float x[4] = {v.x, v.y, v.z, v.w};
-      float part = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (t4 + e >= L) break;
-        bool exact = x[e] >= thr;
-        if (exact) {
-          const int i = atomicAdd(&n_heavy, 1);
-          if (i < kMaxHeavy) heavy_tok[i] = (int)(t4 + e); else exact = false;
-        }
-        if (!exact) part += exp_fast(x[e] - M);
-      }
-      z += (double)part;
-    }
-    z = block_sum(z);  // (its barriers also publish heavy_tok)
-    const int nh = n_heavy < kMaxHeavy ? n_heavy : kMaxHeavy;
-    const double inv = 1.0 / sqrt((double)D);
-    const int64_t q_off = ((int64_t)prob * p.geo.Hq + c * G + g) * D;
-    double zh = 0.0;
-    for (int i = wave; i < nh; i += kTopkWaves) {
-      const int64_t k_off = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, heavy_tok[i]);
-      double acc = 0.0;
-      for (int jj = lane; jj < D; jj += 64) acc += elem_f64<DT>(p.q_last, q_off + jj) * elem_f64<DT>(p.K, k_off + jj);
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
-      if (lane == 0) zh += exp(acc * inv - (double)M);
-    }
-    z += block_sum(zh);
-    if (tid == 0) {
-      s_stat[g].Z = z;
-      s_stat[g].invZ = (float)(1.0 / z);
-    }
-  }
-  __syncthreads();
-  if (tid < G) p.stats[(int64_t)row * G + tid] = s_stat[tid];
-}
-
 constexpr int kCombineThreads = 256;
 constexpr int kMaxG = 64;
 
@@ -722,7 +849,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(CombineParams 
     if (tok >= L) break;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int g = g_lo; g < g_hi; ++g) {
-      const float4 x = *reinterpret_cast<const float4*>(p.logits + logit_index(p.geo, p.n_chunks, row, g, tok));
+      const float4 x = *reinterpret_cast<const float4*>(p.logits + logit_index(p.geo, p.n_chunks, p.chunk, row, g, tok));
       const float M = sM[g], inv = sInv[g];
       acc[0] += exp_times(x.x - M, inv);
       acc[1] += exp_times(x.y - M, inv);
@@ -750,12 +877,12 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(CombineParams 
   }
 }
 
-template <int DT, int D>
+template <int DT, int D, int BPW>
 hipError_t launch_score_g(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
   switch (gb) {
 #define SAGEKV_CASE(N) \
   case N:              \
-    hipLaunchKernelGGL((score_kernel<DT, D, N>), grid, dim3(kScoreThreads), 0, s, p); \
+    hipLaunchKernelGGL((score_kernel<DT, D, N, BPW>), grid, dim3(kScoreThreads), 0, s, p); \
     break;
     SAGEKV_CASE(1) SAGEKV_CASE(2) SAGEKV_CASE(3) SAGEKV_CASE(4)
     SAGEKV_CASE(5) SAGEKV_CASE(6) SAGEKV_CASE(7) SAGEKV_CASE(8)
@@ -766,21 +893,39 @@ hipError_t launch_score_g(const ScoreParams& p, int gb, dim3 grid, hipStream_t s
   return hipGetLastError();
 }
 
-template <int D, int MODE, bool PAGED>
+template <int D>
+hipError_t launch_score_f32(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
+  switch (p.chunk) {
+    case 256: return launch_score_g<DT_F32, D, 1>(p, gb, grid, s);
+    case 512: return launch_score_g<DT_F32, D, 2>(p, gb, grid, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int D, int MODE, bool PAGED, int BPW>
 hipError_t launch_score_mfma_p(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
   if (gb <= 4)
-    hipLaunchKernelGGL((score_mfma_kernel<D, 4, MODE, PAGED>), grid, dim3(kScoreThreads), 0, s, p, gb);
+    hipLaunchKernelGGL((score_mfma_kernel<D, 4, MODE, PAGED, BPW>), grid, dim3(kScoreThreads), 0, s, p, gb);
   else if (gb <= 8)
-    hipLaunchKernelGGL((score_mfma_kernel<D, 8, MODE, PAGED>), grid, dim3(kScoreThreads), 0, s, p, gb);
+    hipLaunchKernelGGL((score_mfma_kernel<D, 8, MODE, PAGED, BPW>), grid, dim3(kScoreThreads), 0, s, p, gb);
   else
-    hipLaunchKernelGGL((score_mfma_kernel<D, 16, MODE, PAGED>), grid, dim3(kScoreThreads), 0, s, p, gb);
+    hipLaunchKernelGGL((score_mfma_kernel<D, 16, MODE, PAGED, BPW>), grid, dim3(kScoreThreads), 0, s, p, gb);
   return hipGetLastError();
+}
+
+template <int D, int MODE, int BPW>
+hipError_t launch_score_mfma_b(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
+  return p.pm.table ? launch_score_mfma_p<D, MODE, true, BPW>(p, gb, grid, s)
+                    : launch_score_mfma_p<D, MODE, false, BPW>(p, gb, grid, s);
 }
 
 template <int D, int MODE>
 hipError_t launch_score_mfma(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
-  return p.pm.table ? launch_score_mfma_p<D, MODE, true>(p, gb, grid, s)
-                    : launch_score_mfma_p<D, MODE, false>(p, gb, grid, s);
+  if constexpr (MODE != SCORE_SCORES) {
+    if (p.chunk == 256) return launch_score_mfma_b<D, MODE, 1>(p, gb, grid, s);
+    if (p.chunk == 512) return launch_score_mfma_b<D, MODE, 2>(p, gb, grid, s);
+  }
+  return launch_score_mfma_b<D, MODE, kScoreChunk / (64 * kScoreWaves)>(p, gb, grid, s);
 }
 
 template <int MODE>
@@ -823,7 +968,9 @@ hipError_t launch_score(const ScoreParams& p0, ScoreMode mode, hipStream_t s) {
   const int rows = p0.geo.n_problems * p0.geo.Hkv;
   const bool bf16 = p0.geo.dtype == DT_BF16;
   if (mode == SCORE_FILTER || (!bf16 && (mode != SCORE_LOGITS || p0.gate.row_flag))) return hipErrorInvalidValue;
-  dim3 grid((unsigned)p0.n_chunks, (unsigned)(p0.gate.row_flag && rows > kGatedRowBlocks ? kGatedRowBlocks : rows));
+  // partials only and scores: whole kScoreChunk chunks, whatever the first pass used
+  const unsigned nx = mode == SCORE_SCORES ? (unsigned)((p0.geo.L + kScoreChunk - 1) / kScoreChunk) : (unsigned)p0.n_chunks;
+  dim3 grid(nx, (unsigned)(p0.gate.row_flag && rows > kGatedRowBlocks ? kGatedRowBlocks : rows));
   const int per_launch = bf16 ? 16 : max_group_per_launch();
   for (int g0 = 0; g0 < p0.geo.G; g0 += per_launch) {
     ScoreParams p = p0;
@@ -831,7 +978,7 @@ hipError_t launch_score(const ScoreParams& p0, ScoreMode mode, hipStream_t s) {
     const int gb = p0.geo.G - g0 < per_launch ? p0.geo.G - g0 : per_launch;
     hipError_t e;
     if (!bf16)
-      e = p.geo.D == 128 ? launch_score_g<DT_F32, 128>(p, gb, grid, s) : launch_score_g<DT_F32, 64>(p, gb, grid, s);
+      e = p.geo.D == 128 ? launch_score_f32<128>(p, gb, grid, s) : launch_score_f32<64>(p, gb, grid, s);
     else if (mode == SCORE_LOGITS)
       e = launch_score_mfma_d<SCORE_LOGITS>(p, gb, grid, s);
     else if (mode == SCORE_PARTIALS)
@@ -845,15 +992,6 @@ hipError_t launch_score(const ScoreParams& p0, ScoreMode mode, hipStream_t s) {
 
 hipError_t launch_stats(const StatsParams& p, int rows, hipStream_t s) {
   hipLaunchKernelGGL(stats_kernel, dim3((unsigned)rows), dim3(64), 0, s, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_stats_exact(const ExactStatsParams& p, hipStream_t s) {
-  const int rows = p.geo.n_problems * p.geo.Hkv;
-  if (p.geo.dtype == DT_BF16)
-    hipLaunchKernelGGL(stats_exact_kernel<DT_BF16>, dim3((unsigned)rows), dim3(kTopkThreads), 0, s, p);
-  else
-    hipLaunchKernelGGL(stats_exact_kernel<DT_F32>, dim3((unsigned)rows), dim3(kTopkThreads), 0, s, p);
   return hipGetLastError();
 }
 

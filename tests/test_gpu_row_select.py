@@ -1,0 +1,72 @@
+"""The one-sweep dense path: rows whose scores one workgroup holds in registers (up to 32768 tokens, four sizes), the
+longer ones behind them, and the softmax terms that a score chunk takes with fp64 exponents."""
+import numpy as np
+import pytest
+
+import synth
+from tests import gpu_util as gu
+from tests.test_gpu_parity import rand_case
+
+pytestmark = pytest.mark.gpu
+BF16, F32 = synth.BF16, synth.F32
+DENSE = 1
+
+
+def parity(ref, dtype, head_mode, q, K, V, S, W, k):
+    """Kept sets of the dense path, with and without the scores written out, against the oracle's."""
+    G = q.shape[1] // K.shape[1]
+    lists = G if head_mode else 1
+    Kc, _, kept, s = ref.select(dtype, head_mode, q, K, V, S, W, k, want_scores=True)
+    for want_scores in (False, True):
+        out = gu.gpu_select(dtype, q, K, V, S, W, k, want_scores=want_scores, flags=DENSE, head_mode=head_mode)
+        exempt = 0
+        for li in range(lists):
+            cut = lambda a: np.concatenate([a[..., :S], a[..., S + li * k:S + (li + 1) * k], a[..., S + lists * k:]], axis=-1)
+            exempt += gu.check_kept(cut(out["kept"]), cut(kept), s[:, :, li], S, W, k)
+        if exempt == 0:
+            np.testing.assert_array_equal(out["Kc"][:, :, : S + lists * k + W], Kc)
+        if want_scores:
+            gu.check_scores(out["scores"].reshape(s.shape), s)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,head_mode", [(BF16, 8, 2, 128, 0), (F32, 4, 2, 64, 0), (BF16, 7, 1, 64, 1), (F32, 20, 1, 128, 0)])
+@pytest.mark.parametrize("L", [9, 255, 4096, 4097, 8192, 8193, 16384, 16389, 32768, 32769])
+def test_row_lengths_around_the_register_sizes(ref, dtype, Hq, Hkv, d, head_mode, L):
+    S, W = min(3, L // 4), max(1, L // 50)
+    E = L - S - W
+    q, K, V = rand_case(L + Hq, 1, Hq, Hkv, d, L, dtype)
+    for k in sorted({1, E // 4 + 1, E - 1}):
+        parity(ref, dtype, head_mode, q, K, V, S, W, k)
+
+
+@pytest.mark.parametrize("L", [700, 9001, 30000])
+def test_thousands_of_equal_scores(ref, L):
+    """q = 0 (every score equal) and keys that repeat eight rows (every score L / 8 times): more near-ties than the band
+    holds; equal scores go to the lowest positions."""
+    P, Hq, Hkv, d, S, W = 1, 8, 2, 64, 2, 5
+    q, K, V = rand_case(L, P, Hq, Hkv, d, L, BF16)
+    K[:] = K[:, :, np.arange(L) % 8]
+    for scale in (0.0, 1.0):
+        qs = synth.round_to_dtype(scale * synth.to_f64(q, BF16), BF16)
+        for k in (1, L // 3, L - S - W - 1):
+            parity(ref, BF16, 0, qs, K, V, S, W, k)
+
+
+@pytest.mark.parametrize("dtype,flags,L", [(BF16, DENSE, 6000), (F32, 0, 6000), (BF16, 0, 40000), (BF16, DENSE, 40000)])
+def test_many_heavy_terms_in_one_chunk(ref, dtype, flags, L):
+    """Peaked attention (queries x 6) and 120 heavy tokens side by side: more exact softmax terms than one batch of
+    them holds.  The kept set needs every head's normaliser to about 1e-7."""
+    P, Hq, Hkv, d, S, W, k = 1, 8, 2, 128, 4, 64, 700
+    G = Hq // Hkv
+    q, K, V = rand_case(L + flags, P, Hq, Hkv, d, L, dtype)
+    q64 = 6.0 * synth.to_f64(q, dtype)
+    unit = q64.reshape(P, Hkv, G, d)
+    unit = unit / np.linalg.norm(unit, axis=-1, keepdims=True)
+    K64 = synth.to_f64(K, dtype)
+    K64[:, :, 2:122] += 4.0 * unit.sum(2)[:, :, None, :]
+    q, K = synth.round_to_dtype(q64, dtype), synth.round_to_dtype(K64, dtype)
+    _, _, kept, s = ref.select(dtype, 0, q, K, V, S, W, k, want_scores=True)
+    top = np.sort(s[0, :, 0].astype(np.float64), axis=-1)[:, ::-1]
+    assert (top[:, :32].sum(1) > 0.3 * G).all()  # a few tokens hold much of the mass
+    out = gu.gpu_select(dtype, q, K, V, S, W, k, want_scores=False, flags=flags)
+    assert gu.check_kept(out["kept"], kept, s[:, :, 0], S, W, k) == 0
