@@ -29,6 +29,7 @@ constexpr int64_t kFillWorkgroups = 512;  // see score_chunk
 struct FastPlan {
   bool ok;
   int nA, nB, nC, validA, validC, rank, cap, Gs;
+  int expect;  // candidates a list usually has at most
   int cap_c;  // candidate slots each score chunk owns; what does not fit goes to the row's overflow pool (cap slots)
   int64_t stepB;
   float wA, wB, wC;
@@ -77,6 +78,7 @@ FastPlan fast_plan(const sagekv_select_desc* d) {
   const double r0 = (1.0 + margin) * (double)d->k * (double)(64 * f.nB) / (double)E;
   const double x = 2.0 + sqrt(4.0 + r0);
   f.rank = (int)ceil(x * x);
+  f.expect = (int)(((double)f.rank + 4.0 * sqrt((double)f.rank)) * (double)f.wB);
   // Room for the candidates: about rank * wB tokens pass a list's threshold, 4 sigma high side
   // (rank + 4 sqrt(rank)) * wB; per-query lists share one candidate list per row (their union).
   // (a heavy-tailed row may raise its rank to twice the planned one, see sample_stats_kernel)
@@ -89,7 +91,7 @@ FastPlan fast_plan(const sagekv_select_desc* d) {
     f.ok = false;
     return f;
   }
-  f.Gs = (G + 3) / 4 * 4;
+  f.Gs = G <= 4 ? 4 : G <= 8 ? 8 : 16;  // whole, aligned 16-byte quads, a power of two of them
   // A chunk's own slots: twice the candidates an average chunk is expected to keep (rank * wB tokens
   // per list over the row's chunks), so that only chunks where the candidates crowd (a needle
   // cluster, the tokens next to the recent window of a trained model) reach into the overflow pool.
@@ -606,6 +608,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     cp.list_info = (float2*)(ws + l.list_info);
     cp.cap = f.cap;
     cp.Gs = f.Gs;
+    cp.expect = f.expect;
     cp.n_lists = l.n_lists;
     cp.q_last = q_last;
     cp.K = K;

@@ -30,140 +30,143 @@ constexpr int kFastMaxG = 16;
 constexpr float kHeavyShare = 0.01f;  // see sample_stats_kernel (0.3 % and 0.1 % measured worse)
 
 // Per row: approximate softmax statistics of every head from the sampled logits; per selection list
-// (one per row, or one per query head): approximate scores of the sampled candidates and their
-// rank-th largest value = the list's filter threshold.  A row with several lists is shared by
-// gridDim.y workgroups, each repeating the (cheap) statistics and taking its part of the lists.
+// (one per row, or one per query head): approximate scores of the sampled candidates and a lower bound
+// of their rank-th largest (within 1/2048 of their range) = the list's filter threshold.
+//
+// One workgroup per row: latency bound, a chain of barriers.  The sampled logits are read once: a thread holds NI
+// items, an item being the logits of one head quad (4 heads, 16 bytes) of one sample slot, and always the same
+// quad.  NI = 0: more items than registers (16 heads and a large sample), they are read from memory in every pass.
+template <int GQ, int NI>
 __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams p) {
-  __shared__ TopkShared sh;
-  __shared__ float2 red[kTopkWaves][kFastMaxG];
-  __shared__ float sM[kFastMaxG], sInv[kFastMaxG], sHeavy[kFastMaxG];
-  __shared__ float ss[8192];  // approximate scores of the sampled candidates
+  __shared__ RegSelect sh;
+  __shared__ float2 red[kTopkWaves][4 * GQ];
+  __shared__ float sM[4 * GQ], sInv[4 * GQ], sZ[4 * GQ], sHeavy[4 * GQ];
 
   const int row = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int G = p.geo.G, Gs = p.Gs;
+  const int G = p.geo.G;
   const bool per_head = p.n_lists > 1;
-  const int lists_per_wg = (p.n_lists + (int)gridDim.y - 1) / (int)gridDim.y;
-  const int list_lo = (int)blockIdx.y * lists_per_wg;
-  const int list_hi = list_lo + lists_per_wg < p.n_lists ? list_lo + lists_per_wg : p.n_lists;
-  const int n_slots = 64 * (p.nA + p.nB + p.nC), nB = 64 * p.nB;
-  const float* slog = p.samp_logit + (int64_t)row * n_slots * Gs;
-  if (tid == 0 && blockIdx.y == 0) {
+  const int n_slots = 64 * (p.nA + p.nB + p.nC), lo_b = 64 * p.nA, nB = 64 * p.nB;
+  const int qd = tid % GQ;  // this thread's head quad
+  const float* slog = p.samp_logit + (int64_t)row * n_slots * (4 * GQ) + 4 * qd;
+  if (tid == 0) {
     p.row_fail[row] = 0;
     p.ovf_count[row] = 0;
     if (row == 0) *p.n_fail = 0;
   }
-
-  // weight of sample slot s (0 = the slot is outside the part its block samples)
+  // slot of item i, and the tokens of the row it stands for (0 = outside the part its block samples)
+  auto slot_of = [&](int i) { return tid / GQ + i * (kTopkThreads / GQ); };
   auto weight = [&](int s) -> float {
     const int b = s >> 6, t = s & 63;
+    if (s >= n_slots) return 0.f;
     if (b < p.nA) return t < p.validA ? p.wA : 0.f;
     if (b < p.nA + p.nB) return p.wB;
-    return 64 * (p.nA + p.nB + p.nC) - s <= p.validC ? p.wC : 0.f;
+    return n_slots - s <= p.validC ? p.wC : 0.f;
   };
-  // logits of heads g4 .. g4 + 3 of sample slot s (rows of samp_logit are padded to a multiple of 4
-  // heads: 16-byte loads)
-  auto load4 = [&](int s, int g4, float (&xs)[4]) {
-    const float4 v = *reinterpret_cast<const float4*>(slog + (int64_t)s * Gs + g4);
-    xs[0] = v.x, xs[1] = v.y, xs[2] = v.z, xs[3] = v.w;
+  auto load = [&](int s) { return *reinterpret_cast<const f32x4_t*>(slog + (int64_t)s * (4 * GQ)); };
+  f32x4_t x[NI > 0 ? NI : 1];  // logits, later exp(logit - M)
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    x[i] = f32x4_t{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    if (weight(slot_of(i)) > 0.f) x[i] = load(slot_of(i));
+  }
+  const int n_items = (n_slots * GQ + kTopkThreads - 1) / kTopkThreads;
+  // f(item's four values, slot, weight) for the thread's items
+  auto each = [&](auto f) {
+    if (NI > 0) {
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const float w = weight(slot_of(i));
+        if (w > 0.f) f(x[i], slot_of(i), w);
+      }
+    } else {
+      for (int i = 0; i < n_items; ++i) {
+        const float w = weight(slot_of(i));
+        if (w > 0.f) {
+          f32x4_t v = load(slot_of(i));
+          f(v, slot_of(i), w);
+        }
+      }
+    }
+  };
+  // over the lanes that share a quad, then the waves: component r of the result is in red[wave][4 * qd + r]
+  auto reduce = [&](float (&a)[4], float (&b)[4], bool maximum) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+#pragma unroll
+      for (int o = 32; o >= GQ; o >>= 1) {
+        const float y = __shfl_xor(a[r], o);
+        a[r] = maximum ? fmaxf(a[r], y) : a[r] + y;
+        if (!maximum) b[r] += __shfl_xor(b[r], o);
+      }
+      if (lane < GQ) red[wave][4 * qd + r] = make_float2(a[r], b[r]);
+    }
+    __syncthreads();
   };
 
-  // approximate softmax statistics per head, one pass: M^ = max, Z^ = sum of weight * exp(l - M^)
-  {
-    float m[kFastMaxG], z[kFastMaxG];
+  // approximate softmax statistics: M^ = max, Z^ = sum of weight * exp(l - M^)
+  float a4[4], b4[4];
 #pragma unroll
-    for (int g = 0; g < kFastMaxG; ++g) {
-      m[g] = -INFINITY;
-      z[g] = 0.f;
+  for (int r = 0; r < 4; ++r) a4[r] = -INFINITY, b4[r] = 0.f;
+  each([&](f32x4_t& v, int, float) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a4[r] = fmaxf(a4[r], v[r]);
+  });
+  reduce(a4, b4, true);
+  if (tid < 4 * GQ) {
+    float M = red[0][tid].x;
+    for (int w = 1; w < kTopkWaves; ++w) M = fmaxf(M, red[w][tid].x);
+    sM[tid] = M;
+  }
+  __syncthreads();
+  float M4[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) M4[r] = sM[4 * qd + r], a4[r] = 0.f, b4[r] = 0.f;
+  auto expo = [&](const f32x4_t& v) {
+    return f32x4_t{exp_fast(v[0] - M4[0]), exp_fast(v[1] - M4[1]), exp_fast(v[2] - M4[2]), exp_fast(v[3] - M4[3])};
+  };
+  each([&](f32x4_t& v, int, float w) {
+    const f32x4_t e = expo(v);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) a4[r] += w * e[r];
+    v = e;  // (registers: from here on the exponentials; from memory: a copy)
+  });
+  reduce(a4, b4, false);
+  if (tid < 4 * GQ) {
+    float z = 0.f;
+    for (int w = 0; w < kTopkWaves; ++w) z += red[w][tid].x;
+    sZ[tid] = z;  // first estimate of Z^, refined below
+  }
+  __syncthreads();
+  // A sampled token that would alone stand for more than 1 % of the head's mass is a heavy token, and heavy
+  // tokens are rare: it is counted once, not once per token it was meant to represent.  (Attention mass sits on
+  // few tokens; scaling such a token up by the sampling rate would put the head's normaliser off by a large
+  // factor and the row could not be certified.  Under-counting only lets a few more candidates through.)
+  float Z4[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) Z4[r] = sZ[4 * qd + r], a4[r] = 0.f, b4[r] = 0.f;
+  each([&](f32x4_t& v, int, float w) {
+    const f32x4_t e = NI > 0 ? v : expo(v);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool heavy = w * e[r] > kHeavyShare * Z4[r];
+      a4[r] += (heavy ? 1.f : w) * e[r];
+      b4[r] += heavy && w > 1.f ? w * e[r] : 0.f;  // a token that stands for itself alone (the sink) is no surprise
     }
-    for (int s = tid; s < n_slots; s += kTopkThreads) {
-      const float w = weight(s);
-      if (w > 0.f) {
-#pragma unroll
-        for (int g4 = 0; g4 < kFastMaxG; g4 += 4)
-          if (g4 < G) {
-            float xs[4];
-            load4(s, g4, xs);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (g4 + e < G) {
-                const int g = g4 + e;
-                const float mn = fmaxf(m[g], xs[e]);
-                z[g] = z[g] * exp_fast(m[g] - mn) + w * exp_fast(xs[e] - mn);
-                m[g] = mn;
-              }
-          }
-      }
+  });
+  reduce(a4, b4, false);
+  if (tid < G) {
+    float zz = 0.f, hh = 0.f;
+    for (int w = 0; w < kTopkWaves; ++w) {
+      zz += red[w][tid].x;
+      hh += red[w][tid].y;
     }
-#pragma unroll
-    for (int g = 0; g < kFastMaxG; ++g)
-      if (g < G) {
-        const float M = wave_max(m[g]);
-        float zz = (m[g] == -INFINITY) ? 0.f : z[g] * exp_fast(m[g] - M);
-        zz = group_sum<64>(zz);
-        if (lane == 0) red[wave][g] = make_float2(M, zz);
-      }
-    __syncthreads();
-    if (tid < G) {
-      float M = red[0][tid].x;
-      for (int w = 1; w < kTopkWaves; ++w) M = fmaxf(M, red[w][tid].x);
-      float zz = 0.f;
-      for (int w = 0; w < kTopkWaves; ++w)
-        zz += (red[w][tid].x == -INFINITY) ? 0.f : red[w][tid].y * exp_fast(red[w][tid].x - M);
-      sM[tid] = M;
-      sInv[tid] = zz;  // first estimate of Z^, refined below
-    }
-    __syncthreads();
-    // Second pass: a sampled token that would alone stand for more than 1 % of the head's mass is a
-    // heavy token, and heavy tokens are rare: it is counted once, not once per token it was meant
-    // to represent.  (Attention mass sits on few tokens; scaling such a token up by the sampling
-    // rate would put the head's normaliser off by a large factor and the row could not be
-    // certified.  Under-counting only lets a few more candidates through.)
-    float zh[kFastMaxG];  // what the heavy tokens had added to the first estimate
-#pragma unroll
-    for (int g = 0; g < kFastMaxG; ++g) z[g] = zh[g] = 0.f;
-    for (int s = tid; s < n_slots; s += kTopkThreads) {
-      const float w = weight(s);
-      if (w > 0.f) {
-#pragma unroll
-        for (int g4 = 0; g4 < kFastMaxG; g4 += 4)
-          if (g4 < G) {
-            float xs[4];
-            load4(s, g4, xs);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (g4 + i < G) {
-                const int g = g4 + i;
-                const float e = exp_fast(xs[i] - sM[g]);
-                const bool heavy = w * e > kHeavyShare * sInv[g];
-                z[g] += (heavy ? 1.f : w) * e;
-                zh[g] += heavy ? w * e : 0.f;
-              }
-          }
-      }
-    }
-    __syncthreads();  // every thread has read the first estimates
-#pragma unroll
-    for (int g = 0; g < kFastMaxG; ++g)
-      if (g < G) {
-        const float zz = group_sum<64>(z[g]);
-        const float hh = group_sum<64>(zh[g]);
-        if (lane == 0) red[wave][g] = make_float2(hh, zz);
-      }
-    __syncthreads();
-    if (tid < G) {
-      float zz = 0.f, hh = 0.f;
-      for (int w = 0; w < kTopkWaves; ++w) {
-        hh += red[w][tid].x;
-        zz += red[w][tid].y;
-      }
-      sHeavy[tid] = hh / sInv[tid];  // share of the first estimate that came from heavy tokens
-      sInv[tid] = 1.0f / zz;
-      if (blockIdx.y == 0) {
-        p.samp_stats[(int64_t)row * G + tid] = make_float2(sM[tid], 1.0f / zz);
-        p.heavy_thr[(int64_t)row * G + tid] = heavy_logit_threshold(sM[tid], zz);
-      }
-    }
+    sHeavy[tid] = hh / sZ[tid];  // share of the first estimate that came from heavy tokens
+    sInv[tid] = 1.0f / zz;
+    p.samp_stats[(int64_t)row * G + tid] = make_float2(sM[tid], 1.0f / zz);
+    p.heavy_thr[(int64_t)row * G + tid] = heavy_logit_threshold(sM[tid], zz);
+  } else if (tid < 4 * GQ) {
+    sInv[tid] = 0.f;  // padding heads add nothing to a score
   }
   __syncthreads();
   // A heavy-tailed row (the sample met heavy tokens) has heads whose normalisers are known with
@@ -179,37 +182,45 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
     rank = (int)((float)p.rank * (1.f + grow));
     if (rank > nB) rank = nB;
   }
+  float I4[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) I4[r] = sInv[4 * qd + r];
 
-  // group-sum: the threshold is on the summed approximate score; per-query: on the head's own
-  for (int li = list_lo; li < list_hi; ++li) {
-    __syncthreads();  // the previous list's select has read ss
-    for (int s = tid; s < nB; s += kTopkThreads) {
-      const float* lg = slog + (int64_t)(64 * p.nA + s) * Gs;
+  // group-sum: the threshold is on the summed approximate score; per-query: on the head's own.  Every thread takes part for
+  // every item (the quads of a slot sit in adjacent lanes); -1: not a sampled candidate, or not this thread's.
+  for (int li = 0; li < p.n_lists; ++li) {
+    auto score = [&](const f32x4_t& e, int s) -> float {
       float a = 0.f;
+      bool mine;
       if (per_head) {
-        a = exp_fast(lg[li] - sM[li]) * sInv[li];
+        mine = qd == (li >> 2);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) a = (li & 3) == r ? e[r] * I4[r] : a;
       } else {
+        mine = qd == 0;
 #pragma unroll
-        for (int g4 = 0; g4 < kFastMaxG; g4 += 4)
-          if (g4 < G) {
-            float xs[4];
-            load4(64 * p.nA + s, g4, xs);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (g4 + i < G) a += exp_fast(xs[i] - sM[g4 + i]) * sInv[g4 + i];
-          }
+        for (int r = 0; r < 4; ++r) a += e[r] * I4[r];
+        if (GQ >= 2) a += __shfl_xor(a, 1);
+        if (GQ >= 4) a += __shfl_xor(a, 2);
       }
-      ss[s] = a;
+      return mine && s >= lo_b && s < lo_b + nB ? a : -1.f;
+    };
+    uint32_t tlo = 0u, thi;
+    if (rank >= 1 && p.rank <= nB) {  // rank beyond the sample: everything passes (the row is then redone densely)
+      bracket_kth<false>(sh, [&](auto f) {
+        if (NI > 0) {
+#pragma unroll
+          for (int i = 0; i < NI; ++i) f(score(x[i], slot_of(i)));
+        } else {
+          for (int i = 0; i < n_items; ++i) {
+            const int s = slot_of(i) < n_slots ? slot_of(i) : n_slots - 1;
+            f(score(expo(load(s)), slot_of(i)));
+          }
+        }
+      }, rank, &tlo, &thi);
     }
-    __syncthreads();
-    float tau_f = 0.f;  // rank beyond the sample: everything passes (the row is then redone densely)
-    if (rank >= 1 && p.rank <= nB) {
-      uint32_t tau;
-      int quota;
-      radix_select(sh, ss, nB, rank, false, &tau, &quota);
-      tau_f = __uint_as_float(tau);
-    }
-    if (tid == 0) p.samp_tau[(int64_t)row * p.n_lists + li] = tau_f;
+    if (tid == 0) p.samp_tau[(int64_t)row * p.n_lists + li] = __uint_as_float(tlo);
+    __syncthreads();  // the histogram is cleared for the next list
   }
 }
 
@@ -222,329 +233,410 @@ __device__ __forceinline__ void flag_row(const TopkCandParams& p, int row, int r
 
 // Shared state of the candidate selection kernels.
 struct CandShared {
-  TopkShared sh;
+  RegSelect rs;
   float sM[kFastMaxG], sInv[kFastMaxG];
   RowStat stat[kFastMaxG];  // exact statistics of the row's heads
   double rho[kFastMaxG], flushed[kFastMaxG];
   float bound[kFastMaxG];   // per-query lists: the bound of each head's list,
   float thr[kFastMaxG];     // and the same bound as a logit of that head
   int n_list[kFastMaxG];    // per-query lists: candidates each list has kept
-  int band_j[kMaxBand], band_tok[kMaxBand];
-  float band_v[kMaxBand];
-  int n_band, n_above;
   int chunk_off[1025];
   int raw_total;
 };
 
-// First half, one workgroup per row: sink and recent indices, the exact softmax statistics of the row's
-// heads, and the candidates' scratch lists.  One list per row (PQ false): cand_score / cand_pos get the
-// exact fp32 score and the token of every candidate; *bound = the bound on a dropped token's score,
-// *n_c = the number of candidates.  Per-query lists (PQ): the row's shared candidate records are read
-// once and list g gets the LOGIT of head g and the token of every candidate that can reach the list's
-// bound (s.bound[g], counts in s.n_list[g]).  False: nothing to select (k = 0) or the row was flagged.
-template <int DT, bool PQ>
-__device__ __forceinline__ bool cand_lists(const TopkCandParams& p, CandShared& s, int row, float* bound, int* n_c) {
-  const int tid = threadIdx.x;
-  const int S = p.S, W = p.W, k = p.k, G = p.geo.G;
-  const int64_t L = p.geo.L;
-  const int n_kept = S + p.n_lists * k + W;
-  int32_t* kept_row = p.kept_idx + (int64_t)row * n_kept;
-
-  for (int t = tid; t < S; t += kTopkThreads) kept_row[t] = t;
-  for (int t = tid; t < W; t += kTopkThreads) kept_row[S + p.n_lists * k + t] = (int32_t)(L - W + t);
-  // the dense stages that redo a flagged row add to its lists' first-digit histograms
-  for (int b = tid; b < kHistBins * p.n_lists; b += kTopkThreads) p.ghist[(int64_t)row * p.n_lists * kHistBins + b] = 0;
-
-  // Exact softmax statistics of the row's heads, one wave per head, from the partials of the
-  // filtering pass; and how far the sampled statistics were off: rho = (exact weight) / (sampled weight).
-  {
-    const int g = tid >> 6;
-    if (g < G) {
-      const RowStat st = merge_partials_wave(p.partials + ((int64_t)row * G + g) * p.n_chunks, p.n_chunks);
-      if ((tid & 63) == 0) {
-        s.stat[g] = st;
-        s.sM[g] = st.M;
-        s.sInv[g] = st.invZ;
-        p.stats[(int64_t)row * G + g] = st;
-        const float2 ss = p.samp_stats[(int64_t)row * G + g];
-        s.rho[g] = exp((double)ss.x - (double)st.M) / (st.Z * (double)ss.y);
-        s.flushed[g] = 0x1p-126 * (double)ss.y;  // the filter's exponentials come out as 0 below 2^-126
-      }
-    }
+// Exact softmax statistics of the row's heads, one wave per head, from the partials of the filtering pass; and how
+// far the sampled statistics were off: rho = (exact weight) / (sampled weight).  A barrier has to follow.
+__device__ __forceinline__ void exact_stats(const TopkCandParams& p, CandShared& s, int row) {
+  const int g = threadIdx.x >> 6, G = p.geo.G;
+  if (g >= G) return;
+  const RowStat st = merge_partials_wave(p.partials + ((int64_t)row * G + g) * p.n_chunks, p.n_chunks);
+  if ((threadIdx.x & 63) == 0) {
+    s.stat[g] = st;
+    s.sM[g] = st.M;
+    s.sInv[g] = st.invZ;
+    p.stats[(int64_t)row * G + g] = st;
+    const float2 ss = p.samp_stats[(int64_t)row * G + g];
+    s.rho[g] = exp((double)ss.x - (double)st.M) / (st.Z * (double)ss.y);
+    s.flushed[g] = 0x1p-126 * (double)ss.y;  // the filter's exponentials come out as 0 below 2^-126
   }
-  if (k == 0) return false;
-
-  // candidates per score chunk -> offsets of a dense list: the chunks' own slots first, the row's
-  // overflow pool behind them
-  const int* cnt = p.cand_count + (int64_t)row * p.n_chunks;
-  {
-    const int raw = tid < p.n_chunks ? cnt[tid] : 0;
-    const int v = raw < p.cap_c ? raw : p.cap_c;
-    int tot, raw_tot;
-    const int incl = block_scan_incl<kTopkThreads>(v, s.sh.wave_tot, &tot);
-    if (tid < p.n_chunks) s.chunk_off[tid] = incl - v;
-    if (tid == 0) s.chunk_off[p.n_chunks] = tot;
-    block_scan_incl<kTopkThreads>(raw, s.sh.wave_tot, &raw_tot);
-    if (tid == 0) s.raw_total = raw_tot;
-  }
-  if (tid == 0) s.n_band = s.n_above = 0;
-  if (tid < kFastMaxG) s.n_list[tid] = 0;
-  __syncthreads();
-  // A token the filter dropped had approximate score < tau^, so its exact score is below rho * tau^
-  // (plus what exponentials flushed to zero could hide, plus fp32 slack), rho the worst head's; a
-  // per-query list has its own head's.
-  if (PQ) {
-    if (tid < G) {
-      const double bd = s.rho[tid] * ((double)p.samp_tau[(int64_t)row * G + tid] + s.flushed[tid]) * 1.001;
-      s.bound[tid] = (float)bd;
-      // exp(x - M) / Z >= bd  <=>  x >= M + log(bd Z); lowered by more than fp32 rounding can move either side
-      s.thr[tid] = (float)((double)s.stat[tid].M + log(bd * s.stat[tid].Z) - 1e-4);
-    }
-  } else {
-    double rho = 0.0, fl = 0.0;
-    for (int g = 0; g < G; ++g) {
-      const double r = s.rho[g];
-      rho = r > rho || !(r == r) ? r : rho;
-      fl += s.flushed[g];
-    }
-    *bound = (float)(rho * ((double)p.samp_tau[row] + fl) * 1.001);
-  }
-  const int n_primary = s.chunk_off[p.n_chunks];
-  const int n_ovf = s.raw_total - n_primary;  // = the row's overflow counter
-  const int n_all = s.raw_total;
-  *n_c = n_all;
-  if (n_all > p.cap || n_all < k || n_ovf > p.cap_o) {  // far more candidates than planned, or the threshold was too high
-    if (tid == 0) flag_row(p, row, 1);
-    return false;
-  }
-  __syncthreads();  // s.thr
-
-  float* cs0 = p.cand_score + (int64_t)row * p.n_lists * p.cs_pitch;
-  int32_t* ci0 = p.cand_pos + (int64_t)row * p.n_lists * p.cs_pitch;
-  const int64_t row_slots = (int64_t)row * p.slots_per_row;
-  const int64_t ovf_base = row_slots + (int64_t)p.n_chunks * p.cap_c;
-  for (int d0 = 0; d0 < n_all; d0 += 4 * kTopkThreads) {
-    int64_t slot[4];  // the candidate's record, -1: past the end
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {  // independent lookups: their loads overlap
-      const int dj = d0 + u * kTopkThreads + tid;
-      int lo_c = 0, hi_c = p.n_chunks;  // chunk with chunk_off[ch] <= dj < chunk_off[ch + 1]
-      while (hi_c - lo_c > 1) {
-        const int mid = (lo_c + hi_c) >> 1;
-        if (s.chunk_off[mid] <= dj) lo_c = mid; else hi_c = mid;
-      }
-      slot[u] = dj >= n_all ? -1
-                : dj < n_primary ? row_slots + (int64_t)lo_c * p.cap_c + (dj - s.chunk_off[lo_c])
-                                 : ovf_base + (dj - n_primary);
-    }
-    int32_t ti[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) ti[u] = p.cand_idx[slot[u] < 0 ? row_slots : slot[u]];
-    if constexpr (PQ) {
-      // four heads at a time: their logits are one 16-byte load per candidate
-      for (int g4 = 0; g4 < G; g4 += 4) {
-        float4 lg[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          lg[u] = *reinterpret_cast<const float4*>(p.cand_logit + (slot[u] < 0 ? row_slots : slot[u]) * p.Gs + g4);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int g = g4 + e;
-          if (g >= G) break;  // workgroup-uniform
-          float* cs = cs0 + (int64_t)g * p.cs_pitch;
-          int32_t* ci = ci0 + (int64_t)g * p.cs_pitch;
-          const float thr = s.thr[g];
-          float x[4];
-          unsigned long long bal[4];
-          int n_wave = 0;
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            x[u] = e == 0 ? lg[u].x : e == 1 ? lg[u].y : e == 2 ? lg[u].z : lg[u].w;
-            bal[u] = __ballot(slot[u] >= 0 && x[u] >= thr);
-            n_wave += __popcll(bal[u]);
-          }
-          if (n_wave) {  // wave-uniform
-            int base = 0;
-            if ((tid & 63) == 0) base = atomicAdd(&s.n_list[g], n_wave);
-            base = __shfl(base, 0);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              if ((bal[u] >> (tid & 63)) & 1ull) {
-                const int pos = base + __popcll(bal[u] & ((1ull << (tid & 63)) - 1ull));
-                cs[pos] = x[u];
-                ci[pos] = ti[u];
-              }
-              base += __popcll(bal[u]);
-            }
-          }
-        }
-      }
-    } else {
-      // exact fp32 scores, same arithmetic and order as the dense combine stage; nearly every candidate
-      // reaches the bound, they stay in place
-      float4 lg[4][kFastMaxG / 4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int64_t sl = slot[u] < 0 ? row_slots : slot[u];
-#pragma unroll
-        for (int g4 = 0; g4 < kFastMaxG / 4; ++g4)
-          if (g4 * 4 < G) lg[u][g4] = *reinterpret_cast<const float4*>(p.cand_logit + sl * p.Gs + g4 * 4);
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int dj = d0 + u * kTopkThreads + tid;
-        if (dj < n_all) {
-          float a = 0.f;
-#pragma unroll
-          for (int g4 = 0; g4 < kFastMaxG / 4; ++g4)
-            if (g4 * 4 < G) {
-              const float x[4] = {lg[u][g4].x, lg[u][g4].y, lg[u][g4].z, lg[u][g4].w};
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (g4 * 4 + e < G) a += exp_times(x[e] - s.sM[g4 * 4 + e], s.sInv[g4 * 4 + e]);
-            }
-          cs0[dj] = a;
-          ci0[dj] = ti[u];
-        }
-      }
-    }
-  }
-  __syncthreads();
-  return true;
 }
 
-// Second half, one workgroup per list: the k best of the list's n_c candidates (cs: scores, or with
-// `logits` the logits of head g_lo, turned into scores here; ci: tokens), certified against `bound`:
-// every token outside the list scores below it.  s.stat[g_lo .. g_hi), s.sM, s.sInv hold the heads'
-// statistics, s.n_band = s.n_above = 0; `kept` = the list's k output slots.
-template <int DT>
-__device__ __forceinline__ void select_list(const TopkCandParams& p, CandShared& s, uint32_t* bitmap, int row, int g_lo,
-                                            int g_hi, float* cs, const int32_t* ci, int n_c, float bound, bool logits,
-                                            int32_t* kept) {
+// Candidates per score chunk -> offsets of a dense list (s.chunk_off): the chunks' own slots first, the row's overflow pool
+// behind them.  Returns how many there are; -1 (workgroup-uniform): far more than planned, or fewer than k.
+__device__ __forceinline__ int candidate_offsets(const TopkCandParams& p, CandShared& s, int row) {
+  const int tid = threadIdx.x;
+  const int raw = tid < p.n_chunks ? p.cand_count[(int64_t)row * p.n_chunks + tid] : 0;
+  const int v = raw < p.cap_c ? raw : p.cap_c;
+  int tot, n_all;
+  const int incl = block_scan_incl<kTopkThreads>(v, s.rs.wave_tot, &tot);
+  if (tid < p.n_chunks) s.chunk_off[tid] = incl - v;
+  if (tid == 0) s.chunk_off[p.n_chunks] = tot;
+  block_scan_incl<kTopkThreads>(raw, s.rs.wave_tot, &n_all);
+  __syncthreads();
+  return n_all > p.cap || n_all < p.k || n_all - tot > p.cap_o ? -1 : n_all;
+}
+
+// Records of N candidates of the dense list (those at n_all or beyond: any record).  The searches advance in step, so
+// that their LDS reads overlap.
+template <int N>
+__device__ __forceinline__ void candidate_slots(const TopkCandParams& p, const CandShared& s, int64_t row_slots, int n_all,
+                                                const int (&dj)[N], int64_t (&slot)[N]) {
+  const int n_primary = s.chunk_off[p.n_chunks];
+  int at[N];  // chunk with chunk_off[ch] <= dj < chunk_off[ch + 1]
+#pragma unroll
+  for (int u = 0; u < N; ++u) at[u] = 0;
+  for (int step = 1 << (31 - __clz(p.n_chunks)); step > 0; step >>= 1) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int next = at[u] + step;
+      if (s.chunk_off[next < p.n_chunks ? next : p.n_chunks] <= dj[u] && next < p.n_chunks) at[u] = next;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u)
+    slot[u] = dj[u] >= n_all       ? row_slots
+              : dj[u] >= n_primary ? row_slots + (int64_t)p.n_chunks * p.cap_c + (dj[u] - n_primary)
+                                   : row_slots + (int64_t)at[u] * p.cap_c + (dj[u] - s.chunk_off[at[u]]);
+}
+
+// Sink and recent positions of a row's kept list.
+__device__ __forceinline__ void write_ends(const TopkCandParams& p, int row) {
+  int32_t* kept_row = p.kept_idx + (int64_t)row * (p.S + p.n_lists * p.k + p.W);
+  for (int t = threadIdx.x; t < p.S; t += kTopkThreads) kept_row[t] = t;
+  for (int t = threadIdx.x; t < p.W; t += kTopkThreads)
+    kept_row[p.S + p.n_lists * p.k + t] = (int32_t)(p.geo.L - p.W + t);
+}
+// The dense stages that redo a flagged row add to its lists' first-digit histograms.
+__device__ __forceinline__ void clear_histograms(const TopkCandParams& p, int row) {
+  for (int b = threadIdx.x; b < kHistBins * p.n_lists; b += kTopkThreads) p.ghist[(int64_t)row * p.n_lists * kHistBins + b] = 0;
+}
+
+// The k best of a list's n_c candidates, certified against `bound`: every token outside the list scores below it.
+// each(f) calls f(score, token) for the thread's candidates, -1 for none, every lane of a wave equally often.
+// s.stat[g_lo .. g_hi) holds the heads' statistics; `kept` = the list's k output slots.  False: the row was flagged.
+template <int DT, class Each>
+__device__ __forceinline__ bool select_list(const TopkCandParams& p, CandShared& s, uint32_t* bitmap, int row, int g_lo,
+                                            int g_hi, int n_c, float bound, Each each, int32_t* kept) {
   const int tid = threadIdx.x;
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
   const int S = p.S, k = p.k;
   const int64_t E = p.geo.L - S - p.W;
   if (n_c < k) {
     if (tid == 0) flag_row(p, row, 2);
-    return;
-  }
-  if (logits) {  // exact fp32 scores, same arithmetic as the dense stages
-    const float M = s.sM[g_lo], inv = s.sInv[g_lo];
-    for (int j = tid; j < n_c; j += kTopkThreads) cs[j] = exp_times(cs[j] - M, inv);
-    __syncthreads();
-  }
-  // coarse k-th score, then the candidates within the band around it are re-scored in fp64 and
-  // ranked exactly (score descending, index ascending); everything above the band is selected
-  uint32_t tau;
-  int quota;
-  radix_select(s.sh, cs, n_c, k, false, &tau, &quota);
-  const float tf = __uint_as_float(tau);
-  const float lo = tf * (1.0f - p.band) - kDenormSlack, hi = tf * (1.0f + p.band) + kDenormSlack;
-  // the row is certified only if no token outside the list can reach the band
-  if (!(lo * (1.0f - p.band) > bound)) {
-    if (tid == 0) flag_row(p, row, 3);
-    return;
+    return false;
   }
   const int n_words = (int)((E + 31) / 32);
   for (int w = tid; w < n_words; w += kTopkThreads) bitmap[w] = 0u;
-  __syncthreads();
-  for (int j0 = 0; j0 < n_c; j0 += kTopkThreads) {
-    const int j = j0 + tid;
-    const float v = j < n_c ? cs[j] : 0.f;
-    const bool above = j < n_c && v > hi;
-    if (above) {
-      const int pos = ci[j] - S;
-      atomicOr(&bitmap[pos >> 5], 1u << (pos & 31));
-    } else if (j < n_c && v >= lo) {
-      const int t = atomicAdd(&s.n_band, 1);
-      if (t < kMaxBand) s.band_j[t] = j;
-    }
-    const unsigned long long bal = __ballot(above);
-    if ((tid & 63) == 0 && bal) atomicAdd(&s.n_above, __popcll(bal));
+  // the k-th score's bracket, then the candidates within the band around it are re-scored in fp64 and
+  // ranked exactly (score descending, index ascending); everything above the band is selected
+  uint32_t tlo, thi;
+  bracket_kth<true>(s.rs, [&](auto f) { each([&](float v, int) { f(v); }); }, k, &tlo, &thi);
+  const float lo = __uint_as_float(tlo) * (1.0f - p.band) - kDenormSlack,
+              hi = __uint_as_float(thi) * (1.0f + p.band) + kDenormSlack;
+  // the row is certified only if no token outside the list can reach the band
+  if (!(lo * (1.0f - p.band) > bound)) {
+    if (tid == 0) flag_row(p, row, 3);
+    return false;
   }
+  int n_above = 0;  // wave-uniform
+  each([&](float v, int tok) {
+    const bool above = v > hi;
+    if (above) {
+      const int pos = tok - S;
+      atomicOr(&bitmap[pos >> 5], 1u << (pos & 31));
+    } else if (v >= 0.f && v >= lo) {
+      const int t = atomicAdd(&s.rs.n_band, 1);
+      if (t < kMaxBand) s.rs.band_tok[t] = tok;
+    }
+    n_above += __popcll(__ballot(above));
+  });
+  if ((tid & 63) == 0 && n_above) atomicAdd(&s.rs.n_above, n_above);
   __syncthreads();
-  const int nb = s.n_band, r = k - s.n_above;
+  const int nb = s.rs.n_band, r = k - s.rs.n_above;
   if (nb > kMaxBand || r < 1 || r > nb) {  // a degenerate row of (nearly) equal scores: dense path
     if (tid == 0) flag_row(p, row, 4);
-    return;
+    return false;
   }
-  for (int t = tid >> 6; t < nb; t += kTopkWaves) {
-    const int tok = ci[s.band_j[t]];
-    const float v = refined_score_wave<DT>(p.geo, p.q_last, p.K, p.pm, p.ks_problem, p.ks_head, p.ks_token, s.stat, prob, c,
-                                           tok, g_lo, g_hi);
-    if ((tid & 63) == 0) {
-      s.band_v[t] = v;
-      s.band_tok[t] = tok;
-    }
-  }
-  __syncthreads();
+  refine_band<DT>(s.rs, nb, p.geo, p.q_last, p.K, p.pm, p.ks_problem, p.ks_head, p.ks_token, s.stat, prob, c, g_lo, g_hi);
   for (int t = tid; t < nb; t += kTopkThreads) {
-    const float v = s.band_v[t];
-    const int tok = s.band_tok[t];
+    const float v = s.rs.band_v[t];
+    const int tok = s.rs.band_tok[t];
     int rank = 0;
-    for (int u = 0; u < nb; ++u) rank += s.band_v[u] > v || (s.band_v[u] == v && s.band_tok[u] < tok);
+    for (int u = 0; u < nb; ++u) rank += s.rs.band_v[u] > v || (s.rs.band_v[u] == v && s.rs.band_tok[u] < tok);
     if (rank < r) atomicOr(&bitmap[(tok - S) >> 5], 1u << ((tok - S) & 31));
   }
   __syncthreads();
-  bitmap_compact(bitmap, n_words, S, kept + S, k, s.sh.wave_tot);
+  bitmap_compact(bitmap, n_words, S, kept + S, k, s.rs.wave_tot);
+  return true;
 }
 
-// One list per row: both halves in one workgroup.
-template <int DT>
+// One list per row, one workgroup per row.  Latency bound: a chain of dependent memory round trips (counts ->
+// records -> the band's keys) and barriers on as many CUs as the call has rows.  So a row's candidates are read
+// once and kept in registers, up to NPT per thread, their loads batched and in flight while the statistics are merged;
+// selecting among scores in memory (three radix passes and a band pass, each with its own round trips, all
+// of a row's keys in a few histogram bins) took 45 instead of 28 us for 8 rows of 128K tokens and 71 instead of 36 us for 256.
+// GQ: head quads of a record.  More than NPT * 1024 candidates (peaked rows): scores and tokens go through memory.
+template <int DT, int NPT, int GQ>
 __global__ __launch_bounds__(kTopkThreads) void topk_cand_kernel(TopkCandParams p) {
+  constexpr int UB = GQ == 1 ? 4 : GQ == 2 ? 2 : 1;  // candidates per batch of loads
+  static_assert(NPT % UB == 0, "whole batches");
   __shared__ CandShared s;
   extern __shared__ __align__(16) uint32_t bitmap[];  // one bit per eviction candidate of the row
-  const int row = blockIdx.x;
-  float bound = 0.f;
-  int n_c = 0;
-  if (!cand_lists<DT, false>(p, s, row, &bound, &n_c)) return;
-  select_list<DT>(p, s, bitmap, row, 0, p.geo.G, p.cand_score + (int64_t)row * p.cs_pitch,
-                  p.cand_pos + (int64_t)row * p.cs_pitch, n_c, bound, false,
-                  p.kept_idx + (int64_t)row * (p.S + p.k + p.W));
+  const int row = blockIdx.x, tid = threadIdx.x, G = p.geo.G;
+  write_ends(p, row);
+  if (p.k == 0) {
+    exact_stats(p, s, row);
+    return;
+  }
+  const int n_all = candidate_offsets(p, s, row);
+  if (n_all < 0) {
+    exact_stats(p, s, row);
+    clear_histograms(p, row);
+    if (tid == 0) flag_row(p, row, 1);
+    return;
+  }
+  const int64_t row_slots = (int64_t)row * p.slots_per_row;
+  struct Batch {
+    float4 lg[UB][GQ];
+    int32_t tok[UB];
+  };
+  auto load_batch = [&](int u0, Batch& b) {
+    int64_t slot[UB];
+    int dj[UB];
+#pragma unroll
+    for (int u = 0; u < UB; ++u) dj[u] = (u0 + u) * kTopkThreads + tid;
+    candidate_slots<UB>(p, s, row_slots, n_all, dj, slot);
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      b.tok[u] = p.cand_idx[slot[u]];
+#pragma unroll
+      for (int q = 0; q < GQ; ++q) b.lg[u][q] = *reinterpret_cast<const float4*>(p.cand_logit + (slot[u] * GQ + q) * 4);
+    }
+  };
+  // exact fp32 score, same arithmetic and order as the dense combine stage
+  auto score = [&](const float4 (&lg)[GQ]) -> float {
+    float a = 0.f;
+#pragma unroll
+    for (int q = 0; q < GQ; ++q) {
+      const float x[4] = {lg[q].x, lg[q].y, lg[q].z, lg[q].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (q * 4 + e < G) a += exp_times(x[e] - s.sM[q * 4 + e], s.sInv[q * 4 + e]);
+    }
+    return a;
+  };
+  Batch b[2];
+  load_batch(0, b[0]);
+  exact_stats(p, s, row);
+  __syncthreads();
+  // A token the filter dropped had approximate score < tau^, so its exact score is below rho * tau^
+  // (plus what exponentials flushed to zero could hide, plus fp32 slack), rho the worst head's.
+  float bound;
+  {
+    double rho = 0.0, fl = 0.0;
+    for (int g = 0; g < G; ++g) {
+      const double r = s.rho[g];
+      rho = r > rho || !(r == r) ? r : rho;
+      fl += s.flushed[g];
+    }
+    bound = (float)(rho * ((double)p.samp_tau[row] + fl) * 1.001);
+  }
+  int32_t* kept = p.kept_idx + (int64_t)row * (p.S + p.k + p.W);
+  bool ok;
+  if (n_all <= NPT * kTopkThreads) {
+    float v[NPT];
+    int32_t tok[NPT];
+#pragma unroll
+    for (int u0 = 0; u0 < NPT; u0 += UB) {
+      const int n = u0 / UB;
+      if (u0 + UB < NPT && (u0 + UB) * kTopkThreads < n_all) load_batch(u0 + UB, b[(n + 1) & 1]);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        v[u0 + u] = -1.f;
+        tok[u0 + u] = p.S;
+        if ((u0 + u) * kTopkThreads + tid < n_all) {
+          v[u0 + u] = score(b[n & 1].lg[u]);
+          tok[u0 + u] = b[n & 1].tok[u];
+        }
+      }
+    }
+    ok = select_list<DT>(p, s, bitmap, row, 0, G, n_all, bound, [&](auto f) {
+#pragma unroll
+      for (int i = 0; i < NPT; ++i) f(v[i], tok[i]);
+    }, kept);
+  } else {
+    float* cs = p.cand_score + (int64_t)row * p.cs_pitch;
+    int32_t* ci = p.cand_pos + (int64_t)row * p.cs_pitch;
+    for (int u0 = 0; u0 * kTopkThreads < n_all; u0 += UB) {
+      load_batch(u0, b[0]);
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int dj = (u0 + u) * kTopkThreads + tid;
+        if (dj < n_all) {
+          cs[dj] = score(b[0].lg[u]);
+          ci[dj] = b[0].tok[u];
+        }
+      }
+    }
+    // (a thread reads back what it wrote: no barrier needed)
+    ok = select_list<DT>(p, s, bitmap, row, 0, G, n_all, bound, [&](auto f) {
+      for (int j0 = 0; j0 < n_all; j0 += kTopkThreads) {
+        const bool in = j0 + tid < n_all;
+        f(in ? cs[j0 + tid] : -1.f, in ? ci[j0 + tid] : p.S);
+      }
+    }, kept);
+  }
+  if (!ok) clear_histograms(p, row);
 }
 
 // Per-query lists, first launch: one workgroup per row splits the row's candidates into the lists
 // (a list re-reading all of the row's records costs more than everything else it does) and leaves
-// each list's count and bound in list_info; count -1: nothing to select for this row.
+// each list's count and bound in list_info; count -1: nothing to select for this row.  List g gets the LOGIT of
+// head g and the token of every candidate that can reach the list's bound.
 // Registers are capped in both launches so that two workgroups share a CU (8 waves per SIMD): the
 // kernels are chains of dependent memory round trips, a second resident workgroup fills the waits.
 template <int DT>
 __global__ __launch_bounds__(kTopkThreads, 8) void cand_split_pq_kernel(TopkCandParams p) {
   __shared__ CandShared s;
-  const int row = blockIdx.x, G = p.geo.G;
-  float bound = 0.f;
-  int n_c = 0;
-  const bool ok = cand_lists<DT, true>(p, s, row, &bound, &n_c);  // its exits are workgroup-uniform
-  if ((int)threadIdx.x < G)
-    p.list_info[(int64_t)row * G + threadIdx.x] = make_float2(__int_as_float(ok ? s.n_list[threadIdx.x] : -1),
-                                                               s.bound[threadIdx.x]);
+  const int row = blockIdx.x, tid = threadIdx.x, G = p.geo.G;
+  write_ends(p, row);
+  clear_histograms(p, row);
+  if (tid < kFastMaxG) s.n_list[tid] = 0;
+  exact_stats(p, s, row);
+  if (p.k == 0) return;
+  const int n_all = candidate_offsets(p, s, row);
+  // A token the filter dropped for head g had approximate probability < tau^_g, so its exact one is below the
+  // list's bound.  exp(x - M) / Z >= bd  <=>  x >= M + log(bd Z); lowered by more than fp32 rounding can move either side
+  if (tid < G) {
+    const double bd = s.rho[tid] * ((double)p.samp_tau[(int64_t)row * G + tid] + s.flushed[tid]) * 1.001;
+    s.bound[tid] = (float)bd;
+    s.thr[tid] = (float)((double)s.stat[tid].M + log(bd * s.stat[tid].Z) - 1e-4);
+  }
+  if (n_all < 0) {
+    if (tid == 0) flag_row(p, row, 1);
+    if (tid < G) p.list_info[(int64_t)row * G + tid] = make_float2(__int_as_float(-1), 0.f);
+    return;
+  }
+  __syncthreads();  // s.thr
+  float* cs0 = p.cand_score + (int64_t)row * p.n_lists * p.cs_pitch;
+  int32_t* ci0 = p.cand_pos + (int64_t)row * p.n_lists * p.cs_pitch;
+  const int64_t row_slots = (int64_t)row * p.slots_per_row;
+  for (int d0 = 0; d0 < n_all; d0 += 4 * kTopkThreads) {
+    int64_t slot[4];
+    int dj[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) dj[u] = d0 + u * kTopkThreads + tid;
+    candidate_slots<4>(p, s, row_slots, n_all, dj, slot);
+    int32_t ti[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ti[u] = p.cand_idx[slot[u]];
+    // four heads at a time: their logits are one 16-byte load per candidate
+    for (int g4 = 0; g4 < G; g4 += 4) {
+      float4 lg[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        lg[u] = *reinterpret_cast<const float4*>(p.cand_logit + slot[u] * p.Gs + g4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int g = g4 + e;
+        if (g >= G) break;  // workgroup-uniform
+        float* cs = cs0 + (int64_t)g * p.cs_pitch;
+        int32_t* ci = ci0 + (int64_t)g * p.cs_pitch;
+        const float thr = s.thr[g];
+        float x[4];
+        unsigned long long bal[4];
+        int n_wave = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          x[u] = e == 0 ? lg[u].x : e == 1 ? lg[u].y : e == 2 ? lg[u].z : lg[u].w;
+          bal[u] = __ballot(dj[u] < n_all && x[u] >= thr);
+          n_wave += __popcll(bal[u]);
+        }
+        if (n_wave) {  // wave-uniform
+          int base = 0;
+          if ((tid & 63) == 0) base = atomicAdd(&s.n_list[g], n_wave);
+          base = __shfl(base, 0);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if ((bal[u] >> (tid & 63)) & 1ull) {
+              const int pos = base + __popcll(bal[u] & ((1ull << (tid & 63)) - 1ull));
+              cs[pos] = x[u];
+              ci[pos] = ti[u];
+            }
+            base += __popcll(bal[u]);
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (tid < G) p.list_info[(int64_t)row * G + tid] = make_float2(__int_as_float(s.n_list[tid]), s.bound[tid]);
 }
 
-// Per-query lists, second launch: one workgroup per (row, head).
-template <int DT>
+// Per-query lists, second launch: one workgroup per (row, head); a list's candidates in registers, up to NPT per thread.
+template <int DT, int NPT>
 __global__ __launch_bounds__(kTopkThreads, 8) void topk_cand_pq_kernel(TopkCandParams p) {
   __shared__ CandShared s;
   extern __shared__ __align__(16) uint32_t bitmap[];
-  const int list = blockIdx.x, G = p.geo.G;
+  const int list = blockIdx.x, tid = threadIdx.x, G = p.geo.G;
   const int row = list / G, g = list % G;
   const float2 info = p.list_info[list];
+  const RowStat st = p.stats[(int64_t)row * G + g];
   const int n_c = __float_as_int(info.x);
   if (n_c < 0) return;
-  if (threadIdx.x == 0) {
-    const RowStat st = p.stats[(int64_t)row * G + g];
-    s.stat[g] = st;
-    s.sM[g] = st.M;
-    s.sInv[g] = st.invZ;
-    s.n_band = s.n_above = 0;
+  float* cs = p.cand_score + (int64_t)list * p.cs_pitch;
+  const int32_t* ci = p.cand_pos + (int64_t)list * p.cs_pitch;
+  if (tid == 0) s.stat[g] = st;  // (select_list has barriers before it is read)
+  int32_t* kept = p.kept_idx + (int64_t)row * (p.S + G * p.k + p.W) + g * p.k;
+  if (n_c <= NPT * kTopkThreads) {
+    float v[NPT];
+    int32_t tok[NPT];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      const int j = u * kTopkThreads + tid;
+      v[u] = -1.f;
+      tok[u] = p.S;
+      if (j < n_c) {
+        v[u] = cs[j];
+        tok[u] = ci[j];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NPT; ++u)  // exact fp32 scores, same arithmetic as the dense stages
+      if (u * kTopkThreads + tid < n_c) v[u] = exp_times(v[u] - st.M, st.invZ);
+    select_list<DT>(p, s, bitmap, row, g, g + 1, n_c, info.y, [&](auto f) {
+#pragma unroll
+      for (int i = 0; i < NPT; ++i) f(v[i], tok[i]);
+    }, kept);
+  } else {
+    for (int j = tid; j < n_c; j += kTopkThreads) cs[j] = exp_times(cs[j] - st.M, st.invZ);
+    select_list<DT>(p, s, bitmap, row, g, g + 1, n_c, info.y, [&](auto f) {
+      for (int j0 = 0; j0 < n_c; j0 += kTopkThreads) {
+        const bool in = j0 + tid < n_c;
+        f(in ? cs[j0 + tid] : -1.f, in ? ci[j0 + tid] : p.S);
+      }
+    }, kept);
   }
-  __syncthreads();
-  select_list<DT>(p, s, bitmap, row, g, g + 1, p.cand_score + (int64_t)list * p.cs_pitch,
-                  p.cand_pos + (int64_t)list * p.cs_pitch, n_c, info.y, true,
-                  p.kept_idx + (int64_t)row * (p.S + G * p.k + p.W) + g * p.k);
 }
 
 }  // namespace
+
+template <int GQ>
+void launch_sample_stats(const SampleParams& p, unsigned rows, int items, hipStream_t s) {
+  const dim3 grid(rows), block(kTopkThreads);
+  if (items <= 3) {
+    hipLaunchKernelGGL((sample_stats_kernel<GQ, 3>), grid, block, 0, s, p);
+  } else if (items <= 6) {
+    hipLaunchKernelGGL((sample_stats_kernel<GQ, 6>), grid, block, 0, s, p);
+  } else if (items <= 9 || GQ == 1) {  // (one quad: the largest sample is 9 items per thread)
+    hipLaunchKernelGGL((sample_stats_kernel<GQ, 9>), grid, block, 0, s, p);
+  } else if constexpr (GQ > 1) {
+    if (items <= 18)
+      hipLaunchKernelGGL((sample_stats_kernel<GQ, 18>), grid, block, 0, s, p);
+    else
+      hipLaunchKernelGGL((sample_stats_kernel<GQ, 0>), grid, block, 0, s, p);
+  }
+}
 
 hipError_t launch_sample(const SampleParams& p, hipStream_t s) {
   const int rows = p.geo.n_problems * p.geo.Hkv;
@@ -553,28 +645,53 @@ hipError_t launch_sample(const SampleParams& p, hipStream_t s) {
   if (e != hipSuccess) return e;
   // one workgroup per row, also with several lists per row: at 7 lists x 448 rows, two workgroups per row
   // took 139 us, one per (row, list) 147 us, one per row 108 us (the statistics dominate, not the selects)
-  hipLaunchKernelGGL(sample_stats_kernel, dim3((unsigned)rows, 1u), dim3(kTopkThreads), 0, s, p);
+  const int gq = p.Gs / 4 > 2 ? 4 : p.Gs / 4;  // head quads in a record, as a power of two
+  const int items = (64 * (p.nA + p.nB + p.nC) * gq + kTopkThreads - 1) / kTopkThreads;
+  if (gq == 1) launch_sample_stats<1>(p, (unsigned)rows, items, s);
+  else if (gq == 2) launch_sample_stats<2>(p, (unsigned)rows, items, s);
+  else launch_sample_stats<4>(p, (unsigned)rows, items, s);
+  return hipGetLastError();
+}
+
+template <int NPT, int GQ>
+hipError_t launch_topk_cand_t(const TopkCandParams& p, unsigned rows, size_t lds, hipStream_t s) {
+  static uint64_t done = 0;
+  const hipError_t e = allow_dynamic_lds((const void*)topk_cand_kernel<DT_BF16, NPT, GQ>, 128 * 1024, &done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((topk_cand_kernel<DT_BF16, NPT, GQ>), dim3(rows), dim3(kTopkThreads), lds, s, p);
+  return hipGetLastError();
+}
+template <int NPT>
+hipError_t launch_topk_cand_n(const TopkCandParams& p, unsigned rows, size_t lds, hipStream_t s) {
+  return p.Gs == 4   ? launch_topk_cand_t<NPT, 1>(p, rows, lds, s)
+         : p.Gs == 8 ? launch_topk_cand_t<NPT, 2>(p, rows, lds, s)
+                     : launch_topk_cand_t<NPT, 4>(p, rows, lds, s);
+}
+template <int NPT>
+hipError_t launch_topk_pq_t(const TopkCandParams& p, unsigned lists, size_t lds, hipStream_t s) {
+  static uint64_t done = 0;
+  const hipError_t e = allow_dynamic_lds((const void*)topk_cand_pq_kernel<DT_BF16, NPT>, 128 * 1024, &done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((topk_cand_pq_kernel<DT_BF16, NPT>), dim3(lists), dim3(kTopkThreads), lds, s, p);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_cand(const TopkCandParams& p, hipStream_t s) {
-  const int rows = p.geo.n_problems * p.geo.Hkv;
+  const unsigned rows = (unsigned)(p.geo.n_problems * p.geo.Hkv);
   const int64_t E = p.geo.L - p.S - p.W;
-  // the bitmap (one bit per candidate, up to 128 KiB) sits next to about 25 KiB of static LDS; a CU has 160 KiB
+  // the bitmap (one bit per candidate, up to 128 KiB) sits next to about 30 KiB of static LDS; a CU has 160 KiB
   const size_t lds = (size_t)((E + 31) / 32) * 4;
   if (lds > 128 * 1024 || p.geo.G > kFastMaxG) return hipErrorInvalidValue;
-  static uint64_t done_one = 0, done_pq = 0;
-  const hipError_t e = p.n_lists > 1
-                           ? allow_dynamic_lds((const void*)topk_cand_pq_kernel<DT_BF16>, 128 * 1024, &done_pq)
-                           : allow_dynamic_lds((const void*)topk_cand_kernel<DT_BF16>, 128 * 1024, &done_one);
-  if (e != hipSuccess) return e;
+  // registers per thread for the candidates a list is expected to have (see TopkCandParams::expect): a row that has
+  // more than that goes through memory, at about the pace that all of them had before
   if (p.n_lists > 1) {
-    hipLaunchKernelGGL(cand_split_pq_kernel<DT_BF16>, dim3((unsigned)rows), dim3(kTopkThreads), 0, s, p);
-    hipLaunchKernelGGL(topk_cand_pq_kernel<DT_BF16>, dim3((unsigned)(rows * p.n_lists)), dim3(kTopkThreads), lds, s, p);
-  } else {
-    hipLaunchKernelGGL(topk_cand_kernel<DT_BF16>, dim3((unsigned)rows), dim3(kTopkThreads), lds, s, p);
+    hipLaunchKernelGGL(cand_split_pq_kernel<DT_BF16>, dim3(rows), dim3(kTopkThreads), 0, s, p);
+    const unsigned lists = rows * (unsigned)p.n_lists;
+    return p.expect <= 4 * kTopkThreads ? launch_topk_pq_t<4>(p, lists, lds, s) : launch_topk_pq_t<12>(p, lists, lds, s);
   }
-  return hipGetLastError();
+  return p.expect <= 4 * kTopkThreads    ? launch_topk_cand_n<4>(p, rows, lds, s)
+         : p.expect <= 12 * kTopkThreads ? launch_topk_cand_n<12>(p, rows, lds, s)
+                                         : launch_topk_cand_n<24>(p, rows, lds, s);
 }
 
 }  // namespace sagekv

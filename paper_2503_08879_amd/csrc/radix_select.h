@@ -225,18 +225,19 @@ struct RegSelect {
 // Two histograms over the keys' own range: 2048 bins from the smallest to the largest key, then 2048 bins
 // inside the bin that holds the k-th.  (Digits of the bit pattern would put most of a row into a few bins: the
 // LDS atomics of a wave then serialise on one address.)  Also clears n_band and n_above.
-template <int N>
-__device__ __forceinline__ void bracket_kth(RegSelect& sh, const float (&v)[N], int k, uint32_t* tlo, uint32_t* thi) {
+// each(f) calls f(score) for the thread's scores, any number of times, in any order, with -1 where there is none.
+// TWO false: the first histogram only, *tlo = the lower edge of the k-th score's bin (a lower bound of it).
+template <bool TWO, class Each>
+__device__ __forceinline__ void bracket_kth(RegSelect& sh, Each each, int k, uint32_t* tlo, uint32_t* thi) {
   const int tid = threadIdx.x, wave = tid >> 6;
   int4* h4 = reinterpret_cast<int4*>(&sh.hist[0][0]);
-  for (int b = tid; b < 2 * kHistBins / 4; b += kTopkThreads) h4[b] = make_int4(0, 0, 0, 0);
+  for (int b = tid; b < (TWO ? 2 : 1) * kHistBins / 4; b += kTopkThreads) h4[b] = make_int4(0, 0, 0, 0);
   int mn = 0x7FFFFFFF, mx = -1;
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int key = __float_as_int(v[i]);
+  each([&](float v) {
+    const int key = __float_as_int(v);
     if (key >= 0) mn = key < mn ? key : mn;
     mx = key > mx ? key : mx;
-  }
+  });
   mn = wave_min_i(mn);
   mx = wave_max_i(mx);
   if ((tid & 63) == 0) {
@@ -252,25 +253,24 @@ __device__ __forceinline__ void bracket_kth(RegSelect& sh, const float (&v)[N], 
   }
   const uint32_t range = mx >= mn ? (uint32_t)(mx - mn) : 0u;
   const int s1 = range < (uint32_t)kHistBins ? 0 : 21 - __clz((int)range);  // range >> s1 < 2048
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int key = __float_as_int(v[i]);
+  each([&](float v) {
+    const int key = __float_as_int(v);
     if (key >= 0) atomicAdd(&sh.hist[0][(uint32_t)(key - mn) >> s1], 1);
-  }
+  });
   __syncthreads();
   int bin, rem;
   pick_digit(sh.hist[0], sh.wave_tot, sh.pick, kHistBins, k, &bin, &rem);
   const int base = mn + (int)((uint32_t)bin << s1);
-  const int s2 = s1 > 11 ? s1 - 11 : 0;
-  if (s1 == 0) {
-    *tlo = *thi = (uint32_t)base;
+  if (!TWO || s1 == 0) {
+    *tlo = (uint32_t)base;
+    *thi = (uint32_t)base + ((1u << s1) - 1u);
     return;
   }
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const int key = __float_as_int(v[i]);
+  const int s2 = s1 > 11 ? s1 - 11 : 0;
+  each([&](float v) {
+    const int key = __float_as_int(v);
     if (key >= 0 && (int)((uint32_t)(key - mn) >> s1) == bin) atomicAdd(&sh.hist[1][(uint32_t)(key - base) >> s2], 1);
-  }
+  });
   __syncthreads();
   pick_digit(sh.hist[1], sh.wave_tot, sh.pick, kHistBins, rem, &bin, &rem);
   *tlo = (uint32_t)base + ((uint32_t)bin << s2);

@@ -494,7 +494,10 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
 
   // the k-th score's bracket, and the band around it (see topk_kernel)
   uint32_t tlo, thi;
-  bracket_kth<N>(sh, v, k, &tlo, &thi);
+  bracket_kth<true>(sh, [&](auto f) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) f(v[i]);
+  }, k, &tlo, &thi);
   const float lo = __uint_as_float(tlo) * (1.0f - p.band) - kDenormSlack,
               hi = __uint_as_float(thi) * (1.0f + p.band) + kDenormSlack;
   int above = 0;  // wave-uniform
