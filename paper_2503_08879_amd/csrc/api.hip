@@ -233,9 +233,13 @@ struct DecodeLayout {
 
 // Splits per row.  With about one row per CU or more, a single 8-wave workgroup per row fills
 // the chip and needs no merge launch; otherwise enough workgroups to fill 256 CUs several times
-// over, at least 128 tokens each.
-int splits_for(int rows, int len) {
-  if (rows >= 192) return 1;
+// over, at least 128 tokens each.  Rows that one workgroup takes in a single pass are not worth the merge launch:
+// bf16 up to 256 tokens (8 rows x 4 heads x 256 tokens 10.3 us split, 8.4 whole; 4 rows x 7 heads 9.6 and 8.2; at 512
+// tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 256 tokens of head_dim 64 (2 rows x 2 heads 11.4 and 8.5; at 512
+// tokens 9.8 and 12.0; 8 rows x 4 heads x 512 tokens of head_dim 128 22 and 42).
+int splits_for(int rows, int len, int dtype, int head_dim) {
+  if (rows >= kWholeRows) return 1;
+  if (dtype == SAGEKV_BF16 ? len <= 256 : (int64_t)len * head_dim <= 256 * 64) return 1;
   int want = (2048 + rows - 1) / rows;
   int most = (len + 127) / 128;
   int n = want < most ? want : most;
@@ -246,7 +250,7 @@ DecodeLayout decode_layout(const sagekv_decode_desc* d) {
   DecodeLayout l;
   l.rows = d->n_problems * d->n_kv_heads;
   l.G = d->n_q_heads / d->n_kv_heads;
-  l.max_splits = splits_for(l.rows, d->compact_capacity);
+  l.max_splits = splits_for(l.rows, d->compact_capacity, d->dtype, d->head_dim);
   size_t off = 0;
   l.part_ml = off;
   off = align_up(off + (size_t)l.rows * l.max_splits * l.G * sizeof(float2));
@@ -372,7 +376,7 @@ sagekv_status run_decode(const sagekv_decode_desc* d, const void* q, const void*
   p.cap = d->compact_capacity;
   // with the count on the device the length of a growing row is not known here: as many slices as
   // the full capacity would take (a fixed-size window has its one length either way)
-  p.n_splits = splits_for(l.rows, ring && d->grow_recent ? d->compact_capacity : len);
+  p.n_splits = splits_for(l.rows, ring && d->grow_recent ? d->compact_capacity : len, d->dtype, d->head_dim);
   if (p.n_splits > l.max_splits) p.n_splits = l.max_splits;
   p.tokens_per_split = split_tokens(len, p.n_splits);
   p.ring = ring;

@@ -23,9 +23,22 @@ namespace {
 struct StepGeom {
   int slot, len, tokens_per_split, n_appended;
 };
+// late: a fixed-size window with its count on the device.  Only the slot depends on the count, so its load need not be
+// waited for in front of everything else: the first loads go out with slot = -1 and late_slot() fills it in.  (One
+// layer's step, 8 rows x 4096 tokens: 15.8 -> 14.5 us together with the queries' loads in front of K's and V's and
+// the maxima over DPP instead of shuffles.)
+__device__ __forceinline__ bool slot_is_late(const DecodeParams& p) { return p.ring && !p.ring_grow; }
+__device__ __forceinline__ int late_slot(const DecodeParams& p, StepGeom& s, int n_appended) {
+  s.n_appended = n_appended;
+  s.slot = p.k_new ? ring_position(p.ring_base, p.ring_W, 0, p.cap, n_appended < 0 ? 0 : n_appended).slot : -1;
+  return s.slot;
+}
+template <bool LATE = false>
 __device__ __forceinline__ StepGeom step_geom(const DecodeParams& p) {
   StepGeom s = {p.k_new ? p.slot : -1, p.len, p.tokens_per_split, 0};
-  if (p.ring) {
+  if (LATE && slot_is_late(p)) {
+    s.slot = -1;
+  } else if (p.ring) {
     s.n_appended = p.ring[0];
     const RingPos r = ring_position(p.ring_base, p.ring_W, p.ring_grow, p.cap, s.n_appended < 0 ? 0 : s.n_appended);
     s.slot = p.k_new ? r.slot : -1;
@@ -216,8 +229,7 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeParams p, int g0)
                      (double)__uint_as_float(kv[i].y) * (double)__uint_as_float(qq.y) +
                      (double)__uint_as_float(kv[i].z) * (double)__uint_as_float(qq.z) +
                      (double)__uint_as_float(kv[i].w) * (double)__uint_as_float(qq.w);
-#pragma unroll
-          for (int o = 1; o < LPT; o <<= 1) a += __shfl_xor(a, o);
+          a = group_sum_f64<LPT>(a);
           a *= 1.0 / sqrt((double)D);
           xd[i][g] = a;
           v = (float)a;
@@ -342,14 +354,11 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
   const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2);
   const char* kn = p.k_new ? (const char*)p.k_new + (int64_t)row * ROWB : nullptr;
   const char* vn = p.v_new ? (const char*)p.v_new + (int64_t)row * ROWB : nullptr;
-  const StepGeom sg = step_geom(p);
-  const int slot = sg.slot;
+  StepGeom sg = step_geom<true>(p);
+  int ring_n = 0;
+  if (slot_is_late(p)) ring_n = p.ring[0];  // on its way while the first loads are issued
   const int t_begin = split * sg.tokens_per_split;
   const int t_end = min(sg.len, t_begin + sg.tokens_per_split);
-  if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window
-    st16(Kr.at(slot) + tid * 16, ld16(kn + tid * 16));
-    st16(Vr.at(slot) + tid * 16, ld16(vn + tid * 16));
-  }
 
   // accumulator rows 4j..4j+3 = (tile slot, heads hbase..hbase+3); slots >= NT stay empty
   const int hbase = (4 * j) % GPAD, tile = (4 * j) / GPAD;
@@ -369,7 +378,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
   uint4* buf = kbuf[wave];
   const int nblk = (t_end - t_begin + BT - 1) / BT;
   uint4 kv[NLOAD], vv[NLOAD];
-  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, slot, wave, 0};
+  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, sg.slot, wave, 0};
   auto load_block = [&](int it, uint4* dst, const CacheRow& base, const char* fresh) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
@@ -381,6 +390,23 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
     src.fill_pages(0);
     load_block(0, kv, Kr, kn);
     load_block(0, vv, Vr, vn);
+  }
+  if (slot_is_late(p)) {
+    src.slot = late_slot(p, sg, ring_n);
+    const int b0 = t_begin + wave * BT;
+    if (src.slot >= b0 && src.slot < b0 + BT) {  // wave-uniform: the first block holds the new token, read above as the old one
+#pragma unroll
+      for (int i = 0; i < NLOAD; ++i)
+        if (b0 + i * TPL + tq == src.slot) {
+          kv[i] = ld16(kn + cl * 16);
+          vv[i] = ld16(vn + cl * 16);
+        }
+    }
+  }
+  const int slot = src.slot;
+  if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window
+    st16(Kr.at(slot) + tid * 16, ld16(kn + tid * 16));
+    st16(Vr.at(slot) + tid * 16, ld16(vn + tid * 16));
   }
   // A operand of tile slot ts, k-step kc, kept in LDS (registers are short here): lane (row m = n,
   // k-group j) reads q[head m % GPAD][8*(4*kc + j) ..+8] if m / GPAD == ts, zeros otherwise
@@ -443,8 +469,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float bm = x[r];
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
+      bm = group16_max(bm);
 #pragma unroll
       for (int o = 16 * (GPAD / 4); o < 64; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
       const float mn = fmaxf(m_run[r], bm);
@@ -493,9 +518,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
   // wave totals: sum of weights per head, accumulators over the TPL token groups
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    float ls = l_part[r];
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) ls += __shfl_xor(ls, o);
+    float ls = group_sum<16>(l_part[r]);
 #pragma unroll
     for (int o = 16 * (GPAD / 4); o < 64; o <<= 1) ls += __shfl_xor(ls, o);
     if (n == 0 && j < GPAD / 4) s_ml[wave][hbase + r] = make_float2(m_run[r], ls);
@@ -580,14 +603,11 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2);
   const char* kn = p.k_new ? (const char*)p.k_new + (int64_t)row * ROWB : nullptr;
   const char* vn = p.v_new ? (const char*)p.v_new + (int64_t)row * ROWB : nullptr;
-  const StepGeom sg = step_geom(p);
-  const int slot = sg.slot;
+  StepGeom sg = step_geom<true>(p);
+  int ring_n = 0;
+  if (slot_is_late(p)) ring_n = p.ring[0];  // on its way while the first loads are issued
   const int t_begin = split * sg.tokens_per_split;
   const int t_end = min(sg.len, t_begin + sg.tokens_per_split);
-  if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window
-    st16(Kr.at(slot) + tid * 16, ld16(kn + tid * 16));
-    st16(Vr.at(slot) + tid * 16, ld16(vn + tid * 16));
-  }
 
   // q.K accumulator a, register r of lane (j, n): head hbase + r, token tile a * TILES + tslot, column n
   const int hbase = (4 * j) % GPAD, tslot = (4 * j) / GPAD;
@@ -605,7 +625,7 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   reinterpret_cast<uint4*>(&pT[wave][0][0])[lane] = make_uint4(0u, 0u, 0u, 0u);  // rows of absent heads stay 0
   const int nblk = (t_end - t_begin + BT - 1) / BT;
   uint4 kv[NLOAD], vv[NLOAD];
-  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, slot, wave, 0};
+  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, sg.slot, wave, 0};
   auto load_block = [&](int it, uint4* dst, const CacheRow& base, const char* fresh) {
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
@@ -613,21 +633,48 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
       dst[i] = STREAM ? ld16_stream(a) : ld16(a);
     }
   };
+  // The queries' loads go out first, then K's, then V's: loads complete in order, so each is waited for when it is
+  // needed and no later one with it.
+  constexpr int QN = (NT * KSTEPS * 64 + kThreads - 1) / kThreads;
+  auto q_operand = [&](const void* q, int it) -> uint4 {
+    const int l = it & 63, kc = (it >> 6) % KSTEPS, ts = (it / (64 * KSTEPS)) % NT;
+    const int m = l & 15, jj = l >> 4;
+    if (m % GPAD >= gb || m / GPAD != ts % TILES) return make_uint4(0u, 0u, 0u, 0u);
+    const int h = c * p.G + g0 + m % GPAD;
+    return ld16((const char*)q + (((int64_t)prob * p.Hq + h) * D + (4 * kc + jj) * 8) * 2);
+  };
+  uint4 qv[QN];
+#pragma unroll
+  for (int i = 0; i < QN; ++i)
+    if (tid + i * kThreads < NT * KSTEPS * 64) qv[i] = q_operand(p.q, tid + i * kThreads);
   if (wave < nblk) {
     src.fill_pages(0);
     load_block(0, kv, Kr, kn);
     load_block(0, vv, Vr, vn);
   }
-  for (int it = tid; it < (p.q_sink ? 2 : 1) * NT * KSTEPS * 64; it += kThreads) {
-    const int l = it & 63, kc = (it >> 6) % KSTEPS, ts = (it / (64 * KSTEPS)) % NT, set = it / (64 * KSTEPS * NT);
-    const int m = l & 15, jj = l >> 4;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (m % GPAD < gb && m / GPAD == ts % TILES) {
-      const int h = c * p.G + g0 + m % GPAD;
-      v = ld16((const char*)(set ? p.q_sink : p.q) + (((int64_t)prob * p.Hq + h) * D + (4 * kc + jj) * 8) * 2);
+  if (slot_is_late(p)) {
+    src.slot = late_slot(p, sg, ring_n);
+    const int b0 = t_begin + wave * BT;
+    if (src.slot >= b0 && src.slot < b0 + BT) {  // wave-uniform: the first block holds the new token, read above as the old one
+#pragma unroll
+      for (int i = 0; i < NLOAD; ++i)
+        if (b0 + i * TPL + tq == src.slot) {
+          kv[i] = ld16(kn + cl * 16);
+          vv[i] = ld16(vn + cl * 16);
+        }
     }
-    qbuf[set][ts][kc][l] = v;
   }
+  const int slot = src.slot;
+  if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window
+    st16(Kr.at(slot) + tid * 16, ld16(kn + tid * 16));
+    st16(Vr.at(slot) + tid * 16, ld16(vn + tid * 16));
+  }
+  uint4* q_lds = &qbuf[0][0][0][0];
+#pragma unroll
+  for (int i = 0; i < QN; ++i)
+    if (tid + i * kThreads < NT * KSTEPS * 64) q_lds[tid + i * kThreads] = qv[i];
+  if (p.q_sink)
+    for (int it = tid; it < NT * KSTEPS * 64; it += kThreads) q_lds[NT * KSTEPS * 64 + it] = q_operand(p.q_sink, it);
   __syncthreads();
 
   // V staging swizzle (16-byte chunk ^= vswz(token)): the four tokens a 16-lane group reads together
@@ -683,8 +730,7 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
       float bm = x[0][r];
 #pragma unroll
       for (int a = 1; a < NACC; ++a) bm = fmaxf(bm, x[a][r]);
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
+      bm = group16_max(bm);
 #pragma unroll
       for (int o = 16 * (GPAD / 4); o < 64; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
       const float mn = fmaxf(m_run[r], bm);
@@ -737,9 +783,7 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   // wave totals: sum of weights per head over the lanes that share it
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    float ls = l_part[r];
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) ls += __shfl_xor(ls, o);
+    float ls = group_sum<16>(l_part[r]);
 #pragma unroll
     for (int o = 16 * (GPAD / 4); o < 64; o <<= 1) ls += __shfl_xor(ls, o);
     if (n == 0 && j < GPAD / 4) s_ml[wave][hbase + r] = make_float2(m_run[r], ls);
@@ -839,7 +883,9 @@ hipError_t launch_decode_mfma_s(const DecodeParams& p, int g0, int gb, dim3 grid
   // (measured 43 vs 47 us at 448 rows x 1024 tokens x 7 heads)
   const bool wide = big && grid.y <= 256;
   if (gb <= 4) {
-    if (big) hipLaunchKernelGGL((decode_mfma_kernel<D, 4, 8, STREAM, PG>), grid, dim3(512), 0, s, p, g0, gb);
+    if (big && grid.y < kWholeRows)  // a few short rows: latency, P.V on the matrix cores (8 rows x 256 tokens: 8.4 vs 9.8 us)
+      hipLaunchKernelGGL((decode_pv_mfma_kernel<D, 4, 8, STREAM, PG>), grid, dim3(512), 0, s, p, g0, gb);
+    else if (big) hipLaunchKernelGGL((decode_mfma_kernel<D, 4, 8, STREAM, PG>), grid, dim3(512), 0, s, p, g0, gb);
     else hipLaunchKernelGGL((decode_pv_mfma_kernel<D, 4, 4, STREAM, PG>), grid, dim3(256), 0, s, p, g0, gb);
   } else if (gb <= 8) {
     if (wide) hipLaunchKernelGGL((decode_pv_mfma_kernel<D, 8, 8, STREAM, PG>), grid, dim3(512), 0, s, p, g0, gb);

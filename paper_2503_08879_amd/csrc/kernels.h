@@ -16,6 +16,7 @@ struct RowStat {
 
 constexpr int kHistBins = 2048;      // first radix digit: key bits 30..20
 constexpr int kScoreChunk = 1024;    // most tokens one score workgroup covers (256, 512 or 1024, see score_chunk)
+constexpr int kWholeRows = 192;      // decode: from so many rows on, every row is one workgroup's
 constexpr int kCombineChunk = 4096;  // tokens one combine workgroup covers
 
 struct RowGeom {

@@ -1,0 +1,45 @@
+"""Decode steps over few, short rows: whole rows in one workgroup up to a length, sliced rows behind it; and the
+device-counted step, which issues its first loads before it knows the new token's slot: the slot wanders through every
+block of the row here."""
+import numpy as np
+import pytest
+
+import synth
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+BF16, F32 = synth.BF16, synth.F32
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (4, 2, 64), (7, 1, 128), (12, 1, 64)])
+@pytest.mark.parametrize("dtype,n", [(BF16, 1), (BF16, 33), (BF16, 255), (BF16, 256), (BF16, 257), (BF16, 600),
+                                     (F32, 1), (F32, 127), (F32, 128), (F32, 129), (F32, 256), (F32, 257), (F32, 600)])
+@pytest.mark.parametrize("ring", [False, True])
+def test_steps_around_the_single_pass_length(ref, dtype, n, Hq, Hkv, d, ring):
+    import torch
+
+    import paper_2503_08879_amd as sk
+
+    P = 2
+    W = n  # the whole row is the window: the slot takes every position
+    rng = np.random.default_rng(n * 31 + Hq + d)
+    draw = lambda *shape: synth.round_to_dtype(rng.standard_normal(shape, dtype=np.float32), dtype)
+    Kc, Vc = draw(P, Hkv, n, d), draw(P, Hkv, n, d)
+    Kd, Vd = synth.host_to_torch(Kc, dtype), synth.host_to_torch(Vc, dtype)
+    desc, ws, out = gu.gpu_decode_setup(dtype, P, Hq, Hkv, d, 0, 0, W, n)
+    state = torch.zeros(2, dtype=torch.int32, device="cuda")
+    # a few steps at spread positions of the window, wrap-around included
+    for t in sorted({0, 1, n // 3, n - 1, n, n + n // 2}):
+        q, kn, vn = draw(P, Hq, d), draw(P, Hkv, d), draw(P, Hkv, d)
+        Kc[:, :, t % W], Vc[:, :, t % W] = kn, vn
+        want = ref.decode_attn(dtype, 0, q, Kc, Vc, n)
+        ins = [synth.host_to_torch(x, dtype) for x in (q, kn, vn)]
+        if ring:
+            state[0] = t
+            sk.sagekv_decode_step_ring(desc, *ins, Kd, Vd, state, out, ws)
+            assert state.tolist() == [t + 1, 0]
+        else:
+            sk.sagekv_decode_step(desc, *ins, Kd, Vd, t, out, ws)
+        assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[dtype], t
+        np.testing.assert_array_equal(synth.torch_to_host(Kd, dtype), Kc)
+        np.testing.assert_array_equal(synth.torch_to_host(Vd, dtype), Vc)
