@@ -23,7 +23,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // of magnitude of margin while the band still holds only a handful of candidates per row.
 constexpr float kBand = 1.0f / 4096.0f;
 
-constexpr int64_t kFillWorkgroups = 512;  // see score_chunk
+constexpr int64_t kFillPrefiltered = 512, kFillDense = 256;  // see score_chunk
 
 // Sizes of the fast (pre-filtered) eviction path for one descriptor; ok = the path applies.
 struct FastPlan {
@@ -36,12 +36,15 @@ struct FastPlan {
 };
 
 // Tokens one workgroup of the first pass over K covers: 1024, less where the call is too small for that to fill the
-// chip (two workgroups per CU, a few rounds of them).  At most 1024 chunks per row (the candidate selection gives each a
-// thread).
-int score_chunk(const sagekv_select_desc* d) {
+// chip.  At most 1024 chunks per row (the candidate selection gives each a thread).
+// Pre-filtered path: at least 512 workgroups, two per CU (8 rows of 32768 tokens: 22 us with 512 workgroups of 512
+// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256).  Dense path: 256 workgroups do; what a token's share of its chunk is decides
+// whether it enters the softmax sum with an fp64 exponent, and small chunks take many more terms that way (8 rows of
+// 30000 tokens: 23 us with 480 workgroups of 512 tokens, 31 with 960 of 256).
+int score_chunk(const sagekv_select_desc* d, int64_t fill) {
   const int64_t rows = (int64_t)d->n_problems * d->n_kv_heads;
   int chunk = d->dtype == SAGEKV_BF16 ? kScoreChunk : 512;
-  while (chunk > 256 && rows * ((d->L + chunk - 1) / chunk) < kFillWorkgroups && (d->L + chunk / 2 - 1) / (chunk / 2) <= 1024) chunk /= 2;
+  while (chunk > 256 && rows * ((d->L + chunk - 1) / chunk) < fill && (d->L + chunk / 2 - 1) / (chunk / 2) <= 1024) chunk /= 2;
   return chunk;
 }
 
@@ -95,7 +98,7 @@ FastPlan fast_plan(const sagekv_select_desc* d) {
   // A chunk's own slots: twice the candidates an average chunk is expected to keep (rank * wB tokens
   // per list over the row's chunks), so that only chunks where the candidates crowd (a needle
   // cluster, the tokens next to the recent window of a trained model) reach into the overflow pool.
-  const int chunk = score_chunk(d);
+  const int chunk = score_chunk(d, kFillPrefiltered);
   const int64_t n_chunks = (d->L + chunk - 1) / chunk;
   const double per_chunk = (double)f.rank * (double)f.wB * lists / (double)n_chunks;
   int cap_c = 32;
@@ -157,10 +160,10 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
   l.G = d->n_q_heads / d->n_kv_heads;
   l.n_lists = d->head_mode == SAGEKV_HEADS_PER_QUERY ? l.G : 1;
   l.Lp = (d->L + 3) / 4 * 4;
-  l.chunk = score_chunk(d);
-  l.n_chunks = (int)((d->L + l.chunk - 1) / l.chunk);
   l.fast = fast_plan(d);
   l.small = l.fast.ok;
+  l.chunk = score_chunk(d, l.small ? kFillPrefiltered : kFillDense);
+  l.n_chunks = (int)((d->L + l.chunk - 1) / l.chunk);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;

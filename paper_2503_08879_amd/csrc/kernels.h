@@ -174,7 +174,7 @@ struct StatsParams {
 };
 
 // One-sweep dense path, rows of up to kRowSelectMax tokens: statistics, scores and selection in one launch.
-constexpr int kRowSelectMax = 32768;
+constexpr int kRowSelectMax = 24576;
 struct RowSelectParams {
   RowGeom geo;
   const float* logits;     // the score pass's scratch

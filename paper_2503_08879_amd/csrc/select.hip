@@ -411,9 +411,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
 // Statistics (fp64 merge of the chunks' partials), scores, top-k and ordered output of one selection list, the
 // list's scores held in registers: thread t owns the quads t, t + 1024, ... of the row (4 consecutive tokens
 // each).  Latency bound (one workgroup per list, a chain of memory round trips and barriers), so it replaces the
-// launches of the general route below wherever a row fits (32768 tokens: 32 registers of scores per thread):
-// statistics + combine + top-k took 21 + 11 + 23 us for 256 rows of 8192 tokens and 9.5 + 4.5 + 15.3 us for
-// 2 rows of 4096.
+// launches of the general route below for rows of up to 24576 tokens (24 registers of scores per thread):
+// statistics + combine + top-k take 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 25; 9.5 + 4.5 + 15.3 and 11
+// for 2 rows of 4096; at 30000 tokens the two are even (46 us, 8 rows), beyond that several workgroups per
+// row win.
 template <int DT, int NQ>
 __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParams p) {
   constexpr int N = 4 * NQ;
@@ -679,7 +680,7 @@ hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s) {
   } else if (quads <= 4) {
     SAGEKV_LAUNCH(4);
   } else {
-    SAGEKV_LAUNCH(8);
+    SAGEKV_LAUNCH(6);
   }
 #undef SAGEKV_LAUNCH
   return hipGetLastError();
