@@ -175,7 +175,7 @@ size_t sagekv_decode_workspace_bytes(const sagekv_decode_desc* desc);
 /* Step 4's attention: out[h] = sum_t softmax_t( q[h] . Kc[c][t] / sqrt(head_dim) ) Vc[c][t],
  * t in [0, len), c = h / G.   q [n_problems, Hq, head_dim]; out [n_problems, Hq, head_dim] fp32.
  * 1 <= len <= compact_capacity.  Logits, softmax and the weighted sum are fp32; with a bf16 cache
- * and more than 4 heads per KV head, or a row split over several workgroups, the softmax weights
+ * and more than 4 heads per KV head, or fewer than 192 rows of more than 128 tokens, the softmax weights
  * are rounded to bf16 (like the values they multiply) and the sum runs on the matrix cores. */
 sagekv_status sagekv_decode_attn(const sagekv_decode_desc* desc, const void* q, const void* Kc, const void* Vc,
                                  int32_t len, float* out, void* workspace, size_t workspace_bytes,

@@ -883,7 +883,9 @@ hipError_t launch_decode_mfma_s(const DecodeParams& p, int g0, int gb, dim3 grid
   // (measured 43 vs 47 us at 448 rows x 1024 tokens x 7 heads)
   const bool wide = big && grid.y <= 256;
   if (gb <= 4) {
-    if (big && grid.y < kWholeRows)  // a few short rows: latency, P.V on the matrix cores (8 rows x 256 tokens: 8.4 vs 9.8 us)
+    // few short rows that took the split kernel before they were whole (more than 128 tokens): latency, P.V on the matrix
+    // cores (8 rows x 256 tokens: 8.4 vs 9.8 us); shorter ones keep their fp32 weights
+    if (big && grid.y < kWholeRows && p.len > 128)
       hipLaunchKernelGGL((decode_pv_mfma_kernel<D, 4, 8, STREAM, PG>), grid, dim3(512), 0, s, p, g0, gb);
     else if (big) hipLaunchKernelGGL((decode_mfma_kernel<D, 4, 8, STREAM, PG>), grid, dim3(512), 0, s, p, g0, gb);
     else hipLaunchKernelGGL((decode_pv_mfma_kernel<D, 4, 4, STREAM, PG>), grid, dim3(256), 0, s, p, g0, gb);

@@ -12,7 +12,7 @@ BF16, F32 = synth.BF16, synth.F32
 
 
 @pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (4, 2, 64), (7, 1, 128), (12, 1, 64)])
-@pytest.mark.parametrize("dtype,n", [(BF16, 1), (BF16, 33), (BF16, 255), (BF16, 256), (BF16, 257), (BF16, 600),
+@pytest.mark.parametrize("dtype,n", [(BF16, 1), (BF16, 33), (BF16, 128), (BF16, 129), (BF16, 255), (BF16, 256), (BF16, 257), (BF16, 600),
                                      (F32, 1), (F32, 127), (F32, 128), (F32, 129), (F32, 256), (F32, 257), (F32, 600)])
 @pytest.mark.parametrize("ring", [False, True])
 def test_steps_around_the_single_pass_length(ref, dtype, n, Hq, Hkv, d, ring):
@@ -40,6 +40,8 @@ def test_steps_around_the_single_pass_length(ref, dtype, n, Hq, Hkv, d, ring):
             assert state.tolist() == [t + 1, 0]
         else:
             sk.sagekv_decode_step(desc, *ins, Kd, Vd, t, out, ws)
-        assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[dtype], t
+        # up to 128 tokens and 4 heads the weights stay fp32: sums of up to 128 products of order 1, fp32 logits
+        atol = 1e-5 if dtype == BF16 and n <= 128 and Hq // Hkv <= 4 else gu.DECODE_ATOL[dtype]
+        assert np.abs(out.cpu().numpy() - want).max() <= atol, t
         np.testing.assert_array_equal(synth.torch_to_host(Kd, dtype), Kc)
         np.testing.assert_array_equal(synth.torch_to_host(Vd, dtype), Vc)
