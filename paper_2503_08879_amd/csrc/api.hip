@@ -701,30 +701,30 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
       t.end(SAGEKV_STAGE_TOPK);
       if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
     } else {
-    t.begin(SAGEKV_STAGE_STATS);
-    e = launch_stats(tp, l.rows, s);
-    t.end(SAGEKV_STAGE_STATS);
-    if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
-    CombineParams cp = {};
-    cp.geo = geo;
-    cp.logits = sp.logits;
-    cp.n_chunks = l.n_chunks;
-    cp.chunk = l.chunk;
-    cp.stats = stats;
-    cp.scores = scores;
-    cp.pitch = pitch;
-    cp.ghist = ghist;
-    cp.S = d->n_sink;
-    cp.W = d->n_recent;
-    cp.n_lists = l.n_lists;
-    t.begin(SAGEKV_STAGE_COMBINE);
-    e = launch_combine(cp, s);
-    t.end(SAGEKV_STAGE_COMBINE);
-    if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
-    t.begin(SAGEKV_STAGE_TOPK);
-    e = launch_topk(kp, s);
-    t.end(SAGEKV_STAGE_TOPK);
-    if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+      t.begin(SAGEKV_STAGE_STATS);
+      e = launch_stats(tp, l.rows, s);
+      t.end(SAGEKV_STAGE_STATS);
+      if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+      CombineParams cp = {};
+      cp.geo = geo;
+      cp.logits = sp.logits;
+      cp.n_chunks = l.n_chunks;
+      cp.chunk = l.chunk;
+      cp.stats = stats;
+      cp.scores = scores;
+      cp.pitch = pitch;
+      cp.ghist = ghist;
+      cp.S = d->n_sink;
+      cp.W = d->n_recent;
+      cp.n_lists = l.n_lists;
+      t.begin(SAGEKV_STAGE_COMBINE);
+      e = launch_combine(cp, s);
+      t.end(SAGEKV_STAGE_COMBINE);
+      if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+      t.begin(SAGEKV_STAGE_TOPK);
+      e = launch_topk(kp, s);
+      t.end(SAGEKV_STAGE_TOPK);
+      if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
     }
   }
 

@@ -10,8 +10,8 @@
 //                     in the slots of their score chunk (no global atomics) or, once a chunk has used
 //                     its slots up, in the row's overflow pool.
 //   topk_cand_kernel  exact (M, Z) per head from the partials and the bound rho * tau^ on the exact
-//                     score of every token that was dropped; exact scores of the candidates, radix select
-//                     of the k-th score, fp64 re-evaluation and exact ranking of the few candidates around
+//                     score of every token that was dropped; exact scores of the candidates (in registers),
+//                     bracket of the k-th score, fp64 re-evaluation and exact ranking of the few candidates around
 //                     it, then an LDS bitmap turns the unordered selection into ascending positions.  The
 //                     row is only accepted if its k-th score clears the bound, i.e. if no dropped token
 //                     could have been selected; otherwise it is flagged and the dense stages redo it.

@@ -28,8 +28,9 @@ constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine laun
 
 // Softmax terms that a wave takes with an fp64 exponent, up to kHeavyBatch at a time: exp(l - m), l = the logit of query
 // row q + q_off and key row K + k_off (D elements each) in fp64.  Sixteen lanes share a term, so the loads of a
-// batch are in flight together (one term after the other costs a memory round trip each: 16 terms of a chunk that
-// holds the sink tokens took 35 us, a batch takes about 2).  Called by all 64 lanes of a wave; rare: out of line.
+// batch are in flight together (one term after the other costs a memory round trip each: the dense score pass over 256
+// rows x 8192 tokens, four of them sink tokens, took 151 us that way, 119 with batches).  Called by all 64 lanes of a
+// wave; rare: out of line.
 constexpr int kHeavyBatch = 32;
 struct HeavyTerms {
   int64_t k_off[kHeavyBatch], q_off[kHeavyBatch];

@@ -2,6 +2,8 @@
 // per row, the k candidates with the largest score, ties to the lower index, written in
 // ascending position between the sink and the recent window; then the gather of K and V.
 //
+// row_select_kernel: one-sweep dense path, rows whose scores one workgroup holds in registers.
+//
 // topk_kernel: one 1024-thread workgroup per row; two passes over the row's scores (steps 1 and
 // 2) on the usual route, all with aligned 16-byte loads.
 //   1. coarse bracket of the k-th score: the first two digits (11 + 11 bits) of a radix select on
