@@ -71,20 +71,32 @@ struct BlockSource {
     my_page = pid < 0 ? 0 : (pid >= K.n_pages ? K.n_pages - 1 : pid);
   }
   __device__ __forceinline__ bool refill_before(int it) const { return PAGED && ((it * GPB) & 63) == 0; }
-  // this lane's token of load i of block it; tokens past the slice become one that is inside it
+  // this lane's token of load i of block it; tokens past the slice become one that is inside it: its first, in pages the first
+  // of the group my_page was filled for
+  __device__ __forceinline__ int token(int it, int i, int tq) const {
+    const int b0 = t_begin + (wave + it * NW) * BT, tok = b0 + i * TPL + tq;
+    const int g0 = b0 + (i * TPL) / 16 * 16;
+    return tok < t_end ? tok : PAGED && g0 < t_end ? g0 : t_begin;
+  }
   __device__ __forceinline__ const char* at(const CacheRow& r, const char* fresh, int it, int i, int tq) const {
-    const int b0 = t_begin + (wave + it * NW) * BT;
-    int tok = b0 + i * TPL + tq;
-    if (!PAGED) {
-      tok = tok < t_end ? tok : t_begin;
-      return tok == slot ? fresh : r.base + (int64_t)tok * ROWB;
-    }
-    const int g = (i * TPL) / 16;
-    const int g0 = b0 + g * 16 < t_end ? b0 + g * 16 : t_begin;  // first token of the group my_page was filled for
-    tok = tok < t_end ? tok : g0;
-    const int pid = __builtin_amdgcn_readlane(my_page, (it * GPB + g) & 63);
+    const int tok = token(it, i, tq);
+    if (!PAGED) return tok == slot ? fresh : r.base + (int64_t)tok * ROWB;
+    const int pid = __builtin_amdgcn_readlane(my_page, (it * GPB + (i * TPL) / 16) & 63);
     const char* page = r.base + (int64_t)pid * r.page_bytes;
     return tok == slot ? fresh : page + (int64_t)(tok & ((1 << r.shift) - 1)) * ROWB;
+  }
+  // the slot has become known after the first block was loaded without it: the lanes that hold the new token's
+  // place (a lane past the slice may, through its replacement) take the new token
+  template <int NLOAD>
+  __device__ __forceinline__ void patch_first(uint4 (&k)[NLOAD], uint4 (&v)[NLOAD], const char* kn, const char* vn, int tq, int cl) const {
+    const int b0 = t_begin + wave * BT;
+    if ((slot < b0 || slot >= b0 + BT) && slot != t_begin) return;  // wave-uniform
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i)
+      if (token(0, i, tq) == slot) {
+        k[i] = ld16(kn + cl * 16);
+        v[i] = ld16(vn + cl * 16);
+      }
   }
 };
 
@@ -393,15 +405,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
   }
   if (slot_is_late(p)) {
     src.slot = late_slot(p, sg, ring_n);
-    const int b0 = t_begin + wave * BT;
-    if (src.slot >= b0 && src.slot < b0 + BT) {  // wave-uniform: the first block holds the new token, read above as the old one
-#pragma unroll
-      for (int i = 0; i < NLOAD; ++i)
-        if (b0 + i * TPL + tq == src.slot) {
-          kv[i] = ld16(kn + cl * 16);
-          vv[i] = ld16(vn + cl * 16);
-        }
-    }
+    src.patch_first(kv, vv, kn, vn, tq, cl);
   }
   const int slot = src.slot;
   if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window
@@ -654,15 +658,7 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   }
   if (slot_is_late(p)) {
     src.slot = late_slot(p, sg, ring_n);
-    const int b0 = t_begin + wave * BT;
-    if (src.slot >= b0 && src.slot < b0 + BT) {  // wave-uniform: the first block holds the new token, read above as the old one
-#pragma unroll
-      for (int i = 0; i < NLOAD; ++i)
-        if (b0 + i * TPL + tq == src.slot) {
-          kv[i] = ld16(kn + cl * 16);
-          vv[i] = ld16(vn + cl * 16);
-        }
-    }
+    src.patch_first(kv, vv, kn, vn, tq, cl);
   }
   const int slot = src.slot;
   if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window

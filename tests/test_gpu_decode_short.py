@@ -45,3 +45,39 @@ def test_steps_around_the_single_pass_length(ref, dtype, n, Hq, Hkv, d, ring):
         assert np.abs(out.cpu().numpy() - want).max() <= atol, t
         np.testing.assert_array_equal(synth.torch_to_host(Kd, dtype), Kc)
         np.testing.assert_array_equal(synth.torch_to_host(Vd, dtype), Vc)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (7, 1, 64), (12, 1, 128)])
+@pytest.mark.parametrize("n,slot", [(45, 0), (100, 0), (200, 0), (200, 192), (601, 0), (601, 512), (601, 592)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_a_non_finite_token_leaves_with_the_step_that_replaces_it(ref, n, slot, Hq, Hkv, d, paged):
+    """The device-counted step reads its first blocks before it knows the slot, and lanes past a ragged end read the first
+    token of their slice (pages: of their group of 16) instead: where that token is the one being replaced, its old
+    value must not reach the sums, not even with weight 0."""
+    import torch
+
+    import paper_2503_08879_amd as sk
+
+    P, page = 2, 16
+    rng = np.random.default_rng(n + slot + Hq)
+    draw = lambda *shape: synth.round_to_dtype(rng.standard_normal(shape, dtype=np.float32), BF16)
+    Kc, Vc, q, kn, vn = draw(P, Hkv, n, d), draw(P, Hkv, n, d), draw(P, Hq, d), draw(P, Hkv, d), draw(P, Hkv, d)
+    Kd, Vd = synth.host_to_torch(Kc, BF16), synth.host_to_torch(Vc, BF16)
+    Kd[:, :, slot] = float("nan")
+    Vd[:, :, slot] = float("inf")
+    Kc[:, :, slot], Vc[:, :, slot] = kn, vn
+    want = ref.decode_attn(BF16, 0, q, Kc, Vc, n)
+    desc, ws, out = gu.gpu_decode_setup(BF16, P, Hq, Hkv, d, 0, 0, n, n)
+    state = torch.tensor([slot, 0], dtype=torch.int32, device="cuda")
+    ins = [synth.host_to_torch(x, BF16) for x in (q, kn, vn)]
+    if paged:
+        per = (n + page - 1) // page
+        pool = lambda X: torch.cat([X, X.new_zeros(P, Hkv, per * page - n, d)], 2).reshape(P, Hkv, per, page, d).transpose(1, 2).reshape(
+            P * per, Hkv, page, d).contiguous()
+        Kp, Vp = pool(Kd), pool(Vd)
+        table = torch.arange(P * per, dtype=torch.int32, device="cuda").reshape(P, per)
+        sk.sagekv_decode_step_paged(desc, sk.compact_pages(table, Kp, Vp), *ins, Kp, Vp, 0, state, out, ws)
+    else:
+        sk.sagekv_decode_step_ring(desc, *ins, Kd, Vd, state, out, ws)
+    assert state.tolist() == [slot + 1, 0]
+    assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[BF16]
