@@ -38,9 +38,9 @@ struct FastPlan {
 // Tokens one workgroup of the first pass over K covers: 1024, less where the call is too small for that to fill the
 // chip.  At most 1024 chunks per row (the candidate selection gives each a thread).
 // Pre-filtered path: at least 512 workgroups, two per CU (8 rows of 32768 tokens: 22 us with 512 workgroups of 512
-// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256).  Dense path: 256 workgroups do; what a token's share of its chunk is decides
-// whether it enters the softmax sum with an fp64 exponent, and small chunks take many more terms that way (8 rows of
-// 30000 tokens: 23 us with 480 workgroups of 512 tokens, 31 with 960 of 256).
+// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256).  Dense path: 256 workgroups do for bf16, whose statistics are merged by
+// one workgroup per row (a pass over 8 rows of 30000 tokens x 4 heads: 65.3 us with chunks of 512 tokens, 67.6 with 256; fp32 would
+// rather have 256: 8 rows of 16384 x 4 heads 53.8 against 58.4).
 int score_chunk(const sagekv_select_desc* d, int64_t fill) {
   const int64_t rows = (int64_t)d->n_problems * d->n_kv_heads;
   int chunk = d->dtype == SAGEKV_BF16 ? kScoreChunk : 512;
@@ -172,7 +172,7 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
   };
   const size_t rows = (size_t)l.rows;
   l.logits = take(l.small ? 0 : rows * l.n_chunks * l.G * l.chunk * sizeof(float));
-  l.partials = take(rows * l.G * l.n_chunks * sizeof(float2));
+  l.partials = take(rows * l.G * l.n_chunks * (l.small ? sizeof(float2) : sizeof(ChunkPartial)));
   l.stats = take(rows * l.G * sizeof(RowStat));
   l.ghist = take(rows * l.n_lists * kHistBins * sizeof(int));
   bool cs_in_scores = false;
@@ -486,6 +486,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
   sp.pm = pm;
   sp.logits = (float*)(ws + l.logits);
   sp.partials = partials;
+  sp.chunk_partials = (ChunkPartial*)(ws + l.partials);
   sp.n_chunks = l.n_chunks;
   sp.chunk = l.chunk;
   sp.g0 = 0;
@@ -675,21 +676,23 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     e = launch_score(sp, SCORE_LOGITS, s);
     t.end(SAGEKV_STAGE_SCORE);
     if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+    DenseRows in = {};
+    in.geo = geo;
+    in.logits = sp.logits;
+    in.partials = sp.chunk_partials;
+    in.n_chunks = l.n_chunks;
+    in.chunk = l.chunk;
+    in.q_last = q_last;
+    in.K = K;
+    in.ks_problem = d->k_stride_problem;
+    in.ks_head = d->k_stride_head;
+    in.ks_token = d->k_stride_token;
+    in.pm = pm;
     if (d->L <= kRowSelectMax) {
       RowSelectParams rp = {};
-      rp.geo = geo;
-      rp.logits = sp.logits;
-      rp.partials = partials;
-      rp.n_chunks = l.n_chunks;
-      rp.chunk = l.chunk;
+      rp.in = in;
       rp.scores = scores_out;
       rp.pitch = pitch;
-      rp.q_last = q_last;
-      rp.K = K;
-      rp.ks_problem = d->k_stride_problem;
-      rp.ks_head = d->k_stride_head;
-      rp.ks_token = d->k_stride_token;
-      rp.pm = pm;
       rp.kept_idx = kept_idx;
       rp.S = d->n_sink;
       rp.W = d->n_recent;
@@ -701,8 +704,9 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
       t.end(SAGEKV_STAGE_TOPK);
       if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
     } else {
+      RowStatsParams xp = {in, stats, ghist, l.n_lists};
       t.begin(SAGEKV_STAGE_STATS);
-      e = launch_stats(tp, l.rows, s);
+      e = launch_row_stats(xp, s);
       t.end(SAGEKV_STAGE_STATS);
       if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
       CombineParams cp = {};

@@ -117,12 +117,13 @@ __device__ __forceinline__ double swap16_f64(double v) {
 }
 template <int LANES>
 __device__ __forceinline__ double group_sum_f64(double v) {
-  static_assert(LANES == 16 || LANES == 32, "");
+  static_assert(LANES == 16 || LANES == 32 || LANES == 64, "");
   v += dpp_f64<0xB1>(v);
   v += dpp_f64<0x4E>(v);
   v += dpp_f64<0x141>(v);
   v += dpp_f64<0x140>(v);
-  if (LANES == 32) v += swap16_f64(v);
+  if (LANES >= 32) v += swap16_f64(v);
+  if (LANES >= 64) v += __shfl_xor(v, 32);
   return v;
 }
 

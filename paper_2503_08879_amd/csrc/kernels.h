@@ -14,6 +14,13 @@ struct RowStat {
   double Z;
 };
 
+// Softmax partial of one score chunk of the one-sweep dense path: the maximum and sum exp(x - max) of the chunk's fp32
+// logits, fp32 terms added in fp64 (a term can be taken out of the sum again, see exact_changes).
+struct ChunkPartial {
+  double sum;
+  float max, unused;
+};
+
 constexpr int kHistBins = 2048;      // first radix digit: key bits 30..20
 constexpr int kScoreChunk = 1024;    // most tokens one score workgroup covers (256, 512 or 1024, see score_chunk)
 constexpr int kWholeRows = 192;      // decode: from so many rows on, every row is one workgroup's
@@ -145,13 +152,14 @@ struct ScoreParams {
   const void* K;
   int64_t ks_problem, ks_head, ks_token;  // elements
   PageMap pm;
-  // [rows][G] or null.  A logit x >= heavy_thr enters its chunk's softmax sum as exp(l - m) with l
+  // SCORE_FILTER, SCORE_PARTIALS: [rows][G].  A logit x >= heavy_thr enters its chunk's softmax sum as exp(l - m) with l
   // recomputed in fp64: an fp32 logit of magnitude |l| is off by about |l| * 2.5e-7, which is the relative
   // error of its exponential, and a head whose mass sits on a few such tokens would get a normaliser that
   // is off by as much; two heads' errors differ, and that can reorder group-sum scores a few 1e-6 apart.
   const float* heavy_thr;
   float* logits;                          // SCORE_LOGITS: [rows][n_chunks][G][chunk]
-  float2* partials;                       // [rows][G][n_chunks]  (max, sum exp(x - max))
+  float2* partials;                       // [rows][G][n_chunks]  (max, sum exp(x - max)); SCORE_LOGITS:
+  ChunkPartial* chunk_partials;           // the same, more precisely and without fp64 exponents (see exact_changes)
   int n_chunks;
   int chunk;  // tokens a workgroup covers (SCORE_SCORES: always kScoreChunk)
   int g0;  // first head of the group handled by this launch
@@ -173,23 +181,36 @@ struct StatsParams {
   int n_lists;     // selection lists per row: 1 (group-sum) or G (per-query)
 };
 
-// One-sweep dense path, rows of up to kRowSelectMax tokens: statistics, scores and selection in one launch.
-constexpr int kRowSelectMax = 24576;
-struct RowSelectParams {
+// One-sweep dense path: a row's logits as the score pass left them, and what it takes to recompute one in fp64.
+struct DenseRows {
   RowGeom geo;
-  const float* logits;     // the score pass's scratch
-  const float2* partials;  // [rows][G][n_chunks]
+  const float* logits;           // [rows][n_chunks][G][chunk]
+  const ChunkPartial* partials;  // [rows][G][n_chunks]
   int n_chunks, chunk;
-  float* scores;           // nullable [rows * n_lists][pitch]: every token's score
-  int64_t pitch;
   const void* q_last;
   const void* K;
   int64_t ks_problem, ks_head, ks_token;
   PageMap pm;
+};
+
+// Rows of up to kRowSelectMax tokens: statistics, scores and selection in one launch.
+constexpr int kRowSelectMax = 24576;
+struct RowSelectParams {
+  DenseRows in;
+  float* scores;           // nullable [rows * n_lists][pitch]: every token's score
+  int64_t pitch;
   int32_t* kept_idx;       // [rows][S + n_lists * k + W]
   int S, W, k;
   int n_lists;             // 1 or G
   float band;
+};
+
+// Longer rows: the statistics alone.
+struct RowStatsParams {
+  DenseRows in;
+  RowStat* stats;  // out [rows][G]
+  int* ghist;      // [rows * n_lists][kHistBins], zeroed here
+  int n_lists;
 };
 
 struct CombineParams {
@@ -344,6 +365,7 @@ hipError_t launch_topk_cand(const TopkCandParams& p, hipStream_t s);
 hipError_t launch_score(const ScoreParams& p, ScoreMode mode, hipStream_t s);  // any mode but SCORE_FILTER
 hipError_t launch_stats(const StatsParams& p, int rows, hipStream_t s);
 hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s);
+hipError_t launch_row_stats(const RowStatsParams& p, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 hipError_t launch_topk(const TopkParams& p, hipStream_t s);
 hipError_t launch_gather(const GatherParams& p, hipStream_t s);

@@ -2,6 +2,8 @@
 // and the fp64 re-evaluation of a token's score.  Shared by the dense and the candidate-list
 // selection kernels; all functions are called by every thread of a 1024-thread workgroup.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -40,6 +42,23 @@ __device__ inline RowStat merge_partials_wave(const float2* pr, int n_chunks) {
   }
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) z += __shfl_xor(z, o);
+  RowStat st;
+  st.M = M;
+  st.Z = z;
+  st.invZ = (float)(1.0 / z);
+  return st;
+}
+
+// The same from the partials of the one-sweep dense path.
+__device__ inline RowStat merge_partials_wave(const ChunkPartial* pr, int n_chunks) {
+  const int lane = threadIdx.x & 63;
+  float M = -INFINITY;
+  for (int i = lane; i < n_chunks; i += 64) M = fmaxf(M, pr[i].max);
+  M = wave_max(M);
+  double z = 0.0;
+#pragma unroll 1
+  for (int i = lane; i < n_chunks; i += 64) z += pr[i].sum * exp((double)pr[i].max - (double)M);
+  z = group_sum_f64<64>(z);
   RowStat st;
   st.M = M;
   st.Z = z;
@@ -205,6 +224,187 @@ __device__ inline float refined_score_wave(const RowGeom& geo, const void* q_las
   return (float)tot;
 }
 
+// ---- normalisers of the one-sweep dense path ----------------------------------------------------
+// The score pass knows nothing about a row before its sweep, so its chunk sums hold fp32 terms only.  Once a head's (M, Z) are
+// merged, the terms heavy enough FOR THE ROW (heavy_logit_threshold: at most 1.4 M^2 of them) are exchanged for ones
+// with an fp64 exponent: only chunks whose maximum reaches the threshold can hold one; their logits are looked through again
+// in scratch.  (A rule on a term's share of its own chunk, applied in the score pass, calls every token of a flat chunk heavy
+// once the logits share an offset: 256 rows x 8192 tokens, 4 heads, logits around -30: 718 us that way, 223 so.)
+// A wave takes every sixteenth segment of 256 tokens of a head, one step further for the next head (neighbouring segments and
+// a segment's heads tend to be heavy together).  Latency bound, two memory round trips (logits, then keys): a segment's
+// logits are asked for one segment ahead, and a wave collects the heavy terms of its segments, up to a batch, before it
+// takes them.  Few instructions on purpose, each thing in one place: the code runs once per row and is fetched cold.
+constexpr int kExactTokens = 256;
+constexpr int kExactBatch = 256;  // at least one segment's
+constexpr int kExactMost = 2048;  // times the heads: heavy terms a wave takes exactly; beyond: as fp32 terms
+struct ExactSums {
+  double change[kTopkWaves][64];  // what a wave's terms change in Z of each head
+  int tok[kTopkWaves][kExactBatch];
+  unsigned char head[kTopkWaves][kExactBatch];
+};
+
+// A batch of a wave: 16 of its segments from seg0 on for each of the heads g0 .. g0 + 3, one (segment, head) per lane.
+struct ExactItem {
+  int g, seg;
+};
+__device__ __forceinline__ ExactItem exact_item(int g0, int seg0, int lane) {
+  const int g = g0 + (lane & 3);
+  return ExactItem{g, seg0 + kTopkWaves * (lane >> 2) + (((int)(threadIdx.x >> 6) - g) & (kTopkWaves - 1))};
+}
+// The maximum of the chunk that this lane's item lies in.
+__device__ __forceinline__ float exact_maximum(const DenseRows& in, int row, int g0, int g_hi, int seg0) {
+  const ExactItem it = exact_item(g0, seg0, threadIdx.x & 63);
+  const int ch = it.seg >> __builtin_ctz((unsigned)in.chunk / kExactTokens);
+  return it.g < g_hi && ch < in.n_chunks ? in.partials[((int64_t)row * in.geo.G + it.g) * in.n_chunks + ch].max : -INFINITY;
+}
+
+// A wave's first cnt listed terms: exp(l - M) - (the fp32 term in the merged sum), l = the logit in fp64, added to its changes.
+// Sixteen lanes share a term, four elements at a time, two terms in flight (fp32: one, registers).  Called by all 64 lanes
+// of a wave.
+template <int DT>
+__device__ __forceinline__ void exact_terms_wave(const DenseRows& in, ExactSums& sh, int cnt, int row, const RowStat* stat) {
+  typedef typename std::conditional<DT == DT_BF16, uint2, uint4>::type Four;  // four elements
+  constexpr int U = DT == DT_BF16 ? 2 : 1;
+  const int D = in.geo.D, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, sub = lane & 15;
+  const int prob = row / in.geo.Hkv, c = row % in.geo.Hkv, chunk_shift = __builtin_ctz((unsigned)in.chunk);
+  auto four = [](const void* base, int64_t i) { return *reinterpret_cast<const Four*>((const char*)base + i * Elem<DT>::bytes); };
+  auto dot = [](const Four& a, const Four& b, double acc) {
+    if constexpr (DT == DT_BF16) {
+      acc += (double)bf16_lo(a.x) * (double)bf16_lo(b.x) + (double)bf16_hi(a.x) * (double)bf16_hi(b.x);
+      return acc + ((double)bf16_lo(a.y) * (double)bf16_lo(b.y) + (double)bf16_hi(a.y) * (double)bf16_hi(b.y));
+    } else {
+      acc += (double)__uint_as_float(a.x) * (double)__uint_as_float(b.x) + (double)__uint_as_float(a.y) * (double)__uint_as_float(b.y);
+      return acc + ((double)__uint_as_float(a.z) * (double)__uint_as_float(b.z) + (double)__uint_as_float(a.w) * (double)__uint_as_float(b.w));
+    }
+  };
+  const double inv = 1.0 / sqrt((double)D);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+  for (int e0 = 0; e0 < cnt; e0 += 4 * U) {
+    Four k0[U], k1[U], q0[U], q1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + 4 * u + grp < cnt ? e0 + 4 * u + grp : cnt - 1;
+      const int64_t ko = kv_offset(in.pm, in.pm.ks_page, in.ks_problem, in.ks_head, in.ks_token, prob, c, sh.tok[wave][e]) + 4 * sub;
+      const int64_t qo = ((int64_t)prob * in.geo.Hq + c * in.geo.G + sh.head[wave][e]) * D + 4 * sub;
+      k0[u] = four(in.K, ko);
+      q0[u] = four(in.q_last, qo);
+      k1[u] = D > 64 ? four(in.K, ko + 64) : Four{};
+      q1[u] = D > 64 ? four(in.q_last, qo + 64) : Four{};
+    }
+    // lanes 0 and 1 of a group: the terms' fp64 exponentials, lanes 2 and 3: their fp32 ones as they were merged
+    const int e = e0 + 4 * (sub & 1) + grp;
+    const bool mine = sub < 4 && (sub & 1) < U && e < cnt;
+    const int g = sh.head[wave][e < cnt ? e : cnt - 1];
+    const float M = stat[g].M;
+    float x = 0.f, mc = M;
+    if (mine && sub >= 2) {
+      x = in.logits[logit_index(in.geo, in.n_chunks, in.chunk, row, g, sh.tok[wave][e])];
+      mc = in.partials[((int64_t)row * in.geo.G + g) * in.n_chunks + (sh.tok[wave][e] >> chunk_shift)].max;
+    }
+    double l = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double a = group_sum_f64<16>(dot(k1[u], q1[u], dot(k0[u], q0[u], 0.0)));
+      l = sub == u ? a * inv : l;
+    }
+    const double ex = exp((sub >= 2 ? (double)mc : l) - (double)M);
+    if (mine) unsafeAtomicAdd(&sh.change[wave][g], sub >= 2 ? -(double)exp_fast(x - mc) * ex : ex);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// What the heavy terms change in Z of heads g_lo .. g_hi of a row (stat, thr: their merged statistics and
+// heavy_logit_threshold of them, in LDS; max: exact_maximum of the first batch, asked for early).  Called by every thread of a
+// 1024-thread workgroup; begins with a barrier.  True (workgroup-uniform): exact_apply has to follow.
+template <int DT>
+__device__ __forceinline__ bool exact_changes(const DenseRows& in, ExactSums& sh, int row, int g_lo, int g_hi, const RowStat* stat,
+                                              const float* thr, float max) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __syncthreads();
+  bool any = false;
+  for (int g = g_lo; g < g_hi; ++g) any |= thr[g] <= stat[g].M;
+  if (!any) return false;  // no term of any head is heavy
+  sh.change[wave][lane] = 0.0;
+  const int n_seg = in.n_chunks * (in.chunk / kExactTokens);
+  int taken = 0, listed = 0;  // wave-uniform
+  bool end = false;
+  for (int g0 = g_lo, seg0 = 0; !end;) {  // the last round only takes what is listed
+    unsigned long long todo = 0ull;
+    end = seg0 >= n_seg;
+    if (!end) {
+      const int g = g0 + (lane & 3);
+      if (g0 > g_lo || seg0 > 0) max = exact_maximum(in, row, g0, g_hi, seg0);
+      todo = __ballot(g < g_hi && max >= thr[g < g_hi ? g : g_lo]);
+    }
+    auto logits_of = [&](const ExactItem& it) -> float4 {
+      const int64_t tok = (int64_t)it.seg * kExactTokens + 4 * lane;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (tok < in.geo.L)
+        v = *reinterpret_cast<const float4*>(in.logits + logit_index(in.geo, in.n_chunks, in.chunk, row, it.g, tok));
+      return v;
+    };
+    ExactItem it = {g_lo, 0}, it_next = it;
+    float4 next = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (todo) {
+      it_next = exact_item(g0, seg0, __ffsll(todo) - 1);
+      next = logits_of(it_next);
+    }
+    do {
+      unsigned long long heavy[4] = {0ull, 0ull, 0ull, 0ull};
+      int total = 0;
+      if (todo) {
+        const float x[4] = {next.x, next.y, next.z, next.w};
+        it = it_next;
+        todo &= todo - 1;
+        if (todo) {
+          it_next = exact_item(g0, seg0, __ffsll(todo) - 1);
+          next = logits_of(it_next);
+        }
+        const float th = thr[it.g];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          heavy[e] = __ballot((int64_t)it.seg * kExactTokens + 4 * lane + e < in.geo.L && x[e] >= th);
+          total += __popcll(heavy[e]);
+        }
+        if (taken + total > kExactMost * (g_hi - g_lo)) continue;
+        taken += total;
+      }
+      if (listed > 0 && (end || listed + total > kExactBatch)) {
+        exact_terms_wave<DT>(in, sh, listed, row, stat);
+        listed = 0;
+      }
+      if (total > 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int w = listed + __popcll(heavy[e] & ((1ull << lane) - 1ull));
+          if ((heavy[e] >> lane) & 1ull) {
+            sh.tok[wave][w] = it.seg * kExactTokens + 4 * lane + e;
+            sh.head[wave][w] = (unsigned char)it.g;
+          }
+          listed += __popcll(heavy[e]);
+        }
+      }
+    } while (todo);
+    g0 += 4;
+    if (g0 >= g_hi) g0 = g_lo, seg0 += 16 * kTopkWaves;
+  }
+  return true;
+}
+// Adds the changes to the statistics; begins and ends with a barrier.
+__device__ __forceinline__ void exact_apply(const ExactSums& sh, int g_lo, int g_hi, RowStat* stat) {
+  const int tid = threadIdx.x;
+  __syncthreads();
+  if (tid >= g_lo && tid < g_hi) {
+    double z = stat[tid].Z;
+#pragma unroll
+    for (int w = 0; w < kTopkWaves; ++w) z += sh.change[w][tid];
+    stat[tid].Z = z;
+    stat[tid].invZ = (float)(1.0 / z);
+  }
+  __syncthreads();
+}
+
 // ---- selection among scores held in registers ---------------------------------------------------
 // N scores per thread of a 1024-thread workgroup, -1: no element.  All functions are called by every thread.
 constexpr int kMaxBand = 1024;  // elements around the k-th that are ranked exactly among themselves
@@ -213,6 +413,7 @@ struct RegSelect {
   union {
     int hist[2][kHistBins];
     double term[kMaxBand];  // refine_band: fp64 terms of a batch of (member, head)
+    ExactSums exact;        // row_select_kernel, before anything is selected
   };
   int wave_tot[kTopkWaves], pick[2];
   int red_min[kTopkWaves], red_max[kTopkWaves];

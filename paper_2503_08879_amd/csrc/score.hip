@@ -9,8 +9,7 @@
 //                   every token's score from known (M, Z) (two-sweep dense path: rows the pre-filter
 //                   could not certify, without a logit scratch).
 //   sample_logits_kernel  logits of the sampled blocks of the pre-filtered path.
-//   stats_kernel    merges the partials of a row into (M, Z) per head, in fp64 (one-sweep rows that row_select_kernel
-//                   cannot hold, two-sweep path).
+//   stats_kernel    merges the partials of a row into (M, Z) per head, in fp64 (two-sweep path).
 //   combine_kernel  score[i] = sum_g exp(logit[g][i] - M_g) / Z_g  (fp32) and the first radix
 //                   histogram of the candidates' scores, merged across workgroups with atomics.
 #include "device_utils.h"
@@ -28,8 +27,7 @@ constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine laun
 
 // Softmax terms that a wave takes with an fp64 exponent, up to kHeavyBatch at a time: exp(l - m), l = the logit of query
 // row q + q_off and key row K + k_off (D elements each) in fp64.  Sixteen lanes share a term, so the loads of a
-// batch are in flight together (one term after the other costs a memory round trip each: the dense score pass over 256
-// rows x 8192 tokens, four of them sink tokens, took 151 us that way, 119 with batches).  Called by all 64 lanes of a
+// batch are in flight together (one term after the other costs a memory round trip each).  Called by all 64 lanes of a
 // wave; rare: out of line.
 constexpr int kHeavyBatch = 32;
 struct HeavyTerms {
@@ -38,7 +36,7 @@ struct HeavyTerms {
   float m[kHeavyBatch];
   int code[kHeavyBatch];  // whose sum the term belongs to
 };
-template <int DT, int D>
+template <int D>
 __device__ __noinline__ void exact_terms(HeavyTerms* h, int cnt, const void* K, const void* q) {
   constexpr int EPT = D / 16;  // elements per lane
   const int lane = threadIdx.x & 63, grp = lane >> 4, sub = lane & 15;
@@ -49,7 +47,7 @@ __device__ __noinline__ void exact_terms(HeavyTerms* h, int cnt, const void* K, 
       const int e = e0 + 4 * u + grp < cnt ? e0 + 4 * u + grp : cnt - 1;
       const int64_t ko = h->k_off[e] + sub * EPT, qo = h->q_off[e] + sub * EPT;
 #pragma unroll
-      for (int i = 0; i < EPT; ++i) acc[u] += elem_f64<DT>(q, qo + i) * elem_f64<DT>(K, ko + i);
+      for (int i = 0; i < EPT; ++i) acc[u] += elem_f64<DT_BF16>(q, qo + i) * elem_f64<DT_BF16>(K, ko + i);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -67,10 +65,7 @@ __device__ __noinline__ void exact_terms(HeavyTerms* h, int cnt, const void* K, 
 // make a block.  After load i the lane with (lane % LPT) == i keeps the reduced dot product,
 // so each lane ends a block owning exactly one token's logits for all heads.
 //
-// The softmax partial (M, Z) of the chunk is taken after the last block, from the logits in registers.  Terms
-// heavy enough for their logit's fp32 error to show in Z (heavy_logit_threshold, with the CHUNK's own M and
-// Z: a term's share of its chunk is at least its share of the row, and a chunk whose Z is good to 1e-7 is
-// all the row's Z needs) enter with a logit recomputed in fp64.
+// The softmax partial of the chunk is taken after the last block, from the logits in registers.
 template <int DT, int D, int GB, int BPW>
 __global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) {
   constexpr int EPL = Elem<DT>::per_lane;
@@ -142,8 +137,8 @@ __global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) 
   }
 
   // (max, sum) of the chunk: lanes -> wave -> workgroup
-  __shared__ float part_m[kScoreWaves][GB], part_s[kScoreWaves][GB];
-  float M[GB];
+  __shared__ float part_m[kScoreWaves][GB];
+  __shared__ double part_s[kScoreWaves][GB];
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
     float m = xs[0][g];
@@ -155,79 +150,27 @@ __global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) 
   __syncthreads();
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
-    M[g] = part_m[0][g];
+    float M = part_m[0][g];
 #pragma unroll
-    for (int w = 1; w < kScoreWaves; ++w) M[g] = fmaxf(M[g], part_m[w][g]);
-    float s = 0.f;
+    for (int w = 1; w < kScoreWaves; ++w) M = fmaxf(M, part_m[w][g]);
+    M = M == -INFINITY ? 0.f : M;  // nothing but -inf: the sum is 0
+    double z = 0.0;
 #pragma unroll
-    for (int blk = 0; blk < BPW; ++blk) s += exp_fast(xs[blk][g] - M[g]);
-    s = group_sum<64>(s);
-    if (lane == 0) part_s[wave][g] = s;
-  }
-  __syncthreads();
-  float thr[GB];
-  bool any_heavy = false;
-#pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    float z = 0.f;
-#pragma unroll
-    for (int w = 0; w < kScoreWaves; ++w) z += part_s[w][g];
-    thr[g] = heavy_logit_threshold(M[g], z);
-#pragma unroll
-    for (int blk = 0; blk < BPW; ++blk) any_heavy |= xs[blk][g] >= thr[g];
-  }
-  __syncthreads();       // part_s has been read
-  __shared__ HeavyTerms heavy[kScoreWaves];
-  if (__any(any_heavy)) {  // wave-uniform: this wave's sums again, the heavy terms with fp64 exponents
-    HeavyTerms* hv = &heavy[wave];
-    for (int done = 0, total = 1; done < total; done += kHeavyBatch) {  // usually one batch
-      total = 0;
-#pragma unroll
-      for (int g = 0; g < GB; ++g)
-#pragma unroll
-        for (int blk = 0; blk < BPW; ++blk) {
-          const unsigned long long b = __ballot(xs[blk][g] >= thr[g]);
-          const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
-          if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
-            const int64_t tok = wave_base + blk * 64 + cl * TPL + tq;
-            hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
-            hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + g) * D;
-            hv->m[e] = M[g];
-            hv->code[e] = g;
-          }
-          total += __popcll(b);
-        }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const int cnt = total - done < kHeavyBatch ? total - done : kHeavyBatch;
-      exact_terms<DT, D>(hv, cnt, p.K, p.q_last);
-#pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        double z = 0.0;
-        if (done == 0) {
-          float s = 0.f;
-#pragma unroll
-          for (int blk = 0; blk < BPW; ++blk) s += xs[blk][g] >= thr[g] ? 0.f : exp_fast(xs[blk][g] - M[g]);
-          z = (double)group_sum<64>(s);
-        } else {
-          z = (double)part_s[wave][g];
-        }
-        for (int e = 0; e < cnt; ++e) z += hv->code[e] == g ? hv->val[e] : 0.0;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (lane == 0) part_s[wave][g] = (float)z;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
+    for (int blk = 0; blk < BPW; ++blk) z += (double)exp_fast(xs[blk][g] - M);
+    z = group_sum_f64<64>(z);
+    if (lane == 0) part_s[wave][g] = z;
   }
   __syncthreads();
   if (threadIdx.x < GB) {
     const int g = threadIdx.x;
-    float m = part_m[0][g], s = 0.f;
+    float m = part_m[0][g];
+    double z = 0.0;
 #pragma unroll
     for (int w = 0; w < kScoreWaves; ++w) {
       m = fmaxf(m, part_m[w][g]);
-      s += part_s[w][g];
+      z += part_s[w][g];
     }
-    p.partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + blockIdx.x] = make_float2(m, s);
+    p.chunk_partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + blockIdx.x] = ChunkPartial{z, m, 0.f};
   }
 }
 
@@ -351,8 +294,8 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   // softmax weights of this lane's 4 heads: the sample's (M^, 1/Z^) for the filter, the exact (M, 1/Z)
   // for the scores; the row's filter threshold(s)
   float fM[4] = {0.f, 0.f, 0.f, 0.f}, fInv[4] = {0.f, 0.f, 0.f, 0.f}, ftau = 0.f;
-  // terms with an fp64 exponent (ScoreParams::heavy_thr): the passes that follow a sample stage; the one-sweep
-  // dense pass (SCORE_LOGITS) takes the thresholds from the chunk's own statistics, after its last block
+  // terms with an fp64 exponent (ScoreParams::heavy_thr): the passes that follow a sample stage.  (The one-sweep
+  // dense pass, SCORE_LOGITS, knows nothing about the row yet: exact_changes takes them once the partials are merged.)
   float hthr[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
   if (HEAVY && p.heavy_thr) {
 #pragma unroll
@@ -509,10 +452,8 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // The wave's heavy terms into z[r], r = its lanes' four heads.  mask(blk, a, r): the lanes whose logit is one; mx[r]: the
-  // maximum the lane's exponentials are relative to; shared: a row block's 16 lanes all take its terms, else each
-  // lane its own.
-  auto add_heavy = [&](double (&z)[4], const float (&mx)[4], auto mask, bool shared) {
+  // The wave's heavy terms (heavy_mask) into z[r], r = its lanes' four heads.
+  auto add_heavy = [&](double (&z)[4]) {
     HeavyTerms* hv = reinterpret_cast<HeavyTerms*>(buf);  // the wave's staging buffer is free after its last block
     static_assert(sizeof(HeavyTerms) <= sizeof(lds[0]), "heavy terms fit the staging buffer");
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -524,29 +465,29 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         for (int blk = 0; blk < BPW; ++blk)
 #pragma unroll
           for (int a = 0; a < NACC; ++a) {
-            const unsigned long long b = mask(blk, a, r);
+            const unsigned long long b = heavy_mask[wave][HEAVY ? blk : 0][a][r];
             const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
             if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
               const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
               hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
               hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + hbase + r) * D;
-              hv->m[e] = mx[r];
-              hv->code[e] = 4 * (shared ? j : lane) + r;
+              hv->m[e] = m[r];
+              hv->code[e] = 4 * lane + r;
             }
             total += __popcll(b);
           }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       const int cnt = total - done < kHeavyBatch ? total - done : kHeavyBatch;
-      exact_terms<DT_BF16, D>(hv, cnt, p.K, p.q_last);
+      exact_terms<D>(hv, cnt, p.K, p.q_last);
       for (int e = 0; e < cnt; ++e)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) z[r] += hv->code[e] == 4 * (shared ? j : lane) + r ? hv->val[e] : 0.0;
+        for (int r = 0; r < 4; ++r) z[r] += hv->code[e] == 4 * lane + r ? hv->val[e] : 0.0;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
   };
   if (HEAVY && seen_heavy) {
     double z[4] = {0.0, 0.0, 0.0, 0.0};
-    add_heavy(z, m, [&](int blk, int a, int r) { return heavy_mask[wave][blk][a][r]; }, false);
+    add_heavy(z);
 #pragma unroll
     for (int r = 0; r < 4; ++r) sum[r] += (float)z[r];
   }
@@ -567,15 +508,9 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         }
       }
     }
-    // softmax partial of the chunk, heavy terms as in score_kernel
-    __shared__ float s_M[16], s_thr[16];
-    auto merge = [&](int g, bool use_max) -> float {  // the chunk's value of head g from part[wave][row block][r]
-      float v = use_max ? -INFINITY : 0.f;
-      for (int w = 0; w < kScoreWaves; ++w)
-        for (int jj = 0; jj < 4; ++jj)
-          if ((4 * jj) % GPAD == (g / 4) * 4) v = use_max ? fmaxf(v, part[w][jj][g % 4].x) : v + part[w][jj][g % 4].y;
-      return v;
-    };
+    // softmax partial of the chunk: lanes -> row blocks of 16 -> workgroup
+    __shared__ double part_z[MODE == SCORE_LOGITS ? kScoreWaves : 1][4][4];
+    const int j0 = (hbase / 4), jstep = GPAD / 4;  // the row blocks that share this one's heads
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       float M = -INFINITY;
@@ -583,61 +518,38 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
       for (int blk = 0; blk < BPW; ++blk)
 #pragma unroll
         for (int a = 0; a < NACC; ++a) M = fmaxf(M, xs[KEEP ? blk : 0][a][r]);
-#pragma unroll
-      for (int o = 8; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+      M = group16_max(M);
       if (n == 0) part[wave][j][r].x = M;
     }
     __syncthreads();
-    if ((int)threadIdx.x < gb) s_M[threadIdx.x] = merge(threadIdx.x, true);
-    __syncthreads();
-    float M4[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      M4[r] = hbase + r < gb ? s_M[hbase + r] : 0.f;
-      float sm = 0.f;
+      float M = -INFINITY;
 #pragma unroll
-      for (int blk = 0; blk < BPW; ++blk)
+      for (int w = 0; w < kScoreWaves; ++w)
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) sm += exp_fast(xs[KEEP ? blk : 0][a][r] - M4[r]);
-      sm = group_sum<16>(sm);
-      if (n == 0) part[wave][j][r].y = sm;
+        for (int jj = 0; jj < 4; jj += jstep) M = fmaxf(M, part[w][j0 + jj][r].x);
+      M = M == -INFINITY ? 0.f : M;  // nothing but -inf (heads past the group among them): the sum is 0
+      double z = 0.0;
+#pragma unroll
+      for (int a = 0; a < NACC; ++a)
+#pragma unroll
+        for (int blk = 0; blk < BPW; ++blk) z += (double)exp_fast(xs[KEEP ? blk : 0][a][r] - M);
+      z = group_sum_f64<16>(z);
+      if (n == 0) part_z[wave][j][r] = z;
     }
     __syncthreads();
-    if ((int)threadIdx.x < gb) s_thr[threadIdx.x] = heavy_logit_threshold(s_M[threadIdx.x], merge(threadIdx.x, false));
-    __syncthreads();
-    bool any_heavy = false;
-    float thr[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      thr[r] = hbase + r < gb ? s_thr[hbase + r] : INFINITY;
-#pragma unroll
-      for (int blk = 0; blk < BPW; ++blk)
-#pragma unroll
-        for (int a = 0; a < NACC; ++a) any_heavy |= xs[KEEP ? blk : 0][a][r] >= thr[r];
+    if ((int)threadIdx.x < gb) {
+      const int g = threadIdx.x;
+      float M = -INFINITY;
+      double z = 0.0;
+      for (int w = 0; w < kScoreWaves; ++w)
+        for (int jj = 0; jj < 4; jj += jstep) {
+          M = fmaxf(M, part[w][g / 4 + jj][g % 4].x);
+          z += part_z[w][g / 4 + jj][g % 4];
+        }
+      p.chunk_partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + chunk] = ChunkPartial{z, M, 0.f};
     }
-    if (__any(any_heavy)) {  // wave-uniform: this wave's sums again, the heavy terms with fp64 exponents
-      double z[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float sm = 0.f;
-#pragma unroll
-        for (int blk = 0; blk < BPW; ++blk)
-#pragma unroll
-          for (int a = 0; a < NACC; ++a) {
-            const float x = xs[KEEP ? blk : 0][a][r];
-            sm += x >= thr[r] ? 0.f : exp_fast(x - M4[r]);
-          }
-        z[r] = (double)group_sum<16>(sm);
-      }
-      add_heavy(z, M4, [&](int blk, int a, int r) { return __ballot(xs[KEEP ? blk : 0][a][r] >= thr[r]); }, true);
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (n == 0) part[wave][j][r].y = (float)z[r];
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < gb)
-      p.partials[((int64_t)row * p.geo.G + p.g0 + threadIdx.x) * p.n_chunks + chunk] =
-          make_float2(s_M[threadIdx.x], merge(threadIdx.x, false));
     return;
   }
   if (MODE == SCORE_SCORES) {

@@ -414,21 +414,23 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
 // list's scores held in registers: thread t owns the quads t, t + 1024, ... of the row (4 consecutive tokens
 // each).  Latency bound (one workgroup per list, a chain of memory round trips and barriers), so it replaces the
 // launches of the general route below for rows of up to 24576 tokens (24 registers of scores per thread):
-// statistics + combine + top-k take 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 25; 9.5 + 4.5 + 15.3 and 11
-// for 2 rows of 4096; at 30000 tokens the two are even (46 us, 8 rows), beyond that several workgroups per
-// row win.
+// statistics + combine + top-k take 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 29; 9.5 + 4.5 + 15.3 and 14
+// for 2 rows of 4096 (the correction of the normalisers for heavy terms, 4 and 2 us of it, included); at 30000 tokens
+// the two are even (46 us, 8 rows, without it), beyond that several workgroups per row win.
 template <int DT, int NQ>
 __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParams p) {
   constexpr int N = 4 * NQ;
   __shared__ RegSelect sh;
   __shared__ RowStat s_stat[64];  // up to 64 heads per KV head
+  __shared__ float s_thr[64];
   __shared__ __align__(16) uint32_t bitmap[NQ * kTopkThreads * 4 / 32];
   const int tid = threadIdx.x, wave = tid >> 6;
   const int list = blockIdx.x;
   const int row = list / p.n_lists, gl = list % p.n_lists;
-  const int G = p.geo.G, S = p.S, W = p.W, k = p.k, L = (int)p.geo.L;
+  const RowGeom& geo = p.in.geo;
+  const int G = geo.G, S = p.S, W = p.W, k = p.k, L = (int)geo.L;
   const int g_lo = p.n_lists > 1 ? gl : 0, g_hi = p.n_lists > 1 ? gl + 1 : G;
-  const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
+  const int prob = row / geo.Hkv, c = row % geo.Hkv;
   int32_t* kept_row = p.kept_idx + (int64_t)row * (S + p.n_lists * k + W);
   int32_t* kept = kept_row + S + gl * k;
 
@@ -438,7 +440,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   }
   if (k == 0 && !p.scores) return;
   // the logits of HB heads at a time, the next ones in flight while the current ones are used; the first are asked for
-  // before the statistics are merged
+  // once a wave has done its part of the statistics
   constexpr int HB = NQ <= 2 ? 4 : NQ <= 4 ? 2 : 1;
   float4 x[2][HB][NQ];
   auto load_heads = [&](int g0, float4 (&dst)[HB][NQ]) {
@@ -448,17 +450,22 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
           const int tok = 4 * (u * kTopkThreads + tid);
-          if (tok < L) dst[h][u] = *reinterpret_cast<const float4*>(p.logits + logit_index(p.geo, p.n_chunks, p.chunk, row, g0 + h, tok));
+          if (tok < L) dst[h][u] = *reinterpret_cast<const float4*>(p.in.logits + logit_index(geo, p.in.n_chunks, p.in.chunk, row, g0 + h, tok));
         }
       }
   };
-  load_heads(g_lo, x[0]);
+  const float max0 = exact_maximum(p.in, row, g_lo, g_hi, 0);
   for (int g = g_lo + wave; g < g_hi; g += kTopkWaves) {  // one wave per head
-    const RowStat st = merge_partials_wave(p.partials + ((int64_t)row * G + g) * p.n_chunks, p.n_chunks);
-    if ((tid & 63) == 0) s_stat[g] = st;
+    const RowStat st = merge_partials_wave(p.in.partials + ((int64_t)row * G + g) * p.in.n_chunks, p.in.n_chunks);
+    if ((tid & 63) == 0) {
+      s_stat[g] = st;
+      s_thr[g] = heavy_logit_threshold(st.M, (float)st.Z);
+    }
   }
   for (int w = tid; w < (int)(sizeof(bitmap) / 4); w += kTopkThreads) bitmap[w] = 0u;
-  __syncthreads();
+  const bool changed = exact_changes<DT>(p.in, sh.exact, row, g_lo, g_hi, s_stat, s_thr, max0);
+  load_heads(g_lo, x[0]);
+  if (changed) exact_apply(sh.exact, g_lo, g_hi, s_stat);
 
   float v[N];
 #pragma unroll
@@ -526,7 +533,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   const int nb = sh.n_band, r = k - sh.n_above;
   bool general = nb > kMaxBand || r < 1 || r > nb;
   if (!general) {
-    refine_band<DT>(sh, nb, p.geo, p.q_last, p.K, p.pm, p.ks_problem, p.ks_head, p.ks_token, s_stat, prob, c, g_lo, g_hi);
+    refine_band<DT>(sh, nb, geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, g_lo, g_hi);
     if (tid == 0) sh.n_band = 0;  // now: 1 = the threshold lies strictly inside the band
     __syncthreads();
     for (int t = tid; t < nb; t += kTopkThreads) {
@@ -553,7 +560,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
 #pragma unroll
       for (int j = 0; j < N; ++j) x = j == i ? v[j] : x;
       if (x >= 0.f && x >= lo && x <= hi) {
-        x = refined_score<DT>(p.geo, p.q_last, p.K, p.pm, p.ks_problem, p.ks_head, p.ks_token, s_stat, prob, c, tok, g_lo, g_hi);
+        x = refined_score<DT>(geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, tok, g_lo, g_hi);
         if (out) out[tok] = x;
       }
 #pragma unroll
@@ -601,6 +608,26 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     __syncthreads();
   }
   bitmap_compact(bitmap, (L + 31) >> 5, 0, kept, k, sh.wave_tot);
+}
+
+// Longer rows: the same statistics, for the combine stage.
+template <int DT>
+__global__ __launch_bounds__(kTopkThreads) void row_stats_kernel(RowStatsParams p) {
+  __shared__ ExactSums sh;
+  __shared__ RowStat s_stat[64];
+  __shared__ float s_thr[64];
+  const int tid = threadIdx.x, row = blockIdx.x, G = p.in.geo.G;
+  for (int b = tid; b < kHistBins * p.n_lists; b += kTopkThreads) p.ghist[(int64_t)row * p.n_lists * kHistBins + b] = 0;
+  const float max0 = exact_maximum(p.in, row, 0, G, 0);
+  for (int g = tid >> 6; g < G; g += kTopkWaves) {
+    const RowStat st = merge_partials_wave(p.in.partials + ((int64_t)row * G + g) * p.in.n_chunks, p.in.n_chunks);
+    if ((tid & 63) == 0) {
+      s_stat[g] = st;
+      s_thr[g] = heavy_logit_threshold(st.M, (float)st.Z);
+    }
+  }
+  if (exact_changes<DT>(p.in, sh, row, 0, G, s_stat, s_thr, max0)) exact_apply(sh, 0, G, s_stat);
+  if (tid < G) p.stats[(int64_t)row * G + tid] = s_stat[tid];
 }
 
 // ---- gather -----------------------------------------------------------------------------------
@@ -667,11 +694,11 @@ hipError_t launch_topk(const TopkParams& p0, hipStream_t s) {
 }
 
 hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s) {
-  if (p.geo.L > kRowSelectMax || p.geo.G > 64) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(p.geo.n_problems * p.geo.Hkv * p.n_lists));
-  const int quads = (int)((p.geo.L + 4 * kTopkThreads - 1) / (4 * kTopkThreads));  // per thread
+  if (p.in.geo.L > kRowSelectMax || p.in.geo.G > 64) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(p.in.geo.n_problems * p.in.geo.Hkv * p.n_lists));
+  const int quads = (int)((p.in.geo.L + 4 * kTopkThreads - 1) / (4 * kTopkThreads));  // per thread
 #define SAGEKV_LAUNCH(NQ)                                                                                       \
-  if (p.geo.dtype == DT_BF16)                                                                                   \
+  if (p.in.geo.dtype == DT_BF16)                                                                                   \
     hipLaunchKernelGGL((row_select_kernel<DT_BF16, NQ>), grid, dim3(kTopkThreads), 0, s, p);                    \
   else                                                                                                          \
     hipLaunchKernelGGL((row_select_kernel<DT_F32, NQ>), grid, dim3(kTopkThreads), 0, s, p)
@@ -685,6 +712,16 @@ hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s) {
     SAGEKV_LAUNCH(6);
   }
 #undef SAGEKV_LAUNCH
+  return hipGetLastError();
+}
+
+hipError_t launch_row_stats(const RowStatsParams& p, hipStream_t s) {
+  if (p.in.geo.G > 64) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(p.in.geo.n_problems * p.in.geo.Hkv));
+  if (p.in.geo.dtype == DT_BF16)
+    hipLaunchKernelGGL(row_stats_kernel<DT_BF16>, grid, dim3(kTopkThreads), 0, s, p);
+  else
+    hipLaunchKernelGGL(row_stats_kernel<DT_F32>, grid, dim3(kTopkThreads), 0, s, p);
   return hipGetLastError();
 }
 

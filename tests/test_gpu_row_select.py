@@ -12,12 +12,12 @@ BF16, F32 = synth.BF16, synth.F32
 DENSE = 1
 
 
-def parity(ref, dtype, head_mode, q, K, V, S, W, k):
+def parity(ref, dtype, head_mode, q, K, V, S, W, k, scores=(False, True)):
     """Kept sets of the dense path, with and without the scores written out, against the oracle's."""
     G = q.shape[1] // K.shape[1]
     lists = G if head_mode else 1
     Kc, _, kept, s = ref.select(dtype, head_mode, q, K, V, S, W, k, want_scores=True)
-    for want_scores in (False, True):
+    for want_scores in scores:
         out = gu.gpu_select(dtype, q, K, V, S, W, k, want_scores=want_scores, flags=DENSE, head_mode=head_mode)
         exempt = 0
         for li in range(lists):
@@ -70,3 +70,66 @@ def test_many_heavy_terms_in_one_chunk(ref, dtype, flags, L):
     assert (top[:, :32].sum(1) > 0.3 * G).all()  # a few tokens hold much of the mass
     out = gu.gpu_select(dtype, q, K, V, S, W, k, want_scores=False, flags=flags)
     assert gu.check_kept(out["kept"], kept, s[:, :, 0], S, W, k) == 0
+
+
+def offset_case(seed, P, Hq, Hkv, d, L, dtype, offset, scale=1.0):
+    """q, K, V with logits of about N(offset, scale): every key has a common component, as trained models' keys do."""
+    q, K, V = rand_case(seed, P, Hq, Hkv, d, L, dtype)
+    G = Hq // Hkv
+    q64 = scale * synth.to_f64(q, dtype)
+    Q = q64.reshape(P, Hkv, G, d)
+    gram = Q @ Q.transpose(0, 1, 3, 2)
+    u = np.linalg.solve(gram, np.full((P, Hkv, G, 1), offset * np.sqrt(d))).transpose(0, 1, 3, 2) @ Q  # q . u / sqrt(d) = offset
+    return synth.round_to_dtype(q64, dtype), synth.round_to_dtype(synth.to_f64(K, dtype) + u, dtype), V
+
+
+@pytest.mark.parametrize("dtype,L", [(BF16, 4090), (BF16, 9001), (F32, 6000), (BF16, 30000), (F32, 25001)])
+@pytest.mark.parametrize("offset,scale", [(-30.0, 1.0), (25.0, 2.0), (-200.0, 1.0)])
+def test_logits_around_an_offset(ref, dtype, L, offset, scale):
+    """A head's exact softmax terms are those that are heavy for the row.  At -200 every token is: more than a wave lists at
+    a time."""
+    q, K, V = offset_case(L, 1, 8, 2, 64, L, dtype, offset, scale)
+    # score values: an fp32 logit of magnitude 200 is off by up to 200 x 2.5e-7 = 5e-5, five times what check_scores allows
+    parity(ref, dtype, 0, q, K, V, 4, 64, L // 5, scores=(False, True) if abs(offset) < 40 else (False,))
+
+
+def test_more_heavy_terms_than_are_taken_exactly(ref):
+    """Flat logits around -400 over 40000 tokens: the rest keeps its fp32 terms (one list per query head: a head's
+    normaliser does not change the order of its own tokens)."""
+    S, W, k, L = 4, 64, 500, 40000
+    q, K, V = offset_case(11, 1, 4, 1, 64, L, BF16, -400.0)
+    Kc, _, kept, s = ref.select(BF16, 1, q, K, V, S, W, k, want_scores=True)
+    out = gu.gpu_select(BF16, q, K, V, S, W, k, want_scores=False, flags=DENSE, head_mode=1)
+    for li in range(4):
+        cut = lambda a: np.concatenate([a[..., :S], a[..., S + li * k:S + (li + 1) * k], a[..., S + 4 * k:]], axis=-1)
+        gu.check_kept(cut(out["kept"]), cut(kept), s[:, :, li], S, W, k)
+
+
+def test_an_offset_costs_a_dense_pass_little():
+    """256 rows x 8192 tokens x 4 heads, logits N(-30, 1) against N(0, 1): 0.4 % against 0 % of the terms are heavy for their
+    rows, 1.02 times the time.  (Heavy by their share of a chunk, a third of them would be: 3.1 times.)"""
+    import torch
+
+    import paper_2503_08879_amd as sk
+
+    P, Hq, Hkv, d, L, S, W, k = 32, 32, 8, 128, 8192, 4, 256, 1788
+    times = []
+    for offset in (0.0, -30.0):
+        q1, K1, V1 = offset_case(3, 1, Hq, Hkv, d, L, BF16, offset)
+        q, K, V = (synth.host_to_torch(x, BF16).repeat(P, *[1] * (x.ndim - 1)) for x in (q1, K1, V1))
+        desc = sk.select_desc(q, K, V, S, W, k)
+        ws = torch.empty(sk.sagekv_select_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+        Kc = torch.empty((P, Hkv, S + k + W, d), dtype=K.dtype, device="cuda")
+        Vc = torch.empty_like(Kc)
+        kept = torch.empty((P, Hkv, S + k + W), dtype=torch.int32, device="cuda")
+        best = 1e9
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                sk.sagekv_select(desc, q, K, V, Kc, Vc, kept, None, ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) / 4)
+        times.append(best)
+    assert times[1] < 1.5 * times[0], times
