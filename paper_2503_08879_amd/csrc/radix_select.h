@@ -413,7 +413,6 @@ struct RegSelect {
   union {
     int hist[2][kHistBins];
     double term[kMaxBand];  // refine_band: fp64 terms of a batch of (member, head)
-    ExactSums exact;        // row_select_kernel, before anything is selected
   };
   int wave_tot[kTopkWaves], pick[2];
   int red_min[kTopkWaves], red_max[kTopkWaves];

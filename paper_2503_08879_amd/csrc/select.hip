@@ -420,7 +420,11 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
 template <int DT, int NQ>
 __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParams p) {
   constexpr int N = 4 * NQ;
-  __shared__ RegSelect sh;
+  __shared__ union {
+    ExactSums exact;  // first the statistics,
+    RegSelect sel;    // then the selection
+  } sh_u;
+  RegSelect& sh = sh_u.sel;
   __shared__ RowStat s_stat[64];  // up to 64 heads per KV head
   __shared__ float s_thr[64];
   __shared__ __align__(16) uint32_t bitmap[NQ * kTopkThreads * 4 / 32];
@@ -463,9 +467,9 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     }
   }
   for (int w = tid; w < (int)(sizeof(bitmap) / 4); w += kTopkThreads) bitmap[w] = 0u;
-  const bool changed = exact_changes<DT>(p.in, sh.exact, row, g_lo, g_hi, s_stat, s_thr, max0);
+  const bool changed = exact_changes<DT>(p.in, sh_u.exact, row, g_lo, g_hi, s_stat, s_thr, max0);
   load_heads(g_lo, x[0]);
-  if (changed) exact_apply(sh.exact, g_lo, g_hi, s_stat);
+  if (changed) exact_apply(sh_u.exact, g_lo, g_hi, s_stat);
 
   float v[N];
 #pragma unroll
