@@ -452,30 +452,34 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // The wave's heavy terms (heavy_mask) into z[r], r = its lanes' four heads.
+  // The wave's heavy terms (heavy_mask) into z[r], r = its lanes' four heads.  A loop over the masks that hold any: one body
+  // per mask, 64 of them with 16 heads, takes 184 to 256 registers and spills (the pass over 64 rows x 128K tokens
+  // of head_dim 64: 16 heads 413 us so, 347 with the loop; 8 heads 311 and 265; 4 heads 232 and 234, over 40000 tokens 108
+  // and 106).
   auto add_heavy = [&](double (&z)[4]) {
     HeavyTerms* hv = reinterpret_cast<HeavyTerms*>(buf);  // the wave's staging buffer is free after its last block
     static_assert(sizeof(HeavyTerms) <= sizeof(lds[0]), "heavy terms fit the staging buffer");
+    constexpr int kMasks = BPW * NACC * 4;  // mask i: block i / (4 NACC), accumulator i / 4 % NACC, register i % 4
+    static_assert(kMasks <= 64, "a mask per lane");
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const unsigned long long mine = lane < kMasks ? (&heavy_mask[HEAVY ? wave : 0][0][0][0])[lane] : 0ull;
     for (int done = 0, total = 1; done < total; done += kHeavyBatch) {  // usually one batch
       total = 0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int blk = 0; blk < BPW; ++blk)
-#pragma unroll
-          for (int a = 0; a < NACC; ++a) {
-            const unsigned long long b = heavy_mask[wave][HEAVY ? blk : 0][a][r];
-            const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
-            if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
-              const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
-              hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
-              hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + hbase + r) * D;
-              hv->m[e] = m[r];
-              hv->code[e] = 4 * lane + r;
-            }
-            total += __popcll(b);
-          }
+#pragma unroll 1
+      for (unsigned long long todo = __ballot(mine != 0ull); todo; todo &= todo - 1) {
+        const int i = __ffsll(todo) - 1, blk = i / (NACC * 4), a = i / 4 % NACC, r = i % 4;
+        const unsigned long long b = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(mine >> 32), i) << 32 |
+                                     (uint32_t)__builtin_amdgcn_readlane((uint32_t)mine, i);
+        const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
+        if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
+          const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
+          hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
+          hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + hbase + r) * D;
+          hv->m[e] = r == 0 ? m[0] : r == 1 ? m[1] : r == 2 ? m[2] : m[3];
+          hv->code[e] = 4 * lane + r;
+        }
+        total += __popcll(b);
+      }
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       const int cnt = total - done < kHeavyBatch ? total - done : kHeavyBatch;
       exact_terms<D>(hv, cnt, p.K, p.q_last);
