@@ -11,6 +11,8 @@
 // L2: measured ~8x slower than two launches.)  The appended token is read from k_new / v_new
 // directly and stored to its slot by the workgroup that owns it, so append and attention are
 // one launch.
+#include <type_traits>
+
 #include "device_utils.h"
 #include "kernels.h"
 
@@ -316,19 +318,22 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeParams p, int g0)
     float M = s_ml[0][g].x;
 #pragma unroll
     for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, s_ml[w][g].x);
-    float a = 0.f, ls = 0.f;
+    // fp32 caches: the waves' parts are added in fp64, so that a row's error does not grow with their number (short
+    // whole rows of 16 waves: 1.25e-7 of the result with fp32 sums, 0.8e-7 so; two slices of four waves had 1.1e-7)
+    typedef typename std::conditional<DT == DT_F32, double, float>::type Sum;
+    Sum a = 0, ls = 0;
 #pragma unroll
     for (int w = 0; w < kDecWaves; ++w) {
       const float2 ml = s_ml[w][g];
       const float f = (ml.x == -INFINITY) ? 0.f : exp_fast(ml.x - M);
-      a += s_acc[w][g][j] * f;
-      ls += ml.y * f;
+      a += (Sum)s_acc[w][g][j] * f;
+      ls += (Sum)ml.y * f;
     }
     if (single) {
-      p.out[((int64_t)prob * p.Hq + c * p.G + g0 + g) * D + j] = a / ls;
+      p.out[((int64_t)prob * p.Hq + c * p.G + g0 + g) * D + j] = (float)(a / ls);
     } else {
-      pa[(int64_t)g * D + j] = a;
-      if (j == 0) pml[g] = make_float2(M, ls);
+      pa[(int64_t)g * D + j] = (float)a;
+      if (j == 0) pml[g] = make_float2(M, (float)ls);
     }
   }
   finish_row(p, sg);

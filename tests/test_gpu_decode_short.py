@@ -81,3 +81,27 @@ def test_a_non_finite_token_leaves_with_the_step_that_replaces_it(ref, n, slot, 
         sk.sagekv_decode_step_ring(desc, *ins, Kd, Vd, state, out, ws)
     assert state.tolist() == [slot + 1, 0]
     assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[BF16]
+
+
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 8])
+def test_whole_short_fp32_rows_keep_their_precision(ref, G):
+    """A row of 256 tokens in one workgroup of 8 or 16 waves has as many parts to merge.  Each part is good to about 0.8e-7 (2-norm
+    over the outputs), which is what two slices of four waves each came to 1.1e-7 with; merged in fp32, 16 waves are at
+    1.25e-7 and 8 at 1.13e-7."""
+    import torch
+
+    import paper_2503_08879_amd as sk
+
+    P, Hkv, d, n = 8, 2, 64, 256
+    rng = np.random.default_rng(G)
+    num = den = 0.0
+    for _ in range(4):
+        q, K, V = (rng.standard_normal(s, dtype=np.float32) for s in ((P, G * Hkv, d), (P, Hkv, n, d), (P, Hkv, n, d)))
+        desc, ws, out = gu.gpu_decode_setup(F32, P, G * Hkv, Hkv, d, 0, 0, n, n)
+        sk.sagekv_decode_attn(desc, *(torch.from_numpy(x).cuda() for x in (q, K, V)), n, out, ws)
+        l = np.matmul(q.reshape(P, Hkv, G, d).astype(np.float64), K.astype(np.float64).transpose(0, 1, 3, 2)) / 8.0
+        w = np.exp(l - l.max(-1, keepdims=True))
+        want = np.matmul(w / w.sum(-1, keepdims=True), V.astype(np.float64)).reshape(P, G * Hkv, d)
+        num += float(((out.cpu().numpy() - want) ** 2).sum())
+        den += float((want ** 2).sum())
+    assert (num / den) ** 0.5 <= 1.0e-7
