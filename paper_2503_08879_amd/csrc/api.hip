@@ -236,10 +236,11 @@ struct DecodeLayout {
 
 // Splits per row.  With about one row per CU or more, a single 8-wave workgroup per row fills
 // the chip and needs no merge launch; otherwise enough workgroups to fill 256 CUs several times
-// over, at least 128 tokens each.  Rows that one workgroup takes in a single pass are not worth the merge launch:
-// bf16 up to 256 tokens (8 rows x 4 heads x 256 tokens 10.3 us split, 8.4 whole; 4 rows x 7 heads 9.6 and 8.2; at 512
-// tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 256 tokens of head_dim 64 (2 rows x 2 heads 11.4 and 8.5; at 512
-// tokens 9.8 and 12.0; 8 rows x 4 heads x 512 tokens of head_dim 128 22 and 42).
+// over, at least 128 tokens each.  Short rows are not worth the merge launch:
+// bf16 up to 256 tokens, a single pass (8 rows x 4 heads x 256 tokens 10.3 us split, 8.4 whole; 4 rows x 7 heads 9.6 and 8.2; at
+// 512 tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 256 tokens of head_dim 64 (8 rows x 256 tokens, one to eight heads: 11.6,
+// 12.5, 15, 17, 20, 22, -, 27 us split, 8.4, 8.5, 9.7, 12, 14, 16, -, 20 whole; 160 rows x 2, 4, 8 heads 14, 19, 50 and 8.8, 13.4, 21;
+// 2 rows x 2 heads x 512 tokens 9.8 and 12.0; 8 rows x 4 heads x 512 tokens of head_dim 128 22 and 42 with 16 waves).
 int splits_for(int rows, int len, int dtype, int head_dim) {
   if (rows >= kWholeRows) return 1;
   if (dtype == SAGEKV_BF16 ? len <= 256 : (int64_t)len * head_dim <= 256 * 64) return 1;

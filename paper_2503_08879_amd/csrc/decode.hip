@@ -853,14 +853,14 @@ template <int DT, int D>
 hipError_t launch_decode_g(const DecodeParams& p, int g0, int gb, dim3 grid, hipStream_t s) {
   const bool single = p.n_splits == 1;  // one workgroup per row: use a big one
   switch (gb) {
+// (4 heads and more spill in 16 waves of 128 registers: 256 rows x 4096 tokens x 4 heads of head_dim 64 took 247 us in
+// them, 127 in 8 waves; 256 rows x 192 tokens 21 and 10.7; 3 heads fit)
 #define SAGEKV_CASE(N)                                                                               \
   case N:                                                                                            \
     if (!single)                                                                                     \
       hipLaunchKernelGGL((decode_kernel<DT, D, N, 4>), grid, dim3(256), 0, s, p, g0);                \
-    else if (N <= 4)                                                                                 \
-      hipLaunchKernelGGL((decode_kernel<DT, D, N, 16>), grid, dim3(1024), 0, s, p, g0);              \
     else                                                                                             \
-      hipLaunchKernelGGL((decode_kernel<DT, D, N, 8>), grid, dim3(512), 0, s, p, g0);                \
+      hipLaunchKernelGGL((decode_kernel<DT, D, N, (N <= 3 ? 16 : 8)>), grid, dim3(N <= 3 ? 1024 : 512), 0, s, p, g0); \
     break;
     SAGEKV_CASE(1) SAGEKV_CASE(2) SAGEKV_CASE(3) SAGEKV_CASE(4)
     SAGEKV_CASE(5) SAGEKV_CASE(6) SAGEKV_CASE(7) SAGEKV_CASE(8)
