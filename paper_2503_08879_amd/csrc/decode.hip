@@ -103,9 +103,10 @@ struct BlockSource {
 };
 
 // Called once per row of a launch whose workgroups own whole rows: the last row to finish advances
-// the device-side count (for sliced rows the merge launch does).  Every workgroup has read ring[0] before it gets here (the
-// value went into its addresses), so the store cannot overtake a reader; the next launch on the
-// stream sees it.  Only the counter itself is exchanged between workgroups: relaxed atomics, no
+// the device-side count (for sliced rows the merge launch does).  Every wave has read ring[0] and used the value (in its
+// addresses, or, where the slot is late, in the slot's comparison) before the barriers that come before this, so the store
+// cannot overtake a reader; a launch without a new token uses it only here, in the one thread that stores.  The next launch
+// on the stream sees it.  Only the counter itself is exchanged between workgroups: relaxed atomics, no
 // cache-wide fence.
 __device__ __forceinline__ void row_done(const DecodeParams& p, const StepGeom& sg) {
   if (!p.ring || !p.ring_advance) return;

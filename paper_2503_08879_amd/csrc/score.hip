@@ -885,7 +885,7 @@ hipError_t launch_score(const ScoreParams& p0, ScoreMode mode, hipStream_t s) {
   const int rows = p0.geo.n_problems * p0.geo.Hkv;
   const bool bf16 = p0.geo.dtype == DT_BF16;
   if (mode == SCORE_FILTER || (!bf16 && (mode != SCORE_LOGITS || p0.gate.row_flag))) return hipErrorInvalidValue;
-  // partials only and scores: whole kScoreChunk chunks, whatever the first pass used
+  // scores: whole kScoreChunk chunks, whatever the first pass used; the others p.chunk tokens per workgroup
   const unsigned nx = mode == SCORE_SCORES ? (unsigned)((p0.geo.L + kScoreChunk - 1) / kScoreChunk) : (unsigned)p0.n_chunks;
   dim3 grid(nx, (unsigned)(p0.gate.row_flag && rows > kGatedRowBlocks ? kGatedRowBlocks : rows));
   const int per_launch = bf16 ? 16 : max_group_per_launch();

@@ -16,6 +16,7 @@ BF16 = synth.BF16
     (8, 2, 128, 65536, (1, 900, 1500, 1900, 4500, 6000), 0),   # 4 heads: 2 to 14 thousand candidates
     (16, 2, 64, 65537, (1000, 1800, 5000), 0),                 # 8 heads
     (12, 1, 128, 50001, (700, 1500, 3000), 0),                 # 12 heads: records padded to 16
+    (16, 1, 64, 120001, (1000, 3000), 0),                      # 16 heads, a sample of more than 9 items per thread
     (4, 1, 64, 200000, (9000,), 0),                            # more than 12288 expected
     (7, 1, 128, 65536, (1, 300, 1500), 1),                     # per-query lists
 ])

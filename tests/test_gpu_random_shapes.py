@@ -12,7 +12,8 @@ from tests.test_gpu_paged import paged_case
 pytestmark = pytest.mark.gpu
 BF16, F32 = synth.BF16, synth.F32
 
-# lengths that straddle the 64-token block, the 1024-token score chunk and the 4096-token combine chunk
+# lengths that straddle the 64-token block, the score chunks and the 4096-token combine chunk.  (With as few rows as here a chunk
+# holds 256 tokens; test_gpu_score_chunks has the calls that are large enough for 512 and 1024.)
 EDGE_L = [65, 127, 128, 129, 1023, 1024, 1025, 2049, 4095, 4096, 4097, 8191, 12289]
 
 
