@@ -111,9 +111,9 @@ struct SelectLayout {
   // small: the pre-filtered path applies to the descriptor; rows it cannot certify (and calls that
   // ask for every score) take the two-sweep dense path, which needs no logit scratch.
   bool small;
-  size_t logits, scores, partials, stats, ghist, total;
+  size_t logits, scores, partials /* small: the chunks' lines */, stats, ghist, total;
   // pre-filtered path
-  size_t samp_logit, samp_stats, heavy_thr, samp_tau, list_info, cand_count, ovf_count, cand_idx, cand_logit, cand_score, cand_pos,
+  size_t samp_logit, samp_stats, heavy_thr, samp_tau, list_info, ovf_count, cand_idx, cand_logit, cand_score, cand_pos,
       row_fail, n_fail;
   int64_t slots_per_row, cs_pitch;
   FastPlan fast;
@@ -172,7 +172,7 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
   };
   const size_t rows = (size_t)l.rows;
   l.logits = take(l.small ? 0 : rows * l.n_chunks * l.G * l.chunk * sizeof(float));
-  l.partials = take(rows * l.G * l.n_chunks * (l.small ? sizeof(float2) : sizeof(ChunkPartial)));
+  l.partials = take(rows * l.n_chunks * (l.small ? chunk_line_words(l.G) * sizeof(float) : l.G * sizeof(ChunkPartial)));
   l.stats = take(rows * l.G * sizeof(RowStat));
   l.ghist = take(rows * l.n_lists * kHistBins * sizeof(int));
   bool cs_in_scores = false;
@@ -184,8 +184,7 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
     l.heavy_thr = take(rows * l.G * sizeof(float));
     l.samp_tau = take(rows * l.n_lists * sizeof(float));
     l.list_info = take(rows * l.n_lists * sizeof(float2));
-    l.slots_per_row = (int64_t)l.n_chunks * f.cap_c + f.cap;
-    l.cand_count = take(rows * l.n_chunks * sizeof(int));
+    l.slots_per_row = ((int64_t)l.n_chunks * f.cap_c + f.cap + 31) / 32 * 32;  // a chunk's slots (cap_c >= 32) are whole lines
     l.ovf_count = take(rows * sizeof(int));
     l.cand_idx = take(rows * l.slots_per_row * sizeof(int32_t));
     l.cand_logit = take(rows * l.slots_per_row * f.Gs * sizeof(float));
@@ -469,7 +468,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
 
   float* scores = scores_out ? scores_out : (float*)(ws + l.scores);
   const int64_t pitch = scores_out ? d->L : l.Lp;
-  float2* partials = (float2*)(ws + l.partials);
+  float* lines = (float*)(ws + l.partials);
   RowStat* stats = (RowStat*)(ws + l.stats);
   int* ghist = (int*)(ws + l.ghist);
   const float scale = (float)(1.0 / sqrt((double)d->head_dim));
@@ -486,7 +485,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
   sp.ks_token = d->k_stride_token;
   sp.pm = pm;
   sp.logits = (float*)(ws + l.logits);
-  sp.partials = partials;
+  sp.lines = lines;
   sp.chunk_partials = (ChunkPartial*)(ws + l.partials);
   sp.n_chunks = l.n_chunks;
   sp.chunk = l.chunk;
@@ -501,7 +500,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
   sp.n_lists = l.n_lists;
 
   StatsParams tp = {};
-  tp.partials = partials;
+  tp.lines = lines;
   tp.stats = stats;
   tp.ghist = ghist;
   tp.G = l.G;
@@ -581,7 +580,6 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     ScoreParams fp = sp;
     fp.filt.samp_stats = samp_stats;
     fp.filt.samp_tau = samp_tau;
-    fp.filt.cand_count = (int*)(ws + l.cand_count);
     fp.filt.ovf_count = (int*)(ws + l.ovf_count);
     fp.filt.cand_idx = (int32_t*)(ws + l.cand_idx);
     fp.filt.cand_logit = (float*)(ws + l.cand_logit);
@@ -599,12 +597,11 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
 
     TopkCandParams cp = {};
     cp.geo = geo;
-    cp.partials = partials;
+    cp.lines = lines;
     cp.stats = stats;
     cp.samp_stats = samp_stats;
     cp.samp_tau = samp_tau;
     cp.ghist = ghist;
-    cp.cand_count = fp.filt.cand_count;
     cp.cand_idx = fp.filt.cand_idx;
     cp.cand_logit = fp.filt.cand_logit;
     cp.cap_c = f.cap_c;

@@ -115,6 +115,15 @@ __device__ __forceinline__ double swap16_f64(double v) {
   const uint32_t l = odd ? lo[0] : lo[1], h = odd ? hi[0] : hi[1];
   return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
 }
+// v of this lane + v of lane ^ 16, lane ^ 32
+__device__ __forceinline__ float swap16_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap32_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 template <int LANES>
 __device__ __forceinline__ double group_sum_f64(double v) {
   static_assert(LANES == 16 || LANES == 32 || LANES == 64, "");

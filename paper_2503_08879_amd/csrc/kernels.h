@@ -21,6 +21,12 @@ struct ChunkPartial {
   float max, unused;
 };
 
+// What the filtering and partials passes leave of a score chunk, one line of memory per (row, chunk): the softmax partials
+// (max, sum exp(x - max)) of the G <= 16 heads, float2 each, and in the line's last word the number of candidates the chunk kept.
+// One workgroup writes whole lines only: lines put together by several workgroups, each on its own XCD with its own L2,
+// reach HBM as partial writes, which hold up the stream of reads out of all proportion to their bytes.
+__host__ __device__ constexpr int chunk_line_words(int G) { return G <= 15 ? 32 : 64; }
+
 constexpr int kHistBins = 2048;      // first radix digit: key bits 30..20
 constexpr int kScoreChunk = 1024;    // most tokens one score workgroup covers (256, 512 or 1024, see score_chunk)
 constexpr int kWholeRows = 192;      // decode: from so many rows on, every row is one workgroup's
@@ -124,8 +130,8 @@ struct FilterParams {
   // Candidate records (token index + exact fp32 logits of the Gs heads).  Each score workgroup owns
   // cap_c slots for its chunk (an LDS counter hands them out: no global atomics); a chunk that keeps
   // more spills into the row's overflow pool of cap_o slots through one global counter per row.
-  // Row r: slots [r * slots_per_row, +n_chunks * cap_c) by chunk, then cap_o overflow slots.
-  int* cand_count;           // [rows][n_chunks]  tokens each chunk kept (may exceed cap_c: the rest overflowed)
+  // Row r: slots [r * slots_per_row, +n_chunks * cap_c) by chunk, then cap_o overflow slots.  A chunk's count of kept
+  // tokens (may exceed cap_c: the rest overflowed) goes into its line, see chunk_line_words.
   int* ovf_count;            // [rows]            tokens sent to the overflow pool (may exceed cap_o: dropped,
                              //                   the row then has more candidates than planned and is redone)
   int32_t* cand_idx;         // [rows][slots_per_row]
@@ -158,8 +164,8 @@ struct ScoreParams {
   // is off by as much; two heads' errors differ, and that can reorder group-sum scores a few 1e-6 apart.
   const float* heavy_thr;
   float* logits;                          // SCORE_LOGITS: [rows][n_chunks][G][chunk]
-  float2* partials;                       // [rows][G][n_chunks]  (max, sum exp(x - max)); SCORE_LOGITS:
-  ChunkPartial* chunk_partials;           // the same, more precisely and without fp64 exponents (see exact_changes)
+  float* lines;                           // [rows][n_chunks][chunk_line_words]  softmax partials and candidate count; SCORE_LOGITS:
+  ChunkPartial* chunk_partials;           // [rows][G][n_chunks], the partials more precisely and without fp64 exponents (see exact_changes)
   int n_chunks;
   int chunk;  // tokens a workgroup covers (SCORE_SCORES: always kScoreChunk)
   int g0;  // first head of the group handled by this launch
@@ -174,7 +180,7 @@ struct ScoreParams {
 };
 
 struct StatsParams {
-  const float2* partials;
+  const float* lines;  // [rows][n_chunks][chunk_line_words]
   RowStat* stats;  // [rows][G]
   int* ghist;      // [rows * n_lists][kHistBins], zeroed here (nullable)
   int G, n_chunks;
@@ -285,13 +291,12 @@ __host__ __device__ inline int64_t sample_token(const SampleParams& p, int b, in
 // Final selection of the fast path, on the candidate list of each row.
 struct TopkCandParams {
   RowGeom geo;
-  const float2* partials;    // [rows][G][n_chunks] exact softmax partials of the filtering pass
+  const float* lines;        // [rows][n_chunks][chunk_line_words]: exact softmax partials and candidate counts of the filtering pass
   RowStat* stats;            // out [rows][G]: exact (M, Z), merged here in fp64
   const float2* samp_stats;  // sample statistics and thresholds, for the bound on a dropped token's score
   const float* samp_tau;
   int* ghist;                // [rows * n_lists][kHistBins]: zeroed here for the dense stages that may follow
-  const int* cand_count;     // see FilterParams
-  const int32_t* cand_idx;
+  const int32_t* cand_idx;   // see FilterParams
   const float* cand_logit;
   int cap_c, cap_o;
   int64_t slots_per_row;

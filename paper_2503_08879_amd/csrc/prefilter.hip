@@ -250,7 +250,7 @@ struct CandShared {
 __device__ __forceinline__ void exact_stats(const TopkCandParams& p, CandShared& s, int row) {
   const int g = threadIdx.x >> 6, G = p.geo.G;
   if (g >= G) return;
-  const RowStat st = merge_partials_wave(p.partials + ((int64_t)row * G + g) * p.n_chunks, p.n_chunks);
+  const RowStat st = merge_partials_wave(p.lines + (int64_t)row * p.n_chunks * chunk_line_words(G) + 2 * g, chunk_line_words(G), p.n_chunks);
   if ((threadIdx.x & 63) == 0) {
     s.stat[g] = st;
     s.sM[g] = st.M;
@@ -265,8 +265,8 @@ __device__ __forceinline__ void exact_stats(const TopkCandParams& p, CandShared&
 // Candidates per score chunk -> offsets of a dense list (s.chunk_off): the chunks' own slots first, the row's overflow pool
 // behind them.  Returns how many there are; -1 (workgroup-uniform): far more than planned, or fewer than k.
 __device__ __forceinline__ int candidate_offsets(const TopkCandParams& p, CandShared& s, int row) {
-  const int tid = threadIdx.x;
-  const int raw = tid < p.n_chunks ? p.cand_count[(int64_t)row * p.n_chunks + tid] : 0;
+  const int tid = threadIdx.x, words = chunk_line_words(p.geo.G);
+  const int raw = tid < p.n_chunks ? __float_as_int(p.lines[((int64_t)row * p.n_chunks + tid) * words + words - 1]) : 0;
   const int v = raw < p.cap_c ? raw : p.cap_c;
   int tot, n_all;
   const int incl = block_scan_incl<kTopkThreads>(v, s.rs.wave_tot, &tot);

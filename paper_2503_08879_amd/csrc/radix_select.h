@@ -27,17 +27,17 @@ __device__ __forceinline__ int64_t logit_index(const RowGeom& geo, int n_chunks,
   return ((((int64_t)row * n_chunks + chunk) * geo.G + g) << shift) + (tok - (chunk << shift));
 }
 
-// Exact softmax statistics of one head of a row from its per-chunk partials (max, sum exp(x - max)):
+// Exact softmax statistics of one head of a row from its per-chunk partials (max, sum exp(x - max)), `stride` floats apart:
 // M = overall maximum of the fp32 logits, Z = sum_i exp(l_i - M) combined in fp64.  Called by all 64
 // lanes of a wave; every lane gets the result.
-__device__ inline RowStat merge_partials_wave(const float2* pr, int n_chunks) {
+__device__ inline RowStat merge_partials_wave(const float* pr, int stride, int n_chunks) {
   const int lane = threadIdx.x & 63;
   float M = -INFINITY;
-  for (int i = lane; i < n_chunks; i += 64) M = fmaxf(M, pr[i].x);
+  for (int i = lane; i < n_chunks; i += 64) M = fmaxf(M, pr[(int64_t)i * stride]);
   M = wave_max(M);
   double z = 0.0;
   for (int i = lane; i < n_chunks; i += 64) {
-    const float2 v = pr[i];
+    const float2 v = *reinterpret_cast<const float2*>(pr + (int64_t)i * stride);
     z += (double)v.y * exp((double)v.x - (double)M);
   }
 #pragma unroll

@@ -209,12 +209,18 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   constexpr bool PARTIALS = MODE == SCORE_FILTER || MODE == SCORE_PARTIALS;  // running sums (SCORE_LOGITS: at the end)
   constexpr bool HEAVY = PARTIALS;
   constexpr int kChunk = 64 * BPW * kScoreWaves;
+  constexpr int kBlockUnroll = FILTER ? 1 : BPW;
 
   __shared__ uint4 lds[kScoreWaves][64 * CH];
   __shared__ float2 part[kScoreWaves][4][4];
   // HEAVY: the lanes whose logit (block, accumulator, register) is a heavy term of the softmax sum
   __shared__ unsigned long long heavy_mask[HEAVY ? kScoreWaves : 1][BPW][NACC][4];
-  __shared__ int n_kept_wg;  // FILTER: candidates this workgroup has kept so far
+  // FILTER: a wave collects its candidates in LDS and stores them in runs, see `flush`
+  constexpr int GQ = GPAD / 4;                                       // float4s in a record (Gs = GPAD)
+  constexpr int kStash = GPAD == 4 ? 128 : GPAD == 8 ? 96 : 48;      // room for at least two accumulators' tokens
+  __shared__ float4 stash_rec[FILTER ? kScoreWaves : 1][FILTER ? kStash * GQ : 1];
+  __shared__ int32_t stash_tok[FILTER ? kScoreWaves : 1][FILTER ? kStash : 1];
+  __shared__ int n_kept_wg;  // candidates this workgroup has stored so far
 
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -330,6 +336,38 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   const int64_t row_slots = (int64_t)row * p.filt.slots_per_row;
   const int64_t slot_base = row_slots + (int64_t)chunk * p.filt.cap_c;
   const int64_t ovf_base = row_slots + (int64_t)p.n_chunks * p.filt.cap_c;
+  // The wave's collected candidates into the next free slots.  In runs, because these few bytes cost what the write-backs of
+  // their lines cost, not what the store instructions do (stored over and over into 16 KB that stay in L2, the pass takes what it takes
+  // with nothing stored).  Nothing stored / stored as met / in runs: 64 rows x 40K tokens in pages, 7 heads 117 / 137 / 124 us,
+  // 112 rows x 128K, 7 lists 549 / 625 / 605, 8 rows x 128K, 4 heads 49 / 52 / 48 (with the lines of the partials).
+  int n_stash = 0;  // wave-uniform
+  auto flush = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&n_kept_wg, n_stash);  // LDS counter
+    base = __builtin_amdgcn_readfirstlane(base);
+    int fit = p.filt.cap_c - base, room = 0;  // candidates that take the chunk's own slots, and the pool's
+    fit = fit < 0 ? 0 : fit < n_stash ? fit : n_stash;
+    int64_t over = 0;
+    if (fit < n_stash) {  // rare: the chunk's own slots are used up
+      int o = 0;
+      if (lane == 0) o = atomicAdd(&p.filt.ovf_count[row], n_stash - fit);
+      o = __builtin_amdgcn_readfirstlane(o);
+      room = o < p.filt.cap_o ? p.filt.cap_o - o : 0;  // pool full: dropped, the row is redone
+      over = ovf_base + o - fit;
+    }
+    const int last = room < n_stash - fit ? fit + room : n_stash;
+    for (int i = lane; i < last * GQ; i += 64) {
+      const int e = i / GQ;
+      const int64_t slot = e < fit ? slot_base + base + e : over + e;
+      reinterpret_cast<float4*>(p.filt.cand_logit)[slot * GQ + i % GQ] = stash_rec[wave][i];
+      if (i % GQ == 0) p.filt.cand_idx[slot] = stash_tok[wave][e];
+    }
+    n_stash = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  const unsigned long long before_mine = (1ull << (((j - j % GQ) << 4) | n)) - 1ull;  // lanes that count tokens before this lane's
+  constexpr unsigned long long kCounting = GPAD == 4 ? ~0ull : GPAD == 8 ? 0x0000FFFF0000FFFFull : 0xFFFFull;  // one lane per token
 
   // Software pipeline: the loads of block b+1 are issued right after block b went to LDS, so
   // their latency overlaps block b's MFMA phase.  Per-token results stay in registers until the wave
@@ -338,7 +376,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   bool seen_heavy = false;
   if (HEAVY && lane < BPW * NACC * 4) (&heavy_mask[wave][0][0][0])[lane] = 0ull;
   float xs[KEEP ? BPW : 1][NACC][4];
-#pragma unroll
+#pragma unroll kBlockUnroll
   for (int blk = 0; blk < BPW; ++blk) {
     const int64_t tok_base = wave_base + (int64_t)blk * kBlockStride;
     if (tok_base < L) {  // wave-uniform
@@ -401,37 +439,25 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         }
         if (FILTER) {
           // the heads of a token sit in GPAD/4 lanes (same n, adjacent j): combine their parts
-          if (GPAD >= 8) {
-            approx += __shfl_xor(approx, 16);
-            any_head |= __shfl_xor(any_head, 16);
+          unsigned long long reach;
+          if (per_head) {
+            reach = __ballot(any_head != 0);
+            if (GPAD >= 8) reach |= (reach >> 16) & 0x0000FFFF0000FFFFull;
+            if (GPAD >= 16) reach |= reach >> 32;
+          } else {
+            if (GPAD >= 8) approx = swap16_sum(approx);
+            if (GPAD >= 16) approx = swap32_sum(approx);
+            reach = __ballot(!(approx < ftau));
           }
-          if (GPAD >= 16) {
-            approx += __shfl_xor(approx, 32);
-            any_head |= __shfl_xor(any_head, 32);
-          }
-          const bool reach = per_head ? any_head != 0 : !(approx < ftau);
-          const bool pass = tok >= p.filt.S && tok < L - p.filt.W && reach;
-          const bool rep = (4 * j) % GPAD == 0;  // one lane per token counts it
-          const unsigned long long bal = __ballot(pass && rep);
+          const unsigned long long bal = reach & __ballot(tok >= p.filt.S && tok < L - p.filt.W) & kCounting;
           if (bal) {  // wave-uniform
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&n_kept_wg, __popcll(bal));  // LDS counter
-            base = __shfl(base, 0);
-            int pos = base + __popcll(bal & ((1ull << lane) - 1ull));
-            const int src = ((j - j % (GPAD / 4)) << 4) | n;  // the token's counting lane
-            pos = __shfl(pos, src);                           // every lane of the token
-            int64_t slot = slot_base + pos;
-            if (base + __popcll(bal) > p.filt.cap_c) {  // wave-uniform, rare: the chunk's own slots are used up
-              int o = 0;
-              if (pass && rep && pos >= p.filt.cap_c) o = atomicAdd(&p.filt.ovf_count[row], 1);
-              o = __shfl(o, src);
-              if (pos >= p.filt.cap_c) slot = o < p.filt.cap_o ? ovf_base + o : -1;  // pool full: dropped, the row is redone
+            if (n_stash + 64 / GQ > kStash) flush();
+            if ((bal >> (((j - j % GQ) << 4) | n)) & 1ull) {  // every lane of the token
+              const int pos = n_stash + __popcll(bal & before_mine);
+              stash_rec[wave][pos * GQ + j % GQ] = make_float4(xs[0][a][0], xs[0][a][1], xs[0][a][2], xs[0][a][3]);
+              if (j % GQ == 0) stash_tok[wave][pos] = (int32_t)tok;
             }
-            if (pass && hbase < gb && slot >= 0) {
-              if (rep) p.filt.cand_idx[slot] = (int32_t)tok;
-              float* rec = p.filt.cand_logit + slot * p.filt.Gs + hbase;
-              *reinterpret_cast<float4*>(rec) = make_float4(xs[0][a][0], xs[0][a][1], xs[0][a][2], xs[0][a][3]);
-            }
+            n_stash += __popcll(bal);
           }
         }
       }
@@ -610,32 +636,39 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
     return;
   }
 
+  if (FILTER && n_stash) flush();
   // (max, sum) of the chunk: the 16 lanes of a row block share their heads
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    float M = m[r];
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    const float M = group16_max(m[r]);
     float sm = (m[r] == -INFINITY) ? 0.f : sum[r] * exp_fast(m[r] - M);
     sm = group_sum<16>(sm);
     if (n == 0) part[wave][j][r] = make_float2(M, sm);
   }
   __syncthreads();
-  if (FILTER && threadIdx.x == 0) p.filt.cand_count[(int64_t)row * p.n_chunks + chunk] = n_kept_wg;
-  if ((int)threadIdx.x < gb) {
-    const int g = threadIdx.x;
-    float M = -INFINITY;
-    for (int w = 0; w < kScoreWaves; ++w)
-      for (int jj = 0; jj < 4; ++jj)
-        if ((4 * jj) % GPAD == (g / 4) * 4) M = fmaxf(M, part[w][jj][g % 4].x);
-    float sm = 0.f;
-    for (int w = 0; w < kScoreWaves; ++w)
-      for (int jj = 0; jj < 4; ++jj)
-        if ((4 * jj) % GPAD == (g / 4) * 4) {
-          const float2 pw = part[w][jj][g % 4];
-          sm += (pw.x == -INFINITY) ? 0.f : pw.y * exp_fast(pw.x - M);
+  // the chunk's line, whole: thread t writes word t
+  const int words = chunk_line_words(p.geo.G), t = threadIdx.x;
+  if (t < words) {
+    float v = 0.f;
+    if (t < 2 * gb) {
+      const int g = t >> 1;
+      float2 pw[kScoreWaves][16 / GPAD];
+      float M = -INFINITY, sm = 0.f;
+#pragma unroll
+      for (int w = 0; w < kScoreWaves; ++w)
+#pragma unroll
+        for (int ts = 0; ts < TILES; ++ts) {
+          pw[w][ts] = part[w][ts * GQ + g / 4][g % 4];
+          M = fmaxf(M, pw[w][ts].x);
         }
-    p.partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + chunk] = make_float2(M, sm);
+#pragma unroll
+      for (int w = 0; w < kScoreWaves; ++w)
+#pragma unroll
+        for (int ts = 0; ts < TILES; ++ts) sm += (pw[w][ts].x == -INFINITY) ? 0.f : pw[w][ts].y * exp_fast(pw[w][ts].x - M);
+      v = t & 1 ? sm : M;
+    }
+    if (FILTER && t == words - 1) v = __int_as_float(n_kept_wg);
+    p.lines[((int64_t)row * p.n_chunks + chunk) * words + t] = v;
   }
 }
 
@@ -731,7 +764,7 @@ __global__ __launch_bounds__(64) void stats_kernel(StatsParams p) {
   if (p.ghist)
     for (int b = lane; b < kHistBins * p.n_lists; b += 64) p.ghist[(int64_t)row * p.n_lists * kHistBins + b] = 0;
   for (int g = 0; g < p.G; ++g) {
-    const RowStat st = merge_partials_wave(p.partials + ((int64_t)row * p.G + g) * p.n_chunks, p.n_chunks);
+    const RowStat st = merge_partials_wave(p.lines + (int64_t)row * p.n_chunks * chunk_line_words(p.G) + 2 * g, chunk_line_words(p.G), p.n_chunks);
     if (lane == 0) p.stats[(int64_t)row * p.G + g] = st;
   }
 }
