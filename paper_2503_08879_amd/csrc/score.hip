@@ -25,41 +25,6 @@ constexpr int kScoreWaves = kScoreThreads / kWave;
 constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine launch
 // A score workgroup takes a chunk of BPW blocks of 64 tokens per wave (BPW = 1, 2, 4: 256, 512, 1024 tokens).
 
-// Softmax terms that a wave takes with an fp64 exponent, up to kHeavyBatch at a time: exp(l - m), l = the logit of query
-// row q + q_off and key row K + k_off (D elements each) in fp64.  Sixteen lanes share a term, so the loads of a
-// batch are in flight together (one term after the other costs a memory round trip each).  Called by all 64 lanes of a
-// wave; rare: out of line.
-constexpr int kHeavyBatch = 32;
-struct HeavyTerms {
-  int64_t k_off[kHeavyBatch], q_off[kHeavyBatch];
-  double val[kHeavyBatch];
-  float m[kHeavyBatch];
-  int code[kHeavyBatch];  // whose sum the term belongs to
-};
-template <int D>
-__device__ __noinline__ void exact_terms(HeavyTerms* h, int cnt, const void* K, const void* q) {
-  constexpr int EPT = D / 16;  // elements per lane
-  const int lane = threadIdx.x & 63, grp = lane >> 4, sub = lane & 15;
-  for (int e0 = 0; e0 < cnt; e0 += 8) {
-    double acc[2] = {0.0, 0.0};
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int e = e0 + 4 * u + grp < cnt ? e0 + 4 * u + grp : cnt - 1;
-      const int64_t ko = h->k_off[e] + sub * EPT, qo = h->q_off[e] + sub * EPT;
-#pragma unroll
-      for (int i = 0; i < EPT; ++i) acc[u] += elem_f64<DT_BF16>(q, qo + i) * elem_f64<DT_BF16>(K, ko + i);
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-      for (int o = 8; o >= 1; o >>= 1) acc[u] += __shfl_xor(acc[u], o);
-      const int e = e0 + 4 * u + grp;
-      if (sub == 0 && e < cnt) h->val[e] = exp(acc[u] / sqrt((double)D) - (double)h->m[e]);
-    }
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-}
-
 // fp32 caches.  One wave handles 64 tokens per block: LPT lanes share a token (16 bytes each), so one
 // 16-byte load instruction covers TPL = 64/LPT whole tokens, fully coalesced; LPT such loads
 // make a block.  After load i the lane with (lane % LPT) == i keeps the reduced dot product,
@@ -213,8 +178,6 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
 
   __shared__ uint4 lds[kScoreWaves][64 * CH];
   __shared__ float2 part[kScoreWaves][4][4];
-  // HEAVY: the lanes whose logit (block, accumulator, register) is a heavy term of the softmax sum
-  __shared__ unsigned long long heavy_mask[HEAVY ? kScoreWaves : 1][BPW][NACC][4];
   // FILTER: a wave collects its candidates in LDS and stores them in runs, see `flush`
   constexpr int GQ = GPAD / 4;                                       // float4s in a record (Gs = GPAD)
   constexpr int kStash = GPAD == 4 ? 128 : GPAD == 8 ? 96 : 48;      // room for at least two accumulators' tokens
@@ -277,7 +240,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   };
   if (wave_base < L) load_block(wave_base);
   // A operand: lane (row m = n, k-group j) holds q[head m % GPAD][8*(4*kc + j) ..+8]
-  const int my_head = n % GPAD, my_slot = n / GPAD;
+  const int my_head = n % GPAD, tslot = (4 * j) / GPAD;
   uint4 qa[KSTEPS];
 #pragma unroll
   for (int kc = 0; kc < KSTEPS; ++kc) {
@@ -373,8 +336,11 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   // their latency overlaps block b's MFMA phase.  Per-token results stay in registers until the wave
   // has loaded its last block: loads and stores share one in-order completion counter, so a
   // store inside the loop would put its write-ack latency on the critical path of every block.
+  // HEAVY: this lane's share of the heavy terms of heads j + 4 i: sum of exp(l - heavy_m) in fp64
   bool seen_heavy = false;
-  if (HEAVY && lane < BPW * NACC * 4) (&heavy_mask[wave][0][0][0])[lane] = 0ull;
+  double heavy_m[GQ], heavy_z[GQ];
+#pragma unroll
+  for (int i = 0; i < GQ; ++i) heavy_m[i] = -INFINITY, heavy_z[i] = 0.0;
   float xs[KEEP ? BPW : 1][NACC][4];
 #pragma unroll kBlockUnroll
   for (int blk = 0; blk < BPW; ++blk) {
@@ -392,20 +358,23 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         asm volatile("" : "+s"(next));  // the addresses of later blocks are not computed (and held) up front
         load_block(next);
       }
+      // Row m of the A operand is head m % GPAD whatever the tile slot, so a tile's product holds every head's logits 16 / GPAD
+      // times over and each lane takes the tile of its slot.  (One accumulator for the tiles, with A zero but for the slot's rows:
+      // a chain of 16 / GPAD times as many products, and as many copies of A in registers.)
       f32x4_t acc[NACC];
 #pragma unroll
       for (int a = 0; a < NACC; ++a) {
-        acc[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ts = 0; ts < TILES; ++ts) {
           const int t = (a * TILES + ts) * 16 + n;
+          f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int kc = 0; kc < KSTEPS; ++kc) {
             const uint4 b = buf[t * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
-            const uint4 qv = (my_slot == ts) ? qa[kc] : make_uint4(0u, 0u, 0u, 0u);
-            acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qv),
-                                                             __builtin_bit_cast(bf16x8_t, b), acc[a], 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qa[kc]), __builtin_bit_cast(bf16x8_t, b), d, 0, 0, 0);
           }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) acc[a][r] = ts == 0 || tslot == ts ? d[r] : acc[a][r];
         }
       }
       // lane (j, n), accumulator a, register r: row 4j + r = (tile slot, head), column n = token
@@ -461,16 +430,55 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
           }
         }
       }
-      if (HEAVY && __any(any_heavy)) {  // wave-uniform, rare: noted here, added after the last block
+      if (HEAVY && __any(any_heavy)) {  // wave-uniform, rare
+        // The block is still in LDS: the fp64 logits of a 16-token tile for every head are D / 4 steps of
+        // v_mfma_f64_16x16x4 on the operands at hand (element e of everybody's 16 bytes per step), about 1 us a tile.  (Listing the
+        // terms and reading their keys again after the last block, sixteen lanes per dot product: 5.7 us for the chunk that holds a
+        // row's sink tokens, which is what the whole launch of a small call then waits for.)
         seen_heavy = true;
+        unsigned long long hv[NACC][4];  // lanes whose logit is a heavy term
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) {
-          const int t_local = (a * TILES + (4 * j) / GPAD) * 16 + n;
+        for (int a = 0; a < NACC; ++a)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            hv[a][r] = __ballot(tok_base + (a * TILES + (4 * j) / GPAD) * 16 + n < L && hbase + r < gb && xs[0][a][r] >= hthr[r]);
+#pragma unroll 1
+        for (int tile = 0; tile < 4; ++tile) {
+          // rows of the tile in its accumulator: lanes 16 GQ (tile % TILES) on; lane (j', n), register r: head 4 (j' % GQ) + r
+          unsigned long long of[4], any = 0ull;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const unsigned long long b = __ballot(tok_base + t_local < L && hbase + r < gb && xs[0][a][r] >= hthr[r]);
-            if (lane == 0) heavy_mask[wave][blk][a][r] = b;
+            of[r] = hv[0][r];
+#pragma unroll
+            for (int a = 1; a < NACC; ++a) of[r] = tile / TILES == a ? hv[a][r] : of[r];
+            of[r] >>= 16 * GQ * (tile % TILES);
+            if (GQ < 4) of[r] &= (1ull << (16 * GQ % 64)) - 1ull;
+            any |= of[r];
           }
+          if (!any) continue;
+          typedef double f64x4_t __attribute__((ext_vector_type(4)));
+          f64x4_t d = {0.0, 0.0, 0.0, 0.0};  // register i of lane (j, n): row 4 i + j = head (4 i + j) % GPAD, token n
+#pragma unroll
+          for (int kc = 0; kc < KSTEPS; ++kc) {
+            const uint4 b = buf[(tile * 16 + n) * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
+            uint32_t qw[4] = {qa[kc].x, qa[kc].y, qa[kc].z, qa[kc].w};
+            const uint32_t bw[4] = {b.x, b.y, b.z, b.w};
+            asm volatile("" : "+v"(qw[0]), "+v"(qw[1]), "+v"(qw[2]), "+v"(qw[3]));  // not converted (and held) up front
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_lo(qw[e]), (double)bf16_lo(bw[e]), d, 0, 0, 0);
+              d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_hi(qw[e]), (double)bf16_hi(bw[e]), d, 0, 0, 0);
+            }
+          }
+          const unsigned long long mine = j == 0 ? of[0] : j == 1 ? of[1] : j == 2 ? of[2] : of[3];
+#pragma unroll
+          for (int i = 0; i < GQ; ++i)
+            if ((mine >> (16 * i + n)) & 1ull) {
+              const double l = d[i] * (1.0 / sqrt((double)D)), m0 = heavy_m[i];
+              const double ex = exp(l > m0 ? m0 - l : l - m0);
+              heavy_z[i] = l > m0 ? heavy_z[i] * ex + 1.0 : heavy_z[i] + ex;
+              heavy_m[i] = l > m0 ? l : m0;
+            }
         }
       }
       // one block ahead is enough, and all that the registers of two workgroups per CU hold: without this the passes
@@ -478,48 +486,27 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // The wave's heavy terms (heavy_mask) into z[r], r = its lanes' four heads.  A loop over the masks that hold any: one body
-  // per mask, 64 of them with 16 heads, takes 184 to 256 registers and spills (the pass over 64 rows x 128K tokens
-  // of head_dim 64: 16 heads 413 us so, 347 with the loop; 8 heads 311 and 265; 4 heads 232 and 234, over 40000 tokens 108
-  // and 106).
-  auto add_heavy = [&](double (&z)[4]) {
-    HeavyTerms* hv = reinterpret_cast<HeavyTerms*>(buf);  // the wave's staging buffer is free after its last block
-    static_assert(sizeof(HeavyTerms) <= sizeof(lds[0]), "heavy terms fit the staging buffer");
-    constexpr int kMasks = BPW * NACC * 4;  // mask i: block i / (4 NACC), accumulator i / 4 % NACC, register i % 4
-    static_assert(kMasks <= 64, "a mask per lane");
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const unsigned long long mine = lane < kMasks ? (&heavy_mask[HEAVY ? wave : 0][0][0][0])[lane] : 0ull;
-    for (int done = 0, total = 1; done < total; done += kHeavyBatch) {  // usually one batch
-      total = 0;
-#pragma unroll 1
-      for (unsigned long long todo = __ballot(mine != 0ull); todo; todo &= todo - 1) {
-        const int i = __ffsll(todo) - 1, blk = i / (NACC * 4), a = i / 4 % NACC, r = i % 4;
-        const unsigned long long b = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(mine >> 32), i) << 32 |
-                                     (uint32_t)__builtin_amdgcn_readlane((uint32_t)mine, i);
-        const int e = total + __popcll(b & ((1ull << lane) - 1ull)) - done;
-        if (((b >> lane) & 1ull) && e >= 0 && e < kHeavyBatch) {
-          const int64_t tok = wave_base + (int64_t)blk * kBlockStride + (a * TILES + (4 * j) / GPAD) * 16 + n;
-          hv->k_off[e] = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
-          hv->q_off[e] = ((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0 + hbase + r) * D;
-          hv->m[e] = r == 0 ? m[0] : r == 1 ? m[1] : r == 2 ? m[2] : m[3];
-          hv->code[e] = 4 * lane + r;
-        }
-        total += __popcll(b);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-      const int cnt = total - done < kHeavyBatch ? total - done : kHeavyBatch;
-      exact_terms<D>(hv, cnt, p.K, p.q_last);
-      for (int e = 0; e < cnt; ++e)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) z[r] += hv->code[e] == 4 * lane + r ? hv->val[e] : 0.0;
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
-  };
+  // the heavy terms join the sums of the lanes that hold their heads (the staging buffer is free after the last block)
   if (HEAVY && seen_heavy) {
-    double z[4] = {0.0, 0.0, 0.0, 0.0};
-    add_heavy(z);
+    double2* hb = reinterpret_cast<double2*>(buf);  // [head][token column]
+    static_assert(GPAD * 16 * sizeof(double2) <= sizeof(lds[0]), "heavy sums fit the staging buffer");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sum[r] += (float)z[r];
+    for (int i = 0; i < GQ; ++i) hb[(j + 4 * i) * 16 + n] = make_double2(heavy_m[i], heavy_z[i]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 1
+    for (int r = 0; r < 4; ++r) {
+      const double2 h = hb[((4 * j) % GPAD + r) * 16 + n];
+      if (j < GQ && h.y > 0.0) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i == r) {
+            const float mn = fmaxf(m[i], (float)h.x);
+            sum[i] = sum[i] * exp_fast(m[i] - mn) + (float)(h.y * exp(h.x - (double)mn));
+            m[i] = mn;
+          }
+      }
+    }
   }
   if (MODE == SCORE_LOGITS) {
 #pragma unroll
