@@ -681,68 +681,60 @@ __global__ __launch_bounds__(kScoreThreads, GPAD == 16 && MODE != SCORE_FILTER ?
   score_mfma_chunk<D, GPAD, MODE, PAGED, BPW>(p, gb, (int)blockIdx.y, (int)chunk);
 }
 
-// Logits of the sampled blocks (fast path), same MFMA scheme as score_mfma_kernel: one wave per
-// 64-token block, logits to samp_logit[row][slot][Gs] (16 bytes per lane).
-template <int D, int GPAD>
-__global__ __launch_bounds__(kScoreThreads) void sample_logits_kernel(SampleParams p) {
-  constexpr int CH = D / 8, TPL = 64 / CH, NLOAD = 64 / TPL, KSTEPS = D / 32;
-  constexpr int TILES = 16 / GPAD, NACC = 4 / TILES;
-  __shared__ uint4 lds[kScoreWaves][64 * CH];
-
+// Logits of the sampled blocks (fast path): one wave per 64-token block, logits to samp_logit[row][slot][Gs] (16 bytes per
+// lane).  A block is four tiles of 16 consecutive tokens (sample_token), and a lane loads its MFMA B operands straight from
+// memory: the four (two) 64-byte pieces of a token go to four lanes, and the tile's 4 (2) KB are one run all the same; no LDS,
+// little code, the pages of a lane's four tokens looked up together (with a table load in front of every load of keys the
+// stage took 29 us instead of 23 for 64 rows x 40K tokens in pages).
+// Plain loads: nontemporal ones take 37 instead of 49 us over 256 rows x 32K tokens, but the filtering pass after them then
+// takes 370 instead of 343 (over 256 x 128K 52 and 75, 1400 and 1270): it is left to push out what the last writer's lines hold of the
+// Infinity Cache.
+template <int D, int GPAD, bool PAGED>
+__global__ __launch_bounds__(kScoreThreads, 4) void sample_logits_kernel(SampleParams p) {
+  constexpr int KSTEPS = D / 32, TILES = 16 / GPAD, NACC = 4 / TILES;
   const int row = blockIdx.y;
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tq = lane / CH, cl = lane % CH;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, j = lane >> 4;
   const int64_t L = p.geo.L;
-  const int G = p.geo.G;
   const int blk = blockIdx.x * kScoreWaves + wave;
   if (blk >= p.nA + p.nB + p.nC) return;  // wave-uniform; no workgroup barrier below
-  uint4* buf = lds[wave];
-  uint4 kv[NLOAD];
+  const char* base = (const char*)p.K + ((PAGED ? 0 : (int64_t)prob * p.ks_problem) + (int64_t)c * p.ks_head) * 2 + 16 * j;
+  int64_t at[4];
 #pragma unroll
-  for (int i = 0; i < NLOAD; ++i) {
-    int64_t tok = sample_token(p, blk, i * TPL + tq);
+  for (int t = 0; t < 4; ++t) {
+    int64_t tok = sample_token(p, blk, 16 * t) + n;
     tok = tok < 0 ? 0 : (tok < L ? tok : L - 1);
-    const int64_t off = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
-    kv[i] = ld16((const char*)p.K + off * 2 + cl * 16);
+    at[t] = PAGED ? (int64_t)page_of(p.pm, prob, tok) * p.pm.ks_page + (tok & ((1 << p.pm.shift) - 1)) * p.ks_token : tok * p.ks_token;
   }
-  const int my_head = n % GPAD, my_slot = n / GPAD;
+  uint4 kv[4][KSTEPS];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int kc = 0; kc < KSTEPS; ++kc) kv[t][kc] = ld16(base + at[t] * 2 + 64 * kc);
+  const int my_head = n % GPAD, tslot = (4 * j) / GPAD;
   uint4 qa[KSTEPS];
 #pragma unroll
   for (int kc = 0; kc < KSTEPS; ++kc) {
     qa[kc] = make_uint4(0u, 0u, 0u, 0u);
-    if (my_head < G) {
-      const int h = c * G + my_head;
-      qa[kc] = ld16((const char*)p.q_last + (((int64_t)prob * p.geo.Hq + h) * D + (4 * kc + j) * 8) * 2);
-    }
+    if (my_head < p.geo.G) qa[kc] = ld16((const char*)p.q_last + (((int64_t)prob * p.geo.Hq + c * p.geo.G + my_head) * D + (4 * kc + j) * 8) * 2);
   }
-#pragma unroll
-  for (int i = 0; i < NLOAD; ++i) {
-    const int t = i * TPL + tq;
-    buf[t * CH + (cl ^ (t & (CH - 1)))] = kv[i];
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   const int hbase = (4 * j) % GPAD;
-  float* out = p.samp_logit + ((int64_t)row * (p.nA + p.nB + p.nC) + blk) * 64 * p.Gs;
+  float* out = p.samp_logit + ((int64_t)row * (p.nA + p.nB + p.nC) + blk) * 64 * GPAD;
 #pragma unroll
   for (int a = 0; a < NACC; ++a) {
-    f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc;  // as in score_mfma_chunk: every tile's product holds all heads, a lane takes the tile of its slot
 #pragma unroll
     for (int ts = 0; ts < TILES; ++ts) {
-      const int t = (a * TILES + ts) * 16 + n;
+      f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kc = 0; kc < KSTEPS; ++kc) {
-        const uint4 b = buf[t * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
-        const uint4 qv = (my_slot == ts) ? qa[kc] : make_uint4(0u, 0u, 0u, 0u);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qv), __builtin_bit_cast(bf16x8_t, b),
-                                                      acc, 0, 0, 0);
-      }
+      for (int kc = 0; kc < KSTEPS; ++kc)
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qa[kc]), __builtin_bit_cast(bf16x8_t, kv[a * TILES + ts][kc]), d, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = ts == 0 || tslot == ts ? d[r] : acc[r];
     }
-    const int t_local = (a * TILES + (4 * j) / GPAD) * 16 + n;
-    if (hbase < p.Gs)
-      *reinterpret_cast<float4*>(out + (int64_t)t_local * p.Gs + hbase) =
-          make_float4(acc[0] * p.scale, acc[1] * p.scale, acc[2] * p.scale, acc[3] * p.scale);
+    *reinterpret_cast<float4*>(out + ((a * TILES + tslot) * 16 + n) * GPAD + hbase) =
+        make_float4(acc[0] * p.scale, acc[1] * p.scale, acc[2] * p.scale, acc[3] * p.scale);
   }
 }
 
@@ -888,11 +880,27 @@ hipError_t launch_sample_logits(const SampleParams& p, hipStream_t s) {
   const int nb = p.nA + p.nB + p.nC;
   if (p.geo.dtype != DT_BF16 || p.geo.G > 16) return hipErrorInvalidValue;
   dim3 grid((unsigned)((nb + kScoreWaves - 1) / kScoreWaves), (unsigned)rows);
-#define SAGEKV_LAUNCH(DD, GP) hipLaunchKernelGGL((sample_logits_kernel<DD, GP>), grid, dim3(kScoreThreads), 0, s, p)
+#define SAGEKV_LAUNCH(DD, GP)                                                                                  \
+  if (p.pm.table)                                                                                               \
+    hipLaunchKernelGGL((sample_logits_kernel<DD, GP, true>), grid, dim3(kScoreThreads), 0, s, p);               \
+  else                                                                                                          \
+    hipLaunchKernelGGL((sample_logits_kernel<DD, GP, false>), grid, dim3(kScoreThreads), 0, s, p)
   if (p.geo.D == 128) {
-    if (p.geo.G <= 4) SAGEKV_LAUNCH(128, 4); else if (p.geo.G <= 8) SAGEKV_LAUNCH(128, 8); else SAGEKV_LAUNCH(128, 16);
+    if (p.geo.G <= 4) {
+      SAGEKV_LAUNCH(128, 4);
+    } else if (p.geo.G <= 8) {
+      SAGEKV_LAUNCH(128, 8);
+    } else {
+      SAGEKV_LAUNCH(128, 16);
+    }
   } else {
-    if (p.geo.G <= 4) SAGEKV_LAUNCH(64, 4); else if (p.geo.G <= 8) SAGEKV_LAUNCH(64, 8); else SAGEKV_LAUNCH(64, 16);
+    if (p.geo.G <= 4) {
+      SAGEKV_LAUNCH(64, 4);
+    } else if (p.geo.G <= 8) {
+      SAGEKV_LAUNCH(64, 8);
+    } else {
+      SAGEKV_LAUNCH(64, 16);
+    }
   }
 #undef SAGEKV_LAUNCH
   return hipGetLastError();
