@@ -222,24 +222,52 @@ __host__ __device__ inline float heavy_logit_threshold(float M, float Z) {
   return M + logf(r * r * Z);
 }
 
-// ---- block-wide inclusive scan of one int per thread (blockDim.x = NT, multiple of 64) ---------
-// `wave_tot` is NT/64 ints of shared memory.  Returns the inclusive prefix; *total gets the block sum.
-template <int NT>
+// ---- reductions over a workgroup of 16 waves ------------------------------------------------------
+// The kernels that give a row to one workgroup are chains of these, and every instruction of a chain costs 4 cycles per wave of
+// the SIMD, 7 ns with four: so the sixteen waves' parts are read by one LDS load, lane l taking wave l % 16's, and
+// combined by DPP moves within rows of 16 lanes, in every wave alike, instead of sixteen loads and a second barrier.
+template <int CTRL>
+__device__ __forceinline__ int dpp_rot_i32(int v) {  // a permutation within rows of 16 lanes: every lane has a source
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+template <bool MAX>
+__device__ __forceinline__ float combine(float a, float b) {
+  return MAX ? fmaxf(a, b) : a + b;
+}
+// Over the lanes of a row of 16 whose numbers are equal modulo GQ (1, 2 or 4); every lane gets its own residue's result.
+template <bool MAX, int GQ>
+__device__ __forceinline__ float row_combine(float v) {
+  v = combine<MAX>(v, dpp_f32<0x128>(v));               // row_ror:8
+  v = combine<MAX>(v, dpp_f32<0x124>(v));               // row_ror:4
+  if (GQ <= 2) v = combine<MAX>(v, dpp_f32<0x122>(v));  // row_ror:2
+  if (GQ == 1) v = combine<MAX>(v, dpp_f32<0x121>(v));  // row_ror:1
+  return v;
+}
+// The same over the whole wave.
+template <bool MAX, int GQ>
+__device__ __forceinline__ float wave_combine(float v) {
+  v = row_combine<MAX, GQ>(v);
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = combine<MAX>(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return combine<MAX>(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// ---- block-wide inclusive scan of one int per thread (1024 threads) ------------------------------
+// `wave_tot` is 16 ints of shared memory that no thread reads any more from an earlier use (a barrier has come after that).
+// Returns the inclusive prefix; *total gets the block sum.  One barrier.
 __device__ __forceinline__ int block_scan_incl(int v, int* wave_tot, int* total) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int x = wave_scan_incl(v);
-  __syncthreads();  // protects wave_tot against the previous use
   if (lane == 63) wave_tot[w] = x;
   __syncthreads();
-  int base = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) {
-    int t = wave_tot[i];
-    if (i < w) base += t;
-    tot += t;
-  }
-  *total = tot;
-  return x + base;
+  int t = wave_tot[lane & 15];
+  t += dpp_i32<0x111, 0xF>(0, t);  // row_shr: inclusive prefix over the 16 waves
+  t += dpp_i32<0x112, 0xF>(0, t);
+  t += dpp_i32<0x114, 0xF>(0, t);
+  t += dpp_i32<0x118, 0xF>(0, t);
+  *total = __builtin_amdgcn_readlane(t, 15);
+  return x + (w > 0 ? __builtin_amdgcn_readlane(t, w - 1) : 0);
 }
 
 }  // namespace sagekv

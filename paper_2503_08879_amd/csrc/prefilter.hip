@@ -41,8 +41,7 @@ constexpr float kHeavyShare = 0.01f;  // see sample_stats_kernel (0.3 % and 0.1 
 template <int GQ, int NI>
 __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams p) {
   __shared__ RegSelect sh;
-  __shared__ float2 red[kTopkWaves][4 * GQ];
-  __shared__ float sM[4 * GQ], sInv[4 * GQ], sZ[4 * GQ], sHeavy[4 * GQ];
+  __shared__ float red[4][4 * GQ][kTopkWaves];
 
   const int row = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -91,86 +90,91 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
       }
     }
   };
-  // over the lanes that share a quad, then the waves: component r of the result is in red[wave][4 * qd + r]
-  auto reduce = [&](float (&a)[4], float (&b)[4], bool maximum) {
+  // Over the lanes that share a quad, then the waves: all[] gets the heads' results (wave-uniform), v[] this thread's quad's.
+  // Ends before its barrier's buffer may be written again: every call has its own.
+  auto reduce = [&](float (&v)[4], float (&all)[4 * GQ], float (*buf)[kTopkWaves], auto maximum) {
+    constexpr bool MAX = decltype(maximum)::value;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-#pragma unroll
-      for (int o = 32; o >= GQ; o >>= 1) {
-        const float y = __shfl_xor(a[r], o);
-        a[r] = maximum ? fmaxf(a[r], y) : a[r] + y;
-        if (!maximum) b[r] += __shfl_xor(b[r], o);
-      }
-      if (lane < GQ) red[wave][4 * qd + r] = make_float2(a[r], b[r]);
+      v[r] = wave_combine<MAX, GQ>(v[r]);
+      if (lane < GQ) buf[4 * qd + r][wave] = v[r];
     }
     __syncthreads();
+#pragma unroll
+    for (int q = 0; q < GQ; ++q) {
+      const float x = row_combine<MAX, 1>(buf[4 * q + (lane >> 4)][lane & 15]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) all[4 * q + r] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 16 * r));
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      v[r] = all[r];
+#pragma unroll
+      for (int q = 1; q < GQ; ++q) v[r] = qd == q ? all[4 * q + r] : v[r];
+    }
   };
+  typedef std::integral_constant<bool, true> Max;
+  typedef std::integral_constant<bool, false> Sum;
 
   // approximate softmax statistics: M^ = max, Z^ = sum of weight * exp(l - M^)
-  float a4[4], b4[4];
+  float M4[4], Mall[4 * GQ], Z4[4], Zall[4 * GQ], z4[4], zall[4 * GQ], h4[4], hall[4 * GQ];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) a4[r] = -INFINITY, b4[r] = 0.f;
+  for (int r = 0; r < 4; ++r) M4[r] = -INFINITY, Z4[r] = z4[r] = h4[r] = 0.f;
   each([&](f32x4_t& v, int, float) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a4[r] = fmaxf(a4[r], v[r]);
+    for (int r = 0; r < 4; ++r) M4[r] = fmaxf(M4[r], v[r]);
   });
-  reduce(a4, b4, true);
-  if (tid < 4 * GQ) {
-    float M = red[0][tid].x;
-    for (int w = 1; w < kTopkWaves; ++w) M = fmaxf(M, red[w][tid].x);
-    sM[tid] = M;
-  }
-  __syncthreads();
-  float M4[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) M4[r] = sM[4 * qd + r], a4[r] = 0.f, b4[r] = 0.f;
+  reduce(M4, Mall, red[0], Max());
   auto expo = [&](const f32x4_t& v) {
     return f32x4_t{exp_fast(v[0] - M4[0]), exp_fast(v[1] - M4[1]), exp_fast(v[2] - M4[2]), exp_fast(v[3] - M4[3])};
   };
   each([&](f32x4_t& v, int, float w) {
     const f32x4_t e = expo(v);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) a4[r] += w * e[r];
+    for (int r = 0; r < 4; ++r) Z4[r] += w * e[r];
     v = e;  // (registers: from here on the exponentials; from memory: a copy)
   });
-  reduce(a4, b4, false);
-  if (tid < 4 * GQ) {
-    float z = 0.f;
-    for (int w = 0; w < kTopkWaves; ++w) z += red[w][tid].x;
-    sZ[tid] = z;  // first estimate of Z^, refined below
-  }
-  __syncthreads();
+  reduce(Z4, Zall, red[1], Sum());  // first estimate of Z^, refined below
   // A sampled token that would alone stand for more than 1 % of the head's mass is a heavy token, and heavy
   // tokens are rare: it is counted once, not once per token it was meant to represent.  (Attention mass sits on
   // few tokens; scaling such a token up by the sampling rate would put the head's normaliser off by a large
   // factor and the row could not be certified.  Under-counting only lets a few more candidates through.)
-  float Z4[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) Z4[r] = sZ[4 * qd + r], a4[r] = 0.f, b4[r] = 0.f;
   each([&](f32x4_t& v, int, float w) {
     const f32x4_t e = NI > 0 ? v : expo(v);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const bool heavy = w * e[r] > kHeavyShare * Z4[r];
-      a4[r] += (heavy ? 1.f : w) * e[r];
-      b4[r] += heavy && w > 1.f ? w * e[r] : 0.f;  // a token that stands for itself alone (the sink) is no surprise
+      z4[r] += (heavy ? 1.f : w) * e[r];
+      h4[r] += heavy && w > 1.f ? w * e[r] : 0.f;  // a token that stands for itself alone (the sink) is no surprise
     }
   });
-  reduce(a4, b4, false);
-  if (tid < G) {
-    float zz = 0.f, hh = 0.f;
-    for (int w = 0; w < kTopkWaves; ++w) {
-      zz += red[w][tid].x;
-      hh += red[w][tid].y;
-    }
-    sHeavy[tid] = hh / sZ[tid];  // share of the first estimate that came from heavy tokens
-    sInv[tid] = 1.0f / zz;
-    p.samp_stats[(int64_t)row * G + tid] = make_float2(sM[tid], 1.0f / zz);
-    p.heavy_thr[(int64_t)row * G + tid] = heavy_logit_threshold(sM[tid], zz);
-  } else if (tid < 4 * GQ) {
-    sInv[tid] = 0.f;  // padding heads add nothing to a score
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {  // (one barrier for both sums: the first goes to its buffer before the second's)
+    h4[r] = wave_combine<false, GQ>(h4[r]);
+    if (lane < GQ) red[3][4 * qd + r][wave] = h4[r];
   }
-  __syncthreads();
+  reduce(z4, zall, red[2], Sum());
+  float I4[4], heavy_share = 0.f;  // largest share of a head's first estimate that came from heavy tokens
+#pragma unroll
+  for (int q = 0; q < GQ; ++q) {
+    const float x = row_combine<false, 1>(red[3][4 * q + (lane >> 4)][lane & 15]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int g = 4 * q + r;
+      hall[g] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 16 * r));
+      if (g < G) heavy_share = fmaxf(heavy_share, hall[g] / Zall[g]);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) I4[r] = 4 * qd + r < G ? 1.0f / z4[r] : 0.f;  // padding heads add nothing to a score
+  if (tid < GQ) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (4 * tid + r < G) {
+        p.samp_stats[(int64_t)row * G + 4 * tid + r] = make_float2(M4[r], I4[r]);
+        p.heavy_thr[(int64_t)row * G + 4 * tid + r] = heavy_logit_threshold(M4[r], z4[r]);
+      }
+  }
   // A heavy-tailed row (the sample met heavy tokens) has heads whose normalisers are known with
   // very different accuracy, whatever the sampler does about the heavy tokens it saw: some head
   // has others it did not see.  The summed score then needs a threshold further down: the rank
@@ -178,15 +182,10 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
   // planned for that).  Per-query lists do not need it: a head's own scale cancels.
   int rank = p.rank;
   if (!per_head) {
-    float h = 0.f;
-    for (int g = 0; g < G; ++g) h = fmaxf(h, sHeavy[g]);
-    const float grow = fminf(1.f, 4.f * fmaxf(0.f, h - 0.04f));
+    const float grow = fminf(1.f, 4.f * fmaxf(0.f, heavy_share - 0.04f));
     rank = (int)((float)p.rank * (1.f + grow));
     if (rank > nB) rank = nB;
   }
-  float I4[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) I4[r] = sInv[4 * qd + r];
 
   // group-sum: the threshold is on the summed approximate score; per-query: on the head's own.  Every thread takes part for
   // every item (the quads of a slot sit in adjacent lanes); -1: not a sampled candidate, or not this thread's.
@@ -242,39 +241,62 @@ struct CandShared {
   float bound[kFastMaxG];   // per-query lists: the bound of each head's list,
   float thr[kFastMaxG];     // and the same bound as a logit of that head
   int n_list[kFastMaxG];    // per-query lists: candidates each list has kept
+  int n_over;               // candidates in the row's overflow pool
   int chunk_off[1025];
 };
 
+// What a row's selection starts from, all of it asked for at once: thread t's chunk's candidate count, wave g's head's partials
+// and sampled statistics.
+struct RowStart {
+  int raw;
+  PartialLoads part;
+  float2 samp;
+};
+__device__ __forceinline__ RowStart row_start(const TopkCandParams& p, int row) {
+  const int tid = threadIdx.x, g = __builtin_amdgcn_readfirstlane(tid >> 6), G = p.geo.G, words = chunk_line_words(G);
+  const float* lines = p.lines + (int64_t)row * p.n_chunks * words;
+  RowStart r = {};
+  if (tid < p.n_chunks) r.raw = __float_as_int(lines[(int64_t)tid * words + words - 1]);
+  if (g < G) {
+    r.part = load_partials(lines + 2 * g, words, p.n_chunks);
+    r.samp = p.samp_stats[(int64_t)row * G + g];
+  }
+  return r;
+}
+
 // Exact softmax statistics of the row's heads, one wave per head, from the partials of the filtering pass; and how
 // far the sampled statistics were off: rho = (exact weight) / (sampled weight).  A barrier has to follow.
-__device__ __forceinline__ void exact_stats(const TopkCandParams& p, CandShared& s, int row) {
-  const int g = threadIdx.x >> 6, G = p.geo.G;
+__device__ __forceinline__ void exact_stats(const TopkCandParams& p, CandShared& s, int row, const RowStart& r) {
+  const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), G = p.geo.G;
   if (g >= G) return;
-  const RowStat st = merge_partials_wave(p.lines + (int64_t)row * p.n_chunks * chunk_line_words(G) + 2 * g, chunk_line_words(G), p.n_chunks);
+  const int words = chunk_line_words(G);
+  const RowStat st = merge_partials_wave(r.part, p.lines + (int64_t)row * p.n_chunks * words + 2 * g, words, p.n_chunks);
   if ((threadIdx.x & 63) == 0) {
     s.stat[g] = st;
     s.sM[g] = st.M;
     s.sInv[g] = st.invZ;
     p.stats[(int64_t)row * G + g] = st;
-    const float2 ss = p.samp_stats[(int64_t)row * G + g];
-    s.rho[g] = exp((double)ss.x - (double)st.M) / (st.Z * (double)ss.y);
-    s.flushed[g] = 0x1p-126 * (double)ss.y;  // the filter's exponentials come out as 0 below 2^-126
+    s.rho[g] = exp((double)r.samp.x - (double)st.M) / (st.Z * (double)r.samp.y);
+    s.flushed[g] = 0x1p-126 * (double)r.samp.y;  // the filter's exponentials come out as 0 below 2^-126
   }
 }
 
 // Candidates per score chunk -> offsets of a dense list (s.chunk_off): the chunks' own slots first, the row's overflow pool
 // behind them.  Returns how many there are; -1 (workgroup-uniform): far more than planned, or fewer than k.
-__device__ __forceinline__ int candidate_offsets(const TopkCandParams& p, CandShared& s, int row) {
-  const int tid = threadIdx.x, words = chunk_line_words(p.geo.G);
-  const int raw = tid < p.n_chunks ? __float_as_int(p.lines[((int64_t)row * p.n_chunks + tid) * words + words - 1]) : 0;
+__device__ __forceinline__ int candidate_offsets(const TopkCandParams& p, CandShared& s, int row, int raw) {
+  const int tid = threadIdx.x;
   const int v = raw < p.cap_c ? raw : p.cap_c;
-  int tot, n_all;
-  const int incl = block_scan_incl<kTopkThreads>(v, s.rs.wave_tot, &tot);
+  if (tid == 0) s.n_over = 0;
+  __syncthreads();
+  if (raw > v) atomicAdd(&s.n_over, raw - v);  // rare
+  int tot;
+  const int incl = block_scan_incl(v, s.rs.wave_tot, &tot);
+  const int n_over = s.n_over;  // (all added before the scan's barrier)
   if (tid < p.n_chunks) s.chunk_off[tid] = incl - v;
   if (tid == 0) s.chunk_off[p.n_chunks] = tot;
-  block_scan_incl<kTopkThreads>(raw, s.rs.wave_tot, &n_all);
   __syncthreads();
-  return n_all > p.cap || n_all < p.k || n_all - tot > p.cap_o ? -1 : n_all;
+  const int n_all = tot + n_over;
+  return n_all > p.cap || n_all < p.k || n_over > p.cap_o ? -1 : n_all;
 }
 
 // Records of N candidates of the dense list (those at n_all or beyond: any record).  The searches advance in step, so
@@ -385,14 +407,13 @@ __global__ __launch_bounds__(kTopkThreads) void topk_cand_kernel(TopkCandParams 
   __shared__ CandShared s;
   extern __shared__ __align__(16) uint32_t bitmap[];  // one bit per eviction candidate of the row
   const int row = blockIdx.x, tid = threadIdx.x, G = p.geo.G;
+  const RowStart start = row_start(p, row);
+  const float tau = p.samp_tau[row];
   write_ends(p, row);
-  if (p.k == 0) {
-    exact_stats(p, s, row);
-    return;
-  }
-  const int n_all = candidate_offsets(p, s, row);
+  exact_stats(p, s, row, start);
+  if (p.k == 0) return;
+  const int n_all = candidate_offsets(p, s, row, start.raw);
   if (n_all < 0) {
-    exact_stats(p, s, row);
     clear_histograms(p, row);
     if (tid == 0) flag_row(p, row, 1);
     return;
@@ -429,8 +450,6 @@ __global__ __launch_bounds__(kTopkThreads) void topk_cand_kernel(TopkCandParams 
   };
   Batch b[2];
   load_batch(0, b[0]);
-  exact_stats(p, s, row);
-  __syncthreads();
   // A token the filter dropped had approximate score < tau^, so its exact score is below rho * tau^
   // (plus what exponentials flushed to zero could hide, plus fp32 slack), rho the worst head's.
   float bound;
@@ -441,7 +460,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_cand_kernel(TopkCandParams 
       rho = r > rho || !(r == r) ? r : rho;
       fl += s.flushed[g];
     }
-    bound = (float)(rho * ((double)p.samp_tau[row] + fl) * 1.001);
+    bound = (float)(rho * ((double)tau + fl) * 1.001);
   }
   int32_t* kept = p.kept_idx + (int64_t)row * (p.S + p.k + p.W);
   bool ok;
@@ -501,12 +520,13 @@ template <int DT>
 __global__ __launch_bounds__(kTopkThreads, 8) void cand_split_pq_kernel(TopkCandParams p) {
   __shared__ CandShared s;
   const int row = blockIdx.x, tid = threadIdx.x, G = p.geo.G;
+  const RowStart start = row_start(p, row);
   write_ends(p, row);
   clear_histograms(p, row);
   if (tid < kFastMaxG) s.n_list[tid] = 0;
-  exact_stats(p, s, row);
+  exact_stats(p, s, row, start);
   if (p.k == 0) return;
-  const int n_all = candidate_offsets(p, s, row);
+  const int n_all = candidate_offsets(p, s, row, start.raw);
   // A token the filter dropped for head g had approximate probability < tau^_g, so its exact one is below the
   // list's bound.  exp(x - M) / Z >= bd  <=>  x >= M + log(bd Z); lowered by more than fp32 rounding can move either side
   if (tid < G) {

@@ -29,19 +29,35 @@ __device__ __forceinline__ int64_t logit_index(const RowGeom& geo, int n_chunks,
 
 // Exact softmax statistics of one head of a row from its per-chunk partials (max, sum exp(x - max)), `stride` floats apart:
 // M = overall maximum of the fp32 logits, Z = sum_i exp(l_i - M) combined in fp64.  Called by all 64
-// lanes of a wave; every lane gets the result.
-__device__ inline RowStat merge_partials_wave(const float* pr, int stride, int n_chunks) {
+// lanes of a wave; every lane gets the result.  PartialLoads: the first 128 chunks' partials, asked for early.
+struct PartialLoads {
+  float2 v[2];
+};
+__device__ __forceinline__ PartialLoads load_partials(const float* pr, int stride, int n_chunks) {
   const int lane = threadIdx.x & 63;
-  float M = -INFINITY;
-  for (int i = lane; i < n_chunks; i += 64) M = fmaxf(M, pr[(int64_t)i * stride]);
-  M = wave_max(M);
+  PartialLoads l;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    l.v[u] = make_float2(-INFINITY, 0.f);
+    if (lane + 64 * u < n_chunks) l.v[u] = *reinterpret_cast<const float2*>(pr + (int64_t)(lane + 64 * u) * stride);
+  }
+  return l;
+}
+__device__ __forceinline__ RowStat merge_partials_wave(const PartialLoads& l, const float* pr, int stride, int n_chunks) {
+  const int lane = threadIdx.x & 63;
+  float M = fmaxf(l.v[0].x, l.v[1].x);
+  for (int i = lane + 128; i < n_chunks; i += 64) M = fmaxf(M, pr[(int64_t)i * stride]);
+  M = wave_combine<true, 1>(M);
   double z = 0.0;
-  for (int i = lane; i < n_chunks; i += 64) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (64 * u < n_chunks) z += l.v[u].y == 0.f ? 0.0 : (double)l.v[u].y * exp((double)l.v[u].x - (double)M);
+#pragma unroll 1
+  for (int i = lane + 128; i < n_chunks; i += 64) {
     const float2 v = *reinterpret_cast<const float2*>(pr + (int64_t)i * stride);
     z += (double)v.y * exp((double)v.x - (double)M);
   }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) z += __shfl_xor(z, o);
+  z = group_sum_f64<64>(z);
   RowStat st;
   st.M = M;
   st.Z = z;
@@ -54,7 +70,7 @@ __device__ inline RowStat merge_partials_wave(const ChunkPartial* pr, int n_chun
   const int lane = threadIdx.x & 63;
   float M = -INFINITY;
   for (int i = lane; i < n_chunks; i += 64) M = fmaxf(M, pr[i].max);
-  M = wave_max(M);
+  M = wave_combine<true, 1>(M);
   double z = 0.0;
 #pragma unroll 1
   for (int i = lane; i < n_chunks; i += 64) z += pr[i].sum * exp((double)pr[i].max - (double)M);
@@ -66,31 +82,26 @@ __device__ inline RowStat merge_partials_wave(const ChunkPartial* pr, int n_chun
   return st;
 }
 
-// Largest digit b such that count(digits >= b) >= k_rem; returns b and the rank left inside it.
+// Largest digit b such that count(digits >= b) >= k_rem; returns b and the rank left inside it (0 and 1 if there are fewer
+// than k_rem).  A barrier has to lie between an earlier block scan on wave_tot and this.
 __device__ inline void pick_digit(const int* hist, int* wave_tot, int* pick /* [2] */, int nb, int k_rem, int* bin,
                                   int* rem) {
   const int t = threadIdx.x;
-  if (t == 0) {
-    pick[0] = 0;
-    pick[1] = 1;
-  }
   const int i0 = nb - 1 - 2 * t, i1 = nb - 2 - 2 * t;  // descending digits
   const int c0 = i0 >= 0 ? hist[i0] : 0;
   const int c1 = i1 >= 0 ? hist[i1] : 0;
   int tot;
-  const int incl = block_scan_incl<kTopkThreads>(c0 + c1, wave_tot, &tot);
+  const int incl = block_scan_incl(c0 + c1, wave_tot, &tot);
   const int before = incl - c0 - c1;
-  if (before < k_rem && k_rem <= before + c0) {
-    pick[0] = i0;
-    pick[1] = k_rem - before;
-  } else if (before + c0 < k_rem && k_rem <= incl) {
-    pick[0] = i1;
-    pick[1] = k_rem - before - c0;
+  if (before < k_rem && k_rem <= incl) {  // one thread, or none (everybody has read an earlier pick before the scan's barrier)
+    const bool first = k_rem <= before + c0;
+    pick[0] = first ? i0 : i1;
+    pick[1] = k_rem - before - (first ? 0 : c0);
   }
   __syncthreads();
-  *bin = pick[0];
-  *rem = pick[1];
-  __syncthreads();
+  const bool found = k_rem >= 1 && k_rem <= tot;
+  *bin = found ? pick[0] : 0;
+  *rem = found ? pick[1] : 1;
 }
 __device__ inline void pick_digit(TopkShared& sh, int nb, int k_rem, int* bin, int* rem) {
   pick_digit(sh.hist, sh.wave_tot, sh.pick, nb, k_rem, bin, rem);
@@ -135,36 +146,34 @@ __device__ inline void radix_select(TopkShared& sh, const float* cand, int64_t E
 }
 
 // Ordered output of a selection kept as a bitmap in LDS (16-byte aligned): writes first + (index of
-// the j-th set bit) to out[j] for j < k.  Every thread takes four consecutive words per round.
+// the j-th set bit) to out[j] for j < k.  Every thread takes one, two or four consecutive words per round: a thread's
+// words are gone through bit by bit, so a short bitmap is spread over all of them.
 __device__ inline void bitmap_compact(const uint32_t* bitmap, int n_words, int first, int32_t* out, int k,
                                       int* wave_tot) {
+  const int per = n_words <= kTopkThreads ? 1 : n_words <= 2 * kTopkThreads ? 2 : 4;
   int run = 0;
-  for (int w0 = 0; w0 < n_words; w0 += 4 * kTopkThreads) {
-    const int w = w0 + 4 * (int)threadIdx.x;
-    uint32_t word[4] = {0u, 0u, 0u, 0u};
-    if (w + 3 < n_words) {
-      const uint4 v = *reinterpret_cast<const uint4*>(bitmap + w);
-      word[0] = v.x, word[1] = v.y, word[2] = v.z, word[3] = v.w;
-    } else {
+  for (int w0 = 0; w0 < n_words; w0 += per * kTopkThreads) {
+    const int w = w0 + per * (int)threadIdx.x;
+    uint32_t word[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (w + j < n_words) word[j] = bitmap[w + j];
-    }
+    for (int j = 0; j < 4; ++j) word[j] = j < per && w + j < n_words ? bitmap[w + j] : 0u;
     const int cnt = __popc(word[0]) + __popc(word[1]) + __popc(word[2]) + __popc(word[3]);
     int tot;
-    const int incl = block_scan_incl<kTopkThreads>(cnt, wave_tot, &tot);
+    if (w0 > 0) __syncthreads();  // wave_tot
+    const int incl = block_scan_incl(cnt, wave_tot, &tot);
     int pos = run + incl - cnt;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t x = word[j];
+    run += tot;
+    int at = first + w * 32;
+#pragma unroll 1
+    for (int j = 0; j < per; ++j, at += 32) {
+      uint32_t x = j == 0 ? word[0] : j == 1 ? word[1] : j == 2 ? word[2] : word[3];
       while (x) {
         const int b = __ffs(x) - 1;
         x &= x - 1;
-        if (pos < k) out[pos] = (int32_t)(first + (w + j) * 32 + b);
+        if (pos < k) out[pos] = (int32_t)(at + b);
         ++pos;
       }
     }
-    run += tot;
   }
 }
 
@@ -210,8 +219,7 @@ __device__ inline double refined_term_wave(const RowGeom& geo, const void* q_las
   const int64_t q_off = ((int64_t)prob * geo.Hq + c * geo.G + g) * D;
   double acc = 0.0;
   for (int j = lane; j < D; j += 64) acc += elem_f64<DT>(q_last, q_off + j) * elem_f64<DT>(K, k_off + j);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
+  acc = group_sum_f64<64>(acc);
   return exp(acc * (1.0 / sqrt((double)D)) - (double)st.M) / st.Z;
 }
 template <int DT>
@@ -415,7 +423,7 @@ struct RegSelect {
     double term[kMaxBand];  // refine_band: fp64 terms of a batch of (member, head)
   };
   int wave_tot[kTopkWaves], pick[2];
-  int red_min[kTopkWaves], red_max[kTopkWaves];
+  int red[2][kTopkWaves];  // ~smallest, largest key of each wave
   int band_tok[kMaxBand];
   float band_v[kMaxBand];
   int n_band, n_above;
@@ -438,19 +446,20 @@ __device__ __forceinline__ void bracket_kth(RegSelect& sh, Each each, int k, uin
     if (key >= 0) mn = key < mn ? key : mn;
     mx = key > mx ? key : mx;
   });
-  mn = wave_min_i(mn);
-  mx = wave_max_i(mx);
+  const int wmn = wave_max_i(~mn), wmx = wave_max_i(mx);
   if ((tid & 63) == 0) {
-    sh.red_min[wave] = mn;
-    sh.red_max[wave] = mx;
+    sh.red[0][wave] = wmn;
+    sh.red[1][wave] = wmx;
   }
   if (tid == 0) sh.n_band = sh.n_above = 0;
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kTopkWaves; ++w) {
-    mn = sh.red_min[w] < mn ? sh.red_min[w] : mn;
-    mx = sh.red_max[w] > mx ? sh.red_max[w] : mx;
-  }
+  int e = sh.red[(tid >> 4) & 1][tid & 15];  // rows 0, 2 of the wave: ~smallest, rows 1, 3: largest
+  e = max(e, dpp_rot_i32<0x128>(e));         // row_ror
+  e = max(e, dpp_rot_i32<0x124>(e));
+  e = max(e, dpp_rot_i32<0x122>(e));
+  e = max(e, dpp_rot_i32<0x121>(e));
+  mn = ~__builtin_amdgcn_readlane(e, 0);
+  mx = __builtin_amdgcn_readlane(e, 16);
   const uint32_t range = mx >= mn ? (uint32_t)(mx - mn) : 0u;
   const int s1 = range < (uint32_t)kHistBins ? 0 : 21 - __clz((int)range);  // range >> s1 < 2048
   each([&](float v) {

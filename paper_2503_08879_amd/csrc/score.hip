@@ -743,7 +743,9 @@ __global__ __launch_bounds__(64) void stats_kernel(StatsParams p) {
   if (p.ghist)
     for (int b = lane; b < kHistBins * p.n_lists; b += 64) p.ghist[(int64_t)row * p.n_lists * kHistBins + b] = 0;
   for (int g = 0; g < p.G; ++g) {
-    const RowStat st = merge_partials_wave(p.lines + (int64_t)row * p.n_chunks * chunk_line_words(p.G) + 2 * g, chunk_line_words(p.G), p.n_chunks);
+    const int stride = chunk_line_words(p.G);
+    const float* pr = p.lines + (int64_t)row * p.n_chunks * stride + 2 * g;
+    const RowStat st = merge_partials_wave(load_partials(pr, stride, p.n_chunks), pr, stride, p.n_chunks);
     if (lane == 0) p.stats[(int64_t)row * p.G + g] = st;
   }
 }

@@ -598,7 +598,8 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
 #pragma unroll
       for (int e = 0; e < 4; ++e) eq += __float_as_uint(x[e]) == prefix;
       int tot;
-      int at = before + block_scan_incl<kTopkThreads>(eq, sh.wave_tot, &tot) - eq;
+      __syncthreads();  // wave_tot
+      int at = before + block_scan_incl(eq, sh.wave_tot, &tot) - eq;
       uint32_t nib = 0u;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
