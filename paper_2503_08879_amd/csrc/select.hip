@@ -638,8 +638,16 @@ __global__ __launch_bounds__(kTopkThreads) void row_stats_kernel(RowStatsParams 
 // ---- gather -----------------------------------------------------------------------------------
 constexpr int kGatherThreads = 256;
 constexpr int kGatherTokens = 64;  // reduced-cache rows one workgroup copies
+// From so many bytes written on, the rows are stored nontemporally, up to so many bytes of keys.  Plain stores leave the Infinity
+// Cache (256 MB) full of lines that have yet to go to memory, and whoever streams next pays for them at a multiple of their
+// bytes (see the filtering pass's candidates).  Repeated passes, plain and nontemporal, us: 67 MB written (64 rows x 8K tokens)
+// 69 and 71, (64 x 32K) 148 and 149; 134 MB (128 x 32K) 271 and 262; 268 MB (256 x 8K) 226 and 208, (256 x 32K) 500 and 475;
+// 470 MB (112 x 128K, 7 lists) 905 and 875; 503 MB (256 x 64K) 912 and 870.  Where the pass itself reads 8.6 GB, the gather and the
+// sample gain as much and the filtering pass loses it again: 256 x 128K, 236 MB 1439 and 1426, 537 MB 1540 and 1574, 1057 MB 1772
+// and 1755.
+constexpr int64_t kStreamGather = 96ll << 20, kStreamGatherKeys = 6ll << 30;
 
-template <int LPT>
+template <int LPT, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherParams p, int eb) {
   const int row = blockIdx.y;
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
@@ -672,8 +680,13 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherParams p, 
   for (int it = 0; it < NIT; ++it) {
     const int t = t0 + it * TPI + sub;
     if (t < p.n_kept) {
-      st16(Kc.at(t) + cl * 16, a[it]);
-      st16(Vc.at(t) + cl * 16, b[it]);
+      if (STREAM) {
+        st16_stream(Kc.at(t) + cl * 16, a[it]);
+        st16_stream(Vc.at(t) + cl * 16, b[it]);
+      } else {
+        st16(Kc.at(t) + cl * 16, a[it]);
+        st16(Vc.at(t) + cl * 16, b[it]);
+      }
     }
   }
 }
@@ -735,12 +748,20 @@ hipError_t launch_gather(const GatherParams& p, hipStream_t s) {
   const int eb = p.geo.dtype == DT_BF16 ? 2 : 4;
   const int lpt = p.geo.D * eb / 16;
   dim3 grid((unsigned)((p.n_kept + kGatherTokens - 1) / kGatherTokens), (unsigned)rows);
+  const int64_t token_bytes = (int64_t)rows * p.geo.D * eb;
+  const bool stream = 2 * token_bytes * p.n_kept > kStreamGather && token_bytes * p.geo.L <= kStreamGatherKeys;
+#define SAGEKV_LAUNCH(LPT)                                                                          \
+  if (stream)                                                                                        \
+    hipLaunchKernelGGL((gather_kernel<LPT, true>), grid, dim3(kGatherThreads), 0, s, p, eb);         \
+  else                                                                                               \
+    hipLaunchKernelGGL((gather_kernel<LPT, false>), grid, dim3(kGatherThreads), 0, s, p, eb)
   switch (lpt) {
-    case 8: hipLaunchKernelGGL(gather_kernel<8>, grid, dim3(kGatherThreads), 0, s, p, eb); break;
-    case 16: hipLaunchKernelGGL(gather_kernel<16>, grid, dim3(kGatherThreads), 0, s, p, eb); break;
-    case 32: hipLaunchKernelGGL(gather_kernel<32>, grid, dim3(kGatherThreads), 0, s, p, eb); break;
+    case 8: SAGEKV_LAUNCH(8); break;
+    case 16: SAGEKV_LAUNCH(16); break;
+    case 32: SAGEKV_LAUNCH(32); break;
     default: return hipErrorInvalidValue;
   }
+#undef SAGEKV_LAUNCH
   return hipGetLastError();
 }
 
