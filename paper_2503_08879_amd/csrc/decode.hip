@@ -118,47 +118,6 @@ __device__ __forceinline__ void row_done(const DecodeParams& p, const StepGeom& 
   }
 }
 
-// out[head g][dim j] of a row from its slices: sum_s acc_s e^{m_s - M} / sum_s l_s e^{m_s - M}.
-// One pass; the loads of up to 32 slices are all issued before the first is used (one memory round
-// trip), the arithmetic then goes through them eight at a time.
-__device__ __forceinline__ float merge_slices(const DecodeParams& p, int row, int g, int j) {
-  const float* ml = reinterpret_cast<const float*>(p.part_ml + (int64_t)row * p.n_splits * p.G + g);
-  const float* a = p.part_acc + ((int64_t)row * p.n_splits * p.G + g) * p.D + j;
-  float M = -INFINITY, num = 0.f, den = 0.f;
-  for (int s0 = 0; s0 < p.n_splits; s0 += 32) {
-    float vm[32], vl[32], av[32];
-#pragma unroll
-    for (int u = 0; u < 32; ++u) {
-      const int s = s0 + u < p.n_splits ? s0 + u : p.n_splits - 1;
-      vm[u] = ml[(int64_t)s * p.G * 2];
-      vl[u] = ml[(int64_t)s * p.G * 2 + 1];
-      av[u] = a[(int64_t)s * p.G * p.D];
-    }
-#pragma unroll
-    for (int u0 = 0; u0 < 32; u0 += 8) {
-      if (s0 + u0 >= p.n_splits) break;
-      float Mn = M;
-#pragma unroll
-      for (int u = u0; u < u0 + 8; ++u) {
-        if (s0 + u >= p.n_splits) vm[u] = -INFINITY;
-        Mn = fmaxf(Mn, vm[u]);
-      }
-      if (Mn == -INFINITY) continue;  // nothing attended in these slices (uniform over the workgroup)
-      const float f0 = (M == -INFINITY) ? 0.f : exp_fast(M - Mn);
-      num *= f0;
-      den *= f0;
-#pragma unroll
-      for (int u = u0; u < u0 + 8; ++u) {
-        const float f = (vm[u] == -INFINITY) ? 0.f : exp_fast(vm[u] - Mn);
-        num = fmaf(av[u], f, num);
-        den = fmaf(vl[u], f, den);
-      }
-      M = Mn;
-    }
-  }
-  return num / den;
-}
-
 // End of a decode workgroup that owns its whole row: the row is done.  (Sliced rows are completed
 // by the merge launch.)
 __device__ __forceinline__ void finish_row(const DecodeParams& p, const StepGeom& sg) {
@@ -292,18 +251,18 @@ __global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeParams p, int g0)
   // merge the TPL token groups of the wave (same cl, different tq)
 #pragma unroll
   for (int g = 0; g < GB; ++g) {
-    float M = m[g];
-#pragma unroll
-    for (int o = LPT; o < 64; o <<= 1) M = fmaxf(M, __shfl_xor(M, o));
+    // (by row swaps: LDS shuffles, twelve in a row for two heads of 64 dims, took 2.5 of the 6.4 us of a tiny step)
+    static_assert(LPT == 16 || LPT == 32, "");
+    auto total = [](float x, float f) {  // sum of x * f; a lane's own product enters its first addition unrounded
+      if (LPT == 16) return swap32_sum(fmaf(x, f, swap16(x * f)));
+      return swap32_sum(x * f);
+    };
+    const float M = swap32_max(LPT == 16 ? swap16_max(m[g]) : m[g]);
     const float f = (m[g] == -INFINITY) ? 0.f : exp_fast(m[g] - M);
-    float ls = l[g] * f;
-#pragma unroll
-    for (int o = LPT; o < 64; o <<= 1) ls += __shfl_xor(ls, o);
+    const float ls = total(l[g], f);
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-      float a = acc[g][e] * f;
-#pragma unroll
-      for (int o = LPT; o < 64; o <<= 1) a += __shfl_xor(a, o);
+      const float a = total(acc[g][e], f);
       if (tq == 0) s_acc[wave][g][cl * EPL + e] = a;
     }
     if (lane == 0) s_ml[wave][g] = make_float2(M, ls);
@@ -586,8 +545,74 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {  // finite, non-negative
   return u >> 16;
 }
 
+// Loads of that kernel.  A wave's it-th block holds the BT tokens from first(it) on; where all of them are in the slice, load i is
+// a wave-uniform address + 16 bytes per lane, and nothing else is computed per load: the new token is not looked for in
+// the addresses, the one block that holds its slot is patched afterwards.  (One layer's step spent 1.9 us on 16 times 13
+// address instructions and on eight rounds of kernel arguments before its first key was asked for.)
+// PAGED: as BlockSource.
+template <bool PG, bool STREAM, int D, int BT, int NW>
+struct SliceLoads {
+  static constexpr int ROWB = D * 2, CH = D / 8, TPL = 64 / CH, NLOAD = BT / TPL, GPB = BT / 16;
+  int t_begin, t_end, slot, wave, lane;
+  // paged: this problem's block table; page ids of the 64 groups at hand
+  const int32_t* tab;
+  int shift, n_pages, my_page;
+
+  __device__ __forceinline__ int first(int it) const { return t_begin + (wave + it * NW) * BT; }
+  __device__ __forceinline__ void fill_pages(int it0) {
+    if (!PG) return;
+    int tok = first(it0 + lane / GPB) + (lane % GPB) * 16;
+    tok = tok < t_end ? tok : t_begin;
+    const int pid = tab[tok >> shift];
+    my_page = pid < 0 ? 0 : (pid >= n_pages ? n_pages - 1 : pid);
+  }
+  __device__ __forceinline__ bool refill_before(int it) const { return PG && ((it * GPB) & 63) == 0; }
+  // this lane's token of load i; past the slice one that is inside it (its first, in pages the first of the group)
+  __device__ __forceinline__ int token(int it, int i) const {
+    const int b0 = first(it), tok = b0 + i * TPL + lane / CH, g0 = b0 + (i * TPL) / 16 * 16;
+    return tok < t_end ? tok : PG && g0 < t_end ? g0 : t_begin;
+  }
+  __device__ __forceinline__ uint4 ld(const char* p) const { return STREAM ? ld16_stream(p) : ld16(p); }
+  // base: the row's first token, or the pool advanced to the row's KV head
+  __device__ __forceinline__ void load(int it, const char* base, int64_t page_bytes, uint4 (&dst)[NLOAD]) const {
+    const int b0 = first(it);
+    if (b0 + BT <= t_end) {  // wave-uniform
+#pragma unroll
+      for (int i = 0; i < NLOAD; ++i) {
+        const int tok = b0 + i * TPL;
+        const char* p = base + (int64_t)tok * ROWB;
+        if (PG)
+          p = base + (int64_t)__builtin_amdgcn_readlane(my_page, (it * GPB + (i * TPL) / 16) & 63) * page_bytes +
+              (int64_t)(tok & ((1 << shift) - 1)) * ROWB;
+        dst[i] = ld(p + lane * 16);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NLOAD; ++i) {
+        const int tok = token(it, i);
+        const char* p = base + (int64_t)tok * ROWB;
+        if (PG)
+          p = base + (int64_t)__builtin_amdgcn_readlane(my_page, (it * GPB + (i * TPL) / 16) & 63) * page_bytes +
+              (int64_t)(tok & ((1 << shift) - 1)) * ROWB;
+        dst[i] = ld(p + (lane % CH) * 16);
+      }
+    }
+  }
+  // Does the block hold the new token (or, past the slice's end, a stand-in that is the new token)?  wave-uniform
+  __device__ __forceinline__ bool holds_slot(int it) const {
+    const int b0 = first(it);
+    return slot >= 0 && ((slot >= b0 && slot < b0 + BT) || (slot == t_begin && b0 + BT > t_end));
+  }
+  // fresh: this lane's 16 bytes of the new token, loaded early
+  __device__ __forceinline__ void patch(int it, const uint4& fresh, uint4 (&dst)[NLOAD]) const {
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i)
+      if (token(it, i) == slot) dst[i] = fresh;
+  }
+};
+
 template <int D, int GPAD, int NW, bool STREAM, bool PG>
-__global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p, int g0, int gb) {
+__global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void decode_pv_mfma_kernel(DecodeParams p, int g0, int gb) {
   constexpr int BT = 32;
   constexpr int CH = D / 8, TPL = 64 / CH, NLOAD = BT / TPL, KSTEPS = D / 32;
   constexpr int TILES = 16 / GPAD;                       // 16-token tiles sharing a q.K accumulator
@@ -601,23 +626,64 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   __shared__ uint4 kbuf[NW][BT * CH];  // K staging, then V staging, at the end the waves' accumulators
   __shared__ __attribute__((aligned(16))) unsigned short pT[NW][16][BT];  // weights, bf16, [head][token]
   __shared__ float2 s_ml[NW][GPAD];
-  __shared__ uint4 qbuf[2][NT][KSTEPS][64];
 
   const int row = blockIdx.y, split = blockIdx.x;
-  const int prob = row / p.Hkv, c = row % p.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tq = lane / CH, cl = lane % CH;  // load role: token sub-index, 16-byte chunk
   const int n = lane & 15, j = lane >> 4;    // MFMA role: column, row block / k-group
+  const int64_t head0 = (int64_t)row * p.G + g0;  // = problem * Hq + KV head * G + g0
 
-  const CacheRow Kr = cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, 2);
-  const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 2);
-  const char* kn = p.k_new ? (const char*)p.k_new + (int64_t)row * ROWB : nullptr;
-  const char* vn = p.v_new ? (const char*)p.v_new + (int64_t)row * ROWB : nullptr;
+  SliceLoads<PG, STREAM, D, BT, NW> src;
+  const char *Kb, *Vb;
+  if (PG) {
+    const int prob = row / p.Hkv, c = row % p.Hkv;
+    Kb = (const char*)p.Kc + ((int64_t)c << p.cpm.shift) * ROWB;
+    Vb = (const char*)p.Vc + ((int64_t)c << p.cpm.shift) * ROWB;
+    src.tab = p.cpm.table + (int64_t)prob * p.cpm.pitch;
+    src.shift = p.cpm.shift;
+    src.n_pages = p.cpm.n_pages;
+  } else {
+    Kb = (const char*)p.Kc + (int64_t)row * p.cap * ROWB;
+    Vb = (const char*)p.Vc + (int64_t)row * p.cap * ROWB;
+  }
+  const int64_t k_page = PG ? p.cpm.ks_page * 2 : 0, v_page = PG ? p.cpm.vs_page * 2 : 0;
   StepGeom sg = step_geom<true>(p);
   int ring_n = 0;
   if (slot_is_late(p)) ring_n = p.ring[0];  // on its way while the first loads are issued
   const int t_begin = split * sg.tokens_per_split;
   const int t_end = min(sg.len, t_begin + sg.tokens_per_split);
+  const int nblk = (t_end - t_begin + BT - 1) / BT;
+  src.t_begin = t_begin, src.t_end = t_end, src.slot = sg.slot, src.wave = wave, src.lane = lane, src.my_page = 0;
+
+  // The queries' loads go out first, then K's, then V's: loads complete in order, so each is waited for when it is
+  // needed and no later one with it.
+  // A operand of the q.K product, the same for every tile: lane (row m = n, k-group j) holds q[head m % GPAD][8*(4*kc + j) ..+8], so a
+  // product holds every head's logits 16 / GPAD times over and a lane takes the tile of its slot.
+  uint4 qa[KSTEPS], qs[KSTEPS];  // qs: the query the sink tokens are scored with, when the caller gives one
+  {
+    const int64_t at = ((head0 + n % GPAD) * D + 8 * j) * 2;
+    const bool mine = n % GPAD < gb;
+#pragma unroll
+    for (int kc = 0; kc < KSTEPS; ++kc) {
+      qa[kc] = qs[kc] = make_uint4(0u, 0u, 0u, 0u);
+      if (mine) qa[kc] = ld16((const char*)p.q + at + 64 * kc);
+    }
+    if (p.q_sink && mine) {
+#pragma unroll
+      for (int kc = 0; kc < KSTEPS; ++kc) qs[kc] = ld16((const char*)p.q_sink + at + 64 * kc);
+    }
+  }
+  uint4 k_fresh = make_uint4(0u, 0u, 0u, 0u), v_fresh = k_fresh;  // this lane's chunk of the new token
+  if (p.k_new) {
+    k_fresh = ld16((const char*)p.k_new + (int64_t)row * ROWB + cl * 16);
+    v_fresh = ld16((const char*)p.v_new + (int64_t)row * ROWB + cl * 16);
+  }
+  uint4 kv[NLOAD], vv[NLOAD];
+  if (wave < nblk) {
+    src.fill_pages(0);
+    src.load(0, Kb, k_page, kv);
+    src.load(0, Vb, v_page, vv);
+  }
 
   // q.K accumulator a, register r of lane (j, n): head hbase + r, token tile a * TILES + tslot, column n
   const int hbase = (4 * j) % GPAD, tslot = (4 * j) / GPAD;
@@ -630,60 +696,25 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
   f32x4_t acc[NDT];  // out[head 4j + r][dim 16 * nd + n]
 #pragma unroll
   for (int nd = 0; nd < NDT; ++nd) acc[nd] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
   uint4* buf = kbuf[wave];
   reinterpret_cast<uint4*>(&pT[wave][0][0])[lane] = make_uint4(0u, 0u, 0u, 0u);  // rows of absent heads stay 0
-  const int nblk = (t_end - t_begin + BT - 1) / BT;
-  uint4 kv[NLOAD], vv[NLOAD];
-  BlockSource<PG, ROWB, BT, NW, TPL> src = {Kr, Vr, t_begin, t_end, sg.slot, wave, 0};
-  auto load_block = [&](int it, uint4* dst, const CacheRow& base, const char* fresh) {
-#pragma unroll
-    for (int i = 0; i < NLOAD; ++i) {
-      const char* a = src.at(base, fresh, it, i, tq) + cl * 16;
-      dst[i] = STREAM ? ld16_stream(a) : ld16(a);
-    }
-  };
-  // The queries' loads go out first, then K's, then V's: loads complete in order, so each is waited for when it is
-  // needed and no later one with it.
-  constexpr int QN = (NT * KSTEPS * 64 + kThreads - 1) / kThreads;
-  auto q_operand = [&](const void* q, int it) -> uint4 {
-    const int l = it & 63, kc = (it >> 6) % KSTEPS, ts = (it / (64 * KSTEPS)) % NT;
-    const int m = l & 15, jj = l >> 4;
-    if (m % GPAD >= gb || m / GPAD != ts % TILES) return make_uint4(0u, 0u, 0u, 0u);
-    const int h = c * p.G + g0 + m % GPAD;
-    return ld16((const char*)q + (((int64_t)prob * p.Hq + h) * D + (4 * kc + jj) * 8) * 2);
-  };
-  uint4 qv[QN];
-#pragma unroll
-  for (int i = 0; i < QN; ++i)
-    if (tid + i * kThreads < NT * KSTEPS * 64) qv[i] = q_operand(p.q, tid + i * kThreads);
-  if (wave < nblk) {
-    src.fill_pages(0);
-    load_block(0, kv, Kr, kn);
-    load_block(0, vv, Vr, vn);
-  }
-  if (slot_is_late(p)) {
-    src.slot = late_slot(p, sg, ring_n);
-    src.patch_first(kv, vv, kn, vn, tq, cl);
-  }
+
+  if (slot_is_late(p)) src.slot = late_slot(p, sg, ring_n);
   const int slot = src.slot;
   if (slot >= t_begin && slot < t_end && tid < CH) {  // Step 4: the new token enters the window
-    st16(Kr.at(slot) + tid * 16, ld16(kn + tid * 16));
-    st16(Vr.at(slot) + tid * 16, ld16(vn + tid * 16));
+    const CacheRow Kr = cache_row(p.Kc, p.cpm, false, row / p.Hkv, row % p.Hkv, row, p.cap, ROWB, 2);
+    const CacheRow Vr = cache_row(p.Vc, p.cpm, true, row / p.Hkv, row % p.Hkv, row, p.cap, ROWB, 2);
+    st16(Kr.at(slot) + tid * 16, k_fresh);
+    st16(Vr.at(slot) + tid * 16, v_fresh);
   }
-  uint4* q_lds = &qbuf[0][0][0][0];
-#pragma unroll
-  for (int i = 0; i < QN; ++i)
-    if (tid + i * kThreads < NT * KSTEPS * 64) q_lds[tid + i * kThreads] = qv[i];
-  if (p.q_sink)
-    for (int it = tid; it < NT * KSTEPS * 64; it += kThreads) q_lds[NT * KSTEPS * 64 + it] = q_operand(p.q_sink, it);
-  __syncthreads();
 
   // V staging swizzle (16-byte chunk ^= vswz(token)): the four tokens a 16-lane group reads together
   // land in different banks
   auto vswz = [](int t) { return CH == 16 ? (((t & 3) << 1) | (((t >> 3) & 1) << 3)) : ((t & 3) << 1); };
 
   for (int b = wave, it = 0; b < nblk; b += NW, ++it) {
+    const bool patch = src.holds_slot(it);  // wave-uniform, one block of the row
+    if (patch) src.patch(it, k_fresh, kv);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // last block's reads of the buffer are done
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
@@ -694,36 +725,48 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
     const bool more = b + NW < nblk;
     if (more) {
       if (src.refill_before(it + 1)) src.fill_pages(it + 1);
-      load_block(it + 1, kv, Kr, kn);
+      src.load(it + 1, Kb, k_page, kv);
     }
 
-    f32x4_t d[NACC], ds[NACC];
+    const int tok0 = t_begin + b * BT;
+    f32x4_t d[NACC];
+    auto qk = [&](const uint4 (&q)[KSTEPS], f32x4_t (&out)[NACC]) {
 #pragma unroll
-    for (int a = 0; a < NACC; ++a) d[a] = ds[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    const bool sink_blk = p.q_sink && t_begin + b * BT < p.qs_S;  // wave-uniform: the block holds sink tokens
+      for (int ts = 0; ts < NT; ++ts) {
+        const int t = ts * 16 + n;
+        f32x4_t x = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ts = 0; ts < NT; ++ts) {
-      const int t = ts * 16 + n, a = ts / TILES;
+        for (int kc = 0; kc < KSTEPS; ++kc) {
+          const uint4 bb = buf[t * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
+          x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, q[kc]), __builtin_bit_cast(bf16x8_t, bb), x, 0, 0, 0);
+        }
 #pragma unroll
-      for (int kc = 0; kc < KSTEPS; ++kc) {
-        const uint4 bb = buf[t * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
-        d[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qbuf[0][ts][kc][lane]),
-                                                       __builtin_bit_cast(bf16x8_t, bb), d[a], 0, 0, 0);
-        if (sink_blk)
-          ds[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qbuf[1][ts][kc][lane]),
-                                                          __builtin_bit_cast(bf16x8_t, bb), ds[a], 0, 0, 0);
+        for (int r = 0; r < 4; ++r) out[ts / TILES][r] = ts % TILES == 0 || tslot == ts % TILES ? x[r] : out[ts / TILES][r];
       }
+    };
+    qk(qa, d);
+    if (p.q_sink && tok0 < p.qs_S) {  // wave-uniform: the block holds sink tokens
+      f32x4_t ds[NACC];
+      qk(qs, ds);
+#pragma unroll
+      for (int a = 0; a < NACC; ++a)
+        if (tok0 + (a * TILES + tslot) * 16 + n < p.qs_S) d[a] = ds[a];
     }
     float x[NACC][4];
 #pragma unroll
     for (int a = 0; a < NACC; ++a) {
-      const int tile = a * TILES + tslot;
-      const int tok = t_begin + b * BT + tile * 16 + n;
+      const int tile = a * TILES + tslot, tok = tok0 + tile * 16 + n;
+      const bool in = tile < NT && tok < t_end;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        x[a][r] = (tile < NT && tok < t_end && hbase + r < gb && head_attends(p.pq_S, p.pq_k, p.G, g0 + hbase + r, tok))
-                      ? (sink_blk && tok < p.qs_S ? ds[a][r] : d[a][r]) * p.scale
-                      : -INFINITY;
+      for (int r = 0; r < 4; ++r) x[a][r] = in && hbase + r < gb ? d[a][r] * p.scale : -INFINITY;
+      if (p.pq_k > 0) {  // per-query rows: a list's token belongs to one head (see head_attends)
+        const int u = tok - p.pq_S;
+        if (u >= 0 && u < p.G * p.pq_k) {
+          const int own = u / p.pq_k - g0 - hbase;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[a][r] = own == r ? x[a][r] : -INFINITY;
+        }
+      }
     }
     // online softmax, once per (token, head); lanes with the same heads agree on the maximum
     float corr[4];
@@ -733,8 +776,8 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
 #pragma unroll
       for (int a = 1; a < NACC; ++a) bm = fmaxf(bm, x[a][r]);
       bm = group16_max(bm);
-#pragma unroll
-      for (int o = 16 * (GPAD / 4); o < 64; o <<= 1) bm = fmaxf(bm, __shfl_xor(bm, o));
+      if (GPAD <= 4) bm = swap16_max(bm);
+      if (GPAD <= 8) bm = swap32_max(bm);
       const float mn = fmaxf(m_run[r], bm);
       corr[r] = (mn == -INFINITY) ? 1.f : exp_fast(m_run[r] - mn);
       float lsum = 0.f;
@@ -751,13 +794,14 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // weights visible; q.K reads of the buffer done
 
     // V of the block into the staging buffer, V of the next block into the registers
+    if (patch) src.patch(it, v_fresh, vv);
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i) {
       const int t = i * TPL + tq;
       buf[t * CH + (cl ^ vswz(t))] = vv[i];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (more) load_block(it + 1, vv, Vr, vn);
+    if (more) src.load(it + 1, Vb, v_page, vv);
 
     // out += P.V: A = weights [head n][tokens 8j..8j+7], B = values [tokens 8j..8j+7][dim 16 nd + n]
     const uint4 pa = *reinterpret_cast<const uint4*>(&pT[wave][n][8 * j]);
@@ -786,53 +830,84 @@ __global__ __launch_bounds__(NW * 64) void decode_pv_mfma_kernel(DecodeParams p,
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     float ls = group_sum<16>(l_part[r]);
-#pragma unroll
-    for (int o = 16 * (GPAD / 4); o < 64; o <<= 1) ls += __shfl_xor(ls, o);
+    if (GPAD <= 4) ls = swap16_sum(ls);
+    if (GPAD <= 8) ls = swap32_sum(ls);
     if (n == 0 && j < GPAD / 4) s_ml[wave][hbase + r] = make_float2(m_run[r], ls);
   }
-  __syncthreads();  // every wave is done with its staging buffer: reuse it for the accumulators
-  float* s_acc = reinterpret_cast<float*>(&kbuf[0][0]);  // [NW][GPAD][D]
+  // a wave's accumulators go to its own staging buffer, [GPAD][D]
+  constexpr int kAccStride = BT * CH * 4;  // floats between the waves' buffers
+  float* s_acc = reinterpret_cast<float*>(&kbuf[0][0]);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
   for (int nd = 0; nd < NDT; ++nd)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (4 * j + r < GPAD) s_acc[((wave * GPAD) + 4 * j + r) * D + nd * 16 + n] = acc[nd][r];
+      if (4 * j + r < GPAD) s_acc[wave * kAccStride + (4 * j + r) * D + nd * 16 + n] = acc[nd][r];
   __syncthreads();
 
   const bool single = p.n_splits == 1;
-  float* pa_out = p.part_acc + (((int64_t)row * p.n_splits + split) * p.G + g0) * D;
-  float2* pml = p.part_ml + ((int64_t)row * p.n_splits + split) * p.G + g0;
-  for (int it = tid; it < gb * D; it += kThreads) {
-    const int g = it / D, jj = it % D;
-    float M = s_ml[0][g].x;
+  const int64_t part = ((int64_t)row * p.n_splits + split) * p.G + g0;
 #pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_ml[w][g].x);
+  for (int i0 = 0; i0 < GPAD * D; i0 += kThreads) {
+    const int g = (i0 + tid) / D, jj = tid % D;
+    if (g >= gb) break;
+    float2 ml[NW];
+    float M = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      ml[w] = s_ml[w][g];
+      M = fmaxf(M, ml[w].x);
+    }
     float a = 0.f, ls = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float2 ml = s_ml[w][g];
-      const float f = (ml.x == -INFINITY) ? 0.f : exp_fast(ml.x - M);
-      a += s_acc[((w * GPAD) + g) * D + jj] * f;
-      ls += ml.y * f;
+      const float f = (ml[w].x == -INFINITY) ? 0.f : exp_fast(ml[w].x - M);
+      a += s_acc[w * kAccStride + g * D + jj] * f;
+      ls += ml[w].y * f;
     }
     if (single) {
-      p.out[((int64_t)prob * p.Hq + c * p.G + g0 + g) * D + jj] = a / ls;
+      p.out[(head0 + g) * D + jj] = a / ls;
     } else {
-      pa_out[(int64_t)g * D + jj] = a;
-      if (jj == 0) pml[g] = make_float2(M, ls);
+      p.part_acc[(part + g) * D + jj] = a;
+      if (jj == 0) p.part_ml[part + g] = make_float2(M, ls);
     }
   }
   finish_row(p, sg);
 }
 
-// Merge launch: the slices of a row -> out (see merge_slices).
+// Merge launch: out[head g][dim j] of a row from its slices, sum_s acc_s e^{m_s - M} / sum_s l_s e^{m_s - M}; a workgroup per (row,
+// head), one thread per dim.  Latency bound: one memory round trip for up to 32 slices, all loads ahead of their first use, and few
+// instructions: a wave's lanes take a slice's (m, l) each and share the factors by readlane (a thread that reads and
+// exponentiates every slice's for itself executes three times as many; 8 rows x 4 heads x 32 slices of 128 dims 3.0 us so, now 2.05).
 __global__ __launch_bounds__(128) void combine_kernel(DecodeParams p) {
-  const int row = blockIdx.x, g = blockIdx.y, j = threadIdx.x;  // one thread per output element
-  const int prob = row / p.Hkv, c = row % p.Hkv;
+  const int row = blockIdx.x, g = blockIdx.y, j = threadIdx.x, sl = threadIdx.x & 31;
   // every slice kernel of the step has finished: the device-side count of appended tokens moves on
   if (p.ring && p.ring_advance && row == 0 && g == 0 && j == 0) p.ring[0] = p.ring[0] + 1;
-  if (j >= p.D) return;
-  p.out[((int64_t)prob * p.Hq + c * p.G + g) * p.D + j] = merge_slices(p, row, g, j);
+  if (j >= p.D) return;  // wave-uniform
+  const int64_t first = (int64_t)row * p.n_splits * p.G + g;
+  const float2* ml = p.part_ml + first;
+  const float* a = p.part_acc + first * p.D + j;
+  const int64_t step = (int64_t)p.G * p.D;
+  float M = -INFINITY, num = 0.f;
+  double den = 0.0;
+  for (int s0 = 0; s0 < p.n_splits; s0 += 32) {
+    float2 v = make_float2(-INFINITY, 0.f);
+    if (s0 + sl < p.n_splits) v = ml[(int64_t)(s0 + sl) * p.G];
+    float av[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) av[u] = a[(s0 + u < p.n_splits ? s0 + u : p.n_splits - 1) * step];
+    const float Mn = fmaxf(M, swap16_max(row_combine<true, 1>(v.x)));  // both halves of the wave hold the same 32 slices
+    if (Mn == -INFINITY) continue;  // nothing attended in these slices (uniform over the workgroup)
+    const float f = v.x == -INFINITY ? 0.f : exp_fast(v.x - Mn);
+    const float f0 = M == -INFINITY ? 0.f : exp_fast(M - Mn);
+    den = den * f0 + group_sum_f64<32>((double)v.y * f);  // (a tree of rounded fp32 products is 1 % further off over four slices)
+    num *= f0;
+#pragma unroll
+    for (int u = 0; u < 32; ++u)
+      num = fmaf(av[u], __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), u)), num);
+    M = Mn;
+  }
+  p.out[((int64_t)row * p.G + g) * p.D + j] = num / (float)den;
 }
 
 template <int LPT>

@@ -118,6 +118,10 @@ __device__ __forceinline__ double swap16_f64(double v) {
   const uint32_t l = odd ? lo[0] : lo[1], h = odd ? hi[0] : hi[1];
   return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
 }
+__device__ __forceinline__ float swap16(float v) {  // v of lane ^ 16
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
+}
 // v of this lane + v of lane ^ 16, lane ^ 32
 __device__ __forceinline__ float swap16_sum(float v) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -126,6 +130,14 @@ __device__ __forceinline__ float swap16_sum(float v) {
 __device__ __forceinline__ float swap32_sum(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float swap32_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 template <int LANES>
 __device__ __forceinline__ double group_sum_f64(double v) {
@@ -250,10 +262,7 @@ __device__ __forceinline__ float row_combine(float v) {
 template <bool MAX, int GQ>
 __device__ __forceinline__ float wave_combine(float v) {
   v = row_combine<MAX, GQ>(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = combine<MAX>(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return combine<MAX>(__uint_as_float(b[0]), __uint_as_float(b[1]));
+  return MAX ? swap32_max(swap16_max(v)) : swap32_sum(swap16_sum(v));
 }
 
 // ---- block-wide inclusive scan of one int per thread (1024 threads) ------------------------------

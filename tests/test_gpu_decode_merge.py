@@ -1,0 +1,30 @@
+"""Rows cut into slices and merged again: one slice, a few, the 32 that a round of the merge takes, more; per-query rows, where a
+head attends nothing in most slices."""
+import numpy as np
+import pytest
+
+import synth
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+BF16, F32 = synth.BF16, synth.F32
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [(BF16, 8, 2, 128), (BF16, 7, 1, 64), (BF16, 12, 1, 128), (F32, 4, 2, 64), (F32, 4, 1, 128)])
+@pytest.mark.parametrize("slices", [2, 3, 31, 32, 33, 65])
+@pytest.mark.parametrize("per_query", [False, True])
+def test_slices(ref, dtype, Hq, Hkv, d, slices, per_query):
+    import paper_2503_08879_amd as sk
+
+    P, G = 1, Hq // Hkv
+    n = 128 * slices - 45  # the last slice is ragged
+    S, lists = 3, G if per_query else 1
+    k = (n - S - 20) // lists
+    W = n - S - lists * k
+    rng = np.random.default_rng(slices * 100 + Hq + d)
+    draw = lambda *shape: synth.round_to_dtype(rng.standard_normal(shape, dtype=np.float32), dtype)
+    q, Kc, Vc = draw(P, Hq, d), draw(P, Hkv, n, d), draw(P, Hkv, n, d)
+    desc, ws, out = gu.gpu_decode_setup(dtype, P, Hq, Hkv, d, S, k, W, n, head_mode=int(per_query))
+    want = ref.decode_attn(dtype, int(per_query), q, Kc, Vc, n, S, k, W)
+    sk.sagekv_decode_attn(desc, *(synth.host_to_torch(x, dtype) for x in (q, Kc, Vc)), n, out, ws)
+    assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[dtype]
