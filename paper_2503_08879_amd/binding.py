@@ -133,13 +133,26 @@ def status_string(code: int) -> str:
 
 
 def _ptr(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_current_stream = None
 
 
 def _stream():
-    import torch
+    """Handle of torch's current stream on the current device.  The raw getters are what
+    torch.cuda.current_stream() wraps: 0.3 us instead of 2.5, of a tiny decode step's 8."""
+    global _current_stream
+    if _current_stream is None:
+        import torch
 
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        torch.cuda.current_stream()  # initialises
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None:
+            _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+        else:
+            _current_stream = lambda: raw(device())
+    return _current_stream()
 
 
 def _dtype_of(t) -> int:
