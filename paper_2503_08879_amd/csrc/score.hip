@@ -472,13 +472,16 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
           }
           const unsigned long long mine = j == 0 ? of[0] : j == 1 ? of[1] : j == 2 ? of[2] : of[3];
 #pragma unroll
-          for (int i = 0; i < GQ; ++i)
-            if ((mine >> (16 * i + n)) & 1ull) {
-              const double l = d[i] * (1.0 / sqrt((double)D)), m0 = heavy_m[i];
-              const double ex = exp(l > m0 ? m0 - l : l - m0);
+          for (int i = 0; i < GQ; ++i) {
+            const bool take = (mine >> (16 * i + n)) & 1ull;
+            const double l = d[i] * (1.0 / sqrt((double)D)), m0 = heavy_m[i];
+            double ex = 0.0;
+            if (__any(take && heavy_z[i] > 0.0)) ex = exp(l > m0 ? m0 - l : l - m0);  // (usually everybody's first)
+            if (take) {
               heavy_z[i] = l > m0 ? heavy_z[i] * ex + 1.0 : heavy_z[i] + ex;
               heavy_m[i] = l > m0 ? l : m0;
             }
+          }
         }
       }
       // one block ahead is enough, and all that the registers of two workgroups per CU hold: without this the passes
@@ -502,7 +505,10 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         for (int i = 0; i < 4; ++i)
           if (i == r) {
             const float mn = fmaxf(m[i], (float)h.x);
-            sum[i] = sum[i] * exp_fast(m[i] - mn) + (float)(h.y * exp(h.x - (double)mn));
+            const double x = h.x - (double)mn;  // usually the rounding of the maximum: the exponential's series to x^3
+            double ex = 1.0 + x * (1.0 + x * (0.5 + x * (1.0 / 6.0)));
+            if (__any(fabs(x) > 0x1p-10)) ex = exp(x);
+            sum[i] = sum[i] * exp_fast(m[i] - mn) + (float)(h.y * ex);
             m[i] = mn;
           }
       }
