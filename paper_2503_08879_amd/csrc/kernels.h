@@ -140,6 +140,7 @@ struct FilterParams {
   int64_t slots_per_row;
   int Gs;
   int S, W;
+  int write_through;  // candidate records bypass L2 (set by launch_score_filter, by the size of the call)
 };
 
 // What a pass over K leaves behind.

@@ -22,6 +22,7 @@ namespace {
 
 constexpr int kScoreThreads = 256;
 constexpr int kScoreWaves = kScoreThreads / kWave;
+constexpr int64_t kWriteThrough = 1ll << 30;
 constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine launch
 // A score workgroup takes a chunk of BPW blocks of 64 tokens per wave (BPW = 1, 2, 4: 256, 512, 1024 tokens).
 
@@ -303,6 +304,11 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   // their lines cost, not what the store instructions do (stored over and over into 16 KB that stay in L2, the pass takes what it takes
   // with nothing stored).  Nothing stored / stored as met / in runs: 64 rows x 40K tokens in pages, 7 heads 117 / 137 / 124 us,
   // 112 rows x 128K, 7 lists 549 / 625 / 605, 8 rows x 128K, 4 heads 49 / 52 / 48 (with the lines of the partials).
+  // Over more than kWriteThrough bytes of keys they are written through L2 at once, not left for it to evict in the middle of
+  // the stream; a small call's selection finds them in the caches.  Whole
+  // pass, left and written through, us: 64 rows x 40K in pages (0.6 GB) 169 and 171, 96 x 32K (0.8 GB) 206 and 206, 128 x 32K (1.1 GB) 256
+  // and 255, 64 x 128K (2.1 GB) 418 and 411, 256 x 32K (2.1 GB) 479 and 472, 112 x 128K with 7 lists (3.8 GB) 871 and 848, 256 x 128K (8.6 GB)
+  // 1542 and 1522.
   int n_stash = 0;  // wave-uniform
   auto flush = [&]() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -323,7 +329,13 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
     for (int i = lane; i < last * GQ; i += 64) {
       const int e = i / GQ;
       const int64_t slot = e < fit ? slot_base + base + e : over + e;
-      reinterpret_cast<float4*>(p.filt.cand_logit)[slot * GQ + i % GQ] = stash_rec[wave][i];
+      const float4 rec = stash_rec[wave][i];
+      if (p.filt.write_through && e < fit)  // (descriptor of the run, bounds not used: the slots are the chunk's own)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, rec),
+                                               __builtin_amdgcn_make_buffer_rsrc(p.filt.cand_logit + (slot_base + base) * (4 * GQ), 0, -1, 0x00027000),
+                                               i * 16, 0, 16 /* sc1 */);
+      else
+        reinterpret_cast<float4*>(p.filt.cand_logit)[slot * GQ + i % GQ] = rec;
       if (i % GQ == 0) p.filt.cand_idx[slot] = stash_tok[wave][e];
     }
     n_stash = 0;
@@ -880,6 +892,7 @@ hipError_t launch_score_filter(const ScoreParams& p0, hipStream_t s) {
   p.g0 = 0;
   p.gate.row_flag = nullptr;
   if (p.geo.dtype != DT_BF16 || p.geo.G > 16) return hipErrorInvalidValue;
+  p.filt.write_through = (int64_t)rows * p.geo.L * p.geo.D * 2 > kWriteThrough;
   return launch_score_mfma_d<SCORE_FILTER>(p, p.geo.G, grid, s);
 }
 
