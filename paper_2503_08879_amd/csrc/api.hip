@@ -38,7 +38,7 @@ struct FastPlan {
 // Tokens one workgroup of the first pass over K covers: 1024, less where the call is too small for that to fill the
 // chip.  At most 1024 chunks per row (the candidate selection gives each a thread).
 // Pre-filtered path: at least 512 workgroups, two per CU (8 rows of 32768 tokens: 22 us with 512 workgroups of 512
-// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256).  Dense path: 256 workgroups do for bf16, whose statistics are merged by
+// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256; as the pass is now 18.7 with 512 and 20.3 with 1024).  Dense path: 256 workgroups do for bf16, whose statistics are merged by
 // one workgroup per row (a pass over 8 rows of 30000 tokens x 4 heads: 65.3 us with chunks of 512 tokens, 67.6 with 256; fp32 would
 // rather have 256: 8 rows of 16384 x 4 heads 53.8 against 58.4).
 int score_chunk(const sagekv_select_desc* d, int64_t fill) {
@@ -236,7 +236,8 @@ struct DecodeLayout {
 // Splits per row.  With about one row per CU or more, a single 8-wave workgroup per row fills
 // the chip and needs no merge launch; otherwise enough workgroups to fill 256 CUs several times
 // over, at least 128 tokens each.  Short rows are not worth the merge launch:
-// bf16 up to 256 tokens, a single pass (8 rows x 4 heads x 256 tokens 10.3 us split, 8.4 whole; 4 rows x 7 heads 9.6 and 8.2; at
+// bf16 up to 256 tokens, a single pass (8 rows x 4 heads x 256 tokens 9.2 us split, 7.7 whole; 4 rows x 7 heads 8.7 and 7.7; before
+// the slice kernel had its present form 10.3 and 8.4, 9.6 and 8.2, and at
 // 512 tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 256 tokens of head_dim 64 (8 rows x 256 tokens, one to eight heads: 11.6,
 // 12.5, 15, 17, 20, 22, -, 27 us split, 8.4, 8.5, 9.7, 12, 14, 16, -, 20 whole; 160 rows x 2, 4, 8 heads 14, 19, 50 and 8.8, 13.4, 21;
 // 2 rows x 2 heads x 512 tokens 9.8 and 12.0; 8 rows x 4 heads x 512 tokens of head_dim 128 22 and 42 with 16 waves).

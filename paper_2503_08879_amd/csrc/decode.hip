@@ -28,7 +28,7 @@ struct StepGeom {
 // late: a fixed-size window with its count on the device.  Only the slot depends on the count, so its load need not be
 // waited for in front of everything else: the first loads go out with slot = -1 and late_slot() fills it in.  (One
 // layer's step, 8 rows x 4096 tokens: 15.8 -> 14.5 us together with the queries' loads in front of K's and V's and
-// the maxima over DPP instead of shuffles.)
+// the maxima over DPP instead of shuffles; 11.3 with the loads of SliceLoads and the merge's shared factors.)
 __device__ __forceinline__ bool slot_is_late(const DecodeParams& p) { return p.ring && !p.ring_grow; }
 __device__ __forceinline__ int late_slot(const DecodeParams& p, StepGeom& s, int n_appended) {
   s.n_appended = n_appended;

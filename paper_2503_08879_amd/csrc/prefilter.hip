@@ -36,7 +36,7 @@ constexpr float kHeavyShare = 0.01f;  // see sample_stats_kernel (0.3 % and 0.1 
 // One workgroup per row: latency bound, a chain of barriers.  The sampled logits are read once: a thread holds NI
 // items, an item being the logits of one head quad (4 heads, 16 bytes) of one sample slot, and always the same
 // quad.  NI = 0: more items than registers (9 to 16 heads and more than 262144 candidates), they are read from memory in
-// every pass.  NI = 18 spills 17 to 19 of its 128 registers and is still ahead of that (a pass over one row of 300000 tokens x
+// every pass.  NI = 18 spills 2 of its 128 registers (17 to 19 when this was measured) and is still ahead of that (a pass over one row of 300000 tokens x
 // 8 heads 90 us and 93, two rows of 200000 x 16 heads 112 and 119).
 template <int GQ, int NI>
 __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams p) {
@@ -397,7 +397,8 @@ __device__ __forceinline__ bool select_list(const TopkCandParams& p, CandShared&
 // records -> the band's keys) and barriers on as many CUs as the call has rows.  So a row's candidates are read
 // once and kept in registers, up to NPT per thread, their loads batched and in flight while the statistics are merged;
 // selecting among scores in memory (three radix passes and a band pass, each with its own round trips, all
-// of a row's keys in a few histogram bins) took 45 instead of 28 us for 8 rows of 128K tokens and 71 instead of 36 us for 256.
+// of a row's keys in a few histogram bins) took 45 us for 8 rows of 128K tokens and 71 for 256, this 28 and 36, and 22
+// and 27 with one barrier per reduction and the row's first loads together (row_start).
 // GQ: head quads of a record.  More than NPT * 1024 candidates (peaked rows): scores and tokens go through memory.  (NPT = 24 with 9
 // to 16 heads spills 7 registers; through memory it would be about even: 313 and 310 us, two rows of 400000 tokens, k = 16000.)
 template <int DT, int NPT, int GQ>

@@ -414,8 +414,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
 // list's scores held in registers: thread t owns the quads t, t + 1024, ... of the row (4 consecutive tokens
 // each).  Latency bound (one workgroup per list, a chain of memory round trips and barriers), so it replaces the
 // launches of the general route below for rows of up to 24576 tokens (24 registers of scores per thread):
-// statistics + combine + top-k take 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 29; 9.5 + 4.5 + 15.3 and 14
-// for 2 rows of 4096 (the correction of the normalisers for heavy terms, 4 and 2 us of it, included); at 30000 tokens
+// statistics + combine + top-k took 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 29, now 22; 9.5 + 4.5 + 15.3 and 14, now 10.7,
+// for 2 rows of 4096 (the correction of the normalisers for heavy terms, 3.5 and 2.4 us of it, included); at 30000 tokens
 // the two are even (46 us, 8 rows, without it), beyond that several workgroups per row win.
 template <int DT, int NQ>
 __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParams p) {
