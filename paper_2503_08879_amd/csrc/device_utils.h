@@ -182,7 +182,7 @@ __device__ __forceinline__ int wave_scan_incl(int v) {
   v += dpp_i32<0x143, 0xC>(0, v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
-// minimum / maximum over the wave, in every lane (wave-uniform)
+// maximum over the wave, in every lane (wave-uniform)
 __device__ __forceinline__ int wave_max_i(int v) {
   constexpr int lo = -0x7FFFFFFF - 1;
   auto mx = [](int a, int b) { return a > b ? a : b; };
@@ -194,7 +194,6 @@ __device__ __forceinline__ int wave_max_i(int v) {
   v = mx(v, dpp_i32<0x143, 0xC>(lo, v));
   return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ __forceinline__ int wave_min_i(int v) { return ~wave_max_i(~v); }
 
 // exp(x) * inv for x <= 0-ish and a normal `inv` in [2^-62, 1] (a softmax weight: inv = 1/Z), via the
 // hardware exp2 with the rounding error of x*log2(e) folded back in (relative error a few 1e-7 where
