@@ -886,8 +886,10 @@ __global__ __launch_bounds__(128) void combine_kernel(DecodeParams p) {
   if (j >= p.D) return;  // wave-uniform
   const int64_t first = (int64_t)row * p.n_splits * p.G + g;
   const float2* ml = p.part_ml + first;
-  const float* a = p.part_acc + first * p.D + j;
-  const int64_t step = (int64_t)p.G * p.D;
+  // Slices past the last read as 0 by the buffer's bound: the last one read again, even times 0, would make an infinite output
+  // NaN.  (It also saves the address arithmetic: a step over 8 rows x 4096 tokens x 4 heads 10.1 -> 9.7 us.)
+  const int step = p.G * p.D * (int)sizeof(float);  // bytes
+  const auto acc = __builtin_amdgcn_make_buffer_rsrc(p.part_acc + first * p.D, 0, (p.n_splits - 1) * step + p.D * (int)sizeof(float), 0x00027000);
   float M = -INFINITY, num = 0.f;
   double den = 0.0;
   for (int s0 = 0; s0 < p.n_splits; s0 += 32) {
@@ -895,7 +897,7 @@ __global__ __launch_bounds__(128) void combine_kernel(DecodeParams p) {
     if (s0 + sl < p.n_splits) v = ml[(int64_t)(s0 + sl) * p.G];
     float av[32];
 #pragma unroll
-    for (int u = 0; u < 32; ++u) av[u] = a[(s0 + u < p.n_splits ? s0 + u : p.n_splits - 1) * step];
+    for (int u = 0; u < 32; ++u) av[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(acc, (s0 + u) * step + j * (int)sizeof(float), 0, 0));
     const float Mn = fmaxf(M, swap16_max(row_combine<true, 1>(v.x)));  // both halves of the wave hold the same 32 slices
     if (Mn == -INFINITY) continue;  // nothing attended in these slices (uniform over the workgroup)
     const float f = v.x == -INFINITY ? 0.f : exp_fast(v.x - Mn);

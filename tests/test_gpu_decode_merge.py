@@ -28,3 +28,27 @@ def test_slices(ref, dtype, Hq, Hkv, d, slices, per_query):
     want = ref.decode_attn(dtype, int(per_query), q, Kc, Vc, n, S, k, W)
     sk.sagekv_decode_attn(desc, *(synth.host_to_torch(x, dtype) for x in (q, Kc, Vc)), n, out, ws)
     assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [(BF16, 8, 2, 128), (BF16, 7, 1, 64), (F32, 4, 2, 64), (F32, 4, 1, 128)])
+@pytest.mark.parametrize("slices", [7, 8, 16, 24, 31, 32, 40])
+@pytest.mark.parametrize("slice_of", [0, -1])
+def test_infinite_value(ref, dtype, Hq, Hkv, d, slices, slice_of):
+    """A value of +inf in the first or the last slice is that dim's output, not NaN: a slice enters the sum once."""
+    import paper_2503_08879_amd as sk
+
+    P, G, n, S = 1, Hq // Hkv, 128 * slices - 45, 3
+    W = 20
+    k = n - S - W
+    rng = np.random.default_rng(slices + Hq + d)
+    draw = lambda *shape: synth.round_to_dtype(rng.standard_normal(shape, dtype=np.float32), dtype)
+    q, Kc, Vc = draw(P, Hq, d), draw(P, Hkv, n, d), draw(P, Hkv, n, d)
+    Vc[0, 0, 10 if slice_of == 0 else n - 30, 5] = 0x7F80 if dtype == BF16 else np.inf
+    desc, ws, out = gu.gpu_decode_setup(dtype, P, Hq, Hkv, d, S, k, W, n)
+    sk.sagekv_decode_attn(desc, *(synth.host_to_torch(x, dtype) for x in (q, Kc, Vc)), n, out, ws)
+    got = out.cpu().numpy()
+    assert np.isposinf(got[0, :G, 5]).all()
+    want = ref.decode_attn(dtype, 0, q, Kc, Vc, n, S, k, W)
+    np.testing.assert_array_equal(np.isinf(got), np.isinf(want))
+    fin = np.isfinite(want)
+    assert np.abs(got[fin] - want[fin]).max() <= gu.DECODE_ATOL[dtype]
