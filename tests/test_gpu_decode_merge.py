@@ -52,3 +52,26 @@ def test_infinite_value(ref, dtype, Hq, Hkv, d, slices, slice_of):
     np.testing.assert_array_equal(np.isinf(got), np.isinf(want))
     fin = np.isfinite(want)
     assert np.abs(got[fin] - want[fin]).max() <= gu.DECODE_ATOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,Hq,d", [(BF16, 2, 128), (BF16, 3, 64), (BF16, 7, 128), (F32, 2, 64), (F32, 3, 128)])
+@pytest.mark.parametrize("slices", [17, 24, 33, 65])
+@pytest.mark.parametrize("S", [0, 3])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_value_of_another_heads_list(ref, dtype, Hq, d, slices, S, bad):
+    """Per-query rows: what is no number in slices where a head attends nothing does not reach that head."""
+    import paper_2503_08879_amd as sk
+
+    n, W = 128 * slices - 45, 20
+    k = (n - S - W) // Hq
+    W = n - S - Hq * k
+    rng = np.random.default_rng(slices + Hq + d)
+    draw = lambda *shape: synth.round_to_dtype(rng.standard_normal(shape, dtype=np.float32), dtype)
+    q, Kc, Vc = draw(1, Hq, d), draw(1, 1, n, d), draw(1, 1, n, d)
+    assert S + k >= 256  # the second slice is head 0's alone
+    Vc[0, 0, 200, 5] = synth.round_to_dtype(np.array([bad], np.float32), dtype)[0]
+    desc, ws, out = gu.gpu_decode_setup(dtype, 1, Hq, 1, d, S, k, W, n, head_mode=1)
+    sk.sagekv_decode_attn(desc, *(synth.host_to_torch(x, dtype) for x in (q, Kc, Vc)), n, out, ws)
+    got, want = out.cpu().numpy(), ref.decode_attn(dtype, 1, q, Kc, Vc, n, S, k, W)
+    assert np.isfinite(got[0, 1:]).all() and not np.isfinite(got[0, 0, 5])
+    assert np.abs(got[0, 1:] - want[0, 1:]).max() <= gu.DECODE_ATOL[dtype]
