@@ -162,6 +162,14 @@ __global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) 
 // PAGED: the chunk's pages (at most 64: pages hold 16 tokens or more) are looked up once, one per
 // lane, and every load takes its page from the lane that holds it.
 // One score chunk (64 * BPW * kScoreWaves tokens of row `row`) by one workgroup of kScoreThreads threads.
+//
+// Partials of 9 to 16 heads of 128 dims: unrolled, each block with its own body for heavy terms, they take 276 registers and a CU
+// one workgroup, with nobody to cover its LDS and MFMA phases; rolled, and held to the 256 of two workgroups, they fit
+// without spilling.  A pass that also returns every score, unrolled and rolled, us: 8 rows x 32K tokens x 16 heads 102.5 and 99.8,
+// 64 x 32K 291 and 268, 256 x 32K 906 and 829, 64 x 128K 838 and 766 (12 heads 832 and 754).  With 64 dims (192
+// registers, two workgroups either way) and with at most 8 heads the two are even.
+template <int D, int GPAD, int MODE>
+constexpr bool kRolledPartials = MODE == SCORE_PARTIALS && D == 128 && GPAD == 16;
 template <int D, int GPAD, int MODE, bool PAGED, int BPW>
 __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, int row, int chunk) {
   constexpr int CH = D / 8;         // 16-byte chunks per token
@@ -175,7 +183,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   constexpr bool PARTIALS = MODE == SCORE_FILTER || MODE == SCORE_PARTIALS;  // running sums (SCORE_LOGITS: at the end)
   constexpr bool HEAVY = PARTIALS;
   constexpr int kChunk = 64 * BPW * kScoreWaves;
-  constexpr int kBlockUnroll = FILTER ? 1 : BPW;
+  constexpr int kBlockUnroll = FILTER || kRolledPartials<D, GPAD, MODE> ? 1 : BPW;
 
   __shared__ uint4 lds[kScoreWaves][64 * CH];
   __shared__ float2 part[kScoreWaves][4][4];
@@ -681,7 +689,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
 // few y-blocks only, each walking over all rows and working on the flagged ones: an empty launch
 // then costs a handful of workgroups instead of one per (chunk, row).
 template <int D, int GPAD, int MODE, bool PAGED, int BPW>
-__global__ __launch_bounds__(kScoreThreads, GPAD == 16 && MODE != SCORE_FILTER ? 1 : 2) void score_mfma_kernel(ScoreParams p, int gb) {
+__global__ __launch_bounds__(kScoreThreads, (GPAD == 16 && MODE != SCORE_FILTER && !kRolledPartials<D, GPAD, MODE> ? 1 : 2)) void score_mfma_kernel(ScoreParams p, int gb) {
   if (MODE != SCORE_FILTER && p.gate.row_flag) {
     if (*p.gate.n_flagged == 0) return;  // the usual case: nothing to redo
     const int rows = p.geo.n_problems * p.geo.Hkv;
