@@ -638,14 +638,22 @@ __global__ __launch_bounds__(kTopkThreads) void row_stats_kernel(RowStatsParams 
 // ---- gather -----------------------------------------------------------------------------------
 constexpr int kGatherThreads = 256;
 constexpr int kGatherTokens = 64;  // reduced-cache rows one workgroup copies
-// From so many bytes written on, the rows are stored nontemporally, up to so many bytes of keys.  Plain stores leave the Infinity
-// Cache (256 MB) full of lines that have yet to go to memory, and whoever streams next pays for them at a multiple of their
-// bytes (see the filtering pass's candidates).  Repeated passes, plain and nontemporal, us: 67 MB written (64 rows x 8K tokens)
-// 69 and 71, (64 x 32K) 148 and 149; 134 MB (128 x 32K) 271 and 262; 268 MB (256 x 8K) 226 and 208, (256 x 32K) 500 and 475;
-// 470 MB (112 x 128K, 7 lists) 905 and 875; 503 MB (256 x 64K) 912 and 870.  Where the pass itself reads 8.6 GB, the gather and the
-// sample gain as much and the filtering pass loses it again: 256 x 128K, 236 MB 1439 and 1426, 537 MB 1540 and 1574, 1057 MB 1772
-// and 1755.
-constexpr int64_t kStreamGather = 96ll << 20, kStreamGatherKeys = 6ll << 30;
+// From so many bytes written on, the rows are stored nontemporally.  Plain stores leave the Infinity Cache (256 MB) full of lines that
+// have yet to go to memory, and whoever streams next pays for them at a multiple of their bytes (see the filtering pass's
+// candidates); nontemporal ones go out during the gather.  So it depends on what follows, us, plain and nontemporal (inputs in
+// rotation, "1 GB": a read of that much, as a model's weights are between a pass and the step's attention, and between steps):
+//   rows x tokens, MB written    pass after pass   pass, 1 GB, step, 1 GB   pass, step, 1 GB
+//   256 x   8K, 134                194   182           733   731               469   470
+//   256 x   8K, 268                229   215           787   781               518   525
+//   256 x  32K, 101                413   406           951   949               691   692
+//   256 x  32K, 201                460   448          1014  1009               744   753
+//   256 x  32K, 268                503   483          1056  1049               784   793
+//   256 x  64K, 537                969   921          1539  1527              1231  1242
+//   256 x 128K, 537               1545  1519          2153  2127              1875  1871
+//   256 x 128K, 1057              1802  1780          2453  2460              2189  2167
+// Where the step reads the cache right behind the pass, it would have found some of it on the chip: 1 % is lost there.  With less
+// written the gain goes (64 rows x 8K, 67 MB: 69 and 71 pass after pass).
+constexpr int64_t kStreamGather = 96ll << 20;
 
 template <int LPT, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherParams p, int eb) {
@@ -748,8 +756,7 @@ hipError_t launch_gather(const GatherParams& p, hipStream_t s) {
   const int eb = p.geo.dtype == DT_BF16 ? 2 : 4;
   const int lpt = p.geo.D * eb / 16;
   dim3 grid((unsigned)((p.n_kept + kGatherTokens - 1) / kGatherTokens), (unsigned)rows);
-  const int64_t token_bytes = (int64_t)rows * p.geo.D * eb;
-  const bool stream = 2 * token_bytes * p.n_kept > kStreamGather && token_bytes * p.geo.L <= kStreamGatherKeys;
+  const bool stream = 2ll * rows * p.geo.D * eb * p.n_kept > kStreamGather;
 #define SAGEKV_LAUNCH(LPT)                                                                          \
   if (stream)                                                                                        \
     hipLaunchKernelGGL((gather_kernel<LPT, true>), grid, dim3(kGatherThreads), 0, s, p, eb);         \
