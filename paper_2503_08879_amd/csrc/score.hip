@@ -193,6 +193,8 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   __shared__ float4 stash_rec[FILTER ? kScoreWaves : 1][FILTER ? kStash * GQ : 1];
   __shared__ int32_t stash_tok[FILTER ? kScoreWaves : 1][FILTER ? kStash : 1];
   __shared__ int n_kept_wg;  // candidates this workgroup has stored so far
+  static_assert(!FILTER || sizeof(lds) + sizeof(part) + sizeof(stash_rec) + sizeof(stash_tok) + sizeof(n_kept_wg) <= 80 * 1024,
+                "two workgroups share a CU's 160 KB");
 
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
