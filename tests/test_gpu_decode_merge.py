@@ -1,5 +1,5 @@
 """Rows cut into slices and merged again: one slice, a few, the 32 that a round of the merge takes, more; per-query rows, where a
-head attends nothing in most slices."""
+head attends nothing in most slices; the new token of a step, wherever its slot lies in a slice."""
 import numpy as np
 import pytest
 
@@ -27,7 +27,7 @@ def test_slices(ref, dtype, Hq, Hkv, d, slices, per_query):
     desc, ws, out = gu.gpu_decode_setup(dtype, P, Hq, Hkv, d, S, k, W, n, head_mode=int(per_query))
     want = ref.decode_attn(dtype, int(per_query), q, Kc, Vc, n, S, k, W)
     sk.sagekv_decode_attn(desc, *(synth.host_to_torch(x, dtype) for x in (q, Kc, Vc)), n, out, ws)
-    assert np.abs(out.cpu().numpy() - want).max() <= gu.DECODE_ATOL[dtype]
+    gu.check_decode(out.cpu().numpy(), want, dtype)
 
 
 @pytest.mark.parametrize("dtype,Hq,Hkv,d", [(BF16, 8, 2, 128), (BF16, 7, 1, 64), (F32, 4, 2, 64), (F32, 4, 1, 128)])
@@ -74,4 +74,51 @@ def test_value_of_another_heads_list(ref, dtype, Hq, d, slices, S, bad):
     sk.sagekv_decode_attn(desc, *(synth.host_to_torch(x, dtype) for x in (q, Kc, Vc)), n, out, ws)
     got, want = out.cpu().numpy(), ref.decode_attn(dtype, 1, q, Kc, Vc, n, S, k, W)
     assert np.isfinite(got[0, 1:]).all() and not np.isfinite(got[0, 0, 5])
-    assert np.abs(got[0, 1:] - want[0, 1:]).max() <= gu.DECODE_ATOL[dtype]
+    gu.check_decode(got[0, 1:], want[0, 1:], dtype)
+
+
+FEW = [(BF16, 1, 8, 2, 128), (BF16, 2, 7, 1, 64), (BF16, 1, 12, 1, 128), (F32, 1, 4, 2, 64)]
+MANY = [(BF16, 192, 7, 1, 128), (BF16, 192, 12, 1, 64), (BF16, 257, 5, 1, 64)]  # whole rows, in 8 waves and in 4
+
+
+@pytest.mark.parametrize("dtype,P,Hq,Hkv,d,slices", [(*f, s) for f in FEW for s in (3, 33)] + [(*m, 3) for m in MANY])
+@pytest.mark.parametrize("at", ["row start", "slice start", "mid row", "last slice", "row end"])
+@pytest.mark.parametrize("call", ["step", "ring", "paged", "paged ring"])
+def test_new_token(ref, dtype, P, Hq, Hkv, d, slices, at, call):
+    """The new token holds about a third of every head's mass: without it in the keys or in the values the output would be off by about
+    its own size (the slices of few rows have 128 tokens, the last one is ragged)."""
+    import torch
+
+    import paper_2503_08879_amd as sk
+
+    n, G = 128 * slices - 45, Hq // Hkv
+    slot = {"row start": 0, "slice start": 128, "mid row": 205, "last slice": 128 * (slices - 1), "row end": n - 1}[at]
+    rng = np.random.default_rng(slices * 100 + Hq + d + slot)
+    draw = lambda *shape: synth.round_to_dtype(rng.standard_normal(shape, dtype=np.float32), dtype)
+    q, Kc, Vc, vn = draw(P, Hq, d), draw(P, Hkv, n, d), draw(P, Hkv, n, d), draw(P, Hkv, d)
+    # the key of least norm whose logit with each query of its group is log(n) (the others' exponentials add up to 1.6 n on average)
+    qf = synth.to_f64(q, dtype).reshape(P, Hkv, G, d)
+    kn = synth.round_to_dtype((np.linalg.pinv(qf) @ np.full((P, Hkv, G, 1), np.log(0.8 * n) * d ** 0.5))[..., 0], dtype)
+    Kd, Vd = synth.host_to_torch(Kc, dtype), synth.host_to_torch(Vc, dtype)
+    Kc[:, :, slot], Vc[:, :, slot] = kn, vn
+    want = ref.decode_attn(dtype, 0, q, Kc, Vc, n)
+    desc, ws, out = gu.gpu_decode_setup(dtype, P, Hq, Hkv, d, 0, 0, n, n)  # the whole row is the window
+    ins = [synth.host_to_torch(x, dtype) for x in (q, kn, vn)]
+    state = torch.tensor([slot, 0], dtype=torch.int32, device="cuda") if "ring" in call else None
+    if "paged" in call:
+        per = -(-n // 16)
+        table = torch.randperm(P * per).to(torch.int32).reshape(P, per).cuda()
+
+        def pool(X):
+            out = torch.full((P * per, Hkv, 16, d), float("nan"), dtype=X.dtype, device="cuda")
+            X = torch.cat([X, X.new_full((P, Hkv, per * 16 - n, d), float("nan"))], 2)
+            out[table.long().reshape(-1)] = X.reshape(P, Hkv, per, 16, d).transpose(1, 2).reshape(P * per, Hkv, 16, d)
+            return out
+
+        Kp, Vp = pool(Kd), pool(Vd)
+        sk.sagekv_decode_step_paged(desc, sk.compact_pages(table, Kp, Vp), *ins, Kp, Vp, slot, state, out, ws)
+    elif state is not None:
+        sk.sagekv_decode_step_ring(desc, *ins, Kd, Vd, state, out, ws)
+    else:
+        sk.sagekv_decode_step(desc, *ins, Kd, Vd, slot, out, ws)
+    gu.check_decode(out.cpu().numpy(), want, dtype)
