@@ -1,6 +1,6 @@
 """The sample of the pre-filtered path: runs that straddle pages and the row's ends, heads padded to 4, 8 and 16, rows shorter than
-the sample itself, samples that are read with plain and (beyond 32 MB of keys) with nontemporal loads.  A wrong logit there does
-not change a kept set but sends its row to the dense path, so the count of redone rows is checked too."""
+the sample itself, a last workgroup with fewer blocks than waves.  A wrong logit there does not change a kept set but sends its row
+to the dense path, so the count of redone rows is checked too."""
 import pytest
 
 import synth
@@ -16,7 +16,7 @@ BF16 = synth.BF16
     (2, 7, 1, 128, 2049, 1, 65, 100, 16),
     (1, 16, 1, 64, 5003, 64, 512, 100, 32),
     (1, 12, 1, 128, 20011, 4, 129, 500, 64),
-    (11, 32, 8, 128, 6001, 4, 512, 200, 16),   # 88 rows x 25 blocks of 16 KB: nontemporal loads
+    (11, 32, 8, 128, 6001, 4, 512, 200, 16),   # 88 rows x 25 blocks: one in the last workgroup
     (20, 56, 8, 64, 9001, 4, 512, 100, 16),
 ])
 @pytest.mark.parametrize("token_major", [False, True])
