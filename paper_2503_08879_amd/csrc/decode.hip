@@ -28,7 +28,7 @@ struct StepGeom {
 // late: a fixed-size window with its count on the device.  Only the slot depends on the count, so its load need not be
 // waited for in front of everything else: the first loads go out with slot = -1 and late_slot() fills it in.  (One
 // layer's step, 8 rows x 4096 tokens: 15.8 -> 14.5 us together with the queries' loads in front of K's and V's and
-// the maxima over DPP instead of shuffles; 11.3 with the loads of SliceLoads and the merge's shared factors.)
+// the maxima over DPP instead of shuffles; 11.3 with the loads of SliceLoads and the shared factors of the merge, 11.0 with its bounded loads.)
 __device__ __forceinline__ bool slot_is_late(const DecodeParams& p) { return p.ring && !p.ring_grow; }
 __device__ __forceinline__ int late_slot(const DecodeParams& p, StepGeom& s, int n_appended) {
   s.n_appended = n_appended;
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void decode_pv_mfma_kerne
 // Merge launch: out[head g][dim j] of a row from its slices, sum_s acc_s e^{m_s - M} / sum_s l_s e^{m_s - M}; a workgroup per (row,
 // head), one thread per dim.  Latency bound: one memory round trip for up to 32 slices, all loads ahead of their first use, and few
 // instructions: a wave's lanes take a slice's (m, l) each and share the factors by readlane (a thread that reads and
-// exponentiates every slice's for itself executes three times as many; 8 rows x 4 heads x 32 slices of 128 dims 3.0 us so, now 2.05).
+// exponentiates every slice's for itself executes three times as many; 8 rows x 4 heads x 32 slices of 128 dims 3.0 us so, 2.05 with the factors shared).
 __global__ __launch_bounds__(128) void combine_kernel(DecodeParams p) {
   const int row = blockIdx.x, g = blockIdx.y, j = threadIdx.x, sl = threadIdx.x & 31;
   // every slice kernel of the step has finished: the device-side count of appended tokens moves on

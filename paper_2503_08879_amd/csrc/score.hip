@@ -146,8 +146,8 @@ __global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) 
 // consecutive elements of ONE token per column lane, while coalesced loads give adjacent lanes
 // adjacent 16-byte chunks of the SAME token, so each wave stages its 64-token block through a
 // private, XOR-swizzled LDS buffer (conflict free both ways).  GPAD = heads padded to 4, 8 or
-// 16: 16/GPAD tiles share an accumulator (the queries of tile t sit in rows t*GPAD..), so after
-// a block every lane owns 4 logits and all stores are coalesced.
+// 16: the operand's rows repeat them 16/GPAD times and a lane takes the product of the tile of its slot, so that
+// 16/GPAD tiles share a set of four registers, after a block every lane owns 4 logits and all stores are coalesced.
 //
 // MODE (ScoreMode) says what the pass leaves behind:
 //   SCORE_LOGITS    every logit, to the scratch of the one-sweep dense path, and the softmax partials;
@@ -355,9 +355,10 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   constexpr unsigned long long kCounting = GPAD == 4 ? ~0ull : GPAD == 8 ? 0x0000FFFF0000FFFFull : 0xFFFFull;  // one lane per token
 
   // Software pipeline: the loads of block b+1 are issued right after block b went to LDS, so
-  // their latency overlaps block b's MFMA phase.  Per-token results stay in registers until the wave
-  // has loaded its last block: loads and stores share one in-order completion counter, so a
-  // store inside the loop would put its write-ack latency on the critical path of every block.
+  // their latency overlaps block b's MFMA phase.  Loads and stores share one in-order completion counter, so a
+  // store inside the loop puts its write-ack latency on the critical path of the next block: what is kept per token stays
+  // in registers until the wave has loaded its last block, and the filter stores only when its stash is full (`flush`; with 6.8 thousand
+  // candidates in a row of 128K tokens, 13 per wave, after the loop).
   // HEAVY: this lane's share of the heavy terms of heads j + 4 i: sum of exp(l - heavy_m) in fp64
   bool seen_heavy = false;
   double heavy_m[GQ], heavy_z[GQ];
