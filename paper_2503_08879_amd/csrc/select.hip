@@ -653,7 +653,10 @@ constexpr int kGatherTokens = 64;  // reduced-cache rows one workgroup copies
 //   256 x 128K, 1057              1802  1780          2453  2460              2189  2167
 // Where the step reads the cache right behind the pass, it would have found some of it on the chip: 1 % is lost there.  With less
 // written the gain goes (64 rows x 8K, 67 MB: 69 and 71 pass after pass).
-constexpr int64_t kStreamGather = 96ll << 20;
+// Beyond so many bytes of keys the stores are plain: there the totals are even (256 x 128K, 537 MB, a pass and 256 steps: 23.6 ms
+// either way, inputs in rotation 1521 and 1517 us a pass), and a pass that stands between steps ends later by what it
+// does not leave to them, 1503 and 1522 us.
+constexpr int64_t kStreamGather = 96ll << 20, kStreamGatherKeys = 6ll << 30;
 
 template <int LPT, bool STREAM>
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherParams p, int eb) {
@@ -756,7 +759,8 @@ hipError_t launch_gather(const GatherParams& p, hipStream_t s) {
   const int eb = p.geo.dtype == DT_BF16 ? 2 : 4;
   const int lpt = p.geo.D * eb / 16;
   dim3 grid((unsigned)((p.n_kept + kGatherTokens - 1) / kGatherTokens), (unsigned)rows);
-  const bool stream = 2ll * rows * p.geo.D * eb * p.n_kept > kStreamGather;
+  const int64_t token_bytes = (int64_t)rows * p.geo.D * eb;
+  const bool stream = 2 * token_bytes * p.n_kept > kStreamGather && token_bytes * p.geo.L <= kStreamGatherKeys;
 #define SAGEKV_LAUNCH(LPT)                                                                          \
   if (stream)                                                                                        \
     hipLaunchKernelGGL((gather_kernel<LPT, true>), grid, dim3(kGatherThreads), 0, s, p, eb);         \
