@@ -163,13 +163,11 @@ __global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) 
 // lane, and every load takes its page from the lane that holds it.
 // One score chunk (64 * BPW * kScoreWaves tokens of row `row`) by one workgroup of kScoreThreads threads.
 //
-// Partials of 9 to 16 heads of 128 dims: unrolled, each block with its own body for heavy terms, they take 276 registers and a CU
-// one workgroup, with nobody to cover its LDS and MFMA phases; rolled, and held to the 256 of two workgroups, they fit
-// without spilling.  A pass that also returns every score, unrolled and rolled, us: 8 rows x 32K tokens x 16 heads 102.5 and 99.8,
-// 64 x 32K 291 and 268, 256 x 32K 906 and 829, 64 x 128K 838 and 766 (12 heads 832 and 754).  With 64 dims (192
-// registers, two workgroups either way) and with at most 8 heads the two are even.
-template <int D, int GPAD, int MODE>
-constexpr bool kRolledPartials = MODE == SCORE_PARTIALS && D == 128 && GPAD == 16;
+// The block loop is rolled where nothing is kept per token: unrolled, each block would have its own body for heavy terms.  The partials
+// of 9 to 16 heads of 128 dims took 276 registers so, and a CU one workgroup, with nobody to cover its LDS and MFMA
+// phases; rolled, and held to the 256 of two workgroups, they fit without spilling.  A pass that also returns every score, unrolled and
+// rolled, us: 8 rows x 32K tokens x 16 heads 102.5 and 99.8, 64 x 32K 291 and 268, 256 x 32K 906 and 829, 64 x 128K 838 and 766 (12
+// heads 832 and 754); with at most 8 heads and with 64 dims the two are even.
 template <int D, int GPAD, int MODE, bool PAGED, int BPW>
 __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, int row, int chunk) {
   constexpr int CH = D / 8;         // 16-byte chunks per token
@@ -183,7 +181,12 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   constexpr bool PARTIALS = MODE == SCORE_FILTER || MODE == SCORE_PARTIALS;  // running sums (SCORE_LOGITS: at the end)
   constexpr bool HEAVY = PARTIALS;
   constexpr int kChunk = 64 * BPW * kScoreWaves;
-  constexpr int kBlockUnroll = FILTER || kRolledPartials<D, GPAD, MODE> ? 1 : BPW;
+  // heavy terms per register of a lane, and tile, up to which they are taken one by one (a round of four 0.3 us, a tile's products 1 us
+  // with 128 dims, 0.6 with 64).  64 rows x 32K tokens of N(60, 1) logits, all tiles / up to 1 / 2 / 3 terms, us: 4 heads of 128 dims 223 175 168 167,
+  // 7 heads 264 213 185 183, 16 heads 350 327 267 261
+  constexpr int kThin = D == 128 ? 3 : 2;
+  constexpr int kAddUnroll = GPAD == 16 ? 1 : 2;  // (16 heads: with four exponentials side by side the filter spills)
+  constexpr int kBlockUnroll = PARTIALS ? 1 : BPW;
 
   __shared__ uint4 lds[kScoreWaves][64 * CH];
   __shared__ float2 part[kScoreWaves][4][4];
@@ -457,52 +460,102 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
         // The block is still in LDS: the fp64 logits of a 16-token tile for every head are D / 4 steps of
         // v_mfma_f64_16x16x4 on the operands at hand (element e of everybody's 16 bytes per step), about 1 us a tile.  (Listing the
         // terms and reading their keys again after the last block, sixteen lanes per dot product: 5.7 us for the chunk that holds a
-        // row's sink tokens, which is what the whole launch of a small call then waits for.)
+        // row's sink tokens, which is what the whole launch of a small call then waits for.)  Terms strewn thin over the tiles, as logits
+        // that share an offset have them, are taken one by one: with tiles alone the pass over 256 rows x 32K tokens of N(60, 1) logits took
+        // 688 us instead of 463 at N(0, 1), so 467 (with the list, and the other kernels of that time, 612).
         seen_heavy = true;
-        unsigned long long hv[NACC][4];  // lanes whose logit is a heavy term
+        unsigned long long hv[NACC][4];  // lanes whose logit is a heavy term: lane (j', n), register r: head 4 (j' % GQ) + r
 #pragma unroll
         for (int a = 0; a < NACC; ++a)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
             hv[a][r] = __ballot(tok_base + (a * TILES + (4 * j) / GPAD) * 16 + n < L && hbase + r < gb && xs[0][a][r] >= hthr[r]);
+        // a term's logit l into the sums of its head, in the lane of its column
+        auto add = [](double& hm, double& hz, bool take, double l) {
+          double ex = 0.0;
+          if (__any(take && hz > 0.0)) ex = exp(l > hm ? hm - l : l - hm);  // (usually everybody's first)
+          if (take) {
+            hz = l > hm ? hz * ex + 1.0 : hz + ex;
+            hm = l > hm ? l : hm;
+          }
+        };
 #pragma unroll 1
-        for (int tile = 0; tile < 4; ++tile) {
-          // rows of the tile in its accumulator: lanes 16 GQ (tile % TILES) on; lane (j', n), register r: head 4 (j' % GQ) + r
-          unsigned long long of[4], any = 0ull;
+        for (int a = 0; a < NACC; ++a) {
+          unsigned long long h[4], any = 0ull;
+          int rounds = 0, tiles = 0;  // terms in the fullest register, tiles that hold any
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            of[r] = hv[0][r];
+            h[r] = hv[0][r];
 #pragma unroll
-            for (int a = 1; a < NACC; ++a) of[r] = tile / TILES == a ? hv[a][r] : of[r];
-            of[r] >>= 16 * GQ * (tile % TILES);
-            if (GQ < 4) of[r] &= (1ull << (16 * GQ % 64)) - 1ull;
-            any |= of[r];
+            for (int aa = 1; aa < NACC; ++aa) h[r] = a == aa ? hv[aa][r] : h[r];
+            any |= h[r];
+            const int cnt = __popcll(h[r]);
+            rounds = cnt > rounds ? cnt : rounds;
           }
           if (!any) continue;
-          typedef double f64x4_t __attribute__((ext_vector_type(4)));
-          f64x4_t d = {0.0, 0.0, 0.0, 0.0};  // register i of lane (j, n): row 4 i + j = head (4 i + j) % GPAD, token n
+          constexpr unsigned long long kTile = GQ < 4 ? (1ull << (16 * GQ % 64)) - 1ull : ~0ull;  // the lanes of a tile's rows
 #pragma unroll
-          for (int kc = 0; kc < KSTEPS; ++kc) {
-            const uint4 b = buf[(tile * 16 + n) * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
-            uint32_t qw[4] = {qa[kc].x, qa[kc].y, qa[kc].z, qa[kc].w};
-            const uint32_t bw[4] = {b.x, b.y, b.z, b.w};
-            asm volatile("" : "+v"(qw[0]), "+v"(qw[1]), "+v"(qw[2]), "+v"(qw[3]));  // not converted (and held) up front
+          for (int ts = 0; ts < TILES; ++ts) tiles += (any >> (16 * GQ * ts)) & kTile ? 1 : 0;
+          if (rounds <= kThin * tiles) {
+            // one by one: dot products on the vector ALU, four at a time, those of heads j + 4 i by the 16 lanes of group j
+            unsigned long long left = j == 0 ? h[0] : j == 1 ? h[1] : j == 2 ? h[2] : h[3];
+#pragma unroll 1
+            for (; rounds > 0; --rounds) {
+              const bool have = left != 0ull;
+              const int bit = have ? __ffsll(left) - 1 : 0, i = (bit >> 4) % GQ, t = (a * TILES + (bit >> 4) / GQ) * 16 + (bit & 15);
+              left &= left - 1ull;
+              const int c = n * CH / 16;  // this lane's 16 bytes of the key; 64 dims: the lower or the upper half of them
+              uint4 kb = buf[t * CH + (c ^ (t & (CH - 1)))], qb;
+              const int from = ((c & 3) << 4) | (4 * i + j);  // the lane that holds the query's
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_lo(qw[e]), (double)bf16_lo(bw[e]), d, 0, 0, 0);
-              d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_hi(qw[e]), (double)bf16_hi(bw[e]), d, 0, 0, 0);
+              for (int kc = 0; kc < KSTEPS; ++kc) {
+                const uint4 x = make_uint4(__shfl(qa[kc].x, from), __shfl(qa[kc].y, from), __shfl(qa[kc].z, from), __shfl(qa[kc].w, from));
+                if (kc == 0 || c >> 2 == kc) qb = x;
+              }
+              if (CH == 8 && (n & 1)) kb.x = kb.z, kb.y = kb.w, qb.x = qb.z, qb.y = qb.w;
+              double l = (double)bf16_lo(qb.x) * (double)bf16_lo(kb.x) + (double)bf16_hi(qb.x) * (double)bf16_hi(kb.x) +
+                         (double)bf16_lo(qb.y) * (double)bf16_lo(kb.y) + (double)bf16_hi(qb.y) * (double)bf16_hi(kb.y);
+              if (CH == 16)
+                l += (double)bf16_lo(qb.z) * (double)bf16_lo(kb.z) + (double)bf16_hi(qb.z) * (double)bf16_hi(kb.z) +
+                     (double)bf16_lo(qb.w) * (double)bf16_lo(kb.w) + (double)bf16_hi(qb.w) * (double)bf16_hi(kb.w);
+              l = group_sum_f64<16>(l) * (1.0 / sqrt((double)D));
+              double hm = heavy_m[0], hz = heavy_z[0];
+#pragma unroll
+              for (int ii = 1; ii < GQ; ++ii) hm = i == ii ? heavy_m[ii] : hm, hz = i == ii ? heavy_z[ii] : hz;
+              add(hm, hz, have && n == (bit & 15), l);
+#pragma unroll
+              for (int ii = 0; ii < GQ; ++ii)
+                if (i == ii) heavy_m[ii] = hm, heavy_z[ii] = hz;
             }
+            continue;
           }
-          const unsigned long long mine = j == 0 ? of[0] : j == 1 ? of[1] : j == 2 ? of[2] : of[3];
+#pragma unroll 1
+          for (int ts = 0; ts < TILES; ++ts) {
+            if (!((any >> (16 * GQ * ts)) & kTile)) continue;
+            typedef double f64x4_t __attribute__((ext_vector_type(4)));
+            f64x4_t d = {0.0, 0.0, 0.0, 0.0};  // register i of lane (j, n): row 4 i + j = head (4 i + j) % GPAD, token n
 #pragma unroll
-          for (int i = 0; i < GQ; ++i) {
-            const bool take = (mine >> (16 * i + n)) & 1ull;
-            const double l = d[i] * (1.0 / sqrt((double)D)), m0 = heavy_m[i];
-            double ex = 0.0;
-            if (__any(take && heavy_z[i] > 0.0)) ex = exp(l > m0 ? m0 - l : l - m0);  // (usually everybody's first)
-            if (take) {
-              heavy_z[i] = l > m0 ? heavy_z[i] * ex + 1.0 : heavy_z[i] + ex;
-              heavy_m[i] = l > m0 ? l : m0;
+            for (int kc = 0; kc < KSTEPS; ++kc) {
+              const uint4 b = buf[((a * TILES + ts) * 16 + n) * CH + ((4 * kc + j) ^ (n & (CH - 1)))];
+              uint32_t qw[4] = {qa[kc].x, qa[kc].y, qa[kc].z, qa[kc].w};
+              const uint32_t bw[4] = {b.x, b.y, b.z, b.w};
+              asm volatile("" : "+v"(qw[0]), "+v"(qw[1]), "+v"(qw[2]), "+v"(qw[3]));  // not converted (and held) up front
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_lo(qw[e]), (double)bf16_lo(bw[e]), d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_hi(qw[e]), (double)bf16_hi(bw[e]), d, 0, 0, 0);
+              }
+            }
+            const unsigned long long own = j == 0 ? h[0] : j == 1 ? h[1] : j == 2 ? h[2] : h[3];  // heads j + 4 i
+#pragma unroll kAddUnroll
+            for (int i = 0; i < GQ; ++i) {
+              double hm = heavy_m[0], hz = heavy_z[0], l = d[0];
+#pragma unroll
+              for (int ii = 1; ii < GQ; ++ii) hm = i == ii ? heavy_m[ii] : hm, hz = i == ii ? heavy_z[ii] : hz, l = i == ii ? d[ii] : l;
+              add(hm, hz, (own >> (16 * (GQ * ts + i) + n)) & 1ull, l * (1.0 / sqrt((double)D)));
+#pragma unroll
+              for (int ii = 0; ii < GQ; ++ii)
+                if (i == ii) heavy_m[ii] = hm, heavy_z[ii] = hz;
             }
           }
         }
@@ -692,7 +745,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
 // few y-blocks only, each walking over all rows and working on the flagged ones: an empty launch
 // then costs a handful of workgroups instead of one per (chunk, row).
 template <int D, int GPAD, int MODE, bool PAGED, int BPW>
-__global__ __launch_bounds__(kScoreThreads, (GPAD == 16 && MODE != SCORE_FILTER && !kRolledPartials<D, GPAD, MODE> ? 1 : 2)) void score_mfma_kernel(ScoreParams p, int gb) {
+__global__ __launch_bounds__(kScoreThreads, GPAD == 16 && (MODE == SCORE_LOGITS || MODE == SCORE_SCORES) ? 1 : 2) void score_mfma_kernel(ScoreParams p, int gb) {
   if (MODE != SCORE_FILTER && p.gate.row_flag) {
     if (*p.gate.n_flagged == 0) return;  // the usual case: nothing to redo
     const int rows = p.geo.n_problems * p.geo.Hkv;
