@@ -185,7 +185,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   // with 128 dims, 0.6 with 64).  64 rows x 32K tokens of N(60, 1) logits, all tiles / up to 1 / 2 / 3 terms, us: 4 heads of 128 dims 223 175 168 167,
   // 7 heads 264 213 185 183, 16 heads 350 327 267 261
   constexpr int kThin = D == 128 ? 3 : 2;
-  constexpr int kAddUnroll = GPAD == 16 ? 1 : 2;  // (16 heads: with four exponentials side by side the filter spills)
+  constexpr int kAddUnroll = GPAD == 16 && (FILTER || D == 128) ? 1 : 4;  // (four exponentials side by side: spills)
   constexpr int kBlockUnroll = PARTIALS ? 1 : BPW;
 
   __shared__ uint4 lds[kScoreWaves][64 * CH];
@@ -456,7 +456,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
           }
         }
       }
-      if (HEAVY && __any(any_heavy)) {  // wave-uniform, rare
+      if (HEAVY && __builtin_expect(__any(any_heavy), 0)) {  // wave-uniform, rare: kept out of the loop's straight line
         // The block is still in LDS: the fp64 logits of a 16-token tile for every head are D / 4 steps of
         // v_mfma_f64_16x16x4 on the operands at hand (element e of everybody's 16 bytes per step), about 1 us a tile.  (Listing the
         // terms and reading their keys again after the last block, sixteen lanes per dot product: 5.7 us for the chunk that holds a
@@ -741,11 +741,22 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
   }
 }
 
+// Workgroups per CU that the registers are held to.  The filter and the partials over chunks of 1024 tokens of 64 dims: three, 168
+// registers, at the price of up to 20 spilled ones in the code for heavy terms with 9 to 16 heads (3 with 5 to 8); left alone they take 173 and 187,
+// and two workgroups.  256 rows x 32K tokens x 16 heads, two and three, us: N(0, 1) logits 390 and 372, queries x 6 547 and 494, N(60, 1) 650 and
+// 564; 7 heads 305 and 284, 365 and 347, 397 and 352; scores of 16 heads 499 and 477, 582 and 517, 751 and 667.  Smaller chunks are for calls
+// that do not fill three.
+template <int D, int GPAD, int MODE, int BPW>
+constexpr int score_workgroups() {
+  if (GPAD == 16 && (MODE == SCORE_LOGITS || MODE == SCORE_SCORES)) return 1;  // every token's values are held to the end
+  return D == 64 && BPW == 4 && (MODE == SCORE_FILTER || MODE == SCORE_PARTIALS) ? 3 : 2;
+}
+
 // grid (chunks, rows).  A gated launch (rows the pre-filter could not certify, usually none) has a
 // few y-blocks only, each walking over all rows and working on the flagged ones: an empty launch
 // then costs a handful of workgroups instead of one per (chunk, row).
 template <int D, int GPAD, int MODE, bool PAGED, int BPW>
-__global__ __launch_bounds__(kScoreThreads, GPAD == 16 && (MODE == SCORE_LOGITS || MODE == SCORE_SCORES) ? 1 : 2) void score_mfma_kernel(ScoreParams p, int gb) {
+__global__ __launch_bounds__(kScoreThreads, (score_workgroups<D, GPAD, MODE, BPW>())) void score_mfma_kernel(ScoreParams p, int gb) {
   if (MODE != SCORE_FILTER && p.gate.row_flag) {
     if (*p.gate.n_flagged == 0) return;  // the usual case: nothing to redo
     const int rows = p.geo.n_problems * p.geo.Hkv;

@@ -1,5 +1,6 @@
 """Registers and LDS of the passes over K, from the built library's own kernel descriptions: two workgroups of four waves have to fit
-a CU (512 registers per lane and SIMD, 160 KB of LDS), else nobody covers a workgroup's LDS and MFMA phases."""
+a CU (512 registers per lane and SIMD, 160 KB of LDS), else nobody covers a workgroup's LDS and MFMA phases; with 64 dims and
+chunks of 1024 tokens three."""
 import os
 import re
 import struct
@@ -47,10 +48,12 @@ def kernels(tmp_path_factory):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads", [4, 8, 16])
 @pytest.mark.parametrize("mode", [FILTER, PARTIALS])
-def test_two_workgroups_per_cu(kernels, d, heads, mode):
-    mine = [f for name, f in kernels.items() if f"score_mfma_kernelILi{d}ELi{heads}ELi{mode}E" in name]
+def test_workgroups_per_cu(kernels, d, heads, mode):
+    mine = {name: f for name, f in kernels.items() if f"score_mfma_kernelILi{d}ELi{heads}ELi{mode}E" in name}
     assert len(mine) == 6  # pages or not, chunks of 256, 512 and 1024 tokens
-    for f in mine:
-        assert int(f["vgpr_count"]) <= 256, f  # both kinds of vector registers
-        assert int(f["group_segment_fixed_size"]) <= 80 * 1024, f
-        assert int(f["vgpr_spill_count"]) == 0, f
+    for name, f in mine.items():
+        fit = 3 if d == 64 and re.search(r"Lb[01]ELi4EE", name) else 2
+        assert int(f["vgpr_count"]) <= 512 // fit // 8 * 8, f  # both kinds of vector registers, in units of 8
+        assert int(f["group_segment_fixed_size"]) <= 160 * 1024 // fit, f
+        if fit == 2:
+            assert int(f["vgpr_spill_count"]) == 0, f
