@@ -456,7 +456,7 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
           }
         }
       }
-      if (HEAVY && __builtin_expect(__any(any_heavy), 0)) {  // wave-uniform, rare: kept out of the loop's straight line
+      if (HEAVY && (FILTER ? __builtin_expect(__any(any_heavy), 0) : __any(any_heavy))) {  // wave-uniform, rare: out of the filter's straight line
         // The block is still in LDS: the fp64 logits of a 16-token tile for every head are D / 4 steps of
         // v_mfma_f64_16x16x4 on the operands at hand (element e of everybody's 16 bytes per step), about 1 us a tile.  (Listing the
         // terms and reading their keys again after the last block, sixteen lanes per dot product: 5.7 us for the chunk that holds a
