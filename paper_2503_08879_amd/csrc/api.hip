@@ -23,7 +23,8 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // of magnitude of margin while the band still holds only a handful of candidates per row.
 constexpr float kBand = 1.0f / 4096.0f;
 
-constexpr int64_t kFillPrefiltered = 512, kFillDense = 256;  // see score_chunk
+constexpr int64_t kFillScores = 256, kFill = 512;  // see score_chunk
+constexpr int64_t kShortFrom = 8192;  // see shortlist_plan
 
 // Sizes of the fast (pre-filtered) eviction path for one descriptor; ok = the path applies.
 struct FastPlan {
@@ -37,10 +38,10 @@ struct FastPlan {
 
 // Tokens one workgroup of the first pass over K covers: 1024, less where the call is too small for that to fill the
 // chip.  At most 1024 chunks per row (the candidate selection gives each a thread).
-// Pre-filtered path: at least 512 workgroups, two per CU (8 rows of 32768 tokens: 22 us with 512 workgroups of 512
-// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256; as the pass is now 18.7 with 512 and 20.3 with 1024).  Dense path: 256 workgroups do for bf16, whose statistics are merged by
-// one workgroup per row (a pass over 8 rows of 30000 tokens x 4 heads: 65.3 us with chunks of 512 tokens, 67.6 with 256; fp32 would
-// rather have 256: 8 rows of 16384 x 4 heads 53.8 against 58.4).
+// At least 512 workgroups, two per CU (filtering pass over 8 rows of 32768 tokens: 22 us with 512 workgroups of 512
+// tokens, 24.7 with 256 of 1024, 27 with 1024 of 256; as the pass is now 18.7 with 512 and 20.3 with 1024; a whole pass of the one-sweep path
+// over 8 rows x 32K 37.3 with 512 and 38.1 with 256, 32 x 8192 43.2 and 44.7).  256 do for a dense call that returns every score, whose
+// statistics are merged by one workgroup per row (8 rows of 30000 tokens x 4 heads: 65.3 us with chunks of 512 tokens, 67.6 with 256).
 int score_chunk(const sagekv_select_desc* d, int64_t fill) {
   const int64_t rows = (int64_t)d->n_problems * d->n_kv_heads;
   int chunk = d->dtype == SAGEKV_BF16 ? kScoreChunk : 512;
@@ -98,13 +99,59 @@ FastPlan fast_plan(const sagekv_select_desc* d) {
   // A chunk's own slots: twice the candidates an average chunk is expected to keep (rank * wB tokens
   // per list over the row's chunks), so that only chunks where the candidates crowd (a needle
   // cluster, the tokens next to the recent window of a trained model) reach into the overflow pool.
-  const int chunk = score_chunk(d, kFillPrefiltered);
+  const int chunk = score_chunk(d, kFill);
   const int64_t n_chunks = (d->L + chunk - 1) / chunk;
   const double per_chunk = (double)f.rank * (double)f.wB * lists / (double)n_chunks;
   int cap_c = 32;
   while (cap_c < 2.0 * per_chunk + 16.0 && cap_c < chunk) cap_c *= 2;
   f.cap_c = cap_c;
   return f;
+}
+
+// Rows of the one-sweep dense path whose selection is spread over many workgroups (shortlist_kernel); ok = that applies.
+struct ShortlistPlan {
+  bool ok;
+  int n_parts, part_tokens, first_run, n_runs, rank, expect;
+  int64_t step;
+};
+
+ShortlistPlan shortlist_plan(const sagekv_select_desc* d) {
+  ShortlistPlan s = {};
+  const int64_t E = d->L - d->n_sink - d->n_recent;
+  const int64_t lists = (int64_t)d->n_problems * (d->head_mode == SAGEKV_HEADS_PER_QUERY ? d->n_q_heads : d->n_kv_heads);
+  auto parts = [&](int tokens) { return (d->L + tokens - 1) / tokens; };
+  s.part_tokens = lists * (parts(kShortTokens) + 1) <= 256 ? kShortTokens : 2 * kShortTokens;  // one workgroup per CU
+  s.n_parts = (int)parts(s.part_tokens);
+  if (d->k < 1 || E > kShortMax || d->L > (int64_t)kShortParts * kShortTokens) return s;
+  // the sample: runs of 16 tokens, aligned (64 bytes of a head's logits), all of them candidates
+  const int64_t r0 = ((int64_t)d->n_sink + 15) / 16, r1 = (d->L - d->n_recent) / 16;
+  const int64_t runs = r1 > r0 ? r1 - r0 : 0;
+  s.first_run = (int)r0;
+  s.n_runs = (int)(runs < kShortRuns ? runs : kShortRuns);
+  s.step = s.n_runs ? (runs << 16) / s.n_runs : 0;
+  // Threshold = the rank-th largest of the n sampled scores.  About rank * E / n tokens of the row reach it, with a relative
+  // sigma of sqrt((1 - n / E) / rank); the rank is the smallest whose 4-sigma low side keeps 1.1 k tokens (scores of neighbours are
+  // not quite independent).
+  const double n = 16.0 * s.n_runs, f = n / (double)E;
+  const double mean = 1.1 * (double)d->k * f, c = 4.0 * sqrt(f < 1.0 ? 1.0 - f : 0.0);
+  const double x = 0.5 * (c + sqrt(c * c + 4.0 * mean));
+  s.rank = (int)ceil(x * x);
+  double most = (double)E;
+  if (s.rank < n) {
+    most = ((double)s.rank + c * sqrt((double)s.rank)) / f;
+    if (most > (double)E) most = (double)E;
+  } else {
+    s.rank = 0;  // everything passes
+  }
+  s.expect = (int)ceil(most);
+  // Registers of the selecting workgroup, and longer rows than one workgroup selects from faster (row_select_kernel): from 8192 tokens on
+  // while the first launch has a CU for every workgroup, us, row_select_kernel and this: 8 rows x 8192 28.9 29.9, x 10000 32.7 30.6, x 24000
+  // 46.9 35.6, 32 x 24000 81 71, 64 x 24000 180 180, 128 x 16384 160 170; always from kRowSelectMax tokens on, up to the logits of
+  // 256 rows x 32K x 4 heads (806 and 806, at twice that 994 and 1008 against separate launches for statistics, scores and selection).
+  s.ok = s.expect <= 16 * 1024 &&
+         (d->L > kRowSelectMax ? 4 * (int64_t)d->n_problems * d->n_q_heads * d->L <= 128ll << 20
+                               : d->L > kShortFrom && lists * (s.n_parts + 1) <= 256);
+  return s;
 }
 
 struct SelectLayout {
@@ -115,8 +162,13 @@ struct SelectLayout {
   // pre-filtered path
   size_t samp_logit, samp_stats, heavy_thr, samp_tau, list_info, ovf_count, cand_idx, cand_logit, cand_score, cand_pos,
       row_fail, n_fail;
+  // one-sweep dense path, many workgroups per row
+  size_t short_cand, short_count, short_tau, flags;
   int64_t slots_per_row, cs_pitch;
   FastPlan fast;
+  ShortlistPlan list;
+  bool one_sweep;  // the one-sweep dense path (small: for a call of few rows),
+  bool shortlist;  // with the shortlist launches
   int64_t Lp;
   int n_chunks, chunk, rows, G, n_lists;
 };
@@ -148,13 +200,33 @@ bool check_select(const sagekv_select_desc* d, sagekv_status* st) {
   return true;
 }
 
+// Calls that the pre-filtered path could serve, but the one-sweep dense path serves faster: its logits (`bytes`) stay in the caches between
+// its passes, and it has two launches in between instead of five.  Whole passes, us, pre-filtered and dense:
+//   rows x tokens, heads     MB                      rows x tokens, heads     MB
+//   8 x 8K, 4                 1    43.5   28.9       64 x 2K, 4                2    40.7   22.8
+//   8 x 32K, 4                4    49.8   37.3       256 x 4K, 4              17     118     92
+//   4 x 128K, 7              15    81.2   66.0       256 x 8K, 4              34     188    171
+//   8 x 128K, 4              17    92.2   86.8       512 x 8K, 4              67     325    315
+//   32 x 32K, 4              17    93.2   88.3       1024 x 8K, 4            134     635    635
+//   16 x 98304, 4            25     109    110       512 x 8K, 7             117     344    348
+//   8 x 256K, 4              34     139    146       8 x 32K, 16              21    88.6   65.3
+//   16 x 64K, 4, 64 dims     17    59.1   53.3       32 x 32K, 7              29    92.0   88.7
+//   16 x 128K, 4, 64 dims    34    78.8   89.9       64 x 20000, 7            36     110    110
+//   per-query lists: 32 x 32K, 7 29 160 126, 64 x 32K, 7 59 246 243, 32 x 32K, 4 17 116 104, 64 x 32K, 4 34 186 187
+bool few_rows(const sagekv_select_desc* d, int G, bool per_query) {
+  const double mb = 4e-6 * (double)d->n_problems * d->n_q_heads * (double)d->L;
+  return mb <= (d->L <= kShortFrom ? 68.0 : G <= 4 && !per_query ? 20.0 : 30.0);
+}
+
 // Workspace layout.  Descriptors the pre-filtered path cannot serve get the one-sweep dense path's
 // scratch (every token's fp32 logits: G * 4 bytes per token).  All others get: a score row per
 // selection list (used by the rows that have to be redone, and by calls that ask for scores_out
 // through the caller's array instead), the candidate records (a few slots per score chunk and an
 // overflow pool per row) and small per-row arrays.  The dense candidate arrays of the final
 // selection live in the list's score row while it is not in use.
-SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
+// few: a call that calls for it (few_rows, rows too long for row_select_kernel) gets the one-sweep dense path with the shortlist launches
+// and their scratch; without, the paths that make do with less.
+SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores, bool few) {
   SelectLayout l = {};
   l.rows = d->n_problems * d->n_kv_heads;
   l.G = d->n_q_heads / d->n_kv_heads;
@@ -162,7 +234,11 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
   l.Lp = (d->L + 3) / 4 * 4;
   l.fast = fast_plan(d);
   l.small = l.fast.ok;
-  l.chunk = score_chunk(d, l.small ? kFillPrefiltered : kFillDense);
+  l.list = shortlist_plan(d);
+  few = few && own_scores;
+  l.one_sweep = !l.small || (few && few_rows(d, l.G, l.n_lists > 1) && (l.list.ok || d->L <= kRowSelectMax));
+  l.shortlist = few && l.list.ok && l.one_sweep;
+  l.chunk = score_chunk(d, l.one_sweep && !few ? kFillScores : kFill);
   l.n_chunks = (int)((d->L + l.chunk - 1) / l.chunk);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -171,12 +247,20 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
     return at;
   };
   const size_t rows = (size_t)l.rows;
-  l.logits = take(l.small ? 0 : rows * l.n_chunks * l.G * l.chunk * sizeof(float));
-  l.partials = take(rows * l.n_chunks * (l.small ? chunk_line_words(l.G) * sizeof(float) : l.G * sizeof(ChunkPartial)));
+  l.n_fail = take(l.small ? sizeof(int) : 0);  // first: at the same place whatever path a call takes
+  l.logits = take(l.one_sweep ? rows * l.n_chunks * l.G * l.chunk * sizeof(float) : 0);
+  l.partials = take(rows * l.n_chunks * (l.one_sweep ? l.G * sizeof(ChunkPartial) : chunk_line_words(l.G) * sizeof(float)));
   l.stats = take(rows * l.G * sizeof(RowStat));
   l.ghist = take(rows * l.n_lists * kHistBins * sizeof(int));
   bool cs_in_scores = false;
-  if (l.small) {
+  const size_t lists = rows * l.n_lists;
+  if (l.small && l.one_sweep) l.flags = take(lists * sizeof(int));
+  if (l.shortlist) {
+    l.short_cand = take(lists * l.list.n_parts * l.list.part_tokens * sizeof(uint2));
+    l.short_count = take(lists * l.list.n_parts * sizeof(int));
+    l.short_tau = take(lists * sizeof(float));
+  }
+  if (!l.one_sweep) {
     const FastPlan& f = l.fast;
     const size_t ns = (size_t)64 * (f.nA + f.nB + f.nC);
     l.samp_logit = take(rows * ns * f.Gs * sizeof(float));
@@ -189,7 +273,6 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
     l.cand_idx = take(rows * l.slots_per_row * sizeof(int32_t));
     l.cand_logit = take(rows * l.slots_per_row * f.Gs * sizeof(float));
     l.row_fail = take(rows * sizeof(int));
-    l.n_fail = take(sizeof(int));
     cs_in_scores = 2 * (int64_t)f.cap <= l.Lp;
     l.cs_pitch = cs_in_scores ? l.Lp : f.cap;
     if (!cs_in_scores) {
@@ -199,7 +282,7 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores) {
   }
   // last, so that no other offset depends on whether the caller brought its own score rows
   // (one-sweep rows whose selection holds its scores in registers need none)
-  own_scores = own_scores && (l.small || d->L > kRowSelectMax);
+  own_scores = own_scores && (!l.one_sweep || l.shortlist || d->L > kRowSelectMax);
   l.scores = take(own_scores ? rows * l.n_lists * l.Lp * sizeof(float) : 0);
   if (cs_in_scores) {  // the first half of a list's score row: exact scores, the second: token indices
     l.cand_score = l.scores;
@@ -434,7 +517,8 @@ const char* sagekv_status_string(sagekv_status s) {
 size_t sagekv_select_workspace_bytes(const sagekv_select_desc* desc) {
   sagekv_status st;
   if (!check_select(desc, &st)) return 0;
-  return select_layout(desc, true).total;
+  const size_t n = select_layout(desc, true, true).total, less = select_layout(desc, true, false).total;
+  return n > less ? n : less;
 }
 
 }  // extern "C"
@@ -450,12 +534,16 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
   if (!aligned16(q_last) || !aligned16(K) || !aligned16(V) || !aligned16(Kc) || !aligned16(Vc) ||
       ((uintptr_t)kept_idx & 3u) || ((uintptr_t)scores_out & 15u) || !aligned16(workspace))
     return SAGEKV_ERR_UNSUPPORTED;
-  const SelectLayout l = select_layout(d, scores_out == nullptr);
+  SelectLayout l = select_layout(d, scores_out == nullptr, false);
   if (!workspace || workspace_bytes < l.total) return SAGEKV_ERR_WORKSPACE;
+  if (scores_out == nullptr) {
+    const SelectLayout few = select_layout(d, true, true);
+    if (few.one_sweep && workspace_bytes >= few.total) l = few;
+  }
   hipStream_t s = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   // per-token scores are only produced by the dense stages
-  const bool fast = l.small && scores_out == nullptr;
+  const bool fast = !l.one_sweep && scores_out == nullptr;
 
   RowGeom geo;
   geo.n_problems = d->n_problems;
@@ -647,7 +735,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     e = launch_topk(kp, s);
     t.end(SAGEKV_STAGE_REDO);
     if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
-  } else if (l.small) {
+  } else if (!l.one_sweep) {
     // ---- every score is asked for, no logit scratch: two sweeps over K (partials, then scores)
     e = run_sample();  // for heavy_thr (it also clears the flags; the marker below follows it)
     if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
@@ -687,7 +775,34 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
     in.ks_head = d->k_stride_head;
     in.ks_token = d->k_stride_token;
     in.pm = pm;
-    if (d->L <= kRowSelectMax) {
+    int* const flags = l.small ? (int*)(ws + l.flags) : nullptr;
+    int* const marker = l.small ? (int*)(ws + l.n_fail) : nullptr;
+    if (l.shortlist) {
+      ShortlistParams hp = {};
+      hp.in = in;
+      hp.stats = stats;
+      hp.scores = scores;
+      hp.pitch = pitch;
+      hp.cand = (uint2*)(ws + l.short_cand);
+      hp.count = (int*)(ws + l.short_count);
+      hp.tau = (float*)(ws + l.short_tau);
+      hp.flag = flags;
+      hp.marker = marker;
+      hp.n_parts = l.list.n_parts;
+      hp.part_tokens = l.list.part_tokens;
+      hp.S = d->n_sink;
+      hp.W = d->n_recent;
+      hp.n_lists = l.n_lists;
+      hp.first_run = l.list.first_run;
+      hp.n_runs = l.list.n_runs;
+      hp.rank = l.list.rank;
+      hp.step = l.list.step;
+      hp.expect = l.list.expect;
+      t.begin(SAGEKV_STAGE_TOPK);
+      e = launch_shortlist(hp, kp, s);
+      t.end(SAGEKV_STAGE_TOPK);
+      if (e != hipSuccess) return SAGEKV_ERR_DEVICE;
+    } else if (d->L <= kRowSelectMax) {
       RowSelectParams rp = {};
       rp.in = in;
       rp.scores = scores_out;
@@ -698,6 +813,8 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
       rp.k = d->k;
       rp.n_lists = l.n_lists;
       rp.band = kBand;
+      rp.flag = flags;
+      rp.marker = marker;
       t.begin(SAGEKV_STAGE_TOPK);
       e = launch_row_select(rp, s);
       t.end(SAGEKV_STAGE_TOPK);
@@ -824,7 +941,7 @@ sagekv_status sagekv_select_redone_rows(const sagekv_select_desc* d, const void*
   sagekv_status st;
   if (!check_select(d, &st)) return st;
   if (!n_rows) return SAGEKV_ERR_INVALID_ARG;
-  const SelectLayout l = select_layout(d, true);
+  const SelectLayout l = select_layout(d, true, false);
   if (!workspace || workspace_bytes < l.total) return SAGEKV_ERR_WORKSPACE;
   *n_rows = -1;
   if (!l.small) return SAGEKV_OK;
@@ -833,6 +950,23 @@ sagekv_status sagekv_select_redone_rows(const sagekv_select_desc* d, const void*
   int n = 0;  // -1: the last call went through the dense stages for every row
   if (hipMemcpy(&n, (const char*)workspace + l.n_fail, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
     return SAGEKV_ERR_DEVICE;
+  if (n == kFlagsPerList) {  // one flag per list
+    const SelectLayout f = select_layout(d, true, true);
+    if (workspace_bytes < f.total) return SAGEKV_ERR_WORKSPACE;
+    const int lists = l.rows * l.n_lists;
+    int flags[1024], last = -1;
+    n = 0;
+    for (int i0 = 0; i0 < lists; i0 += 1024) {
+      const int cnt = lists - i0 < 1024 ? lists - i0 : 1024;
+      if (hipMemcpy(flags, (const char*)workspace + f.flags + i0 * sizeof(int), cnt * sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
+        return SAGEKV_ERR_DEVICE;
+      for (int i = 0; i < cnt; ++i)
+        if (flags[i] != 0 && (i0 + i) / l.n_lists != last) {
+          last = (i0 + i) / l.n_lists;
+          ++n;
+        }
+    }
+  }
   *n_rows = n;
   return SAGEKV_OK;
 }

@@ -210,9 +210,35 @@ struct RowSelectParams {
   int S, W, k;
   int n_lists;             // 1 or G
   float band;
+  int* flag;    // nullable, see ShortlistParams
+  int* marker;
 };
 
-// Longer rows: the statistics alone.
+// Rows spread over many workgroups: statistics, scores and the scores worth looking at in one launch, the selection among those in a
+// second one.
+constexpr int kShortTokens = 4096;    // tokens one workgroup of the first launch looks through, or twice as many
+constexpr int kShortMax = 512 * 1024;  // most eviction candidates per row (one bit each in LDS)
+constexpr int kShortParts = 1024;     // most workgroups per list
+constexpr int kShortRuns = 128;       // most runs of 16 tokens a threshold is sampled from
+constexpr int kFlagsPerList = -2;     // *marker: the call left one flag per list
+struct ShortlistParams {
+  DenseRows in;
+  RowStat* stats;   // out [rows][G]
+  float* scores;    // out [rows * n_lists][pitch]
+  int64_t pitch;    // multiple of 4
+  uint2* cand;      // [rows * n_lists][n_parts][part_tokens]  (score, token)
+  int* count;       // [rows * n_lists][n_parts]
+  float* tau;       // [rows * n_lists]  nothing below it is among cand
+  int* flag;        // nullable [rows * n_lists]: 1 = the list went through its whole score row
+  int* marker;      // set with flag: kFlagsPerList
+  int n_parts, part_tokens, S, W, n_lists;
+  // the sample: n_runs runs of 16 tokens, the first at token 16 * first_run, `step` (48.16 fixed point) such runs apart
+  int first_run, n_runs, rank;
+  int64_t step;
+  int expect;       // scores a list usually hands on at most
+};
+
+// Longer rows, and calls that return every score: the statistics alone.
 struct RowStatsParams {
   DenseRows in;
   RowStat* stats;  // out [rows][G]
@@ -371,6 +397,7 @@ hipError_t launch_topk_cand(const TopkCandParams& p, hipStream_t s);
 hipError_t launch_score(const ScoreParams& p, ScoreMode mode, hipStream_t s);  // any mode but SCORE_FILTER
 hipError_t launch_stats(const StatsParams& p, int rows, hipStream_t s);
 hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s);
+hipError_t launch_shortlist(const ShortlistParams& p, const TopkParams& tp, hipStream_t s);
 hipError_t launch_row_stats(const RowStatsParams& p, hipStream_t s);
 hipError_t launch_combine(const CombineParams& p, hipStream_t s);
 hipError_t launch_topk(const TopkParams& p, hipStream_t s);

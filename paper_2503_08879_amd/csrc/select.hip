@@ -107,14 +107,14 @@ __device__ inline int lanes_below(unsigned long long ballot) {  // set bits of `
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
 }
 
+// One selection list (one per row, group-sum, or one per (row, query head)) from its score row.  p.ghist: the first digit's
+// histogram is there; null: it is taken here.
 template <int DT>
-__global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
+__device__ __forceinline__ void topk_list(const TopkParams& p, uint32_t* bitmap /* bit i + head: candidate i is selected (head: see QuadRow) */,
+                                          int list) {
   __shared__ TopkShared sh;
-  extern __shared__ __align__(16) uint32_t bitmap[];  // bit i + head: candidate i is selected (head: see QuadRow)
   const int tid = threadIdx.x;
-  const int list = blockIdx.x;  // selection list: one per row (group-sum) or one per (row, query head)
   const int row = list / p.n_lists, gl = list % p.n_lists;
-  if (p.gate.row_flag && (*p.gate.n_flagged == 0 || p.gate.row_flag[row] == 0)) return;  // gated launch: only the flagged rows
   const int g_lo = p.n_lists > 1 ? gl : 0, g_hi = p.n_lists > 1 ? gl + 1 : p.geo.G;
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
   const int S = p.S, W = p.W, k = p.k;
@@ -135,8 +135,12 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
   const int edge_i = tid < 8 ? edge_index(qr, tid) : -1;  // this thread's edge element, if any
 
   // 1. bracket of the k-th fp32 score: its first 22 bits
-  for (int b = tid; b < kHistBins; b += kTopkThreads) sh.hist[b] = p.ghist[(int64_t)list * kHistBins + b];
-  __syncthreads();
+  if (p.ghist) {
+    for (int b = tid; b < kHistBins; b += kTopkThreads) sh.hist[b] = p.ghist[(int64_t)list * kHistBins + b];
+    __syncthreads();
+  } else {
+    hist_pass_quads(sh, qr, 0u, 0u, 20, 11);
+  }
   uint32_t tau;
   int quota;
   {
@@ -409,6 +413,14 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
   }
 }
 
+template <int DT>
+__global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
+  extern __shared__ __align__(16) uint32_t bitmap[];
+  const int list = blockIdx.x;
+  if (p.gate.row_flag && (*p.gate.n_flagged == 0 || p.gate.row_flag[list / p.n_lists] == 0)) return;  // gated launch: only the flagged rows
+  topk_list<DT>(p, bitmap, list);
+}
+
 // ---- one-sweep dense path, whole row in one workgroup ------------------------------------------
 // Statistics (fp64 merge of the chunks' partials), scores, top-k and ordered output of one selection list, the
 // list's scores held in registers: thread t owns the quads t, t + 1024, ... of the row (4 consecutive tokens
@@ -458,6 +470,10 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
         }
       }
   };
+  if (tid == 0 && p.flag) {
+    p.flag[list] = 0;
+    if (list == 0) *p.marker = kFlagsPerList;
+  }
   const float max0 = exact_maximum(p.in, row, g_lo, g_hi, 0);
   for (int g = g_lo + wave; g < g_hi; g += kTopkWaves) {  // one wave per head
     const RowStat st = merge_partials_wave(p.in.partials + ((int64_t)row * G + g) * p.in.n_chunks, p.in.n_chunks);
@@ -536,7 +552,10 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   __syncthreads();
   const int nb = sh.n_band, r = k - sh.n_above;
   bool general = nb > kMaxBand || r < 1 || r > nb;
-  if (!general) {
+  if (!general && nb == r && !out) {  // the whole band is selected: no need to rank it
+    for (int t = tid; t < nb; t += kTopkThreads) atomicOr(&bitmap[sh.band_tok[t] >> 5], 1u << (sh.band_tok[t] & 31));
+    __syncthreads();
+  } else if (!general) {
     refine_band<DT>(sh, nb, geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, g_lo, g_hi);
     if (tid == 0) sh.n_band = 0;  // now: 1 = the threshold lies strictly inside the band
     __syncthreads();
@@ -553,6 +572,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     general = sh.n_band == 0;
   }
   if (general) {
+    if (tid == 0 && p.flag) p.flag[list] = 1;
     // near-ties by the thousand, or a refined threshold on the band's edge: refine the whole band in place, then an
     // exact radix select over the registers; equal scores go to the lowest tokens while the quota lasts
     __syncthreads();
@@ -635,6 +655,256 @@ __global__ __launch_bounds__(kTopkThreads) void row_stats_kernel(RowStatsParams 
   if (tid < G) p.stats[(int64_t)row * G + tid] = s_stat[tid];
 }
 
+// ---- one-sweep dense path, a row spread over many workgroups -------------------------------------
+// First launch: a workgroup per list and kShortTokens tokens turns the logits into scores and hands on the few that can be
+// among the k best: those at or above a threshold that every workgroup of a list finds for itself, from the same sample of the list's own
+// scores.  One more workgroup per list takes the heavy terms into the normalisers (exact_changes), which only the fp64
+// scores of the band around the k-th need: 1e-6 of a score against the band's 2e-4.
+// Latency bound: 6.6 us for 8 rows x 32K tokens x 4 heads, of them 2.2 for partials and logits, 1.4 exponentials, 2.4 the threshold; the
+// second launch 5.8 (13.5 for 8 rows x 128K, k = 3580, of them 2.0 to collect the scores, 2.9 bracket, 1.7 band, 3.5 fp64 scores, 2.2
+// output).  Together they stand for statistics, combine and top-k in launches of their own, 4.5 + 7 + 13.5, and for a whole pass over those rows
+// 51.4 -> 37.3 us.  The sample is 128 runs of 16 tokens, 64 bytes of a head's logits each: 512 runs of four cost every workgroup
+// four times the lines (4.0 us instead of 2.2, 10.6 instead of 4.5 with 32 rows).  NQ = 2: half as many workgroups where a CU
+// would get more than one (32 rows x 32K: 25 us and 12 under the profiler).
+template <int DT, int HB, int NQ>
+__global__ __launch_bounds__(kTopkThreads) void shortlist_kernel(ShortlistParams p) {
+  __shared__ union {
+    ExactSums exact;
+    RegSelect sel;
+  } sh_u;
+  __shared__ RowStat s_stat[64];
+  __shared__ float s_thr[64];
+  __shared__ int n_out;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int list = blockIdx.y, row = list / p.n_lists, gl = list % p.n_lists;
+  const RowGeom& geo = p.in.geo;
+  const int G = geo.G, L = (int)geo.L;
+  const int g_lo = p.n_lists > 1 ? gl : 0, g_hi = p.n_lists > 1 ? gl + 1 : G;
+  const ChunkPartial* partials = p.in.partials + (int64_t)row * G * p.in.n_chunks;
+  if (blockIdx.x == 0) {
+    const float max0 = exact_maximum(p.in, row, g_lo, g_hi, 0);
+    for (int g = g_lo + wave; g < g_hi; g += kTopkWaves) {
+      const RowStat st = merge_partials_wave(partials + (int64_t)g * p.in.n_chunks, p.in.n_chunks);
+      if (lane == 0) {
+        s_stat[g] = st;
+        s_thr[g] = heavy_logit_threshold(st.M, (float)st.Z);
+      }
+    }
+    if (exact_changes<DT>(p.in, sh_u.exact, row, g_lo, g_hi, s_stat, s_thr, max0)) exact_apply(sh_u.exact, g_lo, g_hi, s_stat);
+    if (tid >= g_lo && tid < g_hi) p.stats[(int64_t)row * G + tid] = s_stat[tid];
+    return;
+  }
+  constexpr int kPart = 4 * NQ * kTopkThreads;
+  const int part = (int)blockIdx.x - 1;
+  const int tok0 = part * kPart + 4 * tid;  // this thread's first four tokens of NQ times four,
+  const int run0 = 16 * (p.first_run + (int)(((tid >> 2) * p.step) >> 16)) + 4 * (tid & 3);  // and its four of the sample
+  const bool sampled = tid < 4 * p.n_runs;
+  float4 x[HB][NQ], y[HB];
+  auto load = [&](int g0) {
+#pragma unroll
+    for (int h = 0; h < HB; ++h) {
+      y[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < NQ; ++u) x[h][u] = y[h];
+      if (g0 + h < g_hi) {
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) {
+          const int tok = tok0 + 4 * u * kTopkThreads;
+          if (tok < L) x[h][u] = *reinterpret_cast<const float4*>(p.in.logits + logit_index(geo, p.in.n_chunks, p.in.chunk, row, g0 + h, tok));
+        }
+        if (sampled) y[h] = *reinterpret_cast<const float4*>(p.in.logits + logit_index(geo, p.in.n_chunks, p.in.chunk, row, g0 + h, run0));
+      }
+    }
+  };
+  load(g_lo);
+  for (int g = g_lo + (kTopkWaves - 1 - wave); g < g_hi; g += kTopkWaves) {  // (the last waves hold no sample)
+    const RowStat st = merge_partials_wave(partials + (int64_t)g * p.in.n_chunks, p.in.n_chunks);
+    if (lane == 0) s_stat[g] = st;
+  }
+  if (tid == 0) n_out = 0;
+  __syncthreads();
+  float v[NQ][4], w[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < NQ; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[u][e] = 0.f;
+  auto add = [](float (&a)[4], const float4& l, float M, float inv) {
+    a[0] += exp_times(l.x - M, inv);
+    a[1] += exp_times(l.y - M, inv);
+    a[2] += exp_times(l.z - M, inv);
+    a[3] += exp_times(l.w - M, inv);
+  };
+  for (int g0 = g_lo;;) {
+#pragma unroll
+    for (int h = 0; h < HB; ++h)
+      if (g0 + h < g_hi) {
+        const float M = s_stat[g0 + h].M, inv = s_stat[g0 + h].invZ;
+        if (sampled) add(w, y[h], M, inv);
+#pragma unroll
+        for (int u = 0; u < NQ; ++u) add(v[u], x[h][u], M, inv);
+      }
+    g0 += HB;
+    if (g0 >= g_hi) break;
+    load(g0);
+  }
+#pragma unroll
+  for (int u = 0; u < NQ; ++u) {
+    const int tok = tok0 + 4 * u * kTopkThreads;
+    if (tok < L) *reinterpret_cast<float4*>(p.scores + (int64_t)list * p.pitch + tok) = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+  }
+  uint32_t tlo = 0u, thi;
+  if (p.rank > 0)  // (0: everything passes)
+    bracket_kth<false>(sh_u.sel, [&](auto f) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f(sampled ? w[e] : -1.f);
+    }, p.rank, &tlo, &thi);
+  const float tau = __uint_as_float(tlo);
+  bool ok[NQ][4];
+  unsigned long long bal[NQ][4];
+  int n_wave = 0;
+#pragma unroll
+  for (int u = 0; u < NQ; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int tok = tok0 + 4 * u * kTopkThreads + e;
+      ok[u][e] = tok >= p.S && tok < L - p.W && v[u][e] >= tau;
+      bal[u][e] = __ballot(ok[u][e]);
+      n_wave += __popcll(bal[u][e]);
+    }
+  int base = 0;
+  if (lane == 0 && n_wave) base = atomicAdd(&n_out, n_wave);
+  base = __builtin_amdgcn_readfirstlane(base);
+  uint2* out = p.cand + ((int64_t)list * p.n_parts + part) * kPart;
+#pragma unroll
+  for (int u = 0; u < NQ; ++u)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (ok[u][e]) out[base + lanes_below(bal[u][e])] = make_uint2(__float_as_uint(v[u][e]), (uint32_t)(tok0 + 4 * u * kTopkThreads + e));
+      base += __popcll(bal[u][e]);
+    }
+  __syncthreads();
+  if (tid == 0) {
+    p.count[(int64_t)list * p.n_parts + part] = n_out;
+    if (part == 0) p.tau[list] = tau;
+  }
+}
+
+// Second launch: a workgroup per list selects among the scores handed on, in registers, as row_select_kernel does.  Where they do
+// not do (a threshold that turned out too high or far too low, a band of near-ties), the same workgroup goes through the list's
+// score row instead.
+template <int DT, int NPT>
+__global__ __launch_bounds__(kTopkThreads) void shortlist_select_kernel(ShortlistParams p, TopkParams tp) {
+  __shared__ RegSelect sh;
+  __shared__ RowStat s_stat[64];
+  __shared__ int part_off[kShortParts + 1];
+  extern __shared__ __align__(16) uint32_t bitmap[];
+  const int tid = threadIdx.x, list = blockIdx.x;
+  const int row = list / p.n_lists, gl = list % p.n_lists;
+  const RowGeom& geo = tp.geo;
+  const int G = geo.G, S = tp.S, W = tp.W, k = tp.k, L = (int)geo.L, E = L - S - W;
+  const int g_lo = p.n_lists > 1 ? gl : 0, g_hi = p.n_lists > 1 ? gl + 1 : G;
+  const int prob = row / geo.Hkv, c = row % geo.Hkv;
+  int32_t* kept_row = tp.kept_idx + (int64_t)row * (S + p.n_lists * k + W);
+  int32_t* kept = kept_row + S + gl * k;
+
+  const int raw = tid < p.n_parts ? p.count[(int64_t)list * p.n_parts + tid] : 0;
+  const float tau = p.tau[list];
+  if (tid >= g_lo && tid < g_hi) s_stat[tid] = p.stats[(int64_t)row * G + tid];
+  if (gl == 0) {
+    for (int t = tid; t < S; t += kTopkThreads) kept_row[t] = t;
+    for (int t = tid; t < W; t += kTopkThreads) kept_row[S + p.n_lists * k + t] = L - W + t;
+  }
+  if (tid == 0 && p.flag) {
+    p.flag[list] = 0;
+    if (list == 0) *p.marker = kFlagsPerList;
+  }
+  const int n_words = (E + 31) >> 5;
+  for (int w = tid; w < n_words; w += kTopkThreads) bitmap[w] = 0u;
+  int n_c;
+  const int incl = block_scan_incl(raw, sh.wave_tot, &n_c);
+  if (tid < p.n_parts) part_off[tid] = incl - raw;
+  if (tid == 0) part_off[p.n_parts] = n_c;
+  __syncthreads();
+  bool ok = n_c >= k && n_c <= NPT * kTopkThreads;
+  if (ok) {
+    const uint2* in = p.cand + (int64_t)list * p.n_parts * p.part_tokens;
+    float v[NPT];
+    int tok[NPT];
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      v[u] = -1.f;
+      tok[u] = S;
+      const int j0 = u * kTopkThreads + (tid & ~63), j = j0 + (tid & 63);  // a wave's 64 lie in one part or a few adjacent ones
+      if (j0 < n_c) {
+        int at = -1;  // the last part that begins at or before j0
+        for (int q = 0; q < p.n_parts; q += 64) at += __popcll(__ballot(q + (tid & 63) < p.n_parts && part_off[q + (tid & 63)] <= j0));
+        int from = part_off[at], to = part_off[at + 1];
+        while (__any(j >= to && j < n_c)) {
+          if (j >= to && j < n_c) {
+            ++at;
+            from = to;
+            to = part_off[at + 1];
+          }
+        }
+        if (j < n_c) {
+          const uint2 r = in[(int64_t)at * p.part_tokens + (j - from)];
+          v[u] = __uint_as_float(r.x);
+          tok[u] = (int)r.y;
+        }
+      }
+    }
+    uint32_t tlo, thi;
+    bracket_kth<true>(sh, [&](auto f) {
+#pragma unroll
+      for (int u = 0; u < NPT; ++u) f(v[u]);
+    }, k, &tlo, &thi);
+    const float lo = __uint_as_float(tlo) * (1.0f - tp.band) - kDenormSlack,
+                hi = __uint_as_float(thi) * (1.0f + tp.band) + kDenormSlack;
+    int above = 0;  // wave-uniform
+#pragma unroll
+    for (int u = 0; u < NPT; ++u) {
+      const bool gt = v[u] > hi;
+      above += __popcll(__ballot(gt));
+      if (gt) {
+        atomicOr(&bitmap[(tok[u] - S) >> 5], 1u << ((tok[u] - S) & 31));
+      } else if (v[u] >= 0.f && v[u] >= lo) {
+        const int t = atomicAdd(&sh.n_band, 1);
+        if (t < kMaxBand) sh.band_tok[t] = tok[u];
+      }
+    }
+    if ((tid & 63) == 0 && above) atomicAdd(&sh.n_above, above);
+    __syncthreads();
+    const int nb = sh.n_band, r = k - sh.n_above;
+    // (what was not handed on scores below tau: none of it reaches the band; tau = 0: everything was handed on)
+    ok = (lo >= tau || tau == 0.f) && nb <= kMaxBand && r >= 1 && r <= nb;
+    if (ok && nb == r) {  // the whole band is selected: no need to rank it
+      for (int t = tid; t < nb; t += kTopkThreads) atomicOr(&bitmap[(sh.band_tok[t] - S) >> 5], 1u << ((sh.band_tok[t] - S) & 31));
+      __syncthreads();
+    } else if (ok) {
+      refine_band<DT>(sh, nb, geo, tp.q_last, tp.K, tp.pm, tp.ks_problem, tp.ks_head, tp.ks_token, s_stat, prob, c, g_lo, g_hi);
+      if (tid == 0) sh.n_band = 0;  // now: 1 = the threshold lies strictly inside the band
+      __syncthreads();
+      for (int t = tid; t < nb; t += kTopkThreads) {
+        const float x = sh.band_v[t];
+        const int i = sh.band_tok[t];
+        int rank = 0;
+        for (int u = 0; u < nb; ++u) rank += sh.band_v[u] > x || (sh.band_v[u] == x && sh.band_tok[u] < i);
+        if (rank == r - 1 && x > lo && x < hi) sh.n_band = 1;
+        if (rank < r) atomicOr(&bitmap[(i - S) >> 5], 1u << ((i - S) & 31));
+      }
+      __syncthreads();
+      ok = sh.n_band != 0;
+    }
+  }
+  if (ok) {
+    bitmap_compact(bitmap, n_words, S, kept, k, sh.wave_tot);
+  } else {
+    if (tid == 0 && p.flag) p.flag[list] = 1;
+    __syncthreads();
+    topk_list<DT>(tp, bitmap, list);
+  }
+}
+
 // ---- gather -----------------------------------------------------------------------------------
 constexpr int kGatherThreads = 256;
 constexpr int kGatherTokens = 64;  // reduced-cache rows one workgroup copies
@@ -704,6 +974,52 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherParams p, 
 
 }  // namespace
 
+// Room for one bit per candidate, whatever the row's alignment.
+static int64_t bitmap_bytes(const TopkParams& p) { return ((p.geo.L - p.S - p.W + 3 + 31) / 32 + 3) / 4 * 16; }
+
+template <int DT, int NPT>
+static hipError_t launch_shortlist_select(const ShortlistParams& p, const TopkParams& tp, unsigned lists, hipStream_t s) {
+  static uint64_t done = 0;
+  const hipError_t e = allow_dynamic_lds((const void*)shortlist_select_kernel<DT, NPT>, kShortMax / 8 + 16, &done);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((shortlist_select_kernel<DT, NPT>), dim3(lists), dim3(kTopkThreads), tp.bitmap_bytes, s, p, tp);
+  return hipGetLastError();
+}
+
+template <int DT>
+static hipError_t launch_shortlist_t(const ShortlistParams& p, const TopkParams& tp, unsigned lists, hipStream_t s) {
+  const dim3 grid((unsigned)p.n_parts + 1u, lists);
+  const int heads = p.n_lists > 1 ? 1 : p.in.geo.G;
+#define SAGEKV_LAUNCH(HB)                                                                              \
+  if (p.part_tokens == kShortTokens)                                                                   \
+    hipLaunchKernelGGL((shortlist_kernel<DT, HB, 1>), grid, dim3(kTopkThreads), 0, s, p);              \
+  else                                                                                                 \
+    hipLaunchKernelGGL((shortlist_kernel<DT, HB, 2>), grid, dim3(kTopkThreads), 0, s, p)
+  if (heads == 1) {
+    SAGEKV_LAUNCH(1);
+  } else if (heads <= 4 || p.part_tokens != kShortTokens) {
+    SAGEKV_LAUNCH(4);
+  } else {
+    hipLaunchKernelGGL((shortlist_kernel<DT, 8, 1>), grid, dim3(kTopkThreads), 0, s, p);
+  }
+#undef SAGEKV_LAUNCH
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return p.expect <= 4 * kTopkThreads   ? launch_shortlist_select<DT, 4>(p, tp, lists, s)
+         : p.expect <= 8 * kTopkThreads ? launch_shortlist_select<DT, 8>(p, tp, lists, s)
+                                        : launch_shortlist_select<DT, 16>(p, tp, lists, s);
+}
+
+hipError_t launch_shortlist(const ShortlistParams& p, const TopkParams& tp0, hipStream_t s) {
+  const RowGeom& geo = p.in.geo;
+  if (geo.G > 64 || p.n_parts > kShortParts || (p.part_tokens != kShortTokens && p.part_tokens != 2 * kShortTokens) || geo.L - tp0.S - tp0.W > kShortMax) return hipErrorInvalidValue;
+  TopkParams tp = tp0;
+  tp.ghist = nullptr;
+  tp.bitmap_bytes = (int)bitmap_bytes(tp);
+  const unsigned lists = (unsigned)(geo.n_problems * geo.Hkv * p.n_lists);
+  return geo.dtype == DT_BF16 ? launch_shortlist_t<DT_BF16>(p, tp, lists, s) : launch_shortlist_t<DT_F32>(p, tp, lists, s);
+}
+
 hipError_t launch_topk(const TopkParams& p0, hipStream_t s) {
   constexpr int kMaxBitmap = 64 * 1024;
   static uint64_t done_bf16 = 0, done_f32 = 0;
@@ -711,8 +1027,7 @@ hipError_t launch_topk(const TopkParams& p0, hipStream_t s) {
                                          : allow_dynamic_lds((const void*)topk_kernel<DT_F32>, kMaxBitmap, &done_f32);
   if (e != hipSuccess) return e;
   TopkParams p = p0;
-  const int64_t E = p.geo.L - p.S - p.W;
-  const int64_t need = ((E + 3 + 31) / 32 + 3) / 4 * 16;  // one bit per candidate, whatever the row's alignment
+  const int64_t need = bitmap_bytes(p);
   p.bitmap_bytes = need <= kMaxBitmap ? (int)need : 0;
   const int lists = p.geo.n_problems * p.geo.Hkv * p.n_lists;
   if (p.geo.dtype == DT_BF16)
