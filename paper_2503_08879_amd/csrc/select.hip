@@ -426,17 +426,15 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams p) {
 // list's scores held in registers: thread t owns the quads t, t + 1024, ... of the row (4 consecutive tokens
 // each).  Latency bound (one workgroup per list, a chain of memory round trips and barriers), so it replaces the
 // launches of the general route below for rows of up to 24576 tokens (24 registers of scores per thread):
-// statistics + combine + top-k took 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 29, now 22; 9.5 + 4.5 + 15.3 and 14, now 10.7,
-// for 2 rows of 4096 (the correction of the normalisers for heavy terms, 3.5 and 2.4 us of it, included); at 30000 tokens
-// the two are even (46 us, 8 rows, without it), beyond that several workgroups per row win.
-template <int DT, int NQ>
+// statistics + combine + top-k took 21 + 11 + 23 us for 256 rows of 8192 tokens, this kernel 29, now 22; 9.5 + 4.5 + 15.3 and 14, then 10.7, for
+// 2 rows of 4096.  Of the 22 and the 10.7, 3.5 and 2.4 go into the normalisers' heavy terms, and 1.6 into fp64 scores: both are left out
+// where the band around the k-th score holds no more than is selected of it (2 rows x 4096, k = 188: a whole pass 19.9 -> 17.8 us, three
+// such rows in four).  Calls of few, longer rows: see shortlist_kernel.
+template <int DT, int NQ, bool SCORES>
 __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParams p) {
   constexpr int N = 4 * NQ;
-  __shared__ union {
-    ExactSums exact;  // first the statistics,
-    RegSelect sel;    // then the selection
-  } sh_u;
-  RegSelect& sh = sh_u.sel;
+  __shared__ ExactSums sh_exact;
+  __shared__ RegSelect sh;
   __shared__ RowStat s_stat[64];  // up to 64 heads per KV head
   __shared__ float s_thr[64];
   __shared__ __align__(16) uint32_t bitmap[NQ * kTopkThreads * 4 / 32];
@@ -454,7 +452,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     for (int t = tid; t < S; t += kTopkThreads) kept_row[t] = t;
     for (int t = tid; t < W; t += kTopkThreads) kept_row[S + p.n_lists * k + t] = L - W + t;
   }
-  if (k == 0 && !p.scores) return;
+  if (k == 0 && !SCORES) return;
   // the logits of HB heads at a time, the next ones in flight while the current ones are used; the first are asked for
   // once a wave has done its part of the statistics
   constexpr int HB = NQ <= 2 ? 4 : NQ <= 4 ? 2 : 1;
@@ -483,9 +481,14 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     }
   }
   for (int w = tid; w < (int)(sizeof(bitmap) / 4); w += kTopkThreads) bitmap[w] = 0u;
-  const bool changed = exact_changes<DT>(p.in, sh_u.exact, row, g_lo, g_hi, s_stat, s_thr, max0);
+  // The heavy terms change a normaliser by a few 1e-6 at most: scores that are written out have them in, the selection
+  // only needs them where it comes to fp64 scores.
+  auto exact = [&]() {
+    if (exact_changes<DT>(p.in, sh_exact, row, g_lo, g_hi, s_stat, s_thr, max0)) exact_apply(sh_exact, g_lo, g_hi, s_stat);
+  };
+  if (SCORES) exact();
   load_heads(g_lo, x[0]);
-  if (changed) exact_apply(sh_u.exact, g_lo, g_hi, s_stat);
+  if (!SCORES) __syncthreads();
 
   float v[N];
 #pragma unroll
@@ -513,11 +516,11 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     if (g + 2 * HB < g_hi) load_heads(g + 2 * HB, x[0]);
     add_heads(g + HB, x[1]);
   }
-  float* out = p.scores ? p.scores + (int64_t)list * p.pitch : nullptr;
+  float* out = SCORES ? p.scores + (int64_t)list * p.pitch : nullptr;
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int tok = 4 * ((i >> 2) * kTopkThreads + tid) + (i & 3);
-    if (out && tok < L) out[tok] = v[i];
+    if (SCORES && tok < L) out[tok] = v[i];
     if (tok < S || tok >= L - W) v[i] = -1.f;
   }
   if (k == 0) return;
@@ -552,17 +555,21 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   __syncthreads();
   const int nb = sh.n_band, r = k - sh.n_above;
   bool general = nb > kMaxBand || r < 1 || r > nb;
-  if (!general && nb == r && !out) {  // the whole band is selected: no need to rank it
+  const bool whole = !SCORES && !general && nb == r;  // the whole band is selected: no need to rank it
+  if (whole) {
     for (int t = tid; t < nb; t += kTopkThreads) atomicOr(&bitmap[sh.band_tok[t] >> 5], 1u << (sh.band_tok[t] & 31));
     __syncthreads();
-  } else if (!general) {
+  } else if (!SCORES) {
+    exact();
+  }
+  if (!whole && !general) {
     refine_band<DT>(sh, nb, geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, g_lo, g_hi);
     if (tid == 0) sh.n_band = 0;  // now: 1 = the threshold lies strictly inside the band
     __syncthreads();
     for (int t = tid; t < nb; t += kTopkThreads) {
       const float x = sh.band_v[t];
       const int tok = sh.band_tok[t];
-      if (out) out[tok] = x;
+      if (SCORES) out[tok] = x;
       int rank = 0;
       for (int u = 0; u < nb; ++u) rank += sh.band_v[u] > x || (sh.band_v[u] == x && sh.band_tok[u] < tok);
       if (rank == r - 1 && x > lo && x < hi) sh.n_band = 1;
@@ -585,7 +592,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
       for (int j = 0; j < N; ++j) x = j == i ? v[j] : x;
       if (x >= 0.f && x >= lo && x <= hi) {
         x = refined_score<DT>(geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, tok, g_lo, g_hi);
-        if (out) out[tok] = x;
+        if (SCORES) out[tok] = x;
       }
 #pragma unroll
       for (int j = 0; j < N; ++j) v[j] = j == i ? x : v[j];
@@ -1042,10 +1049,14 @@ hipError_t launch_row_select(const RowSelectParams& p, hipStream_t s) {
   const dim3 grid((unsigned)(p.in.geo.n_problems * p.in.geo.Hkv * p.n_lists));
   const int quads = (int)((p.in.geo.L + 4 * kTopkThreads - 1) / (4 * kTopkThreads));  // per thread
 #define SAGEKV_LAUNCH(NQ)                                                                                       \
-  if (p.in.geo.dtype == DT_BF16)                                                                                   \
-    hipLaunchKernelGGL((row_select_kernel<DT_BF16, NQ>), grid, dim3(kTopkThreads), 0, s, p);                    \
+  if (p.in.geo.dtype == DT_BF16 && p.scores)                                                                       \
+    hipLaunchKernelGGL((row_select_kernel<DT_BF16, NQ, true>), grid, dim3(kTopkThreads), 0, s, p);              \
+  else if (p.in.geo.dtype == DT_BF16)                                                                              \
+    hipLaunchKernelGGL((row_select_kernel<DT_BF16, NQ, false>), grid, dim3(kTopkThreads), 0, s, p);             \
+  else if (p.scores)                                                                                            \
+    hipLaunchKernelGGL((row_select_kernel<DT_F32, NQ, true>), grid, dim3(kTopkThreads), 0, s, p);               \
   else                                                                                                          \
-    hipLaunchKernelGGL((row_select_kernel<DT_F32, NQ>), grid, dim3(kTopkThreads), 0, s, p)
+    hipLaunchKernelGGL((row_select_kernel<DT_F32, NQ, false>), grid, dim3(kTopkThreads), 0, s, p)
   if (quads <= 1) {
     SAGEKV_LAUNCH(1);
   } else if (quads <= 2) {
