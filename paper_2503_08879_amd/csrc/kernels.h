@@ -165,6 +165,7 @@ struct ScoreParams {
   // is off by as much; two heads' errors differ, and that can reorder group-sum scores a few 1e-6 apart.
   const float* heavy_thr;
   float* logits;                          // SCORE_LOGITS: [rows][n_chunks][G][chunk]
+  int logits_through;                     // they bypass L2 (set by launch_score)
   float* lines;                           // [rows][n_chunks][chunk_line_words]  softmax partials and candidate count; SCORE_LOGITS:
   ChunkPartial* chunk_partials;           // [rows][G][n_chunks], the partials more precisely and without fp64 exponents (see exact_changes)
   int n_chunks;

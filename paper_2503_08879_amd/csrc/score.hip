@@ -23,6 +23,12 @@ namespace {
 constexpr int kScoreThreads = 256;
 constexpr int kScoreWaves = kScoreThreads / kWave;
 constexpr int64_t kWriteThrough = 1ll << 30;
+// Logits of the one-sweep path go through L2 at once over more than this many bytes of keys, up to four heads: later they would be evicted in the
+// middle of the stream, a few lines at a time.  (Nothing stored: 82 us for 256 rows x 8192 tokens x 4 heads, 537 MB; stored 97, through L2 92.)  Whole
+// pass, us, left and written through: 64 rows x 8192 (134 MB) 68.7 and 69.4, 96 rows 96.0 and 95.9, 128 rows 118 and 117, 192 rows 166 and 163,
+// 256 rows 214 and 211, 512 rows 421 and 416, 256 x 16K 419 and 413, 32 x 32K 88.2 and 87.1.  With more heads a store holds half lines of two heads:
+// 128 rows x 8192 x 7 heads 129 and 131, 16 x 64K 91 and 94.
+constexpr int64_t kLogitsThrough = 200000000;
 constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine launch
 // A score workgroup takes a chunk of BPW blocks of 64 tokens per wave (BPW = 1, 2, 4: 256, 512, 1024 tokens).
 
@@ -600,10 +606,15 @@ __device__ __forceinline__ void score_mfma_chunk(const ScoreParams& p, int gb, i
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           float& x = xs[KEEP ? blk : 0][a][r];
-          if (in && tok < L && hbase + r < gb)
-            p.logits[logit_index(p.geo, p.n_chunks, p.chunk, row, p.g0 + hbase + r, tok)] = x;
-          else
+          if (in && tok < L && hbase + r < gb) {
+            float* at = p.logits + logit_index(p.geo, p.n_chunks, p.chunk, row, p.g0 + hbase + r, tok);
+            if (GPAD == 4 && p.logits_through)
+              __hip_atomic_store(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else
+              *at = x;
+          } else {
             x = -INFINITY;
+          }
         }
       }
     }
@@ -1020,9 +1031,10 @@ hipError_t launch_score(const ScoreParams& p0, ScoreMode mode, hipStream_t s) {
     hipError_t e;
     if (!bf16)
       e = p.geo.D == 128 ? launch_score_f32<128>(p, gb, grid, s) : launch_score_f32<64>(p, gb, grid, s);
-    else if (mode == SCORE_LOGITS)
+    else if (mode == SCORE_LOGITS) {
+      p.logits_through = gb <= 4 && (int64_t)rows * p.geo.L * p.geo.D * 2 > kLogitsThrough;
       e = launch_score_mfma_d<SCORE_LOGITS>(p, gb, grid, s);
-    else if (mode == SCORE_PARTIALS)
+    } else if (mode == SCORE_PARTIALS)
       e = launch_score_mfma_d<SCORE_PARTIALS>(p, gb, grid, s);
     else
       e = launch_score_mfma_d<SCORE_SCORES>(p, gb, grid, s);
