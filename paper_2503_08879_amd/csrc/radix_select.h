@@ -266,25 +266,39 @@ __device__ __forceinline__ float exact_maximum(const DenseRows& in, int row, int
   return it.g < g_hi && ch < in.n_chunks ? in.partials[((int64_t)row * in.geo.G + it.g) * in.n_chunks + ch].max : -INFINITY;
 }
 
+// Four elements of a row, and a product of such fours in fp64.
+template <int DT>
+struct FourElems {
+  typedef uint2 type;
+};
+template <>
+struct FourElems<DT_F32> {
+  typedef uint4 type;
+};
+template <int DT>
+__device__ __forceinline__ typename FourElems<DT>::type four_elems(const void* base, int64_t i) {
+  return *reinterpret_cast<const typename FourElems<DT>::type*>((const char*)base + i * Elem<DT>::bytes);
+}
+template <int DT>
+__device__ __forceinline__ double dot_f64(const typename FourElems<DT>::type& a, const typename FourElems<DT>::type& b, double acc) {
+  if constexpr (DT == DT_BF16) {
+    acc += (double)bf16_lo(a.x) * (double)bf16_lo(b.x) + (double)bf16_hi(a.x) * (double)bf16_hi(b.x);
+    return acc + ((double)bf16_lo(a.y) * (double)bf16_lo(b.y) + (double)bf16_hi(a.y) * (double)bf16_hi(b.y));
+  } else {
+    acc += (double)__uint_as_float(a.x) * (double)__uint_as_float(b.x) + (double)__uint_as_float(a.y) * (double)__uint_as_float(b.y);
+    return acc + ((double)__uint_as_float(a.z) * (double)__uint_as_float(b.z) + (double)__uint_as_float(a.w) * (double)__uint_as_float(b.w));
+  }
+}
+
 // A wave's first cnt listed terms: exp(l - M) - (the fp32 term in the merged sum), l = the logit in fp64, added to its changes.
 // Sixteen lanes share a term, four elements at a time, two terms in flight (fp32: one, registers).  Called by all 64 lanes
 // of a wave.
 template <int DT>
 __device__ __forceinline__ void exact_terms_wave(const DenseRows& in, ExactSums& sh, int cnt, int row, const RowStat* stat) {
-  typedef typename std::conditional<DT == DT_BF16, uint2, uint4>::type Four;  // four elements
+  typedef typename FourElems<DT>::type Four;
   constexpr int U = DT == DT_BF16 ? 2 : 1;
   const int D = in.geo.D, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane >> 4, sub = lane & 15;
   const int prob = row / in.geo.Hkv, c = row % in.geo.Hkv, chunk_shift = __builtin_ctz((unsigned)in.chunk);
-  auto four = [](const void* base, int64_t i) { return *reinterpret_cast<const Four*>((const char*)base + i * Elem<DT>::bytes); };
-  auto dot = [](const Four& a, const Four& b, double acc) {
-    if constexpr (DT == DT_BF16) {
-      acc += (double)bf16_lo(a.x) * (double)bf16_lo(b.x) + (double)bf16_hi(a.x) * (double)bf16_hi(b.x);
-      return acc + ((double)bf16_lo(a.y) * (double)bf16_lo(b.y) + (double)bf16_hi(a.y) * (double)bf16_hi(b.y));
-    } else {
-      acc += (double)__uint_as_float(a.x) * (double)__uint_as_float(b.x) + (double)__uint_as_float(a.y) * (double)__uint_as_float(b.y);
-      return acc + ((double)__uint_as_float(a.z) * (double)__uint_as_float(b.z) + (double)__uint_as_float(a.w) * (double)__uint_as_float(b.w));
-    }
-  };
   const double inv = 1.0 / sqrt((double)D);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll 1
@@ -295,10 +309,10 @@ __device__ __forceinline__ void exact_terms_wave(const DenseRows& in, ExactSums&
       const int e = e0 + 4 * u + grp < cnt ? e0 + 4 * u + grp : cnt - 1;
       const int64_t ko = kv_offset(in.pm, in.pm.ks_page, in.ks_problem, in.ks_head, in.ks_token, prob, c, sh.tok[wave][e]) + 4 * sub;
       const int64_t qo = ((int64_t)prob * in.geo.Hq + c * in.geo.G + sh.head[wave][e]) * D + 4 * sub;
-      k0[u] = four(in.K, ko);
-      q0[u] = four(in.q_last, qo);
-      k1[u] = D > 64 ? four(in.K, ko + 64) : Four{};
-      q1[u] = D > 64 ? four(in.q_last, qo + 64) : Four{};
+      k0[u] = four_elems<DT>(in.K, ko);
+      q0[u] = four_elems<DT>(in.q_last, qo);
+      k1[u] = D > 64 ? four_elems<DT>(in.K, ko + 64) : Four{};
+      q1[u] = D > 64 ? four_elems<DT>(in.q_last, qo + 64) : Four{};
     }
     // lanes 0 and 1 of a group: the terms' fp64 exponentials, lanes 2 and 3: their fp32 ones as they were merged
     const int e = e0 + 4 * (sub & 1) + grp;
@@ -313,7 +327,7 @@ __device__ __forceinline__ void exact_terms_wave(const DenseRows& in, ExactSums&
     double l = 0.0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const double a = group_sum_f64<16>(dot(k1[u], q1[u], dot(k0[u], q0[u], 0.0)));
+      const double a = group_sum_f64<16>(dot_f64<DT>(k1[u], q1[u], dot_f64<DT>(k0[u], q0[u], 0.0)));
       l = sub == u ? a * inv : l;
     }
     const double ex = exp((sub >= 2 ? (double)mc : l) - (double)M);
@@ -509,6 +523,75 @@ __device__ __forceinline__ void refine_band(RegSelect& sh, int nb, const RowGeom
     }
     __syncthreads();
   }
+}
+
+// The heavy terms of a row whose logits pass through registers, listed there as they are met (a few dozen at most, as a rule), and taken
+// together with the band: exact_changes and refine_band in one round trip to the keys, where the lists hold what there is.  One after the
+// other they took 8 of a row's 20 us (256 rows x 8192 tokens, k = 1788, four sink tokens); a whole pass 207 -> 204, over 8 rows 29.7 -> 27.6,
+// 128 rows x 8192 x 7 heads 128 -> 122.6.
+constexpr int kHeavyList = 512;
+struct HeavyList {
+  int n;
+  int tok[kHeavyList];
+  float logit[kHeavyList];
+  unsigned char head[kHeavyList];
+  double change[kHeavyList];  // exact term - the one in the merged sum
+};
+
+// fp64 scores of the band's members into band_v after the listed terms have gone into the statistics (stat, in LDS).  Every 16 lanes
+// take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyList.  Begins (hv.n, band_tok) after a barrier, ends with one.
+template <int DT>
+__device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, int nb, const DenseRows& in, int row, int g_lo, int g_hi, RowStat* stat) {
+  typedef typename FourElems<DT>::type Four;
+  const RowGeom& geo = in.geo;
+  const int D = geo.D, tid = threadIdx.x, sub = tid & 15, heads = g_hi - g_lo, n_heavy = hv.n, n = n_heavy + nb * heads;
+  const int prob = row / geo.Hkv, c = row % geo.Hkv, chunk_shift = __builtin_ctz((unsigned)in.chunk);
+  const double inv = 1.0 / sqrt((double)D);
+#pragma unroll 1
+  for (int t = tid >> 4; t < n; t += kTopkThreads / 16) {
+    const bool heavy = t < n_heavy;
+    const int b = heavy ? 0 : t - n_heavy;
+    const int tok = heavy ? hv.tok[t] : sh.band_tok[b / heads], g = heavy ? hv.head[t] : g_lo + b % heads;
+    const int64_t ko = kv_offset(in.pm, in.pm.ks_page, in.ks_problem, in.ks_head, in.ks_token, prob, c, tok) + 4 * sub;
+    const int64_t qo = ((int64_t)prob * geo.Hq + c * geo.G + g) * D + 4 * sub;
+    const Four k0 = four_elems<DT>(in.K, ko), q0 = four_elems<DT>(in.q_last, qo);
+    Four k1 = {}, q1 = {};
+    if (D > 64) k1 = four_elems<DT>(in.K, ko + 64), q1 = four_elems<DT>(in.q_last, qo + 64);
+    float mc = 0.f;
+    if (heavy) mc = in.partials[((int64_t)row * geo.G + g) * in.n_chunks + (tok >> chunk_shift)].max;
+    const double l = group_sum_f64<16>(dot_f64<DT>(k1, q1, dot_f64<DT>(k0, q0, 0.0))) * inv;
+    if (heavy) {
+      const double M = (double)stat[g].M;
+      if (sub == 0) hv.change[t] = exp(l - M) - (double)exp_fast(hv.logit[t] - mc) * exp((double)mc - M);
+    } else if (sub == 0) {
+      sh.term[b] = l;
+    }
+  }
+  __syncthreads();
+  if (n_heavy > 0) {  // workgroup-uniform; a wave per head
+    for (int g = g_lo + (tid >> 6); g < g_hi; g += kTopkWaves) {
+      double z = 0.0;
+      for (int t = tid & 63; t < n_heavy; t += 64) z += hv.head[t] == g ? hv.change[t] : 0.0;
+      z = group_sum_f64<64>(z);
+      if ((tid & 63) == 0) {
+        z += stat[g].Z;
+        stat[g].Z = z;
+        stat[g].invZ = (float)(1.0 / z);
+      }
+    }
+    __syncthreads();
+  }
+  for (int b = tid; b < nb * heads; b += kTopkThreads) {
+    const RowStat& st = stat[g_lo + b % heads];
+    sh.term[b] = exp(sh.term[b] - (double)st.M) / st.Z;
+  }
+  __syncthreads();
+  for (int t = tid; t < nb; t += kTopkThreads) {
+    double tot = 0.0;
+    for (int g = 0; g < heads; ++g) tot += sh.term[t * heads + g];
+    sh.band_v[t] = (float)tot;
+  }
+  __syncthreads();
 }
 
 }  // namespace sagekv

@@ -435,6 +435,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   constexpr int N = 4 * NQ;
   __shared__ ExactSums sh_exact;
   __shared__ RegSelect sh;
+  __shared__ HeavyList heavy;
   __shared__ RowStat s_stat[64];  // up to 64 heads per KV head
   __shared__ float s_thr[64];
   __shared__ __align__(16) uint32_t bitmap[NQ * kTopkThreads * 4 / 32];
@@ -481,6 +482,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
     }
   }
   for (int w = tid; w < (int)(sizeof(bitmap) / 4); w += kTopkThreads) bitmap[w] = 0u;
+  if (tid == 0) heavy.n = 0;
   // The heavy terms change a normaliser by a few 1e-6 at most: scores that are written out have them in, the selection
   // only needs them where it comes to fp64 scores.
   auto exact = [&]() {
@@ -497,10 +499,25 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
 #pragma unroll
     for (int h = 0; h < HB; ++h)
       if (g0 + h < g_hi) {
-        const float M = s_stat[g0 + h].M, inv = s_stat[g0 + h].invZ;
+        const float M = s_stat[g0 + h].M, inv = s_stat[g0 + h].invZ, thr = SCORES ? INFINITY : s_thr[g0 + h];
 #pragma unroll
         for (int u = 0; u < NQ; ++u) {
-          if (4 * (u * kTopkThreads + tid) < L) {
+          const int tok = 4 * (u * kTopkThreads + tid);
+          if (tok < L) {
+            const float top = fmaxf(fmaxf(src[h][u].x, src[h][u].y), fmaxf(src[h][u].z, src[h][u].w));
+            if (!SCORES && top >= thr) {  // rare
+              const float l[4] = {src[h][u].x, src[h][u].y, src[h][u].z, src[h][u].w};
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (l[e] >= thr && tok + e < L) {
+                  const int t = atomicAdd(&heavy.n, 1);
+                  if (t < kHeavyList) {
+                    heavy.tok[t] = tok + e;
+                    heavy.logit[t] = l[e];
+                    heavy.head[t] = (unsigned char)(g0 + h);
+                  }
+                }
+            }
             v[4 * u] += exp_times(src[h][u].x - M, inv);
             v[4 * u + 1] += exp_times(src[h][u].y - M, inv);
             v[4 * u + 2] += exp_times(src[h][u].z - M, inv);
@@ -556,14 +573,18 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   const int nb = sh.n_band, r = k - sh.n_above;
   bool general = nb > kMaxBand || r < 1 || r > nb;
   const bool whole = !SCORES && !general && nb == r;  // the whole band is selected: no need to rank it
+  const bool together = !SCORES && !general && nb * (g_hi - g_lo) <= kMaxBand && heavy.n <= kHeavyList;
   if (whole) {
     for (int t = tid; t < nb; t += kTopkThreads) atomicOr(&bitmap[sh.band_tok[t] >> 5], 1u << (sh.band_tok[t] & 31));
     __syncthreads();
-  } else if (!SCORES) {
+  } else if (!SCORES && !together) {
     exact();
   }
   if (!whole && !general) {
-    refine_band<DT>(sh, nb, geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, g_lo, g_hi);
+    if (together)
+      refine_band_exact<DT>(sh, heavy, nb, p.in, row, g_lo, g_hi, s_stat);
+    else
+      refine_band<DT>(sh, nb, geo, p.in.q_last, p.in.K, p.in.pm, p.in.ks_problem, p.in.ks_head, p.in.ks_token, s_stat, prob, c, g_lo, g_hi);
     if (tid == 0) sh.n_band = 0;  // now: 1 = the threshold lies strictly inside the band
     __syncthreads();
     for (int t = tid; t < nb; t += kTopkThreads) {

@@ -106,6 +106,22 @@ def test_a_sample_that_misleads(ref, P, Hq, Hkv, L, head_mode):
         assert out["redone"] == (kind == "equal" or L > 8192), kind  # (a shorter row has no sample)
 
 
+@pytest.mark.parametrize("dtype", [BF16, F32])
+@pytest.mark.parametrize("n_heavy", [1, 255, 256, 257, 600])
+def test_heavy_terms_around_the_list(ref, dtype, n_heavy):
+    """Two heads, n_heavy tokens each with a logit near 36 for both: 2 n_heavy terms for the 512 places where a row's heavy terms are
+    listed as its logits pass through the registers."""
+    P, Hq, Hkv, d, L, S, W, k = 2, 2, 1, 64, 6001, 4, 64, 900
+    q, K, V = parity.rand_case(n_heavy, P, Hq, Hkv, d, L, dtype)
+    Kf, qf = synth.to_f64(K, dtype), synth.to_f64(q, dtype)
+    at = np.random.default_rng(n_heavy).permutation(L)[:n_heavy]
+    for p in range(P):
+        u = np.linalg.pinv(qf[p]) @ np.full(Hq, 36.0 * d ** 0.5)
+        Kf[p, 0, at] = u + 0.01 * Kf[p, 0, at]
+    K = synth.round_to_dtype(Kf, dtype)
+    check(ref, dtype, 0, q, K, V, S, W, k, flags=1)
+
+
 def smallest_workspace(desc):
     """The least that calls with this descriptor accept, found through the call that only reads the workspace's first word."""
     import torch
