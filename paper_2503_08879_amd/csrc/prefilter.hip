@@ -45,11 +45,12 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
 
   const int row = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int G = p.geo.G;
-  const bool per_head = p.n_lists > 1;
+  // per-query lists: the heads 4 blockIdx.y .. + 3, a list each; else all of them (G: heads from there on)
+  const bool per_head = GQ == 1 && p.n_lists > 1;
+  const int h0 = per_head ? 4 * (int)blockIdx.y : 0, G = p.geo.G - h0, rec = GQ == 1 ? p.Gs : 4 * GQ;
   const int n_slots = 64 * (p.nA + p.nB + p.nC), lo_b = 64 * p.nA, nB = 64 * p.nB;
   const int qd = tid % GQ;  // this thread's head quad
-  const float* slog = p.samp_logit + (int64_t)row * n_slots * (4 * GQ) + 4 * qd;
+  const float* slog = p.samp_logit + (int64_t)row * n_slots * rec + 4 * qd + h0;
   if (tid == 0) {
     p.row_fail[row] = 0;
     p.ovf_count[row] = 0;
@@ -64,7 +65,7 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
     if (b < p.nA + p.nB) return p.wB;
     return n_slots - s <= p.validC ? p.wC : 0.f;
   };
-  auto load = [&](int s) { return *reinterpret_cast<const f32x4_t*>(slog + (int64_t)s * (4 * GQ)); };
+  auto load = [&](int s) { return *reinterpret_cast<const f32x4_t*>(slog + (int64_t)s * rec); };
   f32x4_t x[NI > 0 ? NI : 1];  // logits, later exp(logit - M)
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       if (4 * tid + r < G) {
-        p.samp_stats[(int64_t)row * G + 4 * tid + r] = make_float2(M4[r], I4[r]);
-        p.heavy_thr[(int64_t)row * G + 4 * tid + r] = heavy_logit_threshold(M4[r], z4[r]);
+        p.samp_stats[(int64_t)row * p.geo.G + h0 + 4 * tid + r] = make_float2(M4[r], I4[r]);
+        p.heavy_thr[(int64_t)row * p.geo.G + h0 + 4 * tid + r] = heavy_logit_threshold(M4[r], z4[r]);
       }
   }
   // A heavy-tailed row (the sample met heavy tokens) has heads whose normalisers are known with
@@ -189,14 +190,15 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
 
   // group-sum: the threshold is on the summed approximate score; per-query: on the head's own.  Every thread takes part for
   // every item (the quads of a slot sit in adjacent lanes); -1: not a sampled candidate, or not this thread's.
-  for (int li = 0; li < p.n_lists; ++li) {
+  const int lists = per_head ? (G < 4 ? G : 4) : 1;
+  for (int li = 0; li < lists; ++li) {
     auto score = [&](const f32x4_t& e, int s) -> float {
       float a = 0.f;
       bool mine;
       if (per_head) {
-        mine = qd == (li >> 2);
+        mine = true;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) a = (li & 3) == r ? e[r] * I4[r] : a;
+        for (int r = 0; r < 4; ++r) a = li == r ? e[r] * I4[r] : a;
       } else {
         mine = qd == 0;
 #pragma unroll
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(kTopkThreads) void sample_stats_kernel(SampleParams
         }
       }, rank, &tlo, &thi);
     }
-    if (tid == 0) p.samp_tau[(int64_t)row * p.n_lists + li] = __uint_as_float(tlo);
+    if (tid == 0) p.samp_tau[(int64_t)row * p.n_lists + h0 + li] = __uint_as_float(tlo);
     __syncthreads();  // the histogram is cleared for the next list
   }
 }
@@ -645,8 +647,8 @@ __global__ __launch_bounds__(kTopkThreads, 8) void topk_cand_pq_kernel(TopkCandP
 }  // namespace
 
 template <int GQ>
-void launch_sample_stats(const SampleParams& p, unsigned rows, int items, hipStream_t s) {
-  const dim3 grid(rows), block(kTopkThreads);
+void launch_sample_stats(const SampleParams& p, unsigned rows, unsigned parts, int items, hipStream_t s) {
+  const dim3 grid(rows, parts), block(kTopkThreads);
   if (items <= 3) {
     hipLaunchKernelGGL((sample_stats_kernel<GQ, 3>), grid, block, 0, s, p);
   } else if (items <= 6) {
@@ -666,13 +668,14 @@ hipError_t launch_sample(const SampleParams& p, hipStream_t s) {
   if (p.geo.dtype != DT_BF16 || p.geo.G > kFastMaxG || p.nB * 64 > 8192) return hipErrorInvalidValue;
   hipError_t e = launch_sample_logits(p, s);
   if (e != hipSuccess) return e;
-  // one workgroup per row, also with several lists per row: at 7 lists x 448 rows, two workgroups per row
-  // took 139 us, one per (row, list) 147 us, one per row 108 us (the statistics dominate, not the selects)
-  const int gq = p.Gs / 4 > 2 ? 4 : p.Gs / 4;  // head quads in a record, as a power of two
+  // One workgroup per row; with several lists per row one for every four of them, as the thresholds are found one after the other (whole pass,
+  // us, one per row and so: 112 rows x 128K x 7 lists 841 and 822, 64 x 32K x 7 247 and 227, 64 x 32K x 4 185 and 184).
+  const int gq = p.n_lists > 1 ? 1 : p.Gs / 4 > 2 ? 4 : p.Gs / 4;  // head quads of a record that a workgroup takes, as a power of two
+  const unsigned parts = p.n_lists > 1 ? (unsigned)(p.geo.G + 3) / 4 : 1;
   const int items = (64 * (p.nA + p.nB + p.nC) * gq + kTopkThreads - 1) / kTopkThreads;
-  if (gq == 1) launch_sample_stats<1>(p, (unsigned)rows, items, s);
-  else if (gq == 2) launch_sample_stats<2>(p, (unsigned)rows, items, s);
-  else launch_sample_stats<4>(p, (unsigned)rows, items, s);
+  if (gq == 1) launch_sample_stats<1>(p, (unsigned)rows, parts, items, s);
+  else if (gq == 2) launch_sample_stats<2>(p, (unsigned)rows, parts, items, s);
+  else launch_sample_stats<4>(p, (unsigned)rows, parts, items, s);
   return hipGetLastError();
 }
 
