@@ -321,12 +321,12 @@ struct DecodeLayout {
 // over, at least 128 tokens each.  Short rows are not worth the merge launch:
 // bf16 up to 256 tokens, a single pass (8 rows x 4 heads x 256 tokens 9.2 us split, 7.7 whole; 4 rows x 7 heads 8.7 and 7.7; before
 // the slice kernel had its present form 10.3 and 8.4, 9.6 and 8.2, and at
-// 512 tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 256 tokens of head_dim 64 (8 rows x 256 tokens, one to eight heads: 11.6,
-// 12.5, 15, 17, 20, 22, -, 27 us split, 8.4, 8.5, 9.7, 12, 14, 16, -, 20 whole; 160 rows x 2, 4, 8 heads 14, 19, 50 and 8.8, 13.4, 21;
-// 2 rows x 2 heads x 512 tokens 9.8 and 12.0; 8 rows x 4 heads x 512 tokens of head_dim 128 22 and 42 with 16 waves).
+// 512 tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 384 tokens of head_dim 64, 192 of 128 (2 rows x 2 heads x 300 and 400 tokens 9.5 and 9.3 us
+// split, 7.2 and 8.1 whole, 512 even; 4 rows x 4 heads x 512 10.0 and 11.0; head_dim 128, 160 tokens: 8 rows x 4 heads 10.4 and 8.0, 4 x 7
+// 12.2 and 10.1, 256 tokens 10.5 and 9.7, 12.2 and 12.5).
 int splits_for(int rows, int len, int dtype, int head_dim) {
   if (rows >= kWholeRows) return 1;
-  if (dtype == SAGEKV_BF16 ? len <= 256 : (int64_t)len * head_dim <= 256 * 64) return 1;
+  if (dtype == SAGEKV_BF16 ? len <= 256 : (int64_t)len * head_dim <= 384 * 64) return 1;
   int want = (2048 + rows - 1) / rows;
   int most = (len + 127) / 128;
   int n = want < most ? want : most;

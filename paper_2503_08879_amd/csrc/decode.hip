@@ -1,10 +1,10 @@
 // Decoding over the reduced cache (paper Sec. 2 Step 4): the new token's (k, v) replaces the
 // oldest entry of the recent window, then every query head attends over the reduced row.
 //
-// decode_kernel: grid (splits, rows).  A workgroup streams its slice of Kc and Vc once for all
-// G heads of the row (16-byte loads, LPT lanes per token), keeps an online softmax per lane
-// group and merges lane groups -> waves -> workgroup.  With one split per row (many rows: all
-// layers of a step in one launch) one workgroup (8 waves bf16, up to 16 fp32) owns the whole row and
+// decode_*_kernel: grid (splits, rows).  A workgroup streams its slice of Kc and Vc once for all
+// G heads of the row (16-byte loads), keeps an online softmax per wave or lane
+// group and merges them -> workgroup.  With one split per row (many rows: all
+// layers of a step in one launch) one workgroup (usually 8 waves) owns the whole row and
 // writes `out` itself; with few rows the row is split, partials (max, sum, acc[G][d]) go to scratch and
 // combine_kernel merges them.  (A last-workgroup-done merge inside one kernel needs a device
 // scope fence in every workgroup, which on this multi-XCD part writes back and invalidates
@@ -124,173 +124,280 @@ __device__ __forceinline__ void finish_row(const DecodeParams& p, const StepGeom
   if (p.n_splits == 1 && threadIdx.x == 0) row_done(p, sg);
 }
 
-template <int DT, int D, int GB, int NW>
-__global__ __launch_bounds__(NW * 64) void decode_kernel(DecodeParams p, int g0) {
-  constexpr int EPL = Elem<DT>::per_lane;
-  constexpr int EB = Elem<DT>::bytes;
-  constexpr int LPT = D / EPL;
-  constexpr int TPL = 64 / LPT;
-  constexpr int SB = (GB > 4 || NW > 4) ? 4 : 8;  // loads per batch
-  constexpr int ROWB = D * EB;
-  constexpr int kDecWaves = NW, kDecThreads = NW * 64;
-
-  __shared__ float s_acc[kDecWaves][GB][D];
-  __shared__ float2 s_ml[kDecWaves][GB];
+// fp32 caches.  Both products and the sums in fp64 (an fp32 logit of magnitude 100 would be off by 2.5e-5, and so would its softmax weight);
+// fp64 and fp32 multiply-adds take the same four cycles.  Bound by vector instructions, so nothing is done twice: eight lanes share a
+// token (four, or two, 16-byte chunks each), a logit's eight parts are summed while heads and lanes change places, and lane s of the eight ends
+// with head s's logit, whose weight it computes once and leaves in LDS for the lanes that hold V's chunks (16 bytes of a token each).
+// A wave works on blocks of 16 or 32 tokens.  (With 16 or 32 lanes per token, every head's logit summed over all of them and its weight
+// computed in all of them, fp32 accumulators, and that kernel now, us: 2 rows x 2 heads x 256 tokens of 64 dims 7.5 and 6.7, 8 rows x 4 x
+// 512 of 128 18.5 and 9.7, 4 x 7 x 2048 28.4 and 12.2, 256 x 4 x 4096 281 and 188, 128 x 7 x 2048 132 and 85.5, in pages 256 x 4 x 2048 233
+// and 103; errors 5 to 30 % smaller.)
+template <int D, int GB, int NW, int BT, bool PG>
+__global__ __launch_bounds__(NW * 64) void decode_f32_kernel(DecodeParams p, int g0) {
+  constexpr int ROWB = D * 4, CH = D / 4, GPB = BT / 16;
+  constexpr bool LATE_V = GB >= 6;  // V's block after the logits, not with K's: else registers spill
+  constexpr int NG = BT / 8, NC = CH / 8;             // K: groups of 8 tokens, a lane's chunks of a token
+  constexpr int TPL = 64 / CH, NV = BT / TPL;         // V: tokens per load, loads
+  constexpr int GP = (GB + 1) / 2 * 2;                // weights of a token in LDS: whole 16-byte pairs
+  constexpr int kThreads = NW * 64, NQ = (GB * D + kThreads - 1) / kThreads;
+  __shared__ __attribute__((aligned(16))) double qd[2][GB * D];  // queries; 1: the one the sink tokens are scored with
+  __shared__ __attribute__((aligned(16))) double pw[NW][BT][GP];
+  __shared__ uint4 s_new[2 * CH];  // the new token's key and value
+  __shared__ float s_acc[NW][GB][D];
+  __shared__ float s_m[NW][GB];
+  __shared__ double s_l[NW][GB];
 
   const int row = blockIdx.y, split = blockIdx.x;
   const int prob = row / p.Hkv, c = row % p.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int tq = lane / LPT, cl = lane % LPT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t8 = lane >> 3, sl = lane & 7;   // K role: token of a group, share of a token; head, once the logits are summed
+  const int tq = lane / CH, cl = lane % CH;  // V role: token of a load, chunk
+  const int64_t head0 = (int64_t)prob * p.Hq + c * p.G + g0;
 
-  const CacheRow Kr = cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, EB);
-  const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, EB);
-  const char* kn = p.k_new ? (const char*)p.k_new + (int64_t)row * ROWB : nullptr;
-  const char* vn = p.v_new ? (const char*)p.v_new + (int64_t)row * ROWB : nullptr;
-  const StepGeom sg = step_geom(p);
-  const int slot = sg.slot;
-
+  StepGeom sg = step_geom<true>(p);
+  int ring_n = 0;
+  if (slot_is_late(p)) ring_n = p.ring[0];  // on its way while the first loads are issued
   const int t_begin = split * sg.tokens_per_split;
   const int t_end = min(sg.len, t_begin + sg.tokens_per_split);
+  const int nblk = (t_end - t_begin + BT - 1) / BT;
+  const CacheRow Kr = cache_row(p.Kc, p.cpm, false, prob, c, row, p.cap, ROWB, 4);
+  const CacheRow Vr = cache_row(p.Vc, p.cpm, true, prob, c, row, p.cap, ROWB, 4);
 
-  if (slot >= t_begin && slot < t_end && tid < LPT) {  // Step 4: the new token enters the window
-    st16(Kr.at(slot) + tid * 16, ld16(kn + tid * 16));
-    st16(Vr.at(slot) + tid * 16, ld16(vn + tid * 16));
+  // loads complete in order: the queries first, then the new token, then K and V
+  float qv[NQ];
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const int at = tid + i * kThreads;
+    qv[i] = at < GB * D ? ((const float*)p.q)[head0 * D + at] : 0.f;
   }
-
-  uint4 q[GB], q2[GB];  // q2: the sink tokens' query (window-relative positions), else = q
+  const bool value = tid >= CH;  // threads 0 .. 2 CH - 1: a chunk of the new key or value
+  uint4 fresh = make_uint4(0u, 0u, 0u, 0u);
+  if (p.k_new && tid < 2 * CH) fresh = ld16((const char*)(value ? p.v_new : p.k_new) + (int64_t)row * ROWB + (tid % CH) * 16);
+  // PG: page ids of the 64 groups of 16 tokens from block it0 on, one per lane
+  int my_page = 0;
+  auto fill_pages = [&](int it0) {
+    int tok = t_begin + (wave + (it0 + lane / GPB) * NW) * BT + (lane % GPB) * 16;
+    tok = tok < t_end ? tok : t_begin;
+    const int pid = Kr.tab[tok >> Kr.shift];
+    my_page = pid < 0 ? 0 : (pid >= Kr.n_pages ? Kr.n_pages - 1 : pid);
+  };
+  // token `at` of block it (at - lane's part is wave-uniform: `base`); past the slice one that is inside it
+  auto token = [&](int it, int base, int at) {
+    const int b0 = t_begin + (wave + it * NW) * BT, g16 = b0 + base / 16 * 16;
+    return b0 + at < t_end ? b0 + at : PG && g16 < t_end ? g16 : t_begin;
+  };
+  auto address = [&](const CacheRow& r, int it, int base, int tok) -> const char* {
+    if (!PG) return r.base + (int64_t)tok * ROWB;
+    const int pid = __builtin_amdgcn_readlane(my_page, (it * GPB + base / 16) & 63);
+    return r.base + (int64_t)pid * r.page_bytes + (int64_t)(tok & ((1 << r.shift) - 1)) * ROWB;
+  };
+  uint4 kv[NG][NC], vv[NV];
+  auto load_k = [&](int it) {
 #pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    const int h = c * p.G + g0 + g;
-    q[g] = ld16((const char*)p.q + (((int64_t)prob * p.Hq + h) * D + cl * EPL) * EB);
-    q2[g] = p.q_sink ? ld16((const char*)p.q_sink + (((int64_t)prob * p.Hq + h) * D + cl * EPL) * EB) : q[g];
+    for (int g = 0; g < NG; ++g) {
+      const char* a = address(Kr, it, 8 * g, token(it, 8 * g, 8 * g + t8)) + sl * 16;
+#pragma unroll
+      for (int ch = 0; ch < NC; ++ch) kv[g][ch] = ld16(a + ch * 128);
+    }
+  };
+  auto load_v = [&](int it) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) vv[i] = ld16(address(Vr, it, i * TPL, token(it, i * TPL, i * TPL + tq)) + cl * 16);
+  };
+  if (wave < nblk) {
+    if (PG) fill_pages(0);
+    load_k(0);
+    if (!LATE_V) load_v(0);
   }
-  float m[GB], l[GB], acc[GB][EPL];
 #pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    m[g] = -INFINITY;
-    l[g] = 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
-  }
-
-  for (int t0 = t_begin + wave * SB * TPL; t0 < t_end; t0 += kDecWaves * SB * TPL) {
-    uint4 kv[SB], vv[SB];
-    bool valid[SB];
-#pragma unroll
-    for (int i = 0; i < SB; ++i) {
-      const int tok = t0 + i * TPL + tq;
-      valid[i] = tok < t_end;
-      const int tc = valid[i] ? tok : t_begin;
-      const char* ks = (tc == slot) ? kn : Kr.at(tc);
-      const char* vs = (tc == slot) ? vn : Vr.at(tc);
-      kv[i] = ld16(ks + cl * 16);
-      vv[i] = ld16(vs + cl * 16);
-    }
-    // fp32 caches: the logit in fp64 (exact products), and below the exponent's argument from the fp64
-    // logit: an fp32 logit of magnitude 100 would be off by 2.5e-5, and so would its softmax weight
-    constexpr bool F64 = DT == DT_F32;
-    float x[SB][GB];
-    double xd[F64 ? SB : 1][F64 ? GB : 1];
-#pragma unroll
-    for (int i = 0; i < SB; ++i)
-#pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        const int tok = t0 + i * TPL + tq;
-        const uint4& qq = tok < p.qs_S ? q2[g] : q[g];
-        float v;
-        if constexpr (F64) {
-          double a = (double)__uint_as_float(kv[i].x) * (double)__uint_as_float(qq.x) +
-                     (double)__uint_as_float(kv[i].y) * (double)__uint_as_float(qq.y) +
-                     (double)__uint_as_float(kv[i].z) * (double)__uint_as_float(qq.z) +
-                     (double)__uint_as_float(kv[i].w) * (double)__uint_as_float(qq.w);
-          a = group_sum_f64<LPT>(a);
-          a *= 1.0 / sqrt((double)D);
-          xd[i][g] = a;
-          v = (float)a;
-        } else {
-          v = group_sum<LPT>(dot16<DT>(kv[i], qq, 0.f)) * p.scale;
-        }
-        x[i][g] = valid[i] && head_attends(p.pq_S, p.pq_k, p.G, g0 + g, tok) ? v : -INFINITY;
-      }
-    float mn[GB];
-    bool any = false;
-#pragma unroll
-    for (int g = 0; g < GB; ++g) {
-      float bm = x[0][g];
-#pragma unroll
-      for (int i = 1; i < SB; ++i) bm = fmaxf(bm, x[i][g]);
-      mn[g] = fmaxf(m[g], bm);
-      any = any || (mn[g] != -INFINITY);
-    }
-    if (any) {  // lanes of one token group agree
-#pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        const float corr = (mn[g] == -INFINITY) ? 1.f : exp_fast(m[g] - mn[g]);  // head with nothing to attend yet
-        l[g] *= corr;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] *= corr;
-        m[g] = mn[g];
-      }
-#pragma unroll
-      for (int i = 0; i < SB; ++i) {
-        float vf[EPL];
-        unpack16<DT>(vv[i], vf);
-#pragma unroll
-        for (int g = 0; g < GB; ++g) {
-          float arg = x[i][g] - mn[g];
-          if constexpr (F64) arg = (float)(xd[i][g] - (double)mn[g]);
-          const float pw = (x[i][g] == -INFINITY) ? 0.f : exp_fast(arg);
-          l[g] += pw;
-#pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(pw, vf[e], acc[g][e]);
-        }
-      }
-    }
-  }
-
-  // merge the TPL token groups of the wave (same cl, different tq)
-#pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    // (by row swaps: LDS shuffles, twelve in a row for two heads of 64 dims, took 2.5 of the 6.4 us of a tiny step)
-    static_assert(LPT == 16 || LPT == 32, "");
-    auto total = [](float x, float f) {  // sum of x * f; a lane's own product enters its first addition unrounded
-      if (LPT == 16) return swap32_sum(fmaf(x, f, swap16(x * f)));
-      return swap32_sum(x * f);
-    };
-    const float M = swap32_max(LPT == 16 ? swap16_max(m[g]) : m[g]);
-    const float f = (m[g] == -INFINITY) ? 0.f : exp_fast(m[g] - M);
-    const float ls = total(l[g], f);
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      const float a = total(acc[g][e], f);
-      if (tq == 0) s_acc[wave][g][cl * EPL + e] = a;
-    }
-    if (lane == 0) s_ml[wave][g] = make_float2(M, ls);
+  for (int i = 0; i < NQ; ++i)
+    if (tid + i * kThreads < GB * D) qd[0][tid + i * kThreads] = (double)qv[i];
+  if (p.q_sink)
+    for (int at = tid; at < GB * D; at += kThreads) qd[1][at] = (double)((const float*)p.q_sink)[head0 * D + at];
+  int slot = sg.slot;
+  if (slot_is_late(p)) slot = late_slot(p, sg, ring_n);
+  if (tid < 2 * CH) {
+    s_new[tid] = fresh;
+    if (slot >= t_begin && slot < t_end) st16((value ? Vr : Kr).at(slot) + (tid % CH) * 16, fresh);  // Step 4: the new token enters the window
   }
   __syncthreads();
 
-  // merge the waves; one split: finish here, else write this split's partial
+  float m = -INFINITY;  // of head sl
+  double l = 0.0, acc[GB][4];
+#pragma unroll
+  for (int g = 0; g < GB; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[g][e] = 0.0;
+
+  for (int b = wave, it = 0; b < nblk; b += NW, ++it) {
+    const int b0 = t_begin + b * BT;
+    // whatever the cache holds in the new token's place was loaded, by lanes past the slice too: the token itself instead
+    const bool patch = slot >= 0 && ((slot >= b0 && slot < b0 + BT) || (b0 + BT > t_end && (slot == t_begin || (PG && slot >= b0 - 16 && slot < t_end))));
+    if (patch) {  // wave-uniform
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+        if (token(it, 8 * g, 8 * g + t8) == slot) {
+#pragma unroll
+          for (int ch = 0; ch < NC; ++ch) kv[g][ch] = s_new[ch * 8 + sl];
+        }
+    }
+
+    // logits: lane's parts, two groups at a time
+    double x[NG];  // of head sl, token 8 g + t8
+    auto logits = [&](auto sink) {
+#pragma unroll
+      for (int gg = 0; gg < NG; gg += 2) {
+#pragma unroll
+        for (int hh = 0; hh < GB; hh += 4) {
+          asm volatile("" ::: "memory");  // the queries are read again, not held for the other groups
+          double a[2][4];
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) a[u][h] = 0.0;
+#pragma unroll
+          for (int ch = 0; ch < NC; ++ch) {
+            double kd[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              kd[u][0] = (double)__uint_as_float(kv[gg + u][ch].x);
+              kd[u][1] = (double)__uint_as_float(kv[gg + u][ch].y);
+              kd[u][2] = (double)__uint_as_float(kv[gg + u][ch].z);
+              kd[u][3] = (double)__uint_as_float(kv[gg + u][ch].w);
+            }
+#pragma unroll
+            for (int h = 0; h < 4 && hh + h < GB; ++h) {
+              const int at = (hh + h) * D + (ch * 8 + sl) * 4;
+#pragma unroll
+              for (int u = 0; u < 2; ++u) {
+                const double* q = qd[0] + at;
+                if constexpr (decltype(sink)::value) q = qd[b0 + 8 * (gg + u) + t8 < p.qs_S ? 1 : 0] + at;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[u][h] = fma(kd[u][e], q[e], a[u][h]);
+              }
+            }
+          }
+          // over the eight lanes of a token; lane s keeps head s
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            double z[2];
+#pragma unroll
+            for (int h = 0; h < 4; ++h) a[u][h] += dpp_f64<0x141>(a[u][h]);  // row_half_mirror
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const double lo = a[u][h], hi = a[u][h + 2];
+              z[h] = (sl & 2 ? hi : lo) + dpp_f64<0x4E>(sl & 2 ? lo : hi);
+            }
+            const double lo = z[0], hi = z[1], r = (sl & 1 ? hi : lo) + dpp_f64<0xB1>(sl & 1 ? lo : hi);
+            x[gg + u] = hh == 0 || sl >= 4 ? r : x[gg + u];
+          }
+        }
+      }
+    };
+    if (p.q_sink && b0 < p.qs_S)  // wave-uniform: the block holds sink tokens
+      logits(std::integral_constant<bool, true>());
+    else
+      logits(std::integral_constant<bool, false>());
+    if (LATE_V) load_v(it);
+    const bool more = b + NW < nblk;
+    if (more) {
+      if (PG && (((it + 1) * GPB) & 63) == 0) fill_pages(it + 1);
+      load_k(it + 1);
+    }
+
+    // softmax weights, once per (token, head)
+    float bm = -INFINITY;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int tok = b0 + 8 * g + t8;
+      const bool in = sl < GB && tok < t_end && head_attends(p.pq_S, p.pq_k, p.G, g0 + sl, tok);
+      x[g] = in ? x[g] * (1.0 / sqrt((double)D)) : -INFINITY;
+      bm = fmaxf(bm, (float)x[g]);
+    }
+    bm = fmaxf(bm, dpp_f32<0x128>(bm));  // row_ror:8
+    bm = swap32_max(swap16_max(bm));
+    const float mn = fmaxf(m, bm);
+    const float corr = mn == -INFINITY ? 1.f : exp_fast(m - mn);  // head with nothing to attend yet
+    l *= (double)corr;
+    m = mn;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the last block's weights are read
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const float w = x[g] == -INFINITY ? 0.f : exp_fast((float)(x[g] - (double)mn));
+      l += (double)w;
+      if (sl < GB) pw[wave][8 * g + t8][sl] = (double)w;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+    // P.V on the lanes that hold V's chunks
+    if (patch) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (token(it, i * TPL, i * TPL + tq) == slot) vv[i] = s_new[CH + cl];
+    }
+#pragma unroll
+    for (int g = 0; g < GB; ++g) {
+      const double f = (double)__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(corr), g));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[g][e] *= f;
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const double v[4] = {(double)__uint_as_float(vv[i].x), (double)__uint_as_float(vv[i].y), (double)__uint_as_float(vv[i].z),
+                           (double)__uint_as_float(vv[i].w)};
+#pragma unroll
+      for (int g = 0; g < GB; ++g) {
+        const double w = pw[wave][i * TPL + tq][g];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[g][e] = fma(w, v[e], acc[g][e]);
+      }
+    }
+    if (!LATE_V && more) load_v(it + 1);
+  }
+
+  // the wave's totals: over the lanes that share a chunk of V, and those that share a head
+  auto swap32_total = [](double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+  };
+#pragma unroll
+  for (int g = 0; g < GB; ++g)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      double a = acc[g][e];
+      if (CH == 16) a += swap16_f64(a);
+      a = swap32_total(a);
+      if (tq == 0) s_acc[wave][g][cl * 4 + e] = (float)a;
+    }
+  l += dpp_f64<0x128>(l);
+  l += swap16_f64(l);
+  l = swap32_total(l);
+  if (lane < GB) {
+    s_m[wave][lane] = m;
+    s_l[wave][lane] = l;
+  }
+  __syncthreads();
+
+  // the waves' parts, added in fp64; one split: finish here, else write this split's partial
   const bool single = p.n_splits == 1;
   float* pa = p.part_acc + (((int64_t)row * p.n_splits + split) * p.G + g0) * D;
   float2* pml = p.part_ml + ((int64_t)row * p.n_splits + split) * p.G + g0;
-  for (int it = tid; it < GB * D; it += kDecThreads) {
+  for (int it = tid; it < GB * D; it += kThreads) {
     const int g = it / D, j = it % D;
-    float M = s_ml[0][g].x;
+    float M = s_m[0][g];
 #pragma unroll
-    for (int w = 1; w < kDecWaves; ++w) M = fmaxf(M, s_ml[w][g].x);
-    // fp32 caches: the waves' parts are added in fp64, so that a row's error does not grow with their number (short
-    // whole rows of 16 waves: 1.25e-7 of the result with fp32 sums, 0.8e-7 so; two slices of four waves had 1.1e-7)
-    typedef typename std::conditional<DT == DT_F32, double, float>::type Sum;
-    Sum a = 0, ls = 0;
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w][g]);
+    double a = 0.0, ls = 0.0;
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
-      const float2 ml = s_ml[w][g];
-      const float f = (ml.x == -INFINITY) ? 0.f : exp_fast(ml.x - M);
-      a += (Sum)s_acc[w][g][j] * f;
-      ls += (Sum)ml.y * f;
+    for (int w = 0; w < NW; ++w) {
+      const double f = s_m[w][g] == -INFINITY ? 0.0 : (double)exp_fast(s_m[w][g] - M);
+      a += (double)s_acc[w][g][j] * f;
+      ls += s_l[w][g] * f;
     }
     if (single) {
-      p.out[((int64_t)prob * p.Hq + c * p.G + g0 + g) * D + j] = (float)(a / ls);
+      p.out[(head0 + g) * D + j] = (float)(a / ls);
     } else {
       pa[(int64_t)g * D + j] = M == -INFINITY ? 0.f : (float)a;  // (nothing attended here: see combine_kernel)
       if (j == 0) pml[g] = make_float2(M, (float)ls);
@@ -928,24 +1035,31 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* p, size_t n, ui
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = v;
 }
 
-template <int DT, int D>
-hipError_t launch_decode_g(const DecodeParams& p, int g0, int gb, dim3 grid, hipStream_t s) {
-  const bool single = p.n_splits == 1;  // one workgroup per row: use a big one
+template <int D, int GB, bool PG>
+void launch_decode_f32_g(const DecodeParams& p, int g0, dim3 grid, hipStream_t s) {
+  if constexpr (D == 128) {
+    hipLaunchKernelGGL((decode_f32_kernel<D, GB, 8, 16, PG>), grid, dim3(512), 0, s, p, g0);
+  } else if (p.n_splits > 1) {
+    hipLaunchKernelGGL((decode_f32_kernel<D, GB, 4, 32, PG>), grid, dim3(256), 0, s, p, g0);
+  } else if constexpr (GB <= 2) {
+    hipLaunchKernelGGL((decode_f32_kernel<D, GB, 8, 16, PG>), grid, dim3(512), 0, s, p, g0);
+  } else {
+    hipLaunchKernelGGL((decode_f32_kernel<D, GB, 8, 32, PG>), grid, dim3(512), 0, s, p, g0);
+  }
+}
+
+template <int D, bool PG>
+hipError_t launch_decode_f32(const DecodeParams& p, int g0, int gb, dim3 grid, hipStream_t s) {
   switch (gb) {
-// (4 heads and more spill in 16 waves of 128 registers: 256 rows x 4096 tokens x 4 heads of head_dim 64 took 247 us in
-// them, 127 in 8 waves; 256 rows x 192 tokens 21 and 10.7; 3 heads fit)
-#define SAGEKV_CASE(N)                                                                               \
-  case N:                                                                                            \
-    if (!single)                                                                                     \
-      hipLaunchKernelGGL((decode_kernel<DT, D, N, 4>), grid, dim3(256), 0, s, p, g0);                \
-    else                                                                                             \
-      hipLaunchKernelGGL((decode_kernel<DT, D, N, (N <= 3 ? 16 : 8)>), grid, dim3(N <= 3 ? 1024 : 512), 0, s, p, g0); \
-    break;
-    SAGEKV_CASE(1) SAGEKV_CASE(2) SAGEKV_CASE(3) SAGEKV_CASE(4)
-    SAGEKV_CASE(5) SAGEKV_CASE(6) SAGEKV_CASE(7) SAGEKV_CASE(8)
-#undef SAGEKV_CASE
-    default:
-      return hipErrorInvalidValue;
+    case 1: launch_decode_f32_g<D, 1, PG>(p, g0, grid, s); break;
+    case 2: launch_decode_f32_g<D, 2, PG>(p, g0, grid, s); break;
+    case 3: launch_decode_f32_g<D, 3, PG>(p, g0, grid, s); break;
+    case 4: launch_decode_f32_g<D, 4, PG>(p, g0, grid, s); break;
+    case 5: launch_decode_f32_g<D, 5, PG>(p, g0, grid, s); break;
+    case 6: launch_decode_f32_g<D, 6, PG>(p, g0, grid, s); break;
+    case 7: launch_decode_f32_g<D, 7, PG>(p, g0, grid, s); break;
+    case 8: launch_decode_f32_g<D, 8, PG>(p, g0, grid, s); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -1003,7 +1117,8 @@ hipError_t launch_decode(const DecodeParams& p, hipStream_t s) {
     if (p.dtype == DT_BF16)
       e = p.D == 128 ? launch_decode_mfma<128>(q, g0, gb, grid, s) : launch_decode_mfma<64>(q, g0, gb, grid, s);
     else
-      e = p.D == 128 ? launch_decode_g<DT_F32, 128>(q, g0, gb, grid, s) : launch_decode_g<DT_F32, 64>(q, g0, gb, grid, s);
+      e = p.cpm.table ? (p.D == 128 ? launch_decode_f32<128, true>(q, g0, gb, grid, s) : launch_decode_f32<64, true>(q, g0, gb, grid, s))
+                      : (p.D == 128 ? launch_decode_f32<128, false>(q, g0, gb, grid, s) : launch_decode_f32<64, false>(q, g0, gb, grid, s));
     if (e != hipSuccess) return e;
   }
   if (p.n_splits > 1) {
