@@ -280,15 +280,7 @@ __global__ __launch_bounds__(NW * 64) void decode_f32_kernel(DecodeParams p, int
           // over the eight lanes of a token; lane s keeps head s
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            double z[2];
-#pragma unroll
-            for (int h = 0; h < 4; ++h) a[u][h] += dpp_f64<0x141>(a[u][h]);  // row_half_mirror
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const double lo = a[u][h], hi = a[u][h + 2];
-              z[h] = (sl & 2 ? hi : lo) + dpp_f64<0x4E>(sl & 2 ? lo : hi);
-            }
-            const double lo = z[0], hi = z[1], r = (sl & 1 ? hi : lo) + dpp_f64<0xB1>(sl & 1 ? lo : hi);
+            const double r = eight_lane_sums(a[u], sl);
             x[gg + u] = hh == 0 || sl >= 4 ? r : x[gg + u];
           }
         }
@@ -356,24 +348,18 @@ __global__ __launch_bounds__(NW * 64) void decode_f32_kernel(DecodeParams p, int
   }
 
   // the wave's totals: over the lanes that share a chunk of V, and those that share a head
-  auto swap32_total = [](double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
-  };
 #pragma unroll
   for (int g = 0; g < GB; ++g)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       double a = acc[g][e];
       if (CH == 16) a += swap16_f64(a);
-      a = swap32_total(a);
+      a = swap32_sum_f64(a);
       if (tq == 0) s_acc[wave][g][cl * 4 + e] = (float)a;
     }
   l += dpp_f64<0x128>(l);
   l += swap16_f64(l);
-  l = swap32_total(l);
+  l = swap32_sum_f64(l);
   if (lane < GB) {
     s_m[wave][lane] = m;
     s_l[wave][lane] = l;

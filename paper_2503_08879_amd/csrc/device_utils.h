@@ -151,6 +151,26 @@ __device__ __forceinline__ double group_sum_f64(double v) {
   return v;
 }
 
+__device__ __forceinline__ double swap32_sum_f64(double v) {  // v + v of lane ^ 32
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+// Four values summed over aligned groups of eight lanes; lane s of a group (`sl`) gets the total of value s % 4.
+__device__ __forceinline__ double eight_lane_sums(double (&a)[4], int sl) {
+  double z[2];
+#pragma unroll
+  for (int h = 0; h < 4; ++h) a[h] += dpp_f64<0x141>(a[h]);  // row_half_mirror
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const double lo = a[h], hi = a[h + 2];
+    z[h] = (sl & 2 ? hi : lo) + dpp_f64<0x4E>(sl & 2 ? lo : hi);  // quad_perm [2,3,0,1]: from the lane that keeps the other two
+  }
+  const double lo = z[0], hi = z[1];
+  return (sl & 1 ? hi : lo) + dpp_f64<0xB1>(sl & 1 ? lo : hi);  // quad_perm [1,0,3,2]
+}
+
 // Maximum over aligned groups of 16 lanes, in every lane of the group.
 __device__ __forceinline__ float group16_max(float v) {
   v = fmaxf(v, dpp_f32<0xB1>(v));   // quad_perm [1,0,3,2]

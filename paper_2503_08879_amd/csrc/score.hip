@@ -1,7 +1,7 @@
 // Eviction pass, scoring stage (paper Sec. 2 Step 2: attention scores of the last token's
 // query against the cached keys).
 //
-//   score_kernel (fp32), score_mfma_kernel (bf16)
+//   score_f32_kernel, score_mfma_kernel (bf16)
 //                   stream K once: logit[g][i] = q[g].K[i]/sqrt(d) for the G heads of a row.  What a
 //                   pass leaves behind depends on its mode (ScoreMode): fp32 logits + per-chunk softmax
 //                   partials (max, sum exp) for the one-sweep dense path; partials + the records of
@@ -32,117 +32,155 @@ constexpr int64_t kLogitsThrough = 200000000;
 constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine launch
 // A score workgroup takes a chunk of BPW blocks of 64 tokens per wave (BPW = 1, 2, 4: 256, 512, 1024 tokens).
 
-// fp32 caches.  One wave handles 64 tokens per block: LPT lanes share a token (16 bytes each), so one
-// 16-byte load instruction covers TPL = 64/LPT whole tokens, fully coalesced; LPT such loads
-// make a block.  After load i the lane with (lane % LPT) == i keeps the reduced dot product,
-// so each lane ends a block owning exactly one token's logits for all heads.
+// fp32 caches.  Products and sums in fp64 (the same four cycles as in fp32), so a logit is rounded once.  Eight lanes share a token, four or two
+// 16-byte chunks each, and its eight parts are summed while heads and lanes change places: lane s of the eight ends with head s's
+// logit (up to eight heads a launch).  A wave takes batches of 32 tokens (16 with 128 dims), lane group t of eight the tokens 4 t .. 4 t + 3 (2 t, 2 t + 1), so that a
+// lane stores four (two) logits at once; the next batch's loads are in flight meanwhile.  (With 16 or 32 lanes per token and every head's logit summed over all of
+// them in fp32 the pass was bound by vector instructions. Whole calls, us: 8 rows x 32K x 4 heads of 128 dims 66.3 and 53.8, 64 x 16K x 4 182
+// and 169, 16 x 32K x 7 117 and 102, in pages 4 x 16K x 7 61.5 and 50.6, 64 x 8192 x 4 of 64 dims 67.3 and 59.7; plain loads instead of streaming
+// ones 113 us for the pass over 64 x 16K, 100 so.)
 //
 // The softmax partial of the chunk is taken after the last block, from the logits in registers.
-template <int DT, int D, int GB, int BPW>
-__global__ __launch_bounds__(kScoreThreads, 2) void score_kernel(ScoreParams p) {
-  constexpr int EPL = Elem<DT>::per_lane;
-  constexpr int EB = Elem<DT>::bytes;
-  constexpr int LPT = D / EPL;
-  constexpr int TPL = 64 / LPT;
-  constexpr int SB = GB > 4 ? 8 : 16;  // loads per batch
+template <int D, int GB, int BPW>
+__global__ __launch_bounds__(kScoreThreads, 2) void score_f32_kernel(ScoreParams p) {
+  constexpr int NC = D / 32;            // chunks of a token per lane
+  constexpr int U = D == 64 ? 4 : 2;    // a lane group's tokens of a batch
+  constexpr int NB = 64 * BPW / (8 * U);  // batches per wave
   constexpr int kChunk = 64 * BPW * kScoreWaves;
+  __shared__ __attribute__((aligned(16))) double qd[GB * D];
+  __shared__ float part_m[kScoreWaves][GB];
+  __shared__ double part_s[kScoreWaves][GB];
 
   const int row = blockIdx.y;
   const int prob = row / p.geo.Hkv, c = row % p.geo.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tq = lane / LPT, cl = lane % LPT;
+  const int t8 = lane >> 3, sl = lane & 7;
   const int64_t L = p.geo.L;
-
-  // batches of SB loads, the next one in flight while the current one is used
-  constexpr int NB = LPT / SB;  // batches per block
   const int64_t wave_base = (int64_t)blockIdx.x * kChunk + (int64_t)wave * BPW * 64;
-  uint4 kv[2][SB];
-  auto load_batch = [&](int n, uint4* dst) {
-    const int64_t tok_base = wave_base + (n / NB) * 64;
-    if (tok_base < L) {  // wave-uniform
+  float qv[(GB * D + kScoreThreads - 1) / kScoreThreads];
 #pragma unroll
-      for (int i = 0; i < SB; ++i) {
-        int64_t tok = tok_base + ((n % NB) * SB + i) * TPL + tq;
+  for (int i = 0; i < (int)(sizeof(qv) / 4); ++i) {
+    const int at = threadIdx.x + i * kScoreThreads;
+    qv[i] = at < GB * D ? ((const float*)p.q_last)[((int64_t)prob * p.geo.Hq + c * p.geo.G + p.g0) * D + at] : 0.f;
+  }
+  uint4 kv[2][U][NC];
+  auto load_batch = [&](int n, uint4 (&dst)[U][NC]) {
+    if (wave_base + 8 * U * n < L) {  // wave-uniform
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        int64_t tok = wave_base + 8 * U * n + U * t8 + u;
         tok = tok < L ? tok : L - 1;  // tail: re-read the last token, masked below
-        const int64_t off = kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok);
-        dst[i] = ld16((const char*)p.K + off * EB + cl * 16);
+        const char* a = (const char*)p.K + kv_offset(p.pm, p.pm.ks_page, p.ks_problem, p.ks_head, p.ks_token, prob, c, tok) * 4 + sl * 16;
+#pragma unroll
+        for (int ch = 0; ch < NC; ++ch) dst[u][ch] = ld16_stream(a + ch * 128);
       }
     }
   };
   load_batch(0, kv[0]);
-  uint4 q[GB];
 #pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    int h = c * p.geo.G + p.g0 + g;
-    q[g] = ld16((const char*)p.q_last + (((int64_t)prob * p.geo.Hq + h) * D + cl * EPL) * EB);
-  }
-  float xs[BPW][GB];  // -INFINITY: no token
+  for (int i = 0; i < (int)(sizeof(qv) / 4); ++i)
+    if ((int)threadIdx.x + i * kScoreThreads < GB * D) qd[threadIdx.x + i * kScoreThreads] = (double)qv[i];
+  __syncthreads();
+
+  float xs[NB][U];  // of head sl; -INFINITY: no token
 #pragma unroll
-  for (int n = 0; n < BPW * NB; ++n) {
-    const int blk = n / NB, i0 = (n % NB) * SB;
-    const int64_t tok_base = wave_base + blk * 64;
-    if (n + 1 < BPW * NB) load_batch(n + 1, kv[(n + 1) & 1]);
+  for (int n = 0; n < NB; ++n) {
+    const int64_t tok0 = wave_base + 8 * U * n + U * t8;
+    if (n + 1 < NB) load_batch(n + 1, kv[(n + 1) & 1]);
     __builtin_amdgcn_sched_barrier(0);
-    if (i0 == 0) {
 #pragma unroll
-      for (int g = 0; g < GB; ++g) xs[blk][g] = 0.f;
-    }
-    if (tok_base < L) {
+    for (int u = 0; u < U; ++u) xs[n][u] = -INFINITY;
+    if (wave_base + 8 * U * n < L) {
 #pragma unroll
-      for (int i = 0; i < SB; ++i) {
+      for (int uu = 0; uu < U; uu += 2) {
 #pragma unroll
-        for (int g = 0; g < GB; ++g) {
-          const float v = group_sum<LPT>(dot16<DT>(kv[n & 1][i], q[g], 0.f));
-          xs[blk][g] = (cl == i0 + i) ? v : xs[blk][g];
+        for (int hh = 0; hh < GB; hh += 4) {
+          asm volatile("" ::: "memory");  // the queries are read again, not held for the other tokens
+          double a[2][4];
+#pragma unroll
+          for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) a[u][h] = 0.0;
+#pragma unroll
+          for (int ch = 0; ch < NC; ++ch) {
+            double kd[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              uint4 k = kv[n & 1][uu + u][ch];
+              if (GB > 4) asm volatile("" : "+v"(k.x), "+v"(k.y), "+v"(k.z), "+v"(k.w));  // converted again for the other four heads, not held
+              kd[u][0] = (double)__uint_as_float(k.x);
+              kd[u][1] = (double)__uint_as_float(k.y);
+              kd[u][2] = (double)__uint_as_float(k.z);
+              kd[u][3] = (double)__uint_as_float(k.w);
+            }
+#pragma unroll
+            for (int h = 0; h < 4 && hh + h < GB; ++h) {
+              const double* q = qd + (hh + h) * D + (ch * 8 + sl) * 4;
+#pragma unroll
+              for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[u][h] = fma(kd[u][e], q[e], a[u][h]);
+            }
+          }
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const float r = (float)(eight_lane_sums(a[u], sl) * (1.0 / sqrt((double)D)));
+            xs[n][uu + u] = hh == 0 || sl >= 4 ? r : xs[n][uu + u];
+          }
         }
       }
-    }
-    if (i0 + SB == LPT) {
-      const int64_t tok = tok_base + cl * TPL + tq;
-#pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        xs[blk][g] = tok < L ? xs[blk][g] * p.scale : -INFINITY;
-        if (tok < L) p.logits[logit_index(p.geo, p.n_chunks, p.chunk, row, p.g0 + g, tok)] = xs[blk][g];
+      // (past the row's end, inside the chunk's scratch: the last token's again)
+      if (sl < GB)
+      {
+        float* at = p.logits + logit_index(p.geo, p.n_chunks, p.chunk, row, p.g0 + sl, tok0);
+        if constexpr (U == 4)
+          *reinterpret_cast<float4*>(at) = make_float4(xs[n][0], xs[n][1], xs[n][2], xs[n][3]);
+        else
+          *reinterpret_cast<float2*>(at) = make_float2(xs[n][0], xs[n][1]);
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (tok0 + u >= L) xs[n][u] = -INFINITY;
     }
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // (max, sum) of the chunk: lanes -> wave -> workgroup
-  __shared__ float part_m[kScoreWaves][GB];
-  __shared__ double part_s[kScoreWaves][GB];
+  // (max, sum) of the chunk: the lanes of a head -> wave -> workgroup
+  float m = -INFINITY;
 #pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    float m = xs[0][g];
+  for (int n = 0; n < NB; ++n)
 #pragma unroll
-    for (int blk = 1; blk < BPW; ++blk) m = fmaxf(m, xs[blk][g]);
-    m = wave_max(m);
-    if (lane == 0) part_m[wave][g] = m;
-  }
+    for (int u = 0; u < U; ++u) m = fmaxf(m, xs[n][u]);
+  m = fmaxf(m, dpp_f32<0x128>(m));  // row_ror:8
+  m = swap32_max(swap16_max(m));
+  if (lane < GB) part_m[wave][lane] = m;
   __syncthreads();
+  float M = -INFINITY;
+  if (sl < GB) {
 #pragma unroll
-  for (int g = 0; g < GB; ++g) {
-    float M = part_m[0][g];
-#pragma unroll
-    for (int w = 1; w < kScoreWaves; ++w) M = fmaxf(M, part_m[w][g]);
-    M = M == -INFINITY ? 0.f : M;  // nothing but -inf: the sum is 0
-    double z = 0.0;
-#pragma unroll
-    for (int blk = 0; blk < BPW; ++blk) z += (double)exp_fast(xs[blk][g] - M);
-    z = group_sum_f64<64>(z);
-    if (lane == 0) part_s[wave][g] = z;
+    for (int w = 0; w < kScoreWaves; ++w) M = fmaxf(M, part_m[w][sl]);
   }
+  M = M == -INFINITY ? 0.f : M;  // nothing but -inf: the sum is 0
+  double z = 0.0;
+#pragma unroll
+  for (int n = 0; n < NB; ++n)
+#pragma unroll
+    for (int u = 0; u < U; ++u) z += (double)exp_fast(xs[n][u] - M);
+  z += dpp_f64<0x128>(z);
+  z += swap16_f64(z);
+  z = swap32_sum_f64(z);
+  if (lane < GB) part_s[wave][lane] = z;
   __syncthreads();
   if (threadIdx.x < GB) {
     const int g = threadIdx.x;
-    float m = part_m[0][g];
-    double z = 0.0;
+    float mm = part_m[0][g];
+    double zz = 0.0;
 #pragma unroll
     for (int w = 0; w < kScoreWaves; ++w) {
-      m = fmaxf(m, part_m[w][g]);
-      z += part_s[w][g];
+      mm = fmaxf(mm, part_m[w][g]);
+      zz += part_s[w][g];
     }
-    p.chunk_partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + blockIdx.x] = ChunkPartial{z, m, 0.f};
+    p.chunk_partials[((int64_t)row * p.geo.G + p.g0 + g) * p.n_chunks + blockIdx.x] = ChunkPartial{zz, mm, 0.f};
   }
 }
 
@@ -912,12 +950,12 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(CombineParams 
   }
 }
 
-template <int DT, int D, int BPW>
+template <int D, int BPW>
 hipError_t launch_score_g(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
   switch (gb) {
 #define SAGEKV_CASE(N) \
   case N:              \
-    hipLaunchKernelGGL((score_kernel<DT, D, N, BPW>), grid, dim3(kScoreThreads), 0, s, p); \
+    hipLaunchKernelGGL((score_f32_kernel<D, N, BPW>), grid, dim3(kScoreThreads), 0, s, p); \
     break;
     SAGEKV_CASE(1) SAGEKV_CASE(2) SAGEKV_CASE(3) SAGEKV_CASE(4)
     SAGEKV_CASE(5) SAGEKV_CASE(6) SAGEKV_CASE(7) SAGEKV_CASE(8)
@@ -931,8 +969,8 @@ hipError_t launch_score_g(const ScoreParams& p, int gb, dim3 grid, hipStream_t s
 template <int D>
 hipError_t launch_score_f32(const ScoreParams& p, int gb, dim3 grid, hipStream_t s) {
   switch (p.chunk) {
-    case 256: return launch_score_g<DT_F32, D, 1>(p, gb, grid, s);
-    case 512: return launch_score_g<DT_F32, D, 2>(p, gb, grid, s);
+    case 256: return launch_score_g<D, 1>(p, gb, grid, s);
+    case 512: return launch_score_g<D, 2>(p, gb, grid, s);
     default: return hipErrorInvalidValue;
   }
 }
