@@ -1033,9 +1033,11 @@ static hipError_t launch_shortlist_t(const ShortlistParams& p, const TopkParams&
 #undef SAGEKV_LAUNCH
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return p.expect <= 4 * kTopkThreads   ? launch_shortlist_select<DT, 4>(p, tp, lists, s)
-         : p.expect <= 8 * kTopkThreads ? launch_shortlist_select<DT, 8>(p, tp, lists, s)
-                                        : launch_shortlist_select<DT, 16>(p, tp, lists, s);
+  return p.expect <= 4 * kTopkThreads    ? launch_shortlist_select<DT, 4>(p, tp, lists, s)
+         : p.expect <= 6 * kTopkThreads  ? launch_shortlist_select<DT, 6>(p, tp, lists, s)
+         : p.expect <= 8 * kTopkThreads  ? launch_shortlist_select<DT, 8>(p, tp, lists, s)
+         : p.expect <= 12 * kTopkThreads ? launch_shortlist_select<DT, 12>(p, tp, lists, s)
+                                         : launch_shortlist_select<DT, 16>(p, tp, lists, s);
 }
 
 hipError_t launch_shortlist(const ShortlistParams& p, const TopkParams& tp0, hipStream_t s) {
