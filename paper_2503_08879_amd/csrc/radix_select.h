@@ -500,20 +500,27 @@ __device__ __forceinline__ void bracket_kth(RegSelect& sh, Each each, int k, uin
   *thi = *tlo + ((1u << s2) - 1u);
 }
 
-// fp64 scores of the band's members (band_tok) into band_v: the (member, head) terms spread over the waves, added
+// fp64 scores of the band's members (band_tok) into band_v: 16 lanes take a (member, head) term, the terms are added
 // in head order.  Ends with a barrier.
 template <int DT>
 __device__ __forceinline__ void refine_band(RegSelect& sh, int nb, const RowGeom& geo, const void* q_last, const void* K,
                                             const PageMap& pm, int64_t ks_problem, int64_t ks_head, int64_t ks_token,
                                             const RowStat* stats, int prob, int c, int g_lo, int g_hi) {
-  const int tid = threadIdx.x, heads = g_hi - g_lo, per = kMaxBand / heads;
+  typedef typename FourElems<DT>::type Four;
+  const int D = geo.D, tid = threadIdx.x, sub = tid & 15, heads = g_hi - g_lo, per = kMaxBand / heads;
+  const double inv = 1.0 / sqrt((double)D);
   for (int m0 = 0; m0 < nb; m0 += per) {
     const int cnt = nb - m0 < per ? nb - m0 : per;
-    for (int t = tid >> 6; t < cnt * heads; t += kTopkWaves) {
+#pragma unroll 1
+    for (int t = tid >> 4; t < cnt * heads; t += kTopkThreads / 16) {
       const int g = g_lo + t % heads;
-      const double x = refined_term_wave<DT>(geo, q_last, K, pm, ks_problem, ks_head, ks_token, stats[g], prob, c,
-                                             sh.band_tok[m0 + t / heads], g);
-      if ((tid & 63) == 0) sh.term[t] = x;
+      const int64_t ko = kv_offset(pm, pm.ks_page, ks_problem, ks_head, ks_token, prob, c, sh.band_tok[m0 + t / heads]) + 4 * sub;
+      const int64_t qo = ((int64_t)prob * geo.Hq + c * geo.G + g) * D + 4 * sub;
+      const Four k0 = four_elems<DT>(K, ko), q0 = four_elems<DT>(q_last, qo);
+      Four k1 = {}, q1 = {};
+      if (D > 64) k1 = four_elems<DT>(K, ko + 64), q1 = four_elems<DT>(q_last, qo + 64);
+      const double l = group_sum_f64<16>(dot_f64<DT>(k1, q1, dot_f64<DT>(k0, q0, 0.0))) * inv;
+      if (sub == 0) sh.term[t] = exp(l - (double)stats[g].M) / stats[g].Z;
     }
     __syncthreads();
     for (int t = tid; t < cnt; t += kTopkThreads) {
