@@ -146,8 +146,8 @@ ShortlistPlan shortlist_plan(const sagekv_select_desc* d) {
   s.expect = (int)ceil(most);
   // Registers of the selecting workgroup, and longer rows than one workgroup selects from faster (row_select_kernel): from 8192 tokens on
   // while the first launch has a CU for every workgroup, us, row_select_kernel and this: 8 rows x 8192 28.9 29.9, x 10000 32.7 30.6, x 24000
-  // 46.9 35.6, 32 x 24000 81 71, 64 x 24000 180 180, 128 x 16384 160 170; always from kRowSelectMax tokens on, up to the logits of
-  // 256 rows x 32K x 4 heads (806 and 806, at twice that 994 and 1008 against separate launches for statistics, scores and selection).
+  // 46.9 35.6, 32 x 24000 81 71, 64 x 24000 180 180, 128 x 16384 160 170; from kRowSelectMax tokens on, up to the logits of
+  // 256 rows x 32K x 4 heads, wherever the pre-filtered path is the alternative (few_rows), else as select_layout says.
   s.ok = s.expect <= 16 * 1024 &&
          (d->L > kRowSelectMax ? 4 * (int64_t)d->n_problems * d->n_q_heads * d->L <= 128ll << 20
                                : d->L > kShortFrom && lists * (s.n_parts + 1) <= 256);
@@ -237,7 +237,12 @@ SelectLayout select_layout(const sagekv_select_desc* d, bool own_scores, bool fe
   l.list = shortlist_plan(d);
   few = few && own_scores;
   l.one_sweep = !l.small || (few && few_rows(d, l.G, l.n_lists > 1) && (l.list.ok || d->L <= kRowSelectMax));
-  l.shortlist = few && l.list.ok && l.one_sweep;
+  // Calls the pre-filtered path does not serve, more than kRowSelectMax tokens: up to two workgroups of the first launch per CU, one with
+  // 64 dims.  Whole passes, us, statistics, combine and top-k in launches of their own and this, by workgroups: 7 per-query lists of 27000 tokens, 280
+  // 58.5 54.2, 420 75.8 68.0, 1680 213 217, 4200 512 523; 4 lists of 30000, 480 119 115, 3840 787 797; rows of 32000 x 4 heads, 320 213 210, 640 386
+  // 388; of 64 dims, 320 128 132, 500 180 183, 600 211 218.
+  const int64_t first = (int64_t)l.rows * l.n_lists * (l.list.n_parts + 1);
+  l.shortlist = few && l.list.ok && l.one_sweep && (l.small || d->L <= kRowSelectMax || first <= (d->head_dim == 64 ? 256 : 512));
   l.chunk = score_chunk(d, l.one_sweep && !few ? kFillScores : kFill);
   l.n_chunks = (int)((d->L + l.chunk - 1) / l.chunk);
   size_t off = 0;

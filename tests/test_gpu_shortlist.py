@@ -53,6 +53,10 @@ def check(ref, dtype, head_mode, q, K, V, S, W, k, flags=0, **dev):
     (BF16, 1, 4, 1, 64, 30000, 4, 28000, 1, 0),        # fewer runs than the sample takes
     (BF16, 1, 4, 2, 64, 200000, 4, 64, 9000, 0),       # about 11 thousand handed on: 16 registers
     (F32, 1, 2, 1, 64, 100000, 4, 64, 4000, 0),        # 8
+    (BF16, 2, 14, 2, 64, 24600, 4, 64, 4900, 1),       # 28 lists, 224 workgroups: the most but a few for 64 dims
+    (BF16, 3, 14, 2, 64, 24600, 4, 64, 4900, 1),       # 42 lists: over that
+    (BF16, 4, 28, 4, 128, 24600, 4, 64, 4900, 1),      # 112 lists of 128 dims, 560 workgroups: over that too
+    (BF16, 7, 8, 2, 128, 65537, 4, 64, 13200, 0),      # one list per row, 14 lists, 252 workgroups
 ])
 def test_few_rows(ref, dtype, P, Hq, Hkv, d, L, S, W, k, head_mode):
     q, K, V = parity.rand_case(L + Hq + k, P, Hq, Hkv, d, L, dtype)
