@@ -537,13 +537,15 @@ __device__ __forceinline__ void refine_band(RegSelect& sh, int nb, const RowGeom
 // other they took 8 of a row's 20 us (256 rows x 8192 tokens, k = 1788, four sink tokens); a whole pass 207 -> 204, over 8 rows 29.7 -> 27.6,
 // 128 rows x 8192 x 7 heads 128 -> 122.6.
 constexpr int kHeavyList = 512;
-struct HeavyList {
+struct HeavyList {  // in the order in which the waves met them
   int n;
-  int tok[kHeavyList];
+  uint32_t key[kHeavyList];  // heavy_key
   float logit[kHeavyList];
+  // exact term - the one in the merged sum, and its head: by key, so that a sum does not depend on the waves' order
+  double change[kHeavyList];
   unsigned char head[kHeavyList];
-  double change[kHeavyList];  // exact term - the one in the merged sum
 };
+__device__ __forceinline__ uint32_t heavy_key(int head, int tok) { return (uint32_t)head << 26 | (uint32_t)tok; }  // 64 heads, 2^26 tokens
 
 // fp64 scores of the band's members into band_v after the listed terms have gone into the statistics (stat, in LDS).  Every 16 lanes
 // take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyList.  Begins (hv.n, band_tok) after a barrier, ends with one.
@@ -558,18 +560,26 @@ __device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, 
   for (int t = tid >> 4; t < n; t += kTopkThreads / 16) {
     const bool heavy = t < n_heavy;
     const int b = heavy ? 0 : t - n_heavy;
-    const int tok = heavy ? hv.tok[t] : sh.band_tok[b / heads], g = heavy ? hv.head[t] : g_lo + b % heads;
+    const uint32_t key = heavy ? hv.key[t] : heavy_key(g_lo + b % heads, sh.band_tok[b / heads]);
+    const int tok = (int)(key & 0x3FFFFFFu), g = (int)(key >> 26);
     const int64_t ko = kv_offset(in.pm, in.pm.ks_page, in.ks_problem, in.ks_head, in.ks_token, prob, c, tok) + 4 * sub;
     const int64_t qo = ((int64_t)prob * geo.Hq + c * geo.G + g) * D + 4 * sub;
     const Four k0 = four_elems<DT>(in.K, ko), q0 = four_elems<DT>(in.q_last, qo);
     Four k1 = {}, q1 = {};
     if (D > 64) k1 = four_elems<DT>(in.K, ko + 64), q1 = four_elems<DT>(in.q_last, qo + 64);
-    float mc = 0.f;
-    if (heavy) mc = in.partials[((int64_t)row * geo.G + g) * in.n_chunks + (tok >> chunk_shift)].max;
+    float mc = 0.f, place = 0.f;
+    if (heavy) {
+      mc = in.partials[((int64_t)row * geo.G + g) * in.n_chunks + (tok >> chunk_shift)].max;
+      for (int u = sub; u < n_heavy; u += 16) place += hv.key[u] < key ? 1.f : 0.f;
+      place = group_sum<16>(place);
+    }
     const double l = group_sum_f64<16>(dot_f64<DT>(k1, q1, dot_f64<DT>(k0, q0, 0.0))) * inv;
     if (heavy) {
       const double M = (double)stat[g].M;
-      if (sub == 0) hv.change[t] = exp(l - M) - (double)exp_fast(hv.logit[t] - mc) * exp((double)mc - M);
+      if (sub == 0) {
+        hv.change[(int)place] = exp(l - M) - (double)exp_fast(hv.logit[t] - mc) * exp((double)mc - M);
+        hv.head[(int)place] = (unsigned char)g;
+      }
     } else if (sub == 0) {
       sh.term[b] = l;
     }

@@ -72,6 +72,25 @@ def test_many_heavy_terms_in_one_chunk(ref, dtype, flags, L):
     assert gu.check_kept(out["kept"], kept, s[:, :, 0], S, W, k) == 0
 
 
+@pytest.mark.parametrize("n_heavy", [1, 40, 250])
+def test_rows_with_heavy_terms_are_deterministic(n_heavy):
+    """The heavy terms are listed in whatever order the waves meet them; nothing may depend on it."""
+    P, Hq, Hkv, d, L, S, W, k = 4, 8, 4, 64, 8000, 4, 64, 900
+    q, K, V = rand_case(n_heavy, P, Hq, Hkv, d, L, BF16)
+    G = Hq // Hkv
+    Q = synth.to_f64(q, BF16).reshape(P, Hkv, G, d)
+    Kf = synth.to_f64(K, BF16)
+    u = (np.linalg.pinv(Q) @ np.full((P, Hkv, G, 1), 36.0 * d ** 0.5))[..., 0]
+    at = np.random.default_rng(n_heavy).permutation(L)[:n_heavy]
+    Kf[:, :, at] = u[:, :, None] + 0.01 * Kf[:, :, at]  # both heads' logits near 36
+    K = synth.round_to_dtype(Kf, BF16)
+    first = gu.gpu_select(BF16, q, K, V, S, W, k, want_scores=False, flags=DENSE)
+    for _ in range(6):
+        again = gu.gpu_select(BF16, q, K, V, S, W, k, want_scores=False, flags=DENSE)
+        for name in ("kept", "Kc", "Vc"):
+            np.testing.assert_array_equal(first[name], again[name])
+
+
 def offset_case(seed, P, Hq, Hkv, d, L, dtype, offset, scale=1.0):
     """q, K, V with logits of about N(offset, scale): every key has a common component, as trained models' keys do."""
     q, K, V = rand_case(seed, P, Hq, Hkv, d, L, dtype)
