@@ -539,13 +539,15 @@ __device__ __forceinline__ void refine_band(RegSelect& sh, int nb, const RowGeom
 constexpr int kHeavyList = 512;
 struct HeavyList {  // in the order in which the waves met them
   int n;
-  uint32_t key[kHeavyList];  // heavy_key
+  int tok[kHeavyList];
   float logit[kHeavyList];
-  // exact term - the one in the merged sum, and its head: by key, so that a sum does not depend on the waves' order
-  double change[kHeavyList];
+  double exact[kHeavyList];  // the logit in fp64
   unsigned char head[kHeavyList];
+  // What a head's terms change in its Z (exact term - the one in the merged sum) in units of 2^-46 of the largest term: a sum of integers does not
+  // depend on the waves' order.  (Sums in the order of head and token, from every term's place among the keys: 64 rows x 8192 x 16 heads,
+  // queries x 6, 500 terms a row, 97.5 us for the pass, so 87.)
+  unsigned long long change[64];
 };
-__device__ __forceinline__ uint32_t heavy_key(int head, int tok) { return (uint32_t)head << 26 | (uint32_t)tok; }  // 64 heads, 2^26 tokens
 
 // fp64 scores of the band's members into band_v after the listed terms have gone into the statistics (stat, in LDS).  Every 16 lanes
 // take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyList.  Begins (hv.n, band_tok) after a barrier, ends with one.
@@ -556,45 +558,48 @@ __device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, 
   const int D = geo.D, tid = threadIdx.x, sub = tid & 15, heads = g_hi - g_lo, n_heavy = hv.n, n = n_heavy + nb * heads;
   const int prob = row / geo.Hkv, c = row % geo.Hkv, chunk_shift = __builtin_ctz((unsigned)in.chunk);
   const double inv = 1.0 / sqrt((double)D);
+  if (n_heavy > 0) {  // workgroup-uniform
+    if (tid < 64) hv.change[tid] = 0ull;
+    __syncthreads();
+  }
+  constexpr int U = DT == DT_BF16 ? 2 : 1, kGroups = kTopkThreads / 16;
 #pragma unroll 1
-  for (int t = tid >> 4; t < n; t += kTopkThreads / 16) {
-    const bool heavy = t < n_heavy;
-    const int b = heavy ? 0 : t - n_heavy;
-    const uint32_t key = heavy ? hv.key[t] : heavy_key(g_lo + b % heads, sh.band_tok[b / heads]);
-    const int tok = (int)(key & 0x3FFFFFFu), g = (int)(key >> 26);
-    const int64_t ko = kv_offset(in.pm, in.pm.ks_page, in.ks_problem, in.ks_head, in.ks_token, prob, c, tok) + 4 * sub;
-    const int64_t qo = ((int64_t)prob * geo.Hq + c * geo.G + g) * D + 4 * sub;
-    const Four k0 = four_elems<DT>(in.K, ko), q0 = four_elems<DT>(in.q_last, qo);
-    Four k1 = {}, q1 = {};
-    if (D > 64) k1 = four_elems<DT>(in.K, ko + 64), q1 = four_elems<DT>(in.q_last, qo + 64);
-    float mc = 0.f, place = 0.f;
-    if (heavy) {
-      mc = in.partials[((int64_t)row * geo.G + g) * in.n_chunks + (tok >> chunk_shift)].max;
-      for (int u = sub; u < n_heavy; u += 16) place += hv.key[u] < key ? 1.f : 0.f;
-      place = group_sum<16>(place);
+  for (int t0 = tid >> 4; t0 < n; t0 += U * kGroups) {
+    Four k0[U], k1[U], q0[U], q1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = t0 + u * kGroups < n ? t0 + u * kGroups : t0;
+      const bool heavy = t < n_heavy;
+      const int b = heavy ? 0 : t - n_heavy;
+      const int tok = heavy ? hv.tok[t] : sh.band_tok[b / heads], g = heavy ? hv.head[t] : g_lo + b % heads;
+      const int64_t ko = kv_offset(in.pm, in.pm.ks_page, in.ks_problem, in.ks_head, in.ks_token, prob, c, tok) + 4 * sub;
+      const int64_t qo = ((int64_t)prob * geo.Hq + c * geo.G + g) * D + 4 * sub;
+      k0[u] = four_elems<DT>(in.K, ko);
+      q0[u] = four_elems<DT>(in.q_last, qo);
+      k1[u] = D > 64 ? four_elems<DT>(in.K, ko + 64) : Four{};
+      q1[u] = D > 64 ? four_elems<DT>(in.q_last, qo + 64) : Four{};
     }
-    const double l = group_sum_f64<16>(dot_f64<DT>(k1, q1, dot_f64<DT>(k0, q0, 0.0))) * inv;
-    if (heavy) {
-      const double M = (double)stat[g].M;
-      if (sub == 0) {
-        hv.change[(int)place] = exp(l - M) - (double)exp_fast(hv.logit[t] - mc) * exp((double)mc - M);
-        hv.head[(int)place] = (unsigned char)g;
-      }
-    } else if (sub == 0) {
-      sh.term[b] = l;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = t0 + u * kGroups;
+      const double l = group_sum_f64<16>(dot_f64<DT>(k1[u], q1[u], dot_f64<DT>(k0[u], q0[u], 0.0))) * inv;
+      if (sub == 0 && t < n) *(t < n_heavy ? &hv.exact[t] : &sh.term[t - n_heavy]) = l;
     }
   }
   __syncthreads();
-  if (n_heavy > 0) {  // workgroup-uniform; a wave per head
-    for (int g = g_lo + (tid >> 6); g < g_hi; g += kTopkWaves) {
-      double z = 0.0;
-      for (int t = tid & 63; t < n_heavy; t += 64) z += hv.head[t] == g ? hv.change[t] : 0.0;
-      z = group_sum_f64<64>(z);
-      if ((tid & 63) == 0) {
-        z += stat[g].Z;
-        stat[g].Z = z;
-        stat[g].invZ = (float)(1.0 / z);
-      }
+  if (n_heavy > 0) {  // a term per thread: sixteen lanes waiting for one's exponentials took longer than the dot products
+    for (int t = tid; t < n_heavy; t += kTopkThreads) {
+      const int g = hv.head[t];
+      const float mc = in.partials[((int64_t)row * geo.G + g) * in.n_chunks + (hv.tok[t] >> chunk_shift)].max;
+      const double M = (double)stat[g].M;
+      const double x = exp(hv.exact[t] - M) - (double)exp_fast(hv.logit[t] - mc) * exp((double)mc - M);
+      atomicAdd(&hv.change[g], (unsigned long long)__double2ll_rn(x * 0x1p46));
+    }
+    __syncthreads();
+    if (tid >= g_lo && tid < g_hi) {
+      const double z = stat[tid].Z + (double)(long long)hv.change[tid] * 0x1p-46;
+      stat[tid].Z = z;
+      stat[tid].invZ = (float)(1.0 / z);
     }
     __syncthreads();
   }

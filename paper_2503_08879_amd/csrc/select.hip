@@ -512,8 +512,9 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
                 if (l[e] >= thr && tok + e < L) {
                   const int t = atomicAdd(&heavy.n, 1);
                   if (t < kHeavyList) {
-                    heavy.key[t] = heavy_key(g0 + h, tok + e);
+                    heavy.tok[t] = tok + e;
                     heavy.logit[t] = l[e];
+                    heavy.head[t] = (unsigned char)(g0 + h);
                   }
                 }
             }
