@@ -427,6 +427,78 @@ __device__ __forceinline__ void exact_apply(const ExactSums& sh, int g_lo, int g
   __syncthreads();
 }
 
+// f(head, token, logit), logits in fours from a token on (-inf: past the row's end), for the heads g_lo .. g_hi - 1 with which(head), which has to be
+// the same for all threads.
+template <class Which, class F>
+__device__ __forceinline__ void each_four(const DenseRows& in, int row, int g_lo, int g_hi, Which which, F f) {
+  constexpr int U = 4;  // loads in flight
+  const int quads = (int)((in.geo.L + 3) >> 2);
+#pragma unroll 1
+  for (int g = g_lo, q = threadIdx.x; g < g_hi;) {
+    float4 x[U];
+    int gu[U], tok[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      while (g < g_hi && !which(g)) ++g;  // workgroup-uniform (q at its start)
+      gu[u] = g;
+      tok[u] = 4 * q;
+      x[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      if (g < g_hi && q < quads) x[u] = *reinterpret_cast<const float4*>(in.logits + logit_index(in.geo, in.n_chunks, in.chunk, row, g, tok[u]));
+      q += kTopkThreads;
+      if (q - (int)threadIdx.x >= quads) q = threadIdx.x, ++g;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (gu[u] >= g_hi) continue;  // workgroup-uniform
+      float l[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) l[e] = tok[u] + e < in.geo.L ? l[e] : -INFINITY;
+      f(gu[u], tok[u], l);
+    }
+  }
+}
+
+// Higher thresholds (thr) for the heads that have more heavy terms than are worth taking.  heavy_logit_threshold is the safe choice where a few terms
+// hold most of a head's mass.  Hundreds of terms over it are all small ones (logits that share an offset, where every tenth token reaches
+// it), and their errors average out: what is left out may be as much as keeps sqrt(sum w_i^2) over ALL terms left out within sqrt(theta), the same
+// bound on Z's error.  That sum comes from the numbers of logits in steps of 1/8 below the maximum, each taken at its step's middle (the last, open one
+// at its upper edge), so it does not depend on any order.  bins: 64 per head.  Called by every thread of a 1024-thread workgroup; begins and ends with a barrier.
+// A term costs one CU some 10 ns.  8 rows x 8192 tokens x 4 heads of N(60, 1) have 6600 terms each over the thresholds and 820 over the raised ones,
+// and Z's error goes from 0.5e-7 to 1e-7; whole passes 141 and 50.5 us (24.4 at N(0, 1)), 64 rows x 8192 x 16 heads 532 and 181 (77), 64 x 2048 x 4
+// 148 and 57 (25), fp32 8 x 8192 x 4 210 and 63 (29).
+template <class Which>
+__device__ __forceinline__ void raise_thresholds(const DenseRows& in, int* bins, int row, int g_lo, int g_hi, const RowStat* stat, float* thr, Which which) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  __syncthreads();
+  for (int b = tid; b < 64 * (g_hi - g_lo); b += kTopkThreads) bins[b] = 0;
+  __syncthreads();
+  each_four(in, row, g_lo, g_hi, which, [&](int g, int, const float (&l)[4]) {
+    const float M = stat[g].M;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float step = 8.f * (M - l[e]);
+      if (step < 63.f) atomicAdd(&bins[64 * (g - g_lo) + (int)fmaxf(step, 0.f)], 1);  // (the rest, often nearly all, would meet in one place)
+    }
+  });
+  __syncthreads();
+  for (int g = g_lo + (tid >> 6); g < g_hi; g += kTopkWaves) {  // a wave per head
+    if (!which(g)) continue;
+    const float M = stat[g].M, t = thr[g];
+    const int in_step = lane < 63 ? bins[64 * (g - g_lo) + lane] : 0;
+    const float above = group_sum<64>((float)in_step);
+    // sum w_i^2 of a step, then of those below it too, times Z^2
+    float left = lane < 63 ? (float)in_step * exp_fast(-0.25f * ((float)lane + 0.5f)) : ((float)in.geo.L - above) * exp_fast(-0.25f * 63.f);
+#pragma unroll
+    for (int o = 1; o < 64; o *= 2) {
+      const float more = __shfl_down(left, o);
+      left += lane + o < 64 ? more : 0.f;
+    }
+    const unsigned long long enough = __ballot(left <= (float)stat[g].Z * exp_fast(t - M));  // theta Z^2
+    if (enough && lane == 0) thr[g] = fmaxf(t, M - 0.125f * (float)(__ffsll(enough) - 1));
+  }
+  __syncthreads();
+}
+
 // ---- selection among scores held in registers ---------------------------------------------------
 // N scores per thread of a 1024-thread workgroup, -1: no element.  All functions are called by every thread.
 constexpr int kMaxBand = 1024;  // elements around the k-th that are ranked exactly among themselves
@@ -537,12 +609,13 @@ __device__ __forceinline__ void refine_band(RegSelect& sh, int nb, const RowGeom
 // other they took 8 of a row's 20 us (256 rows x 8192 tokens, k = 1788, four sink tokens); a whole pass 207 -> 204, over 8 rows 29.7 -> 27.6,
 // 128 rows x 8192 x 7 heads 128 -> 122.6.
 constexpr int kHeavyList = 512;
+constexpr int kHeavyMost = 4096;  // with raised thresholds, see raise_thresholds
 struct HeavyList {  // in the order in which the waves met them
   int n;
-  int tok[kHeavyList];
-  float logit[kHeavyList];
-  double exact[kHeavyList];  // the logit in fp64
-  unsigned char head[kHeavyList];
+  int tok[kHeavyMost];
+  float logit[kHeavyMost];
+  double exact[kHeavyMost];  // the logit in fp64
+  unsigned char head[kHeavyMost];
   // What a head's terms change in its Z (exact term - the one in the merged sum) in units of 2^-46 of the largest term: a sum of integers does not
   // depend on the waves' order.  (Sums in the order of head and token, from every term's place among the keys: 64 rows x 8192 x 16 heads,
   // queries x 6, 500 terms a row, 97.5 us for the pass, so 87.)
@@ -550,7 +623,7 @@ struct HeavyList {  // in the order in which the waves met them
 };
 
 // fp64 scores of the band's members into band_v after the listed terms have gone into the statistics (stat, in LDS).  Every 16 lanes
-// take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyList.  Begins (hv.n, band_tok) after a barrier, ends with one.
+// take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyMost.  Begins (hv.n, band_tok) after a barrier, ends with one.
 template <int DT>
 __device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, int nb, const DenseRows& in, int row, int g_lo, int g_hi, RowStat* stat) {
   typedef typename FourElems<DT>::type Four;

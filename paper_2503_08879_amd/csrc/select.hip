@@ -492,6 +492,13 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   load_heads(g_lo, x[0]);
   if (!SCORES) __syncthreads();
 
+  auto note = [&](int t, int g, int tok, float l) {
+    if (t < kHeavyMost) {
+      heavy.tok[t] = tok;
+      heavy.logit[t] = l;
+      heavy.head[t] = (unsigned char)g;
+    }
+  };
   float v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] = 0.f;
@@ -509,14 +516,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
               const float l[4] = {src[h][u].x, src[h][u].y, src[h][u].z, src[h][u].w};
 #pragma unroll
               for (int e = 0; e < 4; ++e)
-                if (l[e] >= thr && tok + e < L) {
-                  const int t = atomicAdd(&heavy.n, 1);
-                  if (t < kHeavyList) {
-                    heavy.tok[t] = tok + e;
-                    heavy.logit[t] = l[e];
-                    heavy.head[t] = (unsigned char)(g0 + h);
-                  }
-                }
+                if (l[e] >= thr && tok + e < L) note(atomicAdd(&heavy.n, 1), g0 + h, tok + e, l[e]);
             }
             v[4 * u] += exp_times(src[h][u].x - M, inv);
             v[4 * u + 1] += exp_times(src[h][u].y - M, inv);
@@ -573,12 +573,38 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   const int nb = sh.n_band, r = k - sh.n_above;
   bool general = nb > kMaxBand || r < 1 || r > nb;
   const bool whole = !SCORES && !general && nb == r;  // the whole band is selected: no need to rank it
-  const bool together = !SCORES && !general && nb * (g_hi - g_lo) <= kMaxBand && heavy.n <= kHeavyList;
+  bool together = !SCORES && !general && nb * (g_hi - g_lo) <= kMaxBand;
   if (whole) {
     for (int t = tid; t < nb; t += kTopkThreads) atomicOr(&bitmap[sh.band_tok[t] >> 5], 1u << (sh.band_tok[t] & 31));
     __syncthreads();
-  } else if (!SCORES && !together) {
-    exact();
+  } else if (!SCORES) {
+    if (heavy.n > kHeavyList) {
+      auto any = [&](int g) { return s_thr[g] <= s_stat[g].M; };
+      raise_thresholds(p.in, sh.hist[0], row, g_lo, g_hi, s_stat, s_thr, any);  // (the histograms are done with)
+      if (tid == 0) heavy.n = 0;
+      __syncthreads();
+      each_four(p.in, row, g_lo, g_hi, any, [&](int g, int tok, const float (&l)[4]) {
+        const float thr = s_thr[g];
+        unsigned long long in[4];
+        int cnt = 0, at = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          in[e] = __ballot(l[e] >= thr);
+          cnt += __popcll(in[e]);
+        }
+        if (cnt == 0) return;  // wave-uniform
+        if ((tid & 63) == 0) at = atomicAdd(&heavy.n, cnt);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (l[e] >= thr) note(at + lanes_below(in[e]), g, tok + e, l[e]);
+          at += __popcll(in[e]);
+        }
+      });
+      __syncthreads();
+      together &= heavy.n <= kHeavyMost;
+    }
+    if (!together) exact();
   }
   if (!whole && !general) {
     if (together)
