@@ -486,6 +486,7 @@ __device__ __forceinline__ void raise_thresholds(const DenseRows& in, int* bins,
     const float M = stat[g].M, t = thr[g];
     const int in_step = lane < 63 ? bins[64 * (g - g_lo) + lane] : 0;
     const float above = group_sum<64>((float)in_step);
+    if (group_sum<64>((float)lane <= 8.f * (M - t) ? (float)in_step : 0.f) <= 64.f) continue;  // few terms: all of them are taken
     // sum w_i^2 of a step, then of those below it too, times Z^2
     float left = lane < 63 ? (float)in_step * exp_fast(-0.25f * ((float)lane + 0.5f)) : ((float)in.geo.L - above) * exp_fast(-0.25f * 63.f);
 #pragma unroll
