@@ -24,7 +24,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr float kBand = 1.0f / 4096.0f;
 
 constexpr int64_t kFillScores = 256, kFill = 512;  // see score_chunk
-constexpr int64_t kShortFrom = 8192;  // see shortlist_plan
+constexpr int64_t kShortFrom = 8192, kExactFill = 224;  // see shortlist_plan
 
 // Sizes of the fast (pre-filtered) eviction path for one descriptor; ok = the path applies.
 struct FastPlan {
@@ -111,7 +111,7 @@ FastPlan fast_plan(const sagekv_select_desc* d) {
 // Rows of the one-sweep dense path whose selection is spread over many workgroups (shortlist_kernel); ok = that applies.
 struct ShortlistPlan {
   bool ok;
-  int n_parts, part_tokens, first_run, n_runs, rank, expect;
+  int n_parts, part_tokens, n_exact, first_run, n_runs, rank, expect;
   int64_t step;
 };
 
@@ -122,6 +122,11 @@ ShortlistPlan shortlist_plan(const sagekv_select_desc* d) {
   auto parts = [&](int tokens) { return (d->L + tokens - 1) / tokens; };
   s.part_tokens = lists * (parts(kShortTokens) + 1) <= 256 ? kShortTokens : 2 * kShortTokens;  // one workgroup per CU
   s.n_parts = (int)parts(s.part_tokens);
+  // The heads' heavy terms by as many workgroups as there are CUs for: with logits that share an offset one has to look through a whole row's (8 rows x
+  // 32K x 16 heads, N(60, 1), with raised thresholds: 136 us with one, 55 so).  Not on all 256: the others would start later (32 rows x 32K x 4
+  // heads, N(0, 1): 84 us with 224 workgroups in all, 87.5 with 256).
+  const int64_t heads = d->head_mode == SAGEKV_HEADS_PER_QUERY ? 1 : d->n_q_heads / d->n_kv_heads, free_cus = kExactFill / lists - s.n_parts;
+  s.n_exact = (int)(free_cus < 1 ? 1 : free_cus < heads ? free_cus : heads);
   if (d->k < 1 || E > kShortMax || d->L > (int64_t)kShortParts * kShortTokens) return s;
   // the sample: runs of 16 tokens, aligned (64 bytes of a head's logits), all of them candidates
   const int64_t r0 = ((int64_t)d->n_sink + 15) / 16, r1 = (d->L - d->n_recent) / 16;
@@ -795,6 +800,7 @@ sagekv_status select_impl(const sagekv_select_desc* d, const PageMap& pm, const 
       hp.marker = marker;
       hp.n_parts = l.list.n_parts;
       hp.part_tokens = l.list.part_tokens;
+      hp.n_exact = l.list.n_exact;
       hp.S = d->n_sink;
       hp.W = d->n_recent;
       hp.n_lists = l.n_lists;

@@ -233,6 +233,7 @@ struct ShortlistParams {
   int* flag;        // nullable [rows * n_lists]: 1 = the list went through its whole score row
   int* marker;      // set with flag: kFlagsPerList
   int n_parts, part_tokens, S, W, n_lists;
+  int n_exact;  // workgroups per list that take the heavy terms of its heads
   // the sample: n_runs runs of 16 tokens, the first at token 16 * first_run, `step` (48.16 fixed point) such runs apart
   int first_run, n_runs, rank;
   int64_t step;

@@ -712,8 +712,10 @@ __global__ __launch_bounds__(kTopkThreads) void row_stats_kernel(RowStatsParams 
 // ---- one-sweep dense path, a row spread over many workgroups -------------------------------------
 // First launch: a workgroup per list and kShortTokens tokens turns the logits into scores and hands on the few that can be
 // among the k best: those at or above a threshold that every workgroup of a list finds for itself, from the same sample of the list's own
-// scores.  One more workgroup per list takes the heavy terms into the normalisers (exact_changes), which only the fp64
-// scores of the band around the k-th need: 1e-6 of a score against the band's 2e-4.
+// scores.  More workgroups, one per list or several that share its heads, take the heavy terms into the normalisers (exact_changes), which only the fp64
+// scores of the band around the k-th need: 1e-6 of a score against the band's 2e-4.  Heads with heavy terms in nearly every chunk have hundreds of
+// them and raise their thresholds; whole passes over N(60, 1), us, with one workgroup per list that takes every term, and this: 8 rows x 32K x 4 heads
+// 95 and 44.7 (39.3 at N(0, 1)), x 16 heads 267 and 55 (53), 32 x 32K x 7 heads 183 and 103 (92), fp32 8 x 30000 x 4 131 and 58 (53).
 // Latency bound: 6.6 us for 8 rows x 32K tokens x 4 heads, of them 2.2 for partials and logits, 1.4 exponentials, 2.4 the threshold; the
 // second launch 5.8 (13.5 for 8 rows x 128K, k = 3580, of them 2.0 to collect the scores, 2.9 bracket, 1.7 band, 3.5 fp64 scores, 2.2
 // output).  Together they stand for statistics, combine and top-k in launches of their own, 4.5 + 7 + 13.5, and for a whole pass over those rows
@@ -730,26 +732,38 @@ __global__ __launch_bounds__(kTopkThreads) void shortlist_kernel(ShortlistParams
   __shared__ float s_thr[64];
   __shared__ int n_out;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int list = blockIdx.y, row = list / p.n_lists, gl = list % p.n_lists;
+  const int list = blockIdx.y, part = blockIdx.x, row = list / p.n_lists, gl = list % p.n_lists;
   const RowGeom& geo = p.in.geo;
   const int G = geo.G, L = (int)geo.L;
   const int g_lo = p.n_lists > 1 ? gl : 0, g_hi = p.n_lists > 1 ? gl + 1 : G;
   const ChunkPartial* partials = p.in.partials + (int64_t)row * G * p.in.n_chunks;
-  if (blockIdx.x == 0) {
-    const float max0 = exact_maximum(p.in, row, g_lo, g_hi, 0);
-    for (int g = g_lo + wave; g < g_hi; g += kTopkWaves) {
-      const RowStat st = merge_partials_wave(partials + (int64_t)g * p.in.n_chunks, p.in.n_chunks);
+  if (part >= p.n_parts) {
+    const int per = (g_hi - g_lo + p.n_exact - 1) / p.n_exact, lo = g_lo + per * (part - p.n_parts), hi = lo + per < g_hi ? lo + per : g_hi;
+    if (lo >= hi) return;
+    __shared__ bool s_many[64];
+    const float max0 = exact_maximum(p.in, row, lo, hi, 0);
+    for (int g = lo + wave; g < hi; g += kTopkWaves) {
+      const ChunkPartial* pr = partials + (int64_t)g * p.in.n_chunks;
+      const RowStat st = merge_partials_wave(pr, p.in.n_chunks);
+      const float thr = heavy_logit_threshold(st.M, (float)st.Z);
+      int n = 0;  // chunks that hold heavy terms
+      if (thr <= st.M)  // wave-uniform, rare
+        for (int i = 0; i < p.in.n_chunks; i += 64) n += __popcll(__ballot(i + lane < p.in.n_chunks && pr[i + lane].max >= thr));
       if (lane == 0) {
         s_stat[g] = st;
-        s_thr[g] = heavy_logit_threshold(st.M, (float)st.Z);
+        s_thr[g] = thr;
+        s_many[g] = 8 * n > 7 * p.in.n_chunks;
       }
     }
-    if (exact_changes<DT>(p.in, sh_u.exact, row, g_lo, g_hi, s_stat, s_thr, max0)) exact_apply(sh_u.exact, g_lo, g_hi, s_stat);
-    if (tid >= g_lo && tid < g_hi) p.stats[(int64_t)row * G + tid] = s_stat[tid];
+    __syncthreads();
+    bool many = false;
+    for (int g = lo; g < hi; ++g) many |= s_many[g];
+    if (many) raise_thresholds(p.in, reinterpret_cast<int*>(&sh_u), row, lo, hi, s_stat, s_thr, [&](int g) { return s_many[g]; });
+    if (exact_changes<DT>(p.in, sh_u.exact, row, lo, hi, s_stat, s_thr, max0)) exact_apply(sh_u.exact, lo, hi, s_stat);
+    if (tid >= lo && tid < hi) p.stats[(int64_t)row * G + tid] = s_stat[tid];
     return;
   }
   constexpr int kPart = 4 * NQ * kTopkThreads;
-  const int part = (int)blockIdx.x - 1;
   const int tok0 = part * kPart + 4 * tid;  // this thread's first four tokens of NQ times four,
   const int run0 = 16 * (p.first_run + (int)(((tid >> 2) * p.step) >> 16)) + 4 * (tid & 3);  // and its four of the sample
   const bool sampled = tid < 4 * p.n_runs;
@@ -1042,7 +1056,7 @@ static hipError_t launch_shortlist_select(const ShortlistParams& p, const TopkPa
 
 template <int DT>
 static hipError_t launch_shortlist_t(const ShortlistParams& p, const TopkParams& tp, unsigned lists, hipStream_t s) {
-  const dim3 grid((unsigned)p.n_parts + 1u, lists);
+  const dim3 grid((unsigned)(p.n_parts + p.n_exact), lists);
   const int heads = p.n_lists > 1 ? 1 : p.in.geo.G;
 #define SAGEKV_LAUNCH(HB)                                                                              \
   if (p.part_tokens == kShortTokens)                                                                   \
@@ -1068,7 +1082,7 @@ static hipError_t launch_shortlist_t(const ShortlistParams& p, const TopkParams&
 
 hipError_t launch_shortlist(const ShortlistParams& p, const TopkParams& tp0, hipStream_t s) {
   const RowGeom& geo = p.in.geo;
-  if (geo.G > 64 || p.n_parts > kShortParts || (p.part_tokens != kShortTokens && p.part_tokens != 2 * kShortTokens) || geo.L - tp0.S - tp0.W > kShortMax) return hipErrorInvalidValue;
+  if (geo.G > 64 || p.n_parts > kShortParts || p.n_exact < 1 || (p.part_tokens != kShortTokens && p.part_tokens != 2 * kShortTokens) || geo.L - tp0.S - tp0.W > kShortMax) return hipErrorInvalidValue;
   TopkParams tp = tp0;
   tp.ghist = nullptr;
   tp.bitmap_bytes = (int)bitmap_bytes(tp);

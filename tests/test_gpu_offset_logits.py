@@ -1,6 +1,6 @@
 """Logits that share an offset, as keys with a common component have them: thousands of a row's softmax terms are heavy, each of them a little.
-Rows that one workgroup selects from list them again with a higher threshold (raise_thresholds); sizes on both sides of the lists, rows whose terms
-no threshold can thin out, and what such calls may cost beside logits around 0."""
+Rows that one workgroup selects from list them again with a higher threshold (raise_thresholds), longer ones have them taken by workgroups of their own;
+sizes on both sides of the lists, rows whose terms no threshold can thin out, and what such calls may cost beside logits around 0."""
 import numpy as np
 import pytest
 
@@ -24,6 +24,11 @@ DENSE = 1
     (BF16, 1, 4, 1, 64, 24570, 0),
     (F32, 1, 8, 2, 128, 6001, 0),
     (F32, 1, 9, 1, 64, 3000, 1),
+    (BF16, 1, 8, 2, 128, 8193, 0),    # rows spread over several workgroups: one more workgroup per head
+    (BF16, 1, 40, 2, 64, 24577, 0),   # one per head, 20 of them
+    (BF16, 7, 28, 4, 64, 30001, 0),   # one for several heads
+    (BF16, 1, 7, 1, 128, 20000, 1),
+    (F32, 1, 6, 2, 128, 26000, 0),
 ])
 @pytest.mark.parametrize("offset,scale", [(60.0, 1.0), (-200.0, 1.0), (40.0, 3.0)])
 def test_offset_rows(ref, dtype, P, Hq, Hkv, d, L, head_mode, offset, scale):
@@ -78,6 +83,9 @@ def whole_pass(P, Hq, Hkv, d, L, k, offset):
     (1, 32, 8, 128, 8192, 700, 3.0),   # N(0, 1) and N(60, 1): 24.4 and 50.5 us, 2.1 times (with every heavy term taken, 5.8 times)
     (8, 128, 8, 128, 8192, 700, 3.3),  # 77 and 181, 2.4 (6.9)
     (8, 32, 8, 128, 2048, 188, 3.2),   # 24.9 and 56.6, 2.3 (5.9)
+    (1, 32, 8, 128, 32768, 1788, 1.6),   # 39.3 and 44.7, 1.14 (one workgroup per list for every term: 2.4)
+    (1, 128, 8, 128, 32768, 1788, 1.5),  # 53 and 55, 1.03 (5.0)
+    (8, 28, 4, 128, 32768, 1788, 1.5),   # 92 and 103, 1.12 (2.0)
 ])
 def test_an_offset_costs_little(P, Hq, Hkv, d, L, k, most):
     times = [whole_pass(P, Hq, Hkv, d, L, k, offset) for offset in (0.0, 60.0)]
