@@ -1,5 +1,6 @@
 """The filtering pass stores a wave's candidates in runs: none, one run, many (whole blocks of 64 tokens pass), and clusters
-that use a chunk's own slots up and go on in the row's pool.  Groups padded to 4, 8 and 16 heads; chunks of 256 to 1024 tokens."""
+that use a chunk's own slots up and go on in the row's pool.  Groups padded to 4, 8 and 16 heads; chunks of 256 to 1024 tokens.
+(As they are, these calls take the one-sweep path; test_gpu_filter_route has them on the pre-filtered one.)"""
 import numpy as np
 import pytest
 

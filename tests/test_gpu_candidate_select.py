@@ -1,5 +1,6 @@
 """The pre-filtered path's candidate selection: rows whose candidates fit the registers of the workgroup that owns them (4,
-12 or 24 per thread, by what a list is expected to have), and peaked rows that have more and go through memory."""
+12 or 24 per thread, by what a list is expected to have), and peaked rows that have more and go through memory.  As they are, most of these calls are
+small enough for the one-sweep path; test_gpu_filter_route has them on the pre-filtered one."""
 import numpy as np
 import pytest
 
@@ -29,7 +30,7 @@ def test_candidate_counts_around_the_register_sizes(ref, Hq, Hkv, d, L, ks, head
     for k in ks:
         Kc, _, kept, s = ref.select(BF16, head_mode, q, K, V, S, W, k, want_scores=True)
         out = gu.gpu_select(BF16, q, K, V, S, W, k, want_scores=False, head_mode=head_mode)
-        assert out["redone"] >= 0  # the pre-filtered path
+        assert out["redone"] >= 0  # not a dense call
         if scale == 1.0:
             assert out["redone"] == 0
         exempt = 0

@@ -80,7 +80,7 @@ def test_decode_steps_replayed_from_a_graph():
 
 
 def test_select_replayed_from_a_graph(ref):
-    """The eviction pass (pre-filtered path and its gated dense kernels) as one graph."""
+    """The eviction pass as one graph (with the pre-filtered path and its gated dense kernels: test_gpu_filter_route)."""
     import torch
 
     import paper_2503_08879_amd as sk

@@ -1,7 +1,8 @@
 """Softmax terms that the filtering and partials passes take with an fp64 exponent: planted at the edges of tiles, blocks and
 chunks, in the ragged last block, one head at a time.  A term that is missed, taken twice or given to another head would put that
 head's scores off by the term's share of the mass (several per cent).  The partials pass's scores are held to 1e-5.  What the filtering pass
-made of them shows in its kept sets, summed over heads of unlike normalisers, and in that no row had to be redone."""
+made of them shows in its kept sets, summed over heads of unlike normalisers, and in that no row had to be redone.  (As they are, the calls without scores
+take the one-sweep path; test_gpu_filter_route has them on the pre-filtered one.)"""
 import numpy as np
 import pytest
 
@@ -33,7 +34,7 @@ def test_planted_heavy_terms(ref, G, d, L):
         lists = G if head_mode else 1
         Kc, _, kept, s = ref.select(BF16, head_mode, q, K, V, S, W, k, want_scores=True)
         out = gu.gpu_select(BF16, q, K, V, S, W, k, want_scores=False, head_mode=head_mode)
-        assert out["redone"] == 0  # the filtering pass's own result: no row went to the partials pass
+        assert out["redone"] == 0  # the path's own result: no row went another way
         for li in range(lists):
             cut = lambda a: np.concatenate([a[..., :S], a[..., S + li * k:S + (li + 1) * k], a[..., S + lists * k:]], axis=-1)
             gu.check_kept(cut(out["kept"]), cut(kept), s.reshape(1, Hkv, lists, L)[:, :, li], S, W, k)

@@ -1,5 +1,6 @@
 """More rows (and lists, and chunks) to redo than the gated launches have workgroups: rows of equal keys, whose scores tie and whose
-selection is the first k candidates, alone or between rows that the pre-filter certifies."""
+selection is the first k candidates, alone or between rows that the pre-filter certifies.  (As they are, these calls take the one-sweep path; test_gpu_filter_route has
+them on the pre-filtered one.)"""
 import pytest
 
 pytestmark = pytest.mark.gpu

@@ -81,7 +81,7 @@ def paged_case(ref, dtype, P, Hq, Hkv, d, L, S, W, k, page_size, token_major=Fal
     [(16, False), (16, True), (64, False), (256, True), (1024, False), (4096, False)],
 )
 def test_paged_prefiltered_bf16(ref, page_size, token_major):
-    """G = 4, ragged L: pre-filtered path, pages smaller than, equal to and larger than a score chunk."""
+    """G = 4, ragged L: pages smaller than, equal to and larger than a score chunk (on the pre-filtered path: test_gpu_filter_route)."""
     redone = paged_case(ref, BF16, 2, 8, 2, 128, 40000 + 37, 4, 128, 1000, page_size, token_major, seed=page_size)
     assert redone == 0
 
@@ -150,6 +150,6 @@ def test_paged_arguments_are_checked():
 @pytest.mark.parametrize("page,want_scores,flags", [(16, False, 0), (64, True, 0), (256, False, 1)])
 def test_paged_select_with_peaked_attention(ref, page, want_scores, flags):
     """Queries scaled by 9 over a paged cache: the softmax terms that need an fp64 exponent are recomputed
-    from the staged pages (pre-filtered, two-sweep and one-sweep routes)."""
+    from the staged pages (two-sweep and one-sweep routes; pre-filtered: test_gpu_filter_route)."""
     paged_case(ref, BF16, 1, 4, 2, 128, 70001, 4, 65, 9000, page, want_scores=want_scores, flags=flags, seed=41,
                q_scale=9.0)

@@ -1,6 +1,7 @@
 """The sample of the pre-filtered path: runs that straddle pages and the row's ends, heads padded to 4, 8 and 16, rows shorter than
 the sample itself, a last workgroup with fewer blocks than waves.  A wrong logit there does not change a kept set but sends its row
-to the dense path, so the count of redone rows is checked too."""
+to the dense path, so the count of redone rows is checked too.  (As they are, most of these calls take the one-sweep path; test_gpu_filter_route has them on the
+pre-filtered one.)"""
 import pytest
 
 import synth

@@ -1,5 +1,6 @@
-"""Calls large enough for the score pass's larger chunks: 1024 tokens per workgroup (bf16) and 512 (fp32), which take 256
-workgroups on the dense path and 512 on the pre-filtered one; with rows of several chunks and ragged ends."""
+"""Calls large enough for the score pass's larger chunks: 1024 tokens per workgroup (bf16) and 512 (fp32), which take 512
+workgroups (256 in a dense call that returns the scores); with rows of several chunks and ragged ends.  (test_gpu_filter_route has the filtered
+ones on the pre-filtered path whatever their size.)"""
 import pytest
 
 import synth
