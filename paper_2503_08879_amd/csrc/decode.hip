@@ -560,7 +560,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeParams p, in
       if (GPAD > 4) __builtin_amdgcn_sched_barrier(0);  // keep the unrolled steps apart: registers
       const int t_local = i * TPL + tq;
       float vf[EPL];
-      unpack16<DT_BF16>(vv[i], vf);
+      unpack16(vv[i], vf);
       if (more) {  // the register is free: V of the next block, as early as possible
         const char* a = src.at(Vr, vn, it + 1, i, tq) + cl * 16;
         vv[i] = STREAM ? ld16_stream(a) : ld16(a);

@@ -1,5 +1,5 @@
 // Device helpers for the gfx950 kernels: wave64 DPP reductions, typed 16-byte
-// loads, bf16 dot products, block scans.
+// loads, block scans.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -16,51 +16,19 @@ struct Elem;
 template <>
 struct Elem<DT_BF16> {
   static constexpr int bytes = 2;
-  static constexpr int per_lane = 8;  // elements in one 16-byte load
 };
 template <>
 struct Elem<DT_F32> {
   static constexpr int bytes = 4;
-  static constexpr int per_lane = 4;
 };
-
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
-// 16 bytes of K (or V) against 16 bytes of q, accumulated in fp32.
-template <int DT>
-__device__ __forceinline__ float dot16(const uint4& a, const uint4& b, float acc);
-
-template <>
-__device__ __forceinline__ float dot16<DT_BF16>(const uint4& a, const uint4& b, float acc) {
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a.x), __builtin_bit_cast(bf16x2_t, b.x), acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a.y), __builtin_bit_cast(bf16x2_t, b.y), acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a.z), __builtin_bit_cast(bf16x2_t, b.z), acc, false);
-  acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a.w), __builtin_bit_cast(bf16x2_t, b.w), acc, false);
-  return acc;
-}
-template <>
-__device__ __forceinline__ float dot16<DT_F32>(const uint4& a, const uint4& b, float acc) {
-  acc = fmaf(__uint_as_float(a.x), __uint_as_float(b.x), acc);
-  acc = fmaf(__uint_as_float(a.y), __uint_as_float(b.y), acc);
-  acc = fmaf(__uint_as_float(a.z), __uint_as_float(b.z), acc);
-  acc = fmaf(__uint_as_float(a.w), __uint_as_float(b.w), acc);
-  return acc;
-}
-
-// The 16 bytes of one lane as fp32 values (8 for bf16, 4 for fp32).
-template <int DT>
-__device__ __forceinline__ void unpack16(const uint4& a, float* f);
-template <>
-__device__ __forceinline__ void unpack16<DT_BF16>(const uint4& a, float* f) {
+// The 16 bytes of one lane, eight bf16 values, as fp32 values.
+__device__ __forceinline__ void unpack16(const uint4& a, float* f) {
   f[0] = bf16_lo(a.x); f[1] = bf16_hi(a.x); f[2] = bf16_lo(a.y); f[3] = bf16_hi(a.y);
   f[4] = bf16_lo(a.z); f[5] = bf16_hi(a.z); f[6] = bf16_lo(a.w); f[7] = bf16_hi(a.w);
-}
-template <>
-__device__ __forceinline__ void unpack16<DT_F32>(const uint4& a, float* f) {
-  f[0] = __uint_as_float(a.x); f[1] = __uint_as_float(a.y); f[2] = __uint_as_float(a.z); f[3] = __uint_as_float(a.w);
 }
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
@@ -87,13 +55,15 @@ __device__ __forceinline__ float dpp_f32(float v) {
 // Sum over aligned groups of LANES consecutive lanes; every lane of the group gets the total.
 template <int LANES>
 __device__ __forceinline__ float group_sum(float v) {
-  static_assert(LANES == 1 || LANES == 2 || LANES == 4 || LANES == 8 || LANES == 16 || LANES == 32 || LANES == 64, "");
-  if (LANES >= 2) v += dpp_f32<0xB1>(v);   // quad_perm [1,0,3,2]
-  if (LANES >= 4) v += dpp_f32<0x4E>(v);   // quad_perm [2,3,0,1]
-  if (LANES >= 8) v += dpp_f32<0x141>(v);  // row_half_mirror
-  if (LANES >= 16) v += dpp_f32<0x140>(v); // row_mirror
-  if (LANES >= 32) v += __shfl_xor(v, 16);
-  if (LANES >= 64) v += __shfl_xor(v, 32);
+  static_assert(LANES == 16 || LANES == 64, "");
+  v += dpp_f32<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_f32<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_f32<0x141>(v);  // row_half_mirror
+  v += dpp_f32<0x140>(v);  // row_mirror
+  if (LANES >= 64) {
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+  }
   return v;
 }
 
@@ -117,10 +87,6 @@ __device__ __forceinline__ double swap16_f64(double v) {
   const bool odd = (threadIdx.x & 16) != 0;
   const uint32_t l = odd ? lo[0] : lo[1], h = odd ? hi[0] : hi[1];
   return __builtin_bit_cast(double, ((uint64_t)h << 32) | l);
-}
-__device__ __forceinline__ float swap16(float v) {  // v of lane ^ 16
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float((threadIdx.x & 16) ? r[0] : r[1]);
 }
 // v of this lane + v of lane ^ 16, lane ^ 32
 __device__ __forceinline__ float swap16_sum(float v) {
@@ -177,12 +143,6 @@ __device__ __forceinline__ float group16_max(float v) {
   v = fmaxf(v, dpp_f32<0x4E>(v));   // quad_perm [2,3,0,1]
   v = fmaxf(v, dpp_f32<0x141>(v));  // row_half_mirror
   v = fmaxf(v, dpp_f32<0x140>(v));  // row_mirror
-  return v;
-}
-
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
   return v;
 }
 
