@@ -1073,10 +1073,10 @@ static hipError_t launch_shortlist_t(const ShortlistParams& p, const TopkParams&
 #undef SAGEKV_LAUNCH
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // 6 beside 8: 8 rows x 128K, k = 1788 79.4 -> 78.8 us, 8 x 32K, k = 2600 42.1 -> 41.7; 12 beside 16 (8 x 128K, k = 3580; 4 x 128K x 7) was even
   return p.expect <= 4 * kTopkThreads    ? launch_shortlist_select<DT, 4>(p, tp, lists, s)
          : p.expect <= 6 * kTopkThreads  ? launch_shortlist_select<DT, 6>(p, tp, lists, s)
          : p.expect <= 8 * kTopkThreads  ? launch_shortlist_select<DT, 8>(p, tp, lists, s)
-         : p.expect <= 12 * kTopkThreads ? launch_shortlist_select<DT, 12>(p, tp, lists, s)
                                          : launch_shortlist_select<DT, 16>(p, tp, lists, s);
 }
 
