@@ -338,15 +338,17 @@ __device__ __forceinline__ void exact_terms_wave(const DenseRows& in, ExactSums&
 
 // What the heavy terms change in Z of heads g_lo .. g_hi of a row (stat, thr: their merged statistics and
 // heavy_logit_threshold of them, in LDS; max: exact_maximum of the first batch, asked for early).  Called by every thread of a
-// 1024-thread workgroup; begins with a barrier.  True (workgroup-uniform): exact_apply has to follow.
-template <int DT>
+// 1024-thread workgroup; begins with a barrier.  before(): called by all of them where there are heavy terms.  True (workgroup-uniform):
+// exact_apply has to follow.
+template <int DT, class Before>
 __device__ __forceinline__ bool exact_changes(const DenseRows& in, ExactSums& sh, int row, int g_lo, int g_hi, const RowStat* stat,
-                                              const float* thr, float max) {
+                                              const float* thr, float max, Before before) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __syncthreads();
   bool any = false;
   for (int g = g_lo; g < g_hi; ++g) any |= thr[g] <= stat[g].M;
   if (!any) return false;  // no term of any head is heavy
+  before();
   sh.change[wave][lane] = 0.0;
   const int n_seg = in.n_chunks * (in.chunk / kExactTokens);
   int taken = 0, listed = 0;  // wave-uniform

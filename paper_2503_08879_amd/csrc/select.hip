@@ -486,7 +486,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   // The heavy terms change a normaliser by a few 1e-6 at most: scores that are written out have them in, the selection
   // only needs them where it comes to fp64 scores.
   auto exact = [&]() {
-    if (exact_changes<DT>(p.in, sh_exact, row, g_lo, g_hi, s_stat, s_thr, max0)) exact_apply(sh_exact, g_lo, g_hi, s_stat);
+    if (exact_changes<DT>(p.in, sh_exact, row, g_lo, g_hi, s_stat, s_thr, max0, [] {})) exact_apply(sh_exact, g_lo, g_hi, s_stat);
   };
   if (SCORES) exact();
   load_heads(g_lo, x[0]);
@@ -705,7 +705,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_stats_kernel(RowStatsParams 
       s_thr[g] = heavy_logit_threshold(st.M, (float)st.Z);
     }
   }
-  if (exact_changes<DT>(p.in, sh, row, 0, G, s_stat, s_thr, max0)) exact_apply(sh, 0, G, s_stat);
+  if (exact_changes<DT>(p.in, sh, row, 0, G, s_stat, s_thr, max0, [] {})) exact_apply(sh, 0, G, s_stat);
   if (tid < G) p.stats[(int64_t)row * G + tid] = s_stat[tid];
 }
 
@@ -732,13 +732,13 @@ __global__ __launch_bounds__(kTopkThreads) void shortlist_kernel(ShortlistParams
   __shared__ float s_thr[64];
   __shared__ int n_out;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int list = blockIdx.y, part = blockIdx.x, row = list / p.n_lists, gl = list % p.n_lists;
+  const int list = blockIdx.y, part = (int)blockIdx.x - p.n_exact, row = list / p.n_lists, gl = list % p.n_lists;
   const RowGeom& geo = p.in.geo;
   const int G = geo.G, L = (int)geo.L;
   const int g_lo = p.n_lists > 1 ? gl : 0, g_hi = p.n_lists > 1 ? gl + 1 : G;
   const ChunkPartial* partials = p.in.partials + (int64_t)row * G * p.in.n_chunks;
-  if (part >= p.n_parts) {
-    const int per = (g_hi - g_lo + p.n_exact - 1) / p.n_exact, lo = g_lo + per * (part - p.n_parts), hi = lo + per < g_hi ? lo + per : g_hi;
+  if (part < 0) {
+    const int per = (g_hi - g_lo + p.n_exact - 1) / p.n_exact, lo = g_lo + per * (int)blockIdx.x, hi = lo + per < g_hi ? lo + per : g_hi;
     if (lo >= hi) return;
     __shared__ bool s_many[64];
     const float max0 = exact_maximum(p.in, row, lo, hi, 0);
@@ -755,11 +755,12 @@ __global__ __launch_bounds__(kTopkThreads) void shortlist_kernel(ShortlistParams
         s_many[g] = 8 * n > 7 * p.in.n_chunks;
       }
     }
-    __syncthreads();
-    bool many = false;
-    for (int g = lo; g < hi; ++g) many |= s_many[g];
-    if (many) raise_thresholds(p.in, reinterpret_cast<int*>(&sh_u), row, lo, hi, s_stat, s_thr, [&](int g) { return s_many[g]; });
-    if (exact_changes<DT>(p.in, sh_u.exact, row, lo, hi, s_stat, s_thr, max0)) exact_apply(sh_u.exact, lo, hi, s_stat);
+    auto raise = [&] {
+      bool many = false;
+      for (int g = lo; g < hi; ++g) many |= s_many[g];
+      if (many) raise_thresholds(p.in, reinterpret_cast<int*>(&sh_u), row, lo, hi, s_stat, s_thr, [&](int g) { return s_many[g]; });
+    };
+    if (exact_changes<DT>(p.in, sh_u.exact, row, lo, hi, s_stat, s_thr, max0, raise)) exact_apply(sh_u.exact, lo, hi, s_stat);
     if (tid >= lo && tid < hi) p.stats[(int64_t)row * G + tid] = s_stat[tid];
     return;
   }
