@@ -328,16 +328,33 @@ struct DecodeLayout {
 
 // Splits per row.  With about one row per CU or more, a single 8-wave workgroup per row fills
 // the chip and needs no merge launch; otherwise enough workgroups to fill 256 CUs several times
-// over, at least 128 tokens each.  Short rows are not worth the merge launch:
+// over (fp32: see slices_f32), at least 128 tokens each.  Short rows are not worth the merge launch:
 // bf16 up to 256 tokens, a single pass (8 rows x 4 heads x 256 tokens 9.2 us split, 7.7 whole; 4 rows x 7 heads 8.7 and 7.7; before
 // the slice kernel had its present form 10.3 and 8.4, 9.6 and 8.2, and at
 // 512 tokens 10.5 and 11.0, 10.45 and 10.5), fp32 up to 384 tokens of head_dim 64, 192 of 128 (2 rows x 2 heads x 300 and 400 tokens 9.5 and 9.3 us
 // split, 7.2 and 8.1 whole, 512 even; 4 rows x 4 heads x 512 10.0 and 11.0; head_dim 128, 160 tokens: 8 rows x 4 heads 10.4 and 8.0, 4 x 7
 // 12.2 and 10.1, 256 tokens 10.5 and 9.7, 12.2 and 12.5).
-int splits_for(int rows, int len, int dtype, int head_dim) {
+constexpr int kFillDecode = 2048;
+
+// fp32: a slice of 128 tokens is one block for each of its workgroup's waves, with nothing in flight while they start and merge.  So one
+// workgroup per CU of 8 waves (128 dims), two of 4 (64 dims), of as many tokens as that takes; where many rows do not divide them, the slices whose
+// rounds of workgroups, each as long as its blocks and one and a half more, are the shortest in all.  us, slices as for bf16 and so: 64 rows x 2048 tokens of 128 dims
+// 31.8 and 25.4 (1 head), 34 and 26 (2), 41.8 and 31 (7), 16 x 4096 18.8 and 16 (1), 150 x 4000 143.6 and 123.7 (7; with 2 slices 161), of 64 dims
+// 64 x 2048 x 7 heads 24.6 and 20.7, 16 x 8000 x 1 19 and 16, 100 x 3000 x 5 80 and 42.
+int slices_f32(int rows, int len, int head_dim) {
+  const int fill = head_dim == 128 ? 256 : 512, first = fill / rows > 1 ? fill / rows : 1;
+  int best = first, least = 0x7FFFFFFF;
+  if (20 * rows <= 3 * fill) return first;  // they leave 15 % of the workgroups idle at most
+  for (int n = first; n < 4 * first + 4; ++n) {
+    const int blocks = (len + 128 * n - 1) / (128 * n), cost = (rows * n + fill - 1) / fill * (2 * blocks + 3);
+    if (cost < least) best = n, least = cost;
+  }
+  return best;
+}
+
+int splits_for(int rows, int len, int dtype, int head_dim, int want) {
   if (rows >= kWholeRows) return 1;
   if (dtype == SAGEKV_BF16 ? len <= 256 : (int64_t)len * head_dim <= 384 * 64) return 1;
-  int want = (2048 + rows - 1) / rows;
   int most = (len + 127) / 128;
   int n = want < most ? want : most;
   return n < 1 ? 1 : n;
@@ -347,7 +364,8 @@ DecodeLayout decode_layout(const sagekv_decode_desc* d) {
   DecodeLayout l;
   l.rows = d->n_problems * d->n_kv_heads;
   l.G = d->n_q_heads / d->n_kv_heads;
-  l.max_splits = splits_for(l.rows, d->compact_capacity, d->dtype, d->head_dim);
+  // (room for kFillDecode workgroups, whatever a call uses: scratch sizes are part of the interface)
+  l.max_splits = splits_for(l.rows, d->compact_capacity, d->dtype, d->head_dim, (kFillDecode + l.rows - 1) / l.rows);
   size_t off = 0;
   l.part_ml = off;
   off = align_up(off + (size_t)l.rows * l.max_splits * l.G * sizeof(float2));
@@ -473,7 +491,9 @@ sagekv_status run_decode(const sagekv_decode_desc* d, const void* q, const void*
   p.cap = d->compact_capacity;
   // with the count on the device the length of a growing row is not known here: as many slices as
   // the full capacity would take (a fixed-size window has its one length either way)
-  p.n_splits = splits_for(l.rows, ring && d->grow_recent ? d->compact_capacity : len, d->dtype, d->head_dim);
+  const int longest = ring && d->grow_recent ? d->compact_capacity : len;
+  p.n_splits = splits_for(l.rows, longest, d->dtype, d->head_dim,
+                          d->dtype == SAGEKV_BF16 ? (kFillDecode + l.rows - 1) / l.rows : slices_f32(l.rows, longest, d->head_dim));
   if (p.n_splits > l.max_splits) p.n_splits = l.max_splits;
   p.tokens_per_split = split_tokens(len, p.n_splits);
   p.ring = ring;

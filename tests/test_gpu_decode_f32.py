@@ -75,7 +75,8 @@ def test_step(ref, G, d, n, slot, layout):
     (192, 1, 64, 600, 599), (192, 4, 64, 600, 555), (192, 7, 64, 600, 300), (192, 1, 128, 600, 470), (192, 4, 128, 600, 599), (192, 7, 128, 600, 580),
     (194, 1, 128, 2049, 2048), (194, 4, 128, 2049, 1500), (194, 7, 128, 2049, 2047), (194, 2, 64, 2049, 1030), (194, 4, 64, 2049, 1800), (194, 5, 64, 2049, 2048),
     # slices of several blocks per wave
-    (100, 4, 64, 9000, 8999), (100, 7, 128, 9000, 4321), (64, 2, 128, 9000, 300),
+    (100, 4, 64, 9000, 8999), (100, 7, 128, 9000, 4321), (64, 2, 128, 9000, 300), (150, 1, 128, 4001, 4000), (150, 5, 64, 4001, 1333), (190, 4, 128, 1999, 500),
+    (6, 7, 128, 20011, 20010),
 ])
 def test_rows_of_many_blocks(rows, G, d, n, slot):
     many_blocks(rows, G, d, n, slot, paged=False)
