@@ -41,8 +41,11 @@ constexpr int kGatedRowBlocks = 16;  // y-blocks of a gated score / combine laun
 // ones 113 us for the pass over 64 x 16K, 100 so.)
 //
 // The softmax partial of the chunk is taken after the last block, from the logits in registers.
+//
+// 64 dims and seven heads would take 172 registers, two workgroups a CU: held to the 168 of three, without a spill, 64 rows x 40000 218 -> 196 us.  (Eight heads
+// take 190: held to 168 they spill 32, 224 -> 228.)
 template <int D, int GB, int BPW>
-__global__ __launch_bounds__(kScoreThreads, 2) void score_f32_kernel(ScoreParams p) {
+__global__ __launch_bounds__(kScoreThreads, D == 64 && GB == 7 ? 3 : 2) void score_f32_kernel(ScoreParams p) {
   constexpr int NC = D / 32;            // chunks of a token per lane
   constexpr int U = D == 64 ? 4 : 2;    // a lane group's tokens of a batch
   constexpr int NB = 64 * BPW / (8 * U);  // batches per wave
