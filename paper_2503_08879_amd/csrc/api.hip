@@ -149,13 +149,17 @@ ShortlistPlan shortlist_plan(const sagekv_select_desc* d) {
     s.rank = 0;  // everything passes
   }
   s.expect = (int)ceil(most);
-  // Registers of the selecting workgroup, and longer rows than one workgroup selects from faster (row_select_kernel): from 8192 tokens on
+  // Registers of the selecting workgroup, and longer rows than one workgroup selects from faster (row_select_kernel): from 8192 tokens on, more with fewer
+  // heads a list,
   // while the first launch has a CU for every workgroup, us, row_select_kernel and this: 8 rows x 8192 28.9 29.9, x 10000 32.7 30.6, x 24000
-  // 46.9 35.6, 32 x 24000 81 71, 64 x 24000 180 180, 128 x 16384 160 170; from kRowSelectMax tokens on, up to the logits of
+  // 46.9 35.6, 32 x 24000 81 71, 64 x 24000 180 180, 128 x 16384 160 170 (4 heads); 8 rows of 64 dims, fp32, 1 head x 9000 22.2 24.4, x 12000 23.0 25.1, x
+  // 16000 25.7 25.2, 2 heads x 12000 25.1 27.2, x 16000 28.3 27.2, 3 x 9000 26.1 27.6, x 12000 28.4 27.9, 4 x 9000 28.2 28.9, x 12000 30.8 29.8, bf16 1 x 12000
+  // 22.9 23.5, x 16000 23.9 23.3, 2 x 9000 23.3 23.2, x 16000 24.9 24.6; from kRowSelectMax tokens on, up to the logits of
   // 256 rows x 32K x 4 heads, wherever the pre-filtered path is the alternative (few_rows), else as select_layout says.
+  const int64_t from = heads == 1 ? 14336 : heads == 2 ? 12288 : heads == 3 ? 10240 : kShortFrom;
   s.ok = s.expect <= 16 * 1024 &&
          (d->L > kRowSelectMax ? 4 * (int64_t)d->n_problems * d->n_q_heads * d->L <= 128ll << 20
-                               : d->L > kShortFrom && lists * (s.n_parts + 1) <= 256);
+                               : d->L > from && lists * (s.n_parts + 1) <= 256);
   return s;
 }
 

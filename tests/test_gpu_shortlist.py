@@ -64,6 +64,14 @@ def test_few_rows(ref, dtype, P, Hq, Hkv, d, L, S, W, k, head_mode):
     assert out["redone"] in (0, -1)  # -1: descriptors that only the dense path serves
 
 
+@pytest.mark.parametrize("dtype,Hq,L,head_mode", [
+    (BF16, 2, 14336, 0), (BF16, 2, 14337, 0), (F32, 4, 12288, 0), (F32, 4, 12289, 0), (BF16, 6, 10240, 0), (BF16, 6, 10241, 0), (F32, 8, 14336, 1), (BF16, 8, 14337, 1)])
+def test_around_the_rows_of_one_workgroup(ref, dtype, Hq, L, head_mode):
+    """The longest rows that one workgroup selects from and the first ones spread over several, by heads per list."""
+    q, K, V = parity.rand_case(L + Hq, 1, Hq, 2, 64, L, dtype)
+    check(ref, dtype, head_mode, q, K, V, 4, 64, 700)
+
+
 @pytest.mark.parametrize("layout", ["token_major", "wide"])
 @pytest.mark.parametrize("head_mode", [0, 1])
 def test_strided_rows(ref, layout, head_mode):
