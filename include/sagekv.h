@@ -89,10 +89,15 @@ typedef struct {
  * by the dense path (every token's score is materialised).  The kept set is the same either way.
  * SAGEKV_SELECT_DENSE forces the dense path for every row; so does a non-null scores_out, an
  * fp32 cache, G > 16, more than 1048576 tokens per row, or a k so large that the pre-filter
- * would have to keep about half of the row (roughly 5 k lists + 8192 > L - S - W). */
+ * would have to keep about half of the row (roughly 5 k lists + 8192 > L - S - W).  Calls of few
+ * rows (4 bytes x query heads x L of all problems: up to 20 MB, 30 MB with G > 4 or per-query
+ * lists, 68 MB for L <= 8192) take the dense path too, where it is the faster one, if the
+ * workspace has room for it. */
 enum { SAGEKV_SELECT_DENSE = 1u };
 
-/* Bytes of device scratch sagekv_select needs for this descriptor (0 if it is invalid). */
+/* Bytes of device scratch sagekv_select needs for this descriptor (0 if it is invalid).  Less may do:
+ * calls of few rows (see above), and dense calls of few rows of more than 8192 tokens, also run in the
+ * scratch of the paths that make do with less, on those slower paths and with the same results. */
 size_t sagekv_select_workspace_bytes(const sagekv_select_desc* desc);
 
 /* Sec. 2 Steps 1-3.  For every row:
@@ -174,7 +179,8 @@ size_t sagekv_decode_workspace_bytes(const sagekv_decode_desc* desc);
 
 /* Step 4's attention: out[h] = sum_t softmax_t( q[h] . Kc[c][t] / sqrt(head_dim) ) Vc[c][t],
  * t in [0, len), c = h / G.   q [n_problems, Hq, head_dim]; out [n_problems, Hq, head_dim] fp32.
- * 1 <= len <= compact_capacity.  Logits, softmax and the weighted sum are fp32; with a bf16 cache
+ * 1 <= len <= compact_capacity.  Logits, softmax and the weighted sum are fp32, with an fp32 cache the logits
+ * and all sums fp64; with a bf16 cache
  * and more than 4 heads per KV head, or fewer than 192 rows of more than 128 tokens, the softmax weights
  * are rounded to bf16 (like the values they multiply) and the sum runs on the matrix cores. */
 sagekv_status sagekv_decode_attn(const sagekv_decode_desc* desc, const void* q, const void* Kc, const void* Vc,

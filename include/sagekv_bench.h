@@ -14,9 +14,11 @@
 extern "C" {
 #endif
 
-/* Waits for the stream, then reports how many rows of the LAST sagekv_select
- * call that used this workspace were redone by the dense path (-1 if the call was dense anyway).
- * `n_rows` is a host pointer. */
+/* Waits for the stream, then reports how many rows of the LAST sagekv_select call that used this
+ * workspace went a longer way.  A pre-filtered call: rows redone by the dense path.  A call of few rows
+ * that took the dense path because it is the faster one (see sagekv_select): rows with a list that had to be
+ * ranked over all its scores instead of a band or a shortlist of them.  -1 if the descriptor or scores_out
+ * asked for the dense path.  `n_rows` is a host pointer. */
 sagekv_status sagekv_select_redone_rows(const sagekv_select_desc* desc, const void* workspace,
                                         size_t workspace_bytes, void* hip_stream, int32_t* n_rows);
 

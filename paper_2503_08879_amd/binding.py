@@ -223,7 +223,7 @@ def sagekv_select_paged(desc: SelectDesc, pages: PagedKV, q_last, K_pool, V_pool
 
 
 def sagekv_select_redone_rows(desc: SelectDesc, workspace) -> int:
-    """Rows of the last sagekv_select on this workspace that the dense path had to redo (-1: dense call)."""
+    """Rows of the last sagekv_select on this workspace that went a longer way (-1: a call that asked for the dense path)."""
     n = ctypes.c_int32(0)
     _check(lib().sagekv_select_redone_rows(ctypes.byref(desc), _ptr(workspace), _ws_bytes(workspace), _stream(),
                                            ctypes.byref(n)), "sagekv_select_redone_rows")

@@ -18,9 +18,12 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // Relative half-width of the band around the coarse k-th score whose members are re-scored in
-// fp64.  fp32 scores carry a relative error of a few 1e-6 at most (dot products of <= 128
-// exact products summed pairwise, one exp, one multiply per head), so 2^-12 leaves two orders
-// of magnitude of margin while the band still holds only a handful of candidates per row.
+// fp64.  fp32 scores carry a relative error of a few 1e-6 at most with logits of ordinary size (dot products of <= 128
+// exact products summed pairwise, one exp, one multiply per head; on the one-sweep path also the heads' normalisers, whose heavy terms
+// are put right only for the fp64 scores), so 2^-12 leaves two orders
+// of magnitude of margin while the band still holds only a handful of candidates per row.  Dot products and normalisers
+// are off in proportion to the logits, about 1.2e-7 |l| each: at |l| = 500 both together reach half of the band, which is what two scores
+// may be off by towards each other.  (Offsets to +-1000, queries x 1 to 70, 33 thousand calls against fp64: no list differed by more than 1e-6 on this route.)
 constexpr float kBand = 1.0f / 4096.0f;
 
 constexpr int64_t kFillScores = 256, kFill = 512;  // see score_chunk
@@ -165,10 +168,10 @@ ShortlistPlan shortlist_plan(const sagekv_select_desc* d) {
 
 struct SelectLayout {
   // small: the pre-filtered path applies to the descriptor; rows it cannot certify (and calls that
-  // ask for every score) take the two-sweep dense path, which needs no logit scratch.
+  // ask for every score) take the two-sweep dense path, which needs no logit scratch.  The layout is that of the path that one_sweep says.
   bool small;
-  size_t logits, scores, partials /* small: the chunks' lines */, stats, ghist, total;
-  // pre-filtered path
+  size_t logits /* one_sweep */, scores, partials /* one_sweep: ChunkPartial, else the chunks' lines */, stats, ghist, total;
+  // pre-filtered path (n_fail: whenever small)
   size_t samp_logit, samp_stats, heavy_thr, samp_tau, list_info, ovf_count, cand_idx, cand_logit, cand_score, cand_pos,
       row_fail, n_fail;
   // one-sweep dense path, many workgroups per row
