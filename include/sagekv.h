@@ -90,7 +90,7 @@ typedef struct {
  * SAGEKV_SELECT_DENSE forces the dense path for every row; so does a non-null scores_out, an
  * fp32 cache, G > 16, more than 1048576 tokens per row, or a k so large that the pre-filter
  * would have to keep about half of the row (roughly 5 k lists + 8192 > L - S - W).  Calls of few
- * rows (4 bytes x query heads x L of all problems: up to 20 MB, 30 MB with G > 4 or per-query
+ * rows (4 bytes x query heads x L of all problems: up to 8 to 20 MB, 30 MB with G > 4 or per-query
  * lists, 68 MB for L <= 8192) take the dense path too, where it is the faster one, if the
  * workspace has room for it. */
 enum { SAGEKV_SELECT_DENSE = 1u };

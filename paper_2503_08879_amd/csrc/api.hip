@@ -225,9 +225,16 @@ bool check_select(const sagekv_select_desc* d, sagekv_status* st) {
 //   16 x 64K, 4, 64 dims     17    59.1   53.3       32 x 32K, 7              29    92.0   88.7
 //   16 x 128K, 4, 64 dims    34    78.8   89.9       64 x 20000, 7            36     110    110
 //   per-query lists: 32 x 32K, 7 29 160 126, 64 x 32K, 7 59 246 243, 32 x 32K, 4 17 116 104, 64 x 32K, 4 34 186 187
+// Rows too long for row_select_kernel with few heads have more keys and more workgroups of the shortlist's first launch in as many bytes of logits:
+//   64 x 40000, 1             10     140    139       40 x 40000, 2 (64 dims) 13 66.0 64.1      24 x 50000, 4 (64 dims) 19 57.3 58.6
+//   8 x 400000, 1             13     167    171       32 x 65536, 2            17     117    120
+//   24 x 92424, 1, 64 dims     9    74.6   76.2       40 x 54961, 2            18     122    128
 bool few_rows(const sagekv_select_desc* d, int G, bool per_query) {
   const double mb = 4e-6 * (double)d->n_problems * d->n_q_heads * (double)d->L;
-  return mb <= (d->L <= kShortFrom ? 68.0 : G <= 4 && !per_query ? 20.0 : 30.0);
+  if (d->L <= kShortFrom) return mb <= 68.0;
+  if (G > 4 || per_query) return mb <= 30.0;
+  if (d->L <= kRowSelectMax) return mb <= 20.0;
+  return mb <= (G == 1 ? 8.5 : G == 2 ? 13.0 : 18.5);
 }
 
 // Workspace layout.  Descriptors the pre-filtered path cannot serve get the one-sweep dense path's
