@@ -626,7 +626,7 @@ struct HeavyList {  // in the order in which the waves met them
 };
 
 // fp64 scores of the band's members into band_v after the listed terms have gone into the statistics (stat, in LDS).  Every 16 lanes
-// take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyMost.  Begins (hv.n, band_tok) after a barrier, ends with one.
+// take one logit.  nb * heads <= kMaxBand, hv.n <= kHeavyMost, hv.change = 0.  Begins (hv.n, band_tok) after a barrier, ends with one.
 template <int DT>
 __device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, int nb, const DenseRows& in, int row, int g_lo, int g_hi, RowStat* stat) {
   typedef typename FourElems<DT>::type Four;
@@ -634,16 +634,13 @@ __device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, 
   const int D = geo.D, tid = threadIdx.x, sub = tid & 15, heads = g_hi - g_lo, n_heavy = hv.n, n = n_heavy + nb * heads;
   const int prob = row / geo.Hkv, c = row % geo.Hkv, chunk_shift = __builtin_ctz((unsigned)in.chunk);
   const double inv = 1.0 / sqrt((double)D);
-  if (n_heavy > 0) {  // workgroup-uniform
-    if (tid < 64) hv.change[tid] = 0ull;
-    __syncthreads();
-  }
   constexpr int U = DT == DT_BF16 ? 2 : 1, kGroups = kTopkThreads / 16;
 #pragma unroll 1
   for (int t0 = tid >> 4; t0 < n; t0 += U * kGroups) {
     Four k0[U], k1[U], q0[U], q1[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if (u > 0 && n <= kGroups) continue;  // workgroup-uniform: a term a group at most
       const int t = t0 + u * kGroups < n ? t0 + u * kGroups : t0;
       const bool heavy = t < n_heavy;
       const int b = heavy ? 0 : t - n_heavy;
@@ -657,6 +654,7 @@ __device__ __forceinline__ void refine_band_exact(RegSelect& sh, HeavyList& hv, 
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
+      if (u > 0 && n <= kGroups) continue;
       const int t = t0 + u * kGroups;
       const double l = group_sum_f64<16>(dot_f64<DT>(k1[u], q1[u], dot_f64<DT>(k0[u], q0[u], 0.0))) * inv;
       if (sub == 0 && t < n) *(t < n_heavy ? &hv.exact[t] : &sh.term[t - n_heavy]) = l;

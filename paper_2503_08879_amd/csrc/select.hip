@@ -483,6 +483,7 @@ __global__ __launch_bounds__(kTopkThreads) void row_select_kernel(RowSelectParam
   }
   for (int w = tid; w < (int)(sizeof(bitmap) / 4); w += kTopkThreads) bitmap[w] = 0u;
   if (tid == 0) heavy.n = 0;
+  if (tid < 64) heavy.change[tid] = 0ull;
   // The heavy terms change a normaliser by a few 1e-6 at most: scores that are written out have them in, the selection
   // only needs them where it comes to fp64 scores.
   auto exact = [&]() {
