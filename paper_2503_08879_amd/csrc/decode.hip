@@ -280,7 +280,7 @@ __global__ __launch_bounds__(NW * 64) void decode_f32_kernel(DecodeParams p, int
           // over the eight lanes of a token; lane s keeps head s
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            const double r = eight_lane_sums(a[u], sl);
+            const double r = eight_lane_sums<GB>(a[u], sl);
             x[gg + u] = hh == 0 || sl >= 4 ? r : x[gg + u];
           }
         }

@@ -123,8 +123,20 @@ __device__ __forceinline__ double swap32_sum_f64(double v) {  // v + v of lane ^
   const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
   return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
 }
-// Four values summed over aligned groups of eight lanes; lane s of a group (`sl`) gets the total of value s % 4.
+// Four values summed over aligned groups of eight lanes; lane s of a group (`sl`) gets the total of value s % 4.  N = 1, 2: of the first value,
+// of the first two in turn.
+template <int N>
 __device__ __forceinline__ double eight_lane_sums(double (&a)[4], int sl) {
+  if constexpr (N <= 2) {
+    double v = a[0] + dpp_f64<0x141>(a[0]);  // row_half_mirror
+    if (N == 2) {
+      const double w = a[1] + dpp_f64<0x141>(a[1]);
+      v = (sl & 1 ? w : v) + dpp_f64<0xB1>(sl & 1 ? v : w);  // quad_perm [1,0,3,2]
+    } else {
+      v += dpp_f64<0xB1>(v);
+    }
+    return v + dpp_f64<0x4E>(v);  // quad_perm [2,3,0,1]
+  }
   double z[2];
 #pragma unroll
   for (int h = 0; h < 4; ++h) a[h] += dpp_f64<0x141>(a[h]);  // row_half_mirror

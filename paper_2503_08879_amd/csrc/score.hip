@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kScoreThreads, D == 64 && GB == 7 ? 3 : 2) void sco
           }
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            const float r = (float)(eight_lane_sums(a[u], sl) * (1.0 / sqrt((double)D)));
+            const float r = (float)(eight_lane_sums<GB>(a[u], sl) * (1.0 / sqrt((double)D)));
             xs[n][uu + u] = hh == 0 || sl >= 4 ? r : xs[n][uu + u];
           }
         }
